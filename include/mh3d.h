@@ -184,12 +184,13 @@ mh3d_status mh3d_power_iteration(mh3d_plan_t plan, int32_t iters, uint64_t seed,
 mh3d_status mh3d_solve(mh3d_plan_t plan, const float* d, float* rho_inout,
                        const mh3d_solve_opts* opts, mh3d_solve_info* info);
 
-/* Tile shapes of the spectral passes: E spectrum elements per thread and cpw alias
+/* Tile shapes of the passes.  E, cpw and ps shape the class and plane passes of user-PSF
+ * plans (analytic plans check and keep them, and run passes without them); xb shapes the
+ * small-grid passes of every plan.  E spectrum elements per thread and cpw alias
  * classes per workgroup in the class passes (E in {1, 2, 3, 4, 6, 8, 9} divides
  * S = ds0 ds1 ds2 with S/E a power of two <= 64; cpw divides the class count, at
  * most 1024 threads = cpw (nx/ds0) S / E), xb decimated x-planes per
- * workgroup in the small-grid passes (divides nx/ds0; 256 threads per x'-plane, at
- * most 1024).  0 = built-in heuristic.
+ * workgroup in the small-grid passes (divides nx/ds0).  0 = built-in heuristic.
  * ps > 1 splits each x-plane over ps workgroups: all transform the whole plane along
  * its first axis, each takes a share of the second-axis transforms (at most
  * min(nz/2 + 1, (ny + 1)/2) workgroups).  Results do not depend on the tiles (only
@@ -221,20 +222,21 @@ mh3d_status mh3d_solve_static(mh3d_plan_t plan, const float* d, float* rho_inout
  * mh3d_adjoint and mh3d_backproject -- the same operator (Sec. 4.1 eq. dN, Table
  * tab:ops) and solver step (Sec. 4.3) either way:
  *   1  compile-time-geometry passes, where the library has them for the plan's grid,
- *      decimation and harmonic count (scalar model, analytic PSF, no padding).  The
- *      analytic PSF is a product of an x factor per harmonic and a (y, z) factor shared
- *      by all harmonics (Sec. 2, the PSF form), so its spectra are too: a plane pass per
- *      (x-plane, y mod ds1) weights by b, transforms along z and y (the y-transform
- *      split four-step with the column pass) and folds the (y, z) aliases with the
- *      shared factor; a column pass per decimated (y, z) frequency transforms along x
- *      and applies every harmonic's x factor and x fold; the adjoint runs the same
- *      steps backwards.  The default.
- *   0  the general passes (as batches always run).
+ *      decimation and harmonic count (scalar model, analytic PSF, no padding).  The default.
+ *   0  the same passes with run-time sizes (as batches always run), and for user PSFs the
+ *      passes on full per-harmonic spectra.
+ * The analytic PSF is a product of an x factor per harmonic and a (y, z) factor shared by
+ * all harmonics (Sec. 2, the PSF form), so its spectra are too: a plane pass per
+ * (x-plane, y mod ds1) weights by b, transforms along z and y (the y-transform split
+ * four-step with the column pass) and folds the (y, z) aliases with the shared factor; a
+ * column pass per decimated (y, z) frequency transforms along x and applies every
+ * harmonic's x factor and x fold; the adjoint runs the same steps backwards.
  * Results agree to FP32 rounding (the sums run in other orders).  request: 0 or 1 to
  * choose (synchronous; fails if the plan belongs to a batch), -1 to only query;
  * *active (HOST, may be NULL) receives 1 if the compile-time passes will run. */
 mh3d_status mh3d_plan_path(mh3d_plan_t plan, int32_t request, int32_t* active);
-/* Autotuner: times one A + A^T application (mh3d_forward_adjoint, HIP events) for candidate class tiles
+/* Autotuner: times one A + A^T application (mh3d_forward_adjoint, HIP events).  Analytic
+ * plans: for every small-grid xb, the only tile their passes read.  User-PSF plans: for candidate class tiles
  * (per valid E, the smallest cpw giving >= 64, 128, 256, 512 threads), then for
  * every small-grid xb and plane split ps with the best class tiles, each with 512 and
  * 1024 threads per workgroup in the launch that runs the adjoint plane pass beside the
@@ -245,7 +247,7 @@ mh3d_status mh3d_plan_path(mh3d_plan_t plan, int32_t request, int32_t* active);
  * holds no other blocks); mh3d_plan_set_tiles sets both splits to ps, and results do not
  * depend on either.
  * A plan on the compile-time passes of mh3d_plan_path takes only xb from the tiles in
- * its own calls, but runs the general passes in a batch: it is tuned as above with those
+ * its own calls, but runs the run-time passes in a batch: it is tuned as above with those
  * passes switched off (stored under the general key), then xb alone (1, 2, 4 or 8) on
  * the compile-time A + A^T, which its "|compiled" entry keeps beside the general tiles.
  * cache_path (may be NULL): a JSON object keyed by "arch|grid|K|decimation|psf

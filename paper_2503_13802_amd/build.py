@@ -6,11 +6,11 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libmh3d.so")
-SOURCES = [os.path.join(PKG, "csrc", "mh3d.hip")]
+SOURCES = [os.path.join(PKG, "csrc", f) for f in ("mh3d.hip", "sep.hip", "fast.hip")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed FP32 instructions are disabled for every HIP translation unit
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I" + os.path.join(ROOT, "include"),
@@ -19,12 +19,22 @@ FLAGS = [
 
 def build(verbose=True, extra=()):
     """Compile the library; raises CalledProcessError on failure."""
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        return subprocess.Popen(cmd), cmd
+
+    def wait(started):
+        for p, cmd in [(p, cmd) for p, cmd in started if p.wait() != 0]:
+            raise subprocess.CalledProcessError(p.returncode, cmd)
+
+    objs = [src[:-len(".hip")] + ".o" for src in SOURCES]     # the units compile side by side
+    wait([run([HIPCC] + FLAGS + list(extra) + ["-c", src, "-o", obj]) for src, obj in zip(SOURCES, objs)])
     tmp = LIB + ".tmp"
-    cmd = [HIPCC] + FLAGS + list(extra) + SOURCES + ["-o", tmp]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+    wait([run([HIPCC, "--offload-arch=gfx950", "-shared"] + objs + ["-o", tmp])])
     os.replace(tmp, LIB)
+    for obj in objs:
+        os.remove(obj)
     return LIB
 
 

@@ -28,13 +28,12 @@
 //    (q'y, q'z) for the q'z beyond mz/2), transforms it back along y1 and z (C2R) and
 //    multiplies by b.
 //
-// Each call sequence runs only these passes (their intermediate layouts are their own):
-// the fused sequences, the separate forward and adjoint calls and the per-harmonic
-// back-projections (the adjoint calls start from kernels.hpp's small-grid forward
-// transform of the portraits).  User PSFs, vector, padded and batched plans keep the
-// passes of kernels.hpp.
+// They serve the fused sequences, the separate forward and adjoint calls and the
+// per-harmonic back-projections.  Padded and batched volumes and every other grid run the
+// same factorisation with run-time sizes (sep.hpp), plans with user PSFs the passes of
+// kernels.hpp.
 #pragma once
-#include "kernels.hpp"
+#include "passes.hpp"
 
 namespace mh3d {
 
@@ -42,37 +41,6 @@ namespace mh3d {
 // qx[x][column] (the column pass's output), so each plane workgroup reads and writes one
 // contiguous run; the column pass takes its columns in runs of CPC.
 //
-// Plan-time tables of the separable passes (FP64 sums, FP32 storage):
-//   sfs[k][qx]        scale_k F_k(qx) (its real part, or its imaginary part when bit k of
-//                     imag_mask is set), the x factor of the stored spectra
-//   set[y0][q'y][qz]  Et(y0, q'y, qz) = sum_jy w_ny^(y0 qy) Ehat(qy, qz), qz <= nz/2
-__global__ void k_sep_tables(Geo g, const double2* __restrict__ fhat, const double2* __restrict__ ehat,
-                             const double* __restrict__ scale, uint32_t imag_mask,
-                             const double2* __restrict__ tw64y, float* __restrict__ sfs, float2* __restrict__ set) {
-  const int nf = g.K * g.nx;
-  const int ne = g.sy * g.my * g.nzh;
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < nf + ne; t += gridDim.x * blockDim.x) {
-    if (t < nf) {
-      const int k = t / g.nx;
-      const double2 f = fhat[t];
-      sfs[t] = (float)((((imag_mask >> k) & 1u) ? f.y : f.x) * scale[k]);
-    } else {
-      const int r = t - nf;
-      const int y0 = r / (g.my * g.nzh), r2 = r - y0 * (g.my * g.nzh);
-      const int qyp = r2 / g.nzh, qz = r2 - qyp * g.nzh;
-      double sr = 0.0, si = 0.0;
-      for (int jy = 0; jy < g.sy; ++jy) {
-        const int qy = qyp + jy * g.my;
-        const double2 w = tw64y[(long long)y0 * qy % g.ny];   // exp(-2 pi i y0 qy / ny)
-        const double2 e = ehat[(long long)qy * g.nzh + qz];
-        sr += w.x * e.x - w.y * e.y;
-        si += w.x * e.y + w.y * e.x;
-      }
-      set[r] = make_float2((float)sr, (float)si);
-    }
-  }
-}
-
 template <int NX_, int NY_, int NZ_, int SX_, int SY_, int SZ_, int CPC_, int KMAX_, int TP_ = 256, int TPF_ = 256,
           int LSX_ = 0, int LSZ_ = 0>
 struct FastGeo {
@@ -197,7 +165,7 @@ __device__ __forceinline__ void fast_plane_of(int b, int& x, int& y0) {
 // R2C along z, length-my DFT along y1, then the share C(y0; x, q'y, q'z) of the folded
 // plane into cp[y0][x][column].
 template <class G, int SRC>
-__global__ __launch_bounds__(G::TPF) void k_fast_plane_fwd(const VolDesc* __restrict__ vds, const float* __restrict__ a) {
+static __global__ __launch_bounds__(G::TPF) void k_fast_plane_fwd(const VolDesc* __restrict__ vds, const float* __restrict__ a) {
   const VolDesc& vd = vds[0];
   if constexpr (SRC == SRC_FISTA_Y || SRC == SRC_SCALED) {
     if (vd.st->done) return;
@@ -312,10 +280,9 @@ __global__ __launch_bounds__(G::TPF) void k_fast_plane_fwd(const VolDesc* __rest
 }
 
 // ============================================================================ column pass
-// Modes beyond the fused ones (NRM_RESID, NRM_PLAIN, NRM_STORE of kernels.hpp): A alone
-// (the forward products and G, no adjoint) and A^T alone (R_k from the small-grid spectra
-// of the portraits that k_small_fwd left in G', no forward products).
-enum { COL_FWD = 16, COL_ADJ = 17 };
+// Modes beyond the fused ones (NRM_RESID, NRM_PLAIN, NRM_STORE of kernels.hpp): COL_FWD, A
+// alone (the forward products and G, no adjoint), and COL_ADJ, A^T alone (R_k from the
+// portraits' small-grid spectra in G', no forward products), as sep.hpp names them.
 
 // Column block of workgroup b: the workgroups of one XCD (b mod 8) take a run of
 // consecutive column blocks, so the blocks that share a cache line of the shares, of
@@ -337,7 +304,7 @@ __device__ __forceinline__ int fast_col_block(int b) {
 //
 // grid.y > 1 runs one descriptor per y-block (the back-projections of single harmonics).
 template <class G, int MODE>
-__global__ __launch_bounds__(G::TC) void k_fast_col(const VolDesc* __restrict__ vds, int check_done) {
+static __global__ __launch_bounds__(G::TC) void k_fast_col(const VolDesc* __restrict__ vds, int check_done) {
   const VolDesc& vd = vds[blockIdx.y];
   if (check_done && vd.st->done) return;
   constexpr int NX = G::NX, MX = G::MX, SX = G::SX, CPC = G::CPC, KMAX = G::KMAX, LSX = G::LSX;
@@ -718,7 +685,7 @@ __device__ __forceinline__ void fast_plane_adj_body(const VolDesc& vd, int lb, c
 
 // grid.y > 1 (OUT_SCALE_B only): descriptor y and output volume y of consecutive volumes.
 template <class G, int OUT>
-__global__ __launch_bounds__(G::TP) void k_fast_plane_adj(const VolDesc* __restrict__ vds, AdjOut ao) {
+static __global__ __launch_bounds__(G::TP) void k_fast_plane_adj(const VolDesc* __restrict__ vds, AdjOut ao) {
   if constexpr (OUT == OUT_SCALE_B) ao.out += (long long)blockIdx.y * G::NX * G::NY * G::NZ;
   fast_plane_adj_body<G, OUT>(vds[blockIdx.y], blockIdx.x, ao);
 }
@@ -791,7 +758,7 @@ __device__ __forceinline__ void fast_small_inv_dispatch(const VolDesc& vd, int l
 }
 
 template <class G>
-__global__ __launch_bounds__(G::TP) void k_fast_small_inv(const VolDesc* __restrict__ vds, float* __restrict__ d) {
+static __global__ __launch_bounds__(G::TP) void k_fast_small_inv(const VolDesc* __restrict__ vds, float* __restrict__ d) {
   fast_small_inv_dispatch<G>(vds[0], blockIdx.x, d);
 }
 
@@ -849,7 +816,7 @@ __device__ __forceinline__ void fast_small_fwd_body(const VolDesc& vd, int lb, c
 }
 
 template <class G>
-__global__ __launch_bounds__(G::TP) void k_fast_small_fwd(const VolDesc* __restrict__ vds, const float* __restrict__ r,
+static __global__ __launch_bounds__(G::TP) void k_fast_small_fwd(const VolDesc* __restrict__ vds, const float* __restrict__ r,
                                                         float2* __restrict__ out) {
   const VolDesc& vd = vds[0];
   switch (vd.g.xb) {
@@ -863,7 +830,7 @@ __global__ __launch_bounds__(G::TP) void k_fast_small_fwd(const VolDesc* __restr
 // A then A^T after k_fast_col<NRM_STORE>: blocks [0, NBP) run the adjoint plane pass
 // (ao.out = b . v), the others the small-grid inverse pass that writes the portraits d.
 template <class G>
-__global__ __launch_bounds__(G::TP) void k_fast_adj_and_store(const VolDesc* __restrict__ vds, AdjOut ao,
+static __global__ __launch_bounds__(G::TP) void k_fast_adj_and_store(const VolDesc* __restrict__ vds, AdjOut ao,
                                                             float* __restrict__ d) {
   const VolDesc& vd = vds[0];
   if ((int)blockIdx.x < G::NBP) fast_plane_adj_body<G, OUT_SCALE_B>(vd, blockIdx.x, ao);

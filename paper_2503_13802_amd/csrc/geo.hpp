@@ -10,6 +10,7 @@
 // conjugate of the in-plane Hermitian partner (ny - qy, nz - qz), which is exact for
 // the y-z spectrum of a real x-plane.
 #pragma once
+#include <hip/hip_runtime.h>
 #include <stdint.h>
 
 namespace mh3d {
@@ -36,6 +37,39 @@ inline FastDiv make_fastdiv(uint32_t d) {
   return f;
 }
 
+// n / d for 0 <= n < 2^16 with n * d < 2^24, by one 24-bit high multiply (full rate, where
+// a 32-bit one takes four times as long): with m = ceil(2^24 / d) and e = m d - 2^24 < d
+// the quotient (n 2^8)(m) / 2^32 is exact while n e < 2^24.
+struct MDiv {
+  uint32_t m, d;
+  __host__ __device__ __forceinline__ int div(int n) const {
+    const uint32_t a = ((uint32_t)n << 8) & 0xffffffu, b = m & 0xffffffu;
+    const int q = (int)(uint32_t)(((uint64_t)a * b) >> 32);
+    return d == 1 ? n : q;
+  }
+};
+
+inline MDiv make_mdiv(int d) {
+  MDiv r;
+  r.d = (uint32_t)d;
+  r.m = d == 1 ? 0u : (uint32_t)(((1u << 24) + (uint32_t)d - 1) / (uint32_t)d);
+  return r;
+}
+
+// Launch shapes and divisors of the run-time separable and small-grid passes (sep.hpp).
+struct SepGeo {
+  int np;                  // row pairs of a plane block: (my + 1)/2
+  int lsz, lsy;            // LDS line strides of its packed z lines and its y lines
+  int pbuf;                // one of its two LDS buffers (complex values)
+  int cpc, kg;             // columns per column block, harmonics per group of it
+  int lsx, lsm;            // LDS line strides of its x and x' lines
+  int lsmz;                // line stride of the small grid's packed z' lines
+  int nxb;                 // x'-blocks: mx / xb
+  // d_nzv, d_mzv: vectors (4 or 2 values) per row of the plane and of the small grid
+  MDiv d_sy, d_np, d_nzh, d_mzh, d_nzv, d_mz, d_mzv, d_my, d_mx, d_cpc, d_cpcmx, d_cpcxb, d_xb, d_kgcpc, d_klcpc, d_spairs,
+      d_xbmzh, d_nxb;
+};
+
 struct Geo {
   int nx, ny, nz, nzh;     // grid, nzh = nz/2 + 1
   int mx, my, mz, mzh;     // decimated grid, mzh = mz/2 + 1
@@ -60,6 +94,7 @@ struct Geo {
   int mxf, myf, mzf;       // field-of-view portrait dims
   long long Mf;            // mxf*myf*mzf (= M without padding)
   long long hsz;           // spectrum elements per harmonic = ncls*mx*S = plane*nx
+  SepGeo sep;
   FastDiv f_nz, f_nzh, f_nmem, f_mzh, f_sz, f_mz, f_W, f_xb, f_S, f_mxS, f_cpwmx, f_cpwxb, f_ny, f_my;
 };
 

@@ -1,4 +1,6 @@
-// HIP kernels of the MH3D operator A = P H B, its adjoint and the solver updates.
+// HIP kernels of the MH3D operator A = P H B, its adjoint and the solver updates for plans
+// with user PSF arrays (full spectra), and the pieces shared with the separable passes of
+// analytic plans (sep.hpp, fast.hpp).
 //
 // Pipeline of one application of A (Sec. 4.1 eq. dN, Table tab:ops):
 //   plane_fwd  one workgroup per x-plane: u = b . rho, 2-D R2C FFT over (y, z) in
@@ -6,7 +8,7 @@
 //   class_fwd  one workgroup per group of classes: FFT along x, multiply by every
 //              precomputed spectrum H_k, fold the aliases (P in Fourier form),
 //              inverse FFT along the decimated x                                [F_x, H, P]
-//   small_inv  one workgroup per (k, block of x'): 2-D C2R over (y', z') of the
+//   small_inv  (sep.hpp) one workgroup per (k, block of x'): 2-D C2R over (y', z') of the
 //              decimated spectrum -> portrait d_k (optionally minus data)         [F^-1]
 // The adjoint runs the same passes backwards (small_fwd, class_adj, plane_adj):
 // F(P^T r) tiles the small spectrum, H_k^T multiplies by conj(H_k), and the sum
@@ -147,9 +149,8 @@ struct DevState {
 // recorded sequence of launches stays valid on replay.
 struct VolDesc {
   Geo g;
-  const void* hs;          // spectra in the class layout (scaled by 1/N)
-  uint32_t imag_mask;      // compact spectra: bit k set -> harmonic k is imaginary
-  int compact;
+  const void* hs;          // user PSFs: spectra in the class layout (scaled by 1/N)
+  uint32_t imag_mask;      // separable spectra: bit k set -> harmonic k's x factor is imaginary
   const float* b;          // sensitivity
   float2* uperm;           // class-layout yz spectra (forward) / adjoint spectra
   float2* G;               // decimated spectra (forward)
@@ -178,10 +179,10 @@ struct VolDesc {
   // bit k of cmask[i]: component i of harmonic k is present (a PSF block that is
   // identically zero is skipped: no spectrum load, no product)
   uint32_t cmask[3];
-  // Separable analytic spectra (the compile-time passes of fast.hpp): the x factors
+  // Separable analytic spectra (the passes of sep.hpp and fast.hpp): the x factors
   // sfs[k][qx], the y-residue table set[y0][q'y][qz], and their intermediates, both in
-  // uperm's memory: cp[y0][column][x] (the plane pass's folded shares) and
-  // qx[column][x] (the column pass's output for the adjoint plane pass).
+  // uperm's memory: cp[y0][x][column] (the plane pass's folded shares) and
+  // qx[x][column] (the column pass's output for the adjoint plane pass).
   const float* sfs;
   const float2* set;
   float2* cp;
@@ -250,28 +251,10 @@ __device__ float2* r2c_rows(float2* a, float2* b, const float2* twz, int nrows, 
   return X;
 }
 
-// C2R along z: half spectra X[rc.base(row) + q * rc.qstride] in *a -> packed pairs
-// Z[j][lsz] (Z = A + iB with the Hermitian extension), inverse FFT.  The imaginary
-// parts of the q = 0 and q = nz/2 bins are dropped (they vanish for a Hermitian
+// C2R along z of the row pairs [j0, j1): half spectra X[rc.base(row) + q * rc.qstride] in *a
+// -> packed pairs Z[j - j0][lsz] (Z = A + iB with the Hermitian extension), inverse FFT.  The
+// imaginary parts of the q = 0 and q = nz/2 bins are dropped (they vanish for a Hermitian
 // input).  Returns the buffer holding the packed real rows.
-__device__ float2* c2r_rows(float2* a, float2* b, const float2* twz, int nrows, int nz, int npairs,
-                            const RowCols& rc, const FastDiv& f_nz) {
-  const int lsz = pad_odd(nz);
-  const int items = npairs * nz;
-  for (int it = threadIdx.x; it < items; it += blockDim.x) {
-    const int j = (int)f_nz.div((uint32_t)it), q = it - j * nz;
-    const bool up = 2 * q > nz;
-    const int qq = up ? nz - q : q;
-    float2 x = a[rc.base(2 * j) + qq * rc.qstride];
-    float2 y = (2 * j + 1 < nrows) ? a[rc.base(2 * j + 1) + qq * rc.qstride] : make_float2(0.f, 0.f);
-    if (qq == 0 || 2 * qq == nz) { x.y = 0.f; y.y = 0.f; }
-    if (up) { x.y = -x.y; y.y = -y.y; }
-    b[j * lsz + q] = make_float2(x.x - y.y, x.y + y.x);      // x + i y
-  }
-  return fft_lines<+1>(b, a, twz, nz, npairs, lsz);
-}
-
-// c2r_rows restricted to the row pairs [j0, j1): pair j lands at line j - j0.
 __device__ float2* c2r_rows_range(float2* a, float2* b, const float2* twz, int nrows, int nz, int j0, int j1,
                                   const RowCols& rc, const FastDiv& f_nz) {
   const int lsz = pad_odd(nz);
@@ -362,10 +345,8 @@ __device__ __forceinline__ void plane_fwd_body(const VolDesc& vd, int lb, const 
   }
 }
 template <int SRC>
-__global__ __launch_bounds__(1024) void k_plane_fwd(const VolDesc* __restrict__ vds, const int2* __restrict__ tasks,
-                                                    const float* __restrict__ a) {
-  int lb;
-  const VolDesc& vd = vol_of(vds, tasks, lb);
+static __global__ __launch_bounds__(1024) void k_plane_fwd(const VolDesc* __restrict__ vds, const float* __restrict__ a) {
+  const VolDesc& vd = vds[0];
   if constexpr (SRC == SRC_FISTA_Y || SRC == SRC_SCALED) {
     if (vd.st->done) return;
   }
@@ -373,44 +354,13 @@ __global__ __launch_bounds__(1024) void k_plane_fwd(const VolDesc* __restrict__ 
   if constexpr (SRC == SRC_SCALED) {
     if (!a) a = vd.rho[vd.st->k & 1];
   }
-  plane_fwd_body<SRC>(vd, lb, a);
+  plane_fwd_body<SRC>(vd, blockIdx.x, a);
 }
 
 // ============================================================================ pass 2: classes
-// HC = 0: compact spectra (one float per element; harmonic k is real if bit k of
-// imag_mask is clear, purely imaginary if set).  HC = 1: complex spectra.
-template <int HC, int E>
-struct HLoad;
-
-// Compact spectra: one float per element.
+// E consecutive spectrum elements.
 template <int E>
-struct HLoad<0, E> {
-  float v[E];
-  __device__ __forceinline__ void load(const void* base, long long off) {
-    const float* p = reinterpret_cast<const float*>(base) + off;
-    if constexpr (E % 4 == 0) {
-#pragma unroll
-      for (int i = 0; i < E; i += 4) {
-        const float4 t = *reinterpret_cast<const float4*>(p + i);
-        v[i] = t.x; v[i + 1] = t.y; v[i + 2] = t.z; v[i + 3] = t.w;
-      }
-    } else if constexpr (E % 2 == 0) {
-#pragma unroll
-      for (int i = 0; i < E; i += 2) {
-        const float2 t = *reinterpret_cast<const float2*>(p + i);
-        v[i] = t.x; v[i + 1] = t.y;
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < E; ++i) v[i] = p[i];
-    }
-  }
-  __device__ __forceinline__ float re(int i) const { return v[i]; }
-};
-
-// Complex spectra.
-template <int E>
-struct HLoad<1, E> {
+struct HLoad {
   float2 v[E];
   __device__ __forceinline__ void load(const void* base, long long off) {
     const float2* p = reinterpret_cast<const float2*>(base) + off;
@@ -448,9 +398,8 @@ __host__ __device__ inline size_t class_lds_elems(const Geo& g) {
   return (size_t)g.nx + g.mx + 2 * W * g.lsx + 2 * (size_t)g.K * g.cpw * g.mx;
 }
 
-// Harmonics of spectra prefetched ahead in the class kernels: 8 for compact spectra
-// with up to 4 elements per thread (the whole ring costs <= 32 registers), else 4.
-__host__ __device__ constexpr int hpf_of(int HC, int E) { return (HC == 0 && E <= 4) ? 8 : 4; }
+// Harmonics of spectra prefetched ahead in the class kernels.
+constexpr int HPF = 4;
 
 // Position of class-layout element p of a (k, x'-block, class, x'-in-block) store,
 // p over K*cpw*mx, as offsets into F ((k*cpw + c)*mx + x') and G.
@@ -463,13 +412,11 @@ __device__ __forceinline__ void class_g_index(const Geo& g, int p, int c0, int& 
   go = (((long long)k * nxb + xbi) * g.ncls + c0 + c) * g.xb + xi;
 }
 
-// Forward pass 2 of one block (cpw classes).  Threads beyond vd.T_class only take
-// part in the barriers and shuffles (batched launches use the largest block size).
+// Forward pass 2 of one block (cpw classes).
 // VEC: vector model, vd.ncomp components (else one, and the loop folds away).
 // mode (FWD_*) selects where the decimated spectra go.
-template <int HC, int E, bool VEC = false>
+template <int E, bool VEC = false>
 __device__ __forceinline__ void class_fwd_body(const VolDesc& vd, int lb, int mode) {
-  constexpr int HPF = hpf_of(HC, E);
   const Geo& g = vd.g;
   extern __shared__ float2 lds[];
   const int W = g.cpw * g.nmem;
@@ -490,7 +437,6 @@ __device__ __forceinline__ void class_fwd_body(const VolDesc& vd, int lb, int mo
   const int within = rem - qxp * g.S;
   const void* hs = vd.hs;
   const int LG = g.S / E;
-  const uint32_t imag_mask = vd.imag_mask;
   // vector model: the products of every component accumulate in F0 before the one
   // inverse transform (the sum over i commutes with it)
   const int ncomp = VEC ? vd.ncomp : 1;
@@ -500,7 +446,7 @@ __device__ __forceinline__ void class_fwd_body(const VolDesc& vd, int lb, int mo
   const uint32_t pm = VEC ? vd.cmask[comp] : ~0u;
   const long long hoff0 = (long long)c0 * per_cls + e0 + comp * vd.hs_cstride;
   // spectra do not depend on the data: start streaming them first
-  HLoad<HC, E> hb[HPF];
+  HLoad<E> hb[HPF];
 #pragma unroll
   for (int i = 0; i < HPF; ++i)
     if (act && i < g.K && ((pm >> i) & 1u)) hb[i].load(hs, (long long)i * g.hsz + hoff0);
@@ -536,14 +482,8 @@ __device__ __forceinline__ void class_fwd_body(const VolDesc& vd, int lb, int mo
         float2 acc = make_float2(0.f, 0.f);
         if (act) {
           if (pk) {
-            if constexpr (HC == 0) {
 #pragma unroll
-              for (int t = 0; t < E; ++t) { acc.x += hb[i].v[t] * ur[t].x; acc.y += hb[i].v[t] * ur[t].y; }
-              if ((imag_mask >> k) & 1u) acc = make_float2(-acc.y, acc.x);
-            } else {
-#pragma unroll
-              for (int t = 0; t < E; ++t) acc = cadd(acc, cmul(hb[i].v[t], ur[t]));
-            }
+            for (int t = 0; t < E; ++t) acc = cadd(acc, cmul(hb[i].v[t], ur[t]));
           }
           if (k + HPF < g.K && ((pm >> (k + HPF)) & 1u)) hb[i].load(hs, (long long)(k + HPF) * g.hsz + hoff0);
         }
@@ -582,9 +522,8 @@ __device__ __forceinline__ void class_fwd_body(const VolDesc& vd, int lb, int mo
 }
 
 // Adjoint pass 2 of one block.
-template <int HC, int E, bool VEC = false>
+template <int E, bool VEC = false>
 __device__ __forceinline__ void class_adj_body(const VolDesc& vd, int lb) {
-  constexpr int HPF = hpf_of(HC, E);
   const Geo& g = vd.g;
   extern __shared__ float2 lds[];
   const int W = g.cpw * g.nmem;
@@ -603,7 +542,7 @@ __device__ __forceinline__ void class_adj_body(const VolDesc& vd, int lb) {
   const int qxp = (int)g.f_S.div((uint32_t)rem);
   const int within = rem - qxp * g.S;
   const void* hs = vd.hs;
-  HLoad<HC, E> hb[HPF];
+  HLoad<E> hb[HPF];
   const uint32_t pm0 = VEC ? vd.cmask[0] : ~0u;
 #pragma unroll
   for (int i = 0; i < HPF; ++i)
@@ -639,7 +578,6 @@ __device__ __forceinline__ void class_adj_body(const VolDesc& vd, int lb) {
   float2 acc[E];
 #pragma unroll
   for (int t = 0; t < E; ++t) acc[t] = make_float2(0.f, 0.f);
-  const uint32_t imag_mask = vd.imag_mask;
   for (int k0 = 0; k0 < g.K; k0 += HPF) {
 #pragma unroll
     for (int i = 0; i < HPF; ++i) {
@@ -647,15 +585,8 @@ __device__ __forceinline__ void class_adj_body(const VolDesc& vd, int lb) {
       if (act && k < g.K) {
         if ((pm >> k) & 1u) {
           float2 R = F[(k * g.cpw + cl) * g.mx + qxp];
-          if constexpr (HC == 0) {
-            // conj(i h) R = -i h R
-            if ((imag_mask >> k) & 1u) R = make_float2(R.y, -R.x);
 #pragma unroll
-            for (int t = 0; t < E; ++t) { acc[t].x += hb[i].v[t] * R.x; acc[t].y += hb[i].v[t] * R.y; }
-          } else {
-#pragma unroll
-            for (int t = 0; t < E; ++t) acc[t] = cadd(acc[t], cmulcj(hb[i].v[t], R));
-          }
+          for (int t = 0; t < E; ++t) acc[t] = cadd(acc[t], cmulcj(hb[i].v[t], R));
         }
         if (k + HPF < g.K && ((pm >> (k + HPF)) & 1u)) hb[i].load(hs, (long long)(k + HPF) * g.hsz + hoff0);
       }
@@ -687,7 +618,7 @@ __device__ __forceinline__ void class_adj_body(const VolDesc& vd, int lb) {
 // compose to multiplication by M = mx my mz (up to rounding), so the adjoint's decimated
 // spectra are
 //   NRM_RESID  R_k = M Fhat_k - Dt_k, Dt = the x' transform of the measured portraits'
-//              small-grid spectra (k_class_data, in G' as [k][class][qx'])
+//              small-grid spectra (COL_DATA of sep.hpp, in G' as [k][class][qx'])
 //   NRM_PLAIN  R_k = M Fhat_k                       (normal operator)
 //   NRM_STORE  R_k = M Fhat_k, and G = the inverse x' transform of Fhat (the small-grid
 //              pass turns it into the portraits)
@@ -696,14 +627,8 @@ __device__ __forceinline__ void class_adj_body(const VolDesc& vd, int lb) {
 // block's own recently read spectra (L2).
 enum { NRM_RESID = 0, NRM_PLAIN = 1, NRM_STORE = 2 };
 
-// The fused pass keeps every harmonic's spectra of its elements in registers when they
-// fit (compact spectra, K <= 12 at E <= 4): all loads are issued at the start and the
-// adjoint reuses them, so the pass waits on one round of spectrum loads.
-__host__ __device__ constexpr int hpf_normal(int HC, int E) { return (HC == 0 && E <= 4) ? 12 : hpf_of(HC, E); }
-
-template <int HC, int E>
+template <int E>
 __device__ __forceinline__ void class_normal_body(const VolDesc& vd, int lb, int mode) {
-  constexpr int HPF = hpf_normal(HC, E);
   const Geo& g = vd.g;
   extern __shared__ float2 lds[];
   const int W = g.cpw * g.nmem;
@@ -724,17 +649,11 @@ __device__ __forceinline__ void class_normal_body(const VolDesc& vd, int lb, int
   const long long hoff0 = (long long)c0 * per_cls + e0;
   const void* hs = vd.hs;
   const int LG = g.S / E;
-  const uint32_t imag_mask = vd.imag_mask;
   const int KCM = g.K * g.cpw * g.mx;
-  HLoad<HC, E> hb[HPF];
-  // a ring that holds every harmonic is loaded after the x transform (its registers
-  // would otherwise be live across it); a shorter ring starts streaming at once
-  constexpr bool kLate = HPF > hpf_of(HC, E);
-  if constexpr (!kLate) {
+  HLoad<E> hb[HPF];
 #pragma unroll
-    for (int i = 0; i < HPF; ++i)
-      if (act && i < g.K) hb[i].load(hs, (long long)i * g.hsz + hoff0);
-  }
+  for (int i = 0; i < HPF; ++i)
+    if (act && i < g.K) hb[i].load(hs, (long long)i * g.hsz + hoff0);
   // the data term of the block's classes (F1[(k cpw + c) mx + qx'])
   if (mode == NRM_RESID) {
     const float2* __restrict__ Dt = vd.Gp;
@@ -766,11 +685,6 @@ __device__ __forceinline__ void class_normal_body(const VolDesc& vd, int lb, int
     const int jx = (int)g.f_nmem.div((uint32_t)w), m = w - jx * g.nmem;
     ur[i] = act ? U[(cl * g.nmem + m) * g.lsx + qxp + jx * g.mx] : make_float2(0.f, 0.f);
   }
-  if constexpr (kLate) {
-#pragma unroll
-    for (int i = 0; i < HPF; ++i)
-      if (act && i < g.K) hb[i].load(hs, (long long)i * g.hsz + hoff0);
-  }
   // forward: Fhat_k(cl, qx') = sum over the S alias members of Hhat_k U
   for (int k0 = 0; k0 < g.K; k0 += HPF) {
 #pragma unroll
@@ -779,14 +693,8 @@ __device__ __forceinline__ void class_normal_body(const VolDesc& vd, int lb, int
       if (k < g.K) {
         float2 acc = make_float2(0.f, 0.f);
         if (act) {
-          if constexpr (HC == 0) {
 #pragma unroll
-            for (int t = 0; t < E; ++t) { acc.x += hb[i].v[t] * ur[t].x; acc.y += hb[i].v[t] * ur[t].y; }
-            if ((imag_mask >> k) & 1u) acc = make_float2(-acc.y, acc.x);
-          } else {
-#pragma unroll
-            for (int t = 0; t < E; ++t) acc = cadd(acc, cmul(hb[i].v[t], ur[t]));
-          }
+          for (int t = 0; t < E; ++t) acc = cadd(acc, cmul(hb[i].v[t], ur[t]));
           if (k + HPF < g.K) hb[i].load(hs, (long long)(k + HPF) * g.hsz + hoff0);
         }
         for (int o = LG >> 1; o >= 1; o >>= 1) {
@@ -818,15 +726,8 @@ __device__ __forceinline__ void class_normal_body(const VolDesc& vd, int lb, int
         const float2 f = F0[fi];
         float2 R = make_float2(Mf * f.x, Mf * f.y);
         if (mode == NRM_RESID) R = csub(R, F1[fi]);
-        if constexpr (HC == 0) {
-          // conj(i h) R = -i h R
-          if ((imag_mask >> k) & 1u) R = make_float2(R.y, -R.x);
 #pragma unroll
-          for (int t = 0; t < E; ++t) { acc[t].x += hb[i].v[t] * R.x; acc[t].y += hb[i].v[t] * R.y; }
-        } else {
-#pragma unroll
-          for (int t = 0; t < E; ++t) acc[t] = cadd(acc[t], cmulcj(hb[i].v[t], R));
-        }
+        for (int t = 0; t < E; ++t) acc[t] = cadd(acc[t], cmulcj(hb[i].v[t], R));
         if (k + HPF < g.K) hb[i].load(hs, (long long)(k + HPF) * g.hsz + hoff0);
       }
     }
@@ -859,272 +760,34 @@ __device__ __forceinline__ void class_normal_body(const VolDesc& vd, int lb, int
   }
 }
 
-// Dt = the x' transform of the measured portraits' small-grid spectra (G, as k_small_fwd
-// left them), into G' as [k][class][qx'], for class_normal_body's residual.  Same
-// blocks and LDS layout as the class passes.
-__global__ __launch_bounds__(1024) void k_class_data(const VolDesc* __restrict__ vds) {
-  const VolDesc& vd = vds[0];
-  const Geo& g = vd.g;
-  const int lb = blockIdx.x;
-  extern __shared__ float2 lds[];
-  const int W = g.cpw * g.nmem;
-  float2* twm = lds + g.nx;
-  float2* F0 = twm + g.mx + 2 * W * g.lsx;
-  float2* F1 = F0 + g.K * g.cpw * g.mx;
-  const int c0 = lb * g.cpw;
-  const int KCM = g.K * g.cpw * g.mx;
-  load_table(twm, vd.tw + vd.off[3], g.mx);
-  const float2* __restrict__ Dh = vd.G;
-  batched<8, float2>(KCM,
-                     [&](int p) {
-                       int fo;
-                       long long go;
-                       class_g_index(g, p, c0, fo, go);
-                       return Dh[go];
-                     },
-                     [&](int p, float2 v) {
-                       int fo;
-                       long long go;
-                       class_g_index(g, p, c0, fo, go);
-                       F0[fo] = v;
-                     });
-  const float2* F = fft_lines<-1>(F0, F1, twm, g.mx, g.K * g.cpw, g.mx);
-  float2* __restrict__ Dt = vd.Gp;
-  for (int p = threadIdx.x; p < KCM; p += blockDim.x) {
-    const int k = (int)g.f_cpwmx.div((uint32_t)p), r = p - k * g.cpw * g.mx;
-    const int c = r / g.mx, q = r - c * g.mx;
-    Dt[((long long)k * g.ncls + c0 + c) * g.mx + q] = F[p];
-  }
-}
-
 // Single-volume class passes, grid = ncls/cpw blocks of T_class threads.
 // check_done skips the launch once the volume's solve is done.
 // XCD-aware: consecutive class blocks run on one XCD, so the short runs of G, G' and
 // the class-layout spectra that neighbouring blocks share are fetched into one L2.
-template <int HC, int E, bool VEC>
-__global__ __launch_bounds__(1024) void k_class_fwd(const VolDesc* __restrict__ vds, int check_done, int mode) {
-  int lb;
-  const VolDesc& vd = vol_of(vds, nullptr, lb);
+template <int E, bool VEC>
+static __global__ __launch_bounds__(1024) void k_class_fwd(const VolDesc* __restrict__ vds, int check_done, int mode) {
+  const VolDesc& vd = vds[0];
+  const int lb = blockIdx.x;
   if (check_done && vd.st->done) return;
-  class_fwd_body<HC, E, VEC>(vd, plane_of_block(lb, gridDim.x), mode);
+  class_fwd_body<E, VEC>(vd, plane_of_block(lb, gridDim.x), mode);
 }
-template <int HC, int E>
-__global__ __launch_bounds__(1024) void k_class_normal(const VolDesc* __restrict__ vds, int check_done, int mode) {
-  int lb;
-  const VolDesc& vd = vol_of(vds, nullptr, lb);
+template <int E>
+static __global__ __launch_bounds__(1024) void k_class_normal(const VolDesc* __restrict__ vds, int check_done, int mode) {
+  const VolDesc& vd = vds[0];
+  const int lb = blockIdx.x;
   if (check_done && vd.st->done) return;
-  class_normal_body<HC, E>(vd, plane_of_block(lb, gridDim.x), mode);
+  class_normal_body<E>(vd, plane_of_block(lb, gridDim.x), mode);
 }
-template <int HC, int E, bool VEC>
-__global__ __launch_bounds__(1024) void k_class_adj(const VolDesc* __restrict__ vds, int check_done) {
-  int lb;
-  const VolDesc& vd = vol_of(vds, nullptr, lb);
+template <int E, bool VEC>
+static __global__ __launch_bounds__(1024) void k_class_adj(const VolDesc* __restrict__ vds, int check_done) {
+  const VolDesc& vd = vds[0];
+  const int lb = blockIdx.x;
   if (check_done && vd.st->done) return;
-  class_adj_body<HC, E, VEC>(vd, plane_of_block(lb, gridDim.x));
+  class_adj_body<E, VEC>(vd, plane_of_block(lb, gridDim.x));
 }
-
-// Batched class passes over a task table (compact spectra), the element split E
-// of each volume dispatched per block.  Volumes whose solve is done are skipped.
-#define MH3D_E_SWITCH(BODY, ...)                         \
-  switch (vd.g.E) {                                      \
-    case 8: BODY<0, 8>(vd, lb __VA_ARGS__); break;       \
-    case 6: BODY<0, 6>(vd, lb __VA_ARGS__); break;       \
-    case 4: BODY<0, 4>(vd, lb __VA_ARGS__); break;       \
-    case 3: BODY<0, 3>(vd, lb __VA_ARGS__); break;       \
-    case 2: BODY<0, 2>(vd, lb __VA_ARGS__); break;       \
-    case 9: BODY<0, 9>(vd, lb __VA_ARGS__); break;       \
-    default: BODY<0, 1>(vd, lb __VA_ARGS__); break;      \
-  }
-// Padded volumes of a batch (mode FWD_G: their small-grid pass crops to the field of view).
-__global__ __launch_bounds__(1024) void k_class_fwd_batch(const VolDesc* __restrict__ vds, const int2* __restrict__ tasks,
-                                                          int mode) {
-  int lb;
-  const VolDesc& vd = vol_of(vds, tasks, lb);
-  if (vd.st->done) return;
-  MH3D_E_SWITCH(class_fwd_body, , mode)
-}
-// mode: NRM_RESID (solver) or NRM_PLAIN (power iteration); volumes without padding.
-__global__ __launch_bounds__(1024) void k_class_normal_batch(const VolDesc* __restrict__ vds, const int2* __restrict__ tasks,
-                                                             int mode) {
-  int lb;
-  const VolDesc& vd = vol_of(vds, tasks, lb);
-  if (vd.st->done) return;
-  MH3D_E_SWITCH(class_normal_body, , mode)
-}
-__global__ __launch_bounds__(1024) void k_class_adj_batch(const VolDesc* __restrict__ vds, const int2* __restrict__ tasks) {
-  int lb;
-  const VolDesc& vd = vol_of(vds, tasks, lb);
-  if (vd.st->done) return;
-  MH3D_E_SWITCH(class_adj_body, )
-}
-#undef MH3D_E_SWITCH
 
 // ============================================================================ pass 3: small grid
 enum { EPI_STORE = 0, EPI_RESID = 1, EPI_RESID_BACK = 2, EPI_BACK = 3, EPI_STORE_BACK = 4 };
-
-// Small-grid LDS layout: column (xi, q'z) holds the y' line at
-// X[(xi*mzh + q'z)*lsmy + y'], rows r = xi*my + y' of real data are packed in pairs.
-__device__ __forceinline__ RowCols small_rowcols(const Geo& g) {
-  RowCols rc;
-  rc.qstride = g.lsmy;
-  rc.per_blk = g.my;
-  rc.f_blk = g.f_my;
-  rc.blk_stride = g.mzh * g.lsmy;
-  return rc;
-}
-
-// 2-D R2C over (y', z') of the small-grid rows held as packed pairs in *a, then
-// store the class layout G[k][xbi][class][xi].
-__device__ void small_r2c_and_store(const Geo& g, float2* a, float2* b, const float2* twy, const float2* twz,
-                                    float2* __restrict__ Gout, int k, int xbi) {
-  const int rows = g.xb * g.my;
-  float2* X = r2c_rows(a, b, twz, rows, g.mz, g.mzh, g.spairs, small_rowcols(g), g.f_mzh);
-  float2* Y = fft_lines<-1>(X, X == a ? b : a, twy, g.my, g.xb * g.mzh, g.lsmy);
-  const int nxb = g.mx / g.xb;
-  float2* dst = Gout + ((long long)k * nxb + xbi) * g.ncls * g.xb;
-  for (int p = threadIdx.x; p < g.ncls * g.xb; p += blockDim.x) {
-    const int c = (int)g.f_xb.div((uint32_t)p), xi = p - c * g.xb;
-    const int qy = (int)g.f_mzh.div((uint32_t)c), qz = c - qy * g.mzh;
-    dst[p] = Y[(xi * g.mzh + qz) * g.lsmy + qy];
-  }
-}
-
-// Portrait index of element p = (xi*my + y')*mz + z' of x'-block xbi, harmonic k, in
-// the field-of-view portraits [K][mxf][myf][mzf]; -1 for a sample of the padding.
-__device__ __forceinline__ long long fov_index(const Geo& g, int k, int xbi, int p) {
-  const int r = (int)g.f_mz.div((uint32_t)p), z = p - r * g.mz;
-  const int xi = (int)g.f_my.div((uint32_t)r), y = r - xi * g.my;
-  const int xf = xbi * g.xb + xi - g.pxs, yf = y - g.pys, zf = z - g.pzs;
-  if ((unsigned)xf >= (unsigned)g.mxf || (unsigned)yf >= (unsigned)g.myf || (unsigned)zf >= (unsigned)g.mzf) return -1;
-  return (long long)k * g.Mf + ((long long)xf * g.myf + yf) * g.mzf + zf;
-}
-
-// Forward pass 3 (and, with EPI_RESID_BACK / EPI_BACK, the first adjoint pass on
-// the result).  One block per (k, x'-block).  EPI_RESID_BACK uses the volume's data
-// and is skipped once its solve is done.  LDS: tables (my + mz) + 2 * small_lds.
-template <int EPI>
-__device__ __forceinline__ void small_inv_body(const VolDesc& vd, int lb, float* __restrict__ d) {
-  const Geo& g = vd.g;
-  if constexpr (EPI == EPI_RESID_BACK || EPI == EPI_BACK) {
-    if (vd.st->done) return;
-  }
-  const float* __restrict__ dmeas = vd.d;
-  extern __shared__ float2 lds[];
-  const int sl = small_lds(g);
-  float2* twy = lds;
-  float2* twz = twy + g.my;
-  float2* P0 = twz + g.mz;
-  float2* P1 = P0 + sl;
-  load_table(twy, vd.tw + vd.off[4], g.my);
-  load_table(twz, vd.tw + vd.off[5], g.mz);
-  const int nxb = g.mx / g.xb;
-  const int k = lb / nxb, xbi = lb - (lb / nxb) * nxb;
-  const float2* src = vd.G + ((long long)k * nxb + xbi) * g.ncls * g.xb;
-  batched<8, float2>(g.ncls * g.xb, [&](int p) { return src[p]; },
-                     [&](int p, float2 v) {
-                       const int c = (int)g.f_xb.div((uint32_t)p), xi = p - c * g.xb;
-                       const int qy = (int)g.f_mzh.div((uint32_t)c), qz = c - qy * g.mzh;
-                       P0[(xi * g.mzh + qz) * g.lsmy + qy] = v;
-                     });
-  float2* X = fft_lines<+1>(P0, P1, twy, g.my, g.xb * g.mzh, g.lsmy);
-  const int rows = g.xb * g.my;
-  float2* Z = c2r_rows(X, X == P0 ? P1 : P0, twz, rows, g.mz, g.spairs, small_rowcols(g), g.f_mz);
-  // Z holds packed real rows: row r at pair r/2, .x (even) / .y (odd), line stride lsmz
-  const int lsmz = pad_odd(g.mz);
-  float* Zf = reinterpret_cast<float*>(Z);
-  const long long obase = (long long)k * g.M + (long long)xbi * g.xb * g.my * g.mz;
-  const int n = rows * g.mz;
-  auto lidx = [&](int p) {
-    const int r = (int)g.f_mz.div((uint32_t)p), z = p - r * g.mz;
-    return 2 * ((r >> 1) * lsmz + z) + (r & 1);
-  };
-  if (g.padded) {
-    // boundary padding: only the field-of-view samples are data (C P); the padding's
-    // samples of the residual are zero (C^T C P)
-    if constexpr (EPI == EPI_STORE || EPI == EPI_STORE_BACK) {
-      for (int p = threadIdx.x; p < n; p += blockDim.x) {
-        const long long di = fov_index(g, k, xbi, p);
-        const int li = lidx(p);
-        if (di >= 0) d[di] = Zf[li];
-        else if (EPI == EPI_STORE_BACK) Zf[li] = 0.f;
-      }
-    } else if constexpr (EPI == EPI_RESID) {
-      for (int p = threadIdx.x; p < n; p += blockDim.x) {
-        const long long di = fov_index(g, k, xbi, p);
-        if (di >= 0) d[di] = Zf[lidx(p)] - dmeas[di];
-      }
-    } else if constexpr (EPI == EPI_RESID_BACK) {
-      for (int p = threadIdx.x; p < n; p += blockDim.x) {
-        const long long di = fov_index(g, k, xbi, p);
-        const int li = lidx(p);
-        Zf[li] = di >= 0 ? Zf[li] - dmeas[di] : 0.f;
-      }
-    } else if constexpr (EPI == EPI_BACK) {
-      for (int p = threadIdx.x; p < n; p += blockDim.x)
-        if (fov_index(g, k, xbi, p) < 0) Zf[lidx(p)] = 0.f;
-    }
-  } else if constexpr (EPI == EPI_STORE || EPI == EPI_STORE_BACK) {
-    for (int p = threadIdx.x; p < n; p += blockDim.x) d[obase + p] = Zf[lidx(p)];
-  } else if constexpr (EPI == EPI_RESID) {
-    batched<8, float>(n, [&](int p) { return dmeas[obase + p]; },
-                      [&](int p, float m) { d[obase + p] = Zf[lidx(p)] - m; });
-  } else if constexpr (EPI == EPI_RESID_BACK) {
-    batched<8, float>(n, [&](int p) { return dmeas[obase + p]; },
-                      [&](int p, float m) { const int li = lidx(p); Zf[li] = Zf[li] - m; });
-  }
-  // EPI_BACK keeps the values in place; EPI_STORE_BACK stores them and transforms them back
-  if constexpr (EPI == EPI_RESID_BACK || EPI == EPI_BACK || EPI == EPI_STORE_BACK) {
-    if (rows & 1) {
-      for (int z = threadIdx.x; z < g.mz; z += blockDim.x) Zf[2 * ((rows >> 1) * lsmz + z) + 1] = 0.f;
-    }
-    small_r2c_and_store(g, Z, Z == P0 ? P1 : P0, twy, twz, vd.Gp, k, xbi);
-  }
-}
-template <int EPI>
-__global__ __launch_bounds__(1024) void k_small_inv(const VolDesc* __restrict__ vds, const int2* __restrict__ tasks,
-                                                    float* __restrict__ d) {
-  int lb;
-  const VolDesc& vd = vol_of(vds, tasks, lb);
-  small_inv_body<EPI>(vd, lb, d);
-}
-
-// Adjoint pass 3: R2C of the portraits r.  One block per (k, x'-block).
-// out: the spectra's destination (NULL: G').
-__global__ __launch_bounds__(1024) void k_small_fwd(const VolDesc* __restrict__ vds, const float* __restrict__ r,
-                                                   float2* __restrict__ out) {
-  int lb;
-  const VolDesc& vd = vol_of(vds, nullptr, lb);
-  const Geo& g = vd.g;
-  extern __shared__ float2 lds[];
-  const int sl = small_lds(g);
-  float2* twy = lds;
-  float2* twz = twy + g.my;
-  float2* P0 = twz + g.mz;
-  float2* P1 = P0 + sl;
-  load_table(twy, vd.tw + vd.off[4], g.my);
-  load_table(twz, vd.tw + vd.off[5], g.mz);
-  const int nxb = g.mx / g.xb;
-  const int k = lb / nxb, xbi = lb - (lb / nxb) * nxb;
-  const int rows = g.xb * g.my;
-  const int lsmz = pad_odd(g.mz);
-  const long long ibase = (long long)k * g.M + (long long)xbi * g.xb * g.my * g.mz;
-  float* Zf = reinterpret_cast<float*>(P0);
-  const int n = rows * g.mz;
-  // with boundary padding the portraits cover the field of view: C^T r is zero outside
-  batched<8, float>(n, [&](int p) {
-                      if (!g.padded) return r[ibase + p];
-                      const long long di = fov_index(g, k, xbi, p);
-                      return di >= 0 ? r[di] : 0.f;
-                    },
-                    [&](int p, float v) {
-                      const int rr = (int)g.f_mz.div((uint32_t)p), z = p - rr * g.mz;
-                      Zf[2 * ((rr >> 1) * lsmz + z) + (rr & 1)] = v;
-                    });
-  if (rows & 1) {
-    for (int z = threadIdx.x; z < g.mz; z += blockDim.x) Zf[2 * ((rows >> 1) * lsmz + z) + 1] = 0.f;
-  }
-  small_r2c_and_store(g, P0, P1, twy, twz, out ? out : vd.Gp, k, xbi);
-}
 
 // ============================================================================ pass 1 adjoint
 enum { OUT_SCALE_B = 0, OUT_U = 1, OUT_STEP_NORMAL = 2, OUT_STEP_FISTA = 3 };
@@ -1396,11 +1059,8 @@ __device__ __forceinline__ void plane_adj_body(const VolDesc& vd, int lb, const 
   }
 }
 template <int OUT>
-__global__ __launch_bounds__(1024) void k_plane_adj(const VolDesc* __restrict__ vds, const int2* __restrict__ tasks,
-                                                    AdjOut ao) {
-  int lb;
-  const VolDesc& vd = vol_of(vds, tasks, lb);
-  plane_adj_body<OUT>(vd, lb, ao);
+static __global__ __launch_bounds__(1024) void k_plane_adj(const VolDesc* __restrict__ vds, AdjOut ao) {
+  plane_adj_body<OUT>(vds[0], blockIdx.x, ao);
 }
 
 // A solver update's adjoint plane pass and step (OUT_STEP_FISTA), then, in the same
@@ -1409,27 +1069,14 @@ __global__ __launch_bounds__(1024) void k_plane_adj(const VolDesc* __restrict__ 
 // only that plane's y, so with one workgroup per x-plane (ps = 1) no other block is
 // awaited, and the next update starts at its class pass.  If this step ends the solve,
 // the extra forward pass is unused.  grid = nx blocks (ps must be 1).
-__global__ __launch_bounds__(1024) void k_step_and_fwd(const VolDesc* __restrict__ vds, const int2* __restrict__ tasks,
-                                                       AdjOut ao) {
-  int lb;
-  const VolDesc& vd = vol_of(vds, tasks, lb);
+static __global__ __launch_bounds__(1024) void k_step_and_fwd(const VolDesc* __restrict__ vds, AdjOut ao) {
+  const VolDesc& vd = vds[0];
+  const int lb = blockIdx.x;
   if (vd.st->done) return;
   const float* ynext = vd.y[(vd.st->k + 1) & 1];
   plane_adj_body<OUT_STEP_FISTA>(vd, lb, ao);
   __syncthreads();   // the block's stores of y^{k+1} are visible to it; the LDS is free
   plane_fwd_body<SRC_PLAIN>(vd, lb, ynext);
-}
-
-// The two passes after the fused class pass in A then A^T, in one launch: both read only
-// what that pass wrote, so blocks [0, ps nx) run the adjoint plane pass (ao.out = b . v)
-// while the others run the small-grid inverse pass that writes the portraits d.  The
-// plane blocks come first (their XCD-aware plane order assumes block ids 0 .. ps nx - 1);
-// the small-grid blocks run beside them.  Both bodies loop over blockDim (512 or 1024).
-__global__ __launch_bounds__(1024) void k_adj_and_store(const VolDesc* __restrict__ vds, AdjOut ao, float* __restrict__ d) {
-  const VolDesc& vd = vds[0];
-  const int nplane = vd.g.ps * vd.g.nx;
-  if ((int)blockIdx.x < nplane) plane_adj_body<OUT_SCALE_B>(vd, blockIdx.x, ao);
-  else small_inv_body<EPI_STORE>(vd, blockIdx.x - nplane, d);
 }
 
 // Blocks of the volume-wide update pass, each a contiguous run of whole UPD_THREADS-voxel
@@ -1446,10 +1093,9 @@ __host__ __device__ inline int update_blocks(long long n) {
 // block leaves its FP64 sums in vd.partials; k_vol_finish reduces them and updates the
 // state.  grid = vd.nb_upd blocks of UPD_THREADS threads per volume.
 template <int UPD>
-__global__ __launch_bounds__(UPD_THREADS) void k_vol_update(const VolDesc* __restrict__ vds, const int2* __restrict__ tasks,
-                                                    AdjOut ao) {
-  int lb;
-  const VolDesc& vd = vol_of(vds, tasks, lb);
+static __global__ __launch_bounds__(UPD_THREADS) void k_vol_update(const VolDesc* __restrict__ vds, AdjOut ao) {
+  const VolDesc& vd = vds[0];
+  const int lb = blockIdx.x;
   const Geo& g = vd.g;
   if (vd.st->done) return;
   __shared__ double red[64];
@@ -1486,7 +1132,7 @@ __global__ __launch_bounds__(UPD_THREADS) void k_vol_update(const VolDesc* __res
 // t, t + 256, ..., then the fixed-order block reduction) and advances the state.
 // One block per volume; the kernel boundary orders it after every partial store.
 template <int UPD>
-__global__ __launch_bounds__(256) void k_vol_finish(const VolDesc* __restrict__ vds, const int2* __restrict__ tasks) {
+static __global__ __launch_bounds__(256) void k_vol_finish(const VolDesc* __restrict__ vds, const int2* __restrict__ tasks) {
   int lb;
   const VolDesc& vd = vol_of(vds, tasks, lb);
   DevState* st = vd.st;
@@ -1541,7 +1187,7 @@ struct MhadW {
   double cinv[32];    // 1 / c_k
 };
 
-__global__ __launch_bounds__(256) void k_mhad(const float* __restrict__ d, int K, MhadW wk, double lam, int m,
+static __global__ __launch_bounds__(256) void k_mhad(const float* __restrict__ d, int K, MhadW wk, double lam, int m,
                                               long long C, int CB, float* __restrict__ out) {
   extern __shared__ float2 sm[];
   const int ls = pad_odd(m);
@@ -1603,7 +1249,7 @@ __global__ __launch_bounds__(256) void k_mhad(const float* __restrict__ d, int K
 // y^{k0} = rho^{k0} + (k0-1)/(k0+2) (rho^{k0} - rho^{k0-1}) for a (re)started solve.
 // y^{k0} = rho^{k0} + beta (rho^{k0} - rho^{k0-1}), rounded as the step forms y^{k+1}
 // (no contraction), so a resumed solve continues bitwise as the uninterrupted one.
-__global__ void k_fista_init(long long n, const float* __restrict__ rk, const float* __restrict__ rkm1,
+static __global__ void k_fista_init(long long n, const float* __restrict__ rk, const float* __restrict__ rkm1,
                              float beta, float* __restrict__ y) {
 #pragma clang fp contract(off)
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
@@ -1614,7 +1260,7 @@ __global__ void k_fista_init(long long n, const float* __restrict__ rk, const fl
 
 // ============================================================================ plan-time kernels
 // Twiddle tables exp(-2 pi i t / n), FP64 evaluation, FP32 and FP64 copies.
-__global__ void k_twiddles(int n, float2* __restrict__ t32, double2* __restrict__ t64) {
+static __global__ void k_twiddles(int n, float2* __restrict__ t32, double2* __restrict__ t64) {
   for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
     double s, c;
     sincospi(2.0 * (double)t / (double)n, &s, &c);
@@ -1624,7 +1270,7 @@ __global__ void k_twiddles(int n, float2* __restrict__ t32, double2* __restrict_
 }
 
 // Gaussian sensitivity, peak 1 at the geometric centre ((N-1)/2 voxel).
-__global__ void k_sensitivity(Geo g, double vox, double sx, double sy, double sz, float* __restrict__ b) {
+static __global__ void k_sensitivity(Geo g, double vox, double sx, double sy, double sz, float* __restrict__ b) {
   const long long n = g.N;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
     const int z = (int)(i % g.nz);
@@ -1641,7 +1287,7 @@ __device__ __forceinline__ int signed_offset(int i, int n) { return (2 * i < n) 
 
 // Drive-axis profiles f_k(x) = L^(order_k)(a vox w(x)) (symmetric mean at x = nx/2
 // for even nx), their FFT along x in FP64, and ||f_k||^2.  grid = K blocks.
-__global__ __launch_bounds__(256) void k_psf_profile(int nx, const int* __restrict__ order, double a_vox,
+static __global__ __launch_bounds__(256) void k_psf_profile(int nx, const int* __restrict__ order, double a_vox,
                                                      const double2* __restrict__ tw64,
                                                      double* __restrict__ prof, double2* __restrict__ fhat,
                                                      double* __restrict__ fnorm2) {
@@ -1674,7 +1320,7 @@ __global__ __launch_bounds__(256) void k_psf_profile(int nx, const int* __restri
 
 // Transverse envelope E(y, z) = L'(a r)/r, E(0) = L'(0) 4 asinh(1)/vox, one row per
 // block, then FFT along z (FP64).  Also per-row sum of E^2.  grid = ny blocks.
-__global__ __launch_bounds__(256) void k_psf_env_rows(int ny, int nz, double a, double vox,
+static __global__ __launch_bounds__(256) void k_psf_env_rows(int ny, int nz, double a, double vox,
                                                       const double2* __restrict__ tw64z,
                                                       double* __restrict__ env, double2* __restrict__ tmp,
                                                       double* __restrict__ rowsum) {
@@ -1704,7 +1350,7 @@ __global__ __launch_bounds__(256) void k_psf_env_rows(int ny, int nz, double a, 
 }
 
 // FFT along y of the row-transformed envelope, one column per block (qz <= nz/2).
-__global__ __launch_bounds__(256) void k_psf_env_cols(int ny, int nz, const double2* __restrict__ tw64y,
+static __global__ __launch_bounds__(256) void k_psf_env_cols(int ny, int nz, const double2* __restrict__ tw64y,
                                                       const double2* __restrict__ tmp, double2* __restrict__ ehat) {
   extern __shared__ double2 lds64[];
   double2* tw = lds64;
@@ -1718,7 +1364,7 @@ __global__ __launch_bounds__(256) void k_psf_env_cols(int ny, int nz, const doub
 }
 
 // scale[k] = 1 / (||f_k|| ||E|| N)   (unit-norm PSF, unnormalised FFTs downstream)
-__global__ void k_psf_scales(int K, int ny, long long N, const double* __restrict__ fnorm2,
+static __global__ void k_psf_scales(int K, int ny, long long N, const double* __restrict__ fnorm2,
                              const double* __restrict__ rowsum, double* __restrict__ scale) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     double e2 = 0.0;
@@ -1727,39 +1373,58 @@ __global__ void k_psf_scales(int K, int ny, long long N, const double* __restric
   }
 }
 
-// Spectrum in the class layout [k][class][q'x][jx][member], scaled by 1/N:
-// Hs = F_k(qx) Ehat(qy, qz) scale_k.  Compact form stores Re (odd order) or Im
-// (even order); complex form stores both.
-__global__ void k_psf_assemble(Geo g, const double2* __restrict__ fhat, const double2* __restrict__ ehat,
-                               const double* __restrict__ scale, uint32_t imag_mask, int compact,
-                               void* __restrict__ hs) {
-  const long long total = (long long)g.K * g.hsz;
-  const int per_cls = g.mx * g.S;
+// Plan-time tables of the separable passes (FP64 sums, FP32 storage):
+//   sfs[k][qx]        scale_k F_k(qx) (its real part, or its imaginary part when bit k of
+//                     imag_mask is set), the x factor of the stored spectra
+//   set[y0][q'y][qz]  Et(y0, q'y, qz) = sum_jy w_ny^(y0 qy) Ehat(qy, qz), qz <= nz/2
+static __global__ void k_sep_tables(Geo g, const double2* __restrict__ fhat, const double2* __restrict__ ehat,
+                             const double* __restrict__ scale, uint32_t imag_mask,
+                             const double2* __restrict__ tw64y, float* __restrict__ sfs, float2* __restrict__ set) {
+  const int nf = g.K * g.nx;
+  const int ne = g.sy * g.my * g.nzh;
+  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < nf + ne; t += gridDim.x * blockDim.x) {
+    if (t < nf) {
+      const int k = t / g.nx;
+      const double2 f = fhat[t];
+      sfs[t] = (float)((((imag_mask >> k) & 1u) ? f.y : f.x) * scale[k]);
+    } else {
+      const int r = t - nf;
+      const int y0 = r / (g.my * g.nzh), r2 = r - y0 * (g.my * g.nzh);
+      const int qyp = r2 / g.nzh, qz = r2 - qyp * g.nzh;
+      double sr = 0.0, si = 0.0;
+      for (int jy = 0; jy < g.sy; ++jy) {
+        const int qy = qyp + jy * g.my;
+        const double2 w = tw64y[(long long)y0 * qy % g.ny];   // exp(-2 pi i y0 qy / ny)
+        const double2 e = ehat[(long long)qy * g.nzh + qz];
+        sr += w.x * e.x - w.y * e.y;
+        si += w.x * e.y + w.y * e.x;
+      }
+      set[r] = make_float2((float)sr, (float)si);
+    }
+  }
+}
+
+// fft(h_k) of the analytic PSF, [k][nx][ny][nzh] complex, from its factors: F_k(qx) Ehat(qy,
+// qz) scale_k N, rounded to FP32 as the separable tables round it (its real part for odd
+// orders, its imaginary part for even ones; tests and tools).
+static __global__ void k_spectrum_analytic(Geo g, const double2* __restrict__ fhat, const double2* __restrict__ ehat,
+                                    const double* __restrict__ scale, uint32_t imag_mask, float2* __restrict__ out) {
+  const long long per_k = (long long)g.nx * g.ny * g.nzh, total = (long long)g.K * per_k;
+  const float Nf = (float)g.N;
   for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t < total; t += (long long)gridDim.x * blockDim.x) {
-    const int k = (int)(t / g.hsz);
-    const long long r = t % g.hsz;
-    const int c = (int)(r / per_cls);
-    const int r2 = (int)(r % per_cls);
-    const int qxp = r2 / g.S, w = r2 % g.S;
-    const int jx = w / g.nmem, m = w % g.nmem;
-    const int qx = qxp + jx * g.mx;
-    const int qy = (c / g.mzh) + (m / g.sz) * g.my;
-    const int qz = (c % g.mzh) + (m % g.sz) * g.mz;
-    double2 e;
-    if (2 * qz <= g.nz) e = ehat[(long long)qy * g.nzh + qz];
-    else { e = ehat[(long long)((g.ny - qy) % g.ny) * g.nzh + (g.nz - qz)]; e.y = -e.y; }
-    const double2 f = fhat[(long long)k * g.nx + qx];
+    const int k = (int)(t / per_k);
+    const long long r = t % per_k;
+    const double2 f = fhat[(long long)k * g.nx + r / ((long long)g.ny * g.nzh)];
+    const double2 e = ehat[r % ((long long)g.ny * g.nzh)];
     const double s = scale[k];
-    const double hr = (f.x * e.x - f.y * e.y) * s;
-    const double hi = (f.x * e.y + f.y * e.x) * s;
-    if (compact) reinterpret_cast<float*>(hs)[t] = (float)(((imag_mask >> k) & 1u) ? hi : hr);
-    else reinterpret_cast<float2*>(hs)[t] = make_float2((float)hr, (float)hi);
+    out[t] = ((imag_mask >> k) & 1u) ? make_float2(0.f, (float)((f.x * e.y + f.y * e.x) * s) * Nf)
+                                     : make_float2((float)((f.x * e.x - f.y * e.y) * s) * Nf, 0.f);
   }
 }
 
 // User PSF spectra: FFT along x of the class-layout yz spectrum of h_k, scaled by
 // 1/N, stored complex in the class layout.  grid = ncls/cpw blocks, cpw*nmem lines.
-__global__ __launch_bounds__(1024) void k_class_hcopy(Geo g, int k, const float2* __restrict__ uperm,
+static __global__ __launch_bounds__(1024) void k_class_hcopy(Geo g, int k, const float2* __restrict__ uperm,
                                                       float2* __restrict__ hs, const float2* __restrict__ tw_x) {
   extern __shared__ float2 lds[];
   float2* twx = lds;
@@ -1792,7 +1457,7 @@ __global__ __launch_bounds__(1024) void k_class_hcopy(Geo g, int k, const float2
 // Flags of the PSF blocks that are not identically zero: blockIdx.x = j selects the
 // (component, harmonic) block psf + j * N, blockIdx.y = s one of gridDim.y strided
 // shares of it; flags[j * gridDim.y + s] = any nonzero in the share.
-__global__ __launch_bounds__(256) void k_nonzero_blocks(const float* __restrict__ psf, long long N,
+static __global__ __launch_bounds__(256) void k_nonzero_blocks(const float* __restrict__ psf, long long N,
                                                         int* __restrict__ flags) {
   const float* p = psf + (long long)blockIdx.x * N;
   const long long step = (long long)gridDim.y * blockDim.x;
@@ -1803,8 +1468,7 @@ __global__ __launch_bounds__(256) void k_nonzero_blocks(const float* __restrict_
 }
 
 // Back from the class layout to [k][nx][ny][nzh] complex, times N (tests/tools).
-__global__ void k_spectrum_export(Geo g, const void* __restrict__ hs, uint32_t imag_mask, int compact,
-                                  float2* __restrict__ out) {
+static __global__ void k_spectrum_export(Geo g, const float2* __restrict__ hs, float2* __restrict__ out) {
   const long long per_k = (long long)g.nx * g.ny * g.nzh;
   const long long total = (long long)g.K * per_k;
   const int per_cls = g.mx * g.S;
@@ -1820,11 +1484,7 @@ __global__ void k_spectrum_export(Geo g, const void* __restrict__ hs, uint32_t i
     const int qxs = cj ? (g.nx - qx) % g.nx : qx;   // conjugate partner also negates qx
     const int qxp = qxs % g.mx, jx = qxs / g.mx;
     const long long idx = (long long)k * g.hsz + (long long)c * per_cls + qxp * g.S + jx * g.nmem + m;
-    float2 v;
-    if (compact) {
-      const float f = reinterpret_cast<const float*>(hs)[idx];
-      v = ((imag_mask >> k) & 1u) ? make_float2(0.f, f) : make_float2(f, 0.f);
-    } else v = reinterpret_cast<const float2*>(hs)[idx];
+    float2 v = hs[idx];
     if (cj) v.y = -v.y;
     const float Nf = (float)g.N;
     out[t] = make_float2(v.x * Nf, v.y * Nf);
@@ -1846,7 +1506,7 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32
   }
 }
 
-__global__ void k_philox_uniform(long long n, uint64_t seed, uint32_t stream, float* __restrict__ out,
+static __global__ void k_philox_uniform(long long n, uint64_t seed, uint32_t stream, float* __restrict__ out,
                                  double* __restrict__ partials, DevState* st) {
   __shared__ double red[64];
   double acc[1] = {0.0};
@@ -1867,7 +1527,7 @@ __global__ void k_philox_uniform(long long n, uint64_t seed, uint32_t stream, fl
 }
 
 // Raw Philox words for the known-answer test.
-__global__ void k_philox_words(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1,
+static __global__ void k_philox_words(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1,
                                uint32_t* __restrict__ out) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     uint32_t c[4] = {c0, c1, c2, c3};

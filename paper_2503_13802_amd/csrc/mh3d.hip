@@ -16,7 +16,7 @@
 
 #include "../../include/mh3d.h"
 #include "kernels.hpp"
-#include "fast.hpp"
+#include "passes.hpp"
 
 using namespace mh3d;
 
@@ -66,7 +66,70 @@ struct Launch {
   // with 512 two blocks share a CU, so more small-grid blocks run beside the plane blocks
   int T_merge;
   size_t lds_plane, lds_class, lds_small;
+  // the separable passes of analytic plans (sep.hpp)
+  int T_sep, T_col, col_blocks;
+  bool col_any;            // column passes of the general form (more than one group or 4 x aliases)
+  size_t lds_sep, lds_col, lds_col_resid, lds_col_plain;
+  size_t lds_col_of(int mode) const {
+    return mode == NRM_RESID ? lds_col_resid : mode == NRM_PLAIN ? lds_col_plain : lds_col;
+  }
 };
+
+static int pow2_at_least(int n) {
+  int p = 1;
+  while (p < n) p *= 2;
+  return p;
+}
+
+// Launch shapes of the separable and small-grid passes.
+static void derive_sep(Geo& g, Launch& L) {
+  SepGeo& s = g.sep;
+  s.np = (g.my + 1) / 2;
+  s.lsz = pad_odd(g.nz);
+  s.lsy = pad_odd(g.my);
+  s.pbuf = std::max(s.np * s.lsz, g.nzh * s.lsy);
+  // columns per block: 4 (32-byte runs of the shares, of Q and of G), more while a block
+  // would have less than a wave of (column, q'x) threads, fewer beyond 256 (the largest
+  // blocks leave too few per CU to overlap their chains)
+  s.cpc = 4;
+  while (s.cpc * g.mx < 64 && s.cpc < 16) s.cpc *= 2;
+  while (s.cpc * g.mx > 256 && s.cpc > 2) s.cpc /= 2;
+  // x lines: with 4 lines per block a stride of 6 mod 32 spreads the lanes of a stage over
+  // the banks (an odd one does from 8 lines on)
+  s.lsx = g.nx;
+  if (s.cpc <= 4) while (s.lsx % 32 != 6) ++s.lsx;
+  else s.lsx = pad_odd(g.nx);
+  s.lsm = pad_odd(g.mx);
+  // harmonics per group: as many folded spectra as leave room for two blocks per CU
+  const size_t fixed = sizeof(float2) * ((size_t)g.nx + g.mx + 2 * (size_t)s.cpc * s.lsx) +
+                       sizeof(float) * (((size_t)g.K * g.nx + 1) & ~(size_t)1);
+  const size_t per = sizeof(float2) * (size_t)s.cpc * s.lsm;
+  s.kg = 1;
+  while (s.kg < g.K && fixed + 2 * (s.kg + 1) * per <= kLdsLimit / 2) ++s.kg;
+  L.lds_col = fixed + 2 * s.kg * per;
+  // without G to store (and the x aliases in registers) a pass needs no F0, and F1 only for
+  // the data terms: more blocks per CU in the solver
+  L.col_any = s.kg < g.K || g.sx > SXR;
+  L.lds_col_resid = g.sx <= 4 ? fixed + s.kg * per : L.lds_col;
+  L.lds_col_plain = g.sx <= 4 ? fixed : L.lds_col;
+  L.T_col = std::max(128, (s.cpc * g.mx + 63) / 64 * 64);
+  L.col_blocks = (g.ncls + s.cpc - 1) / s.cpc;
+  // plane and small-grid blocks: four points per thread (two threads per radix-8 butterfly:
+  // the loads, the splits and the stores are shared by more threads than the stages need)
+  L.T_sep = std::min(512, std::max(128, pow2_at_least(s.np * g.nz / 4)));
+  L.lds_sep = sizeof(float2) * ((size_t)g.nz + g.my + 2 * (size_t)s.pbuf);
+  s.lsmz = pad_odd(g.mz);
+  s.nxb = g.mx / g.xb;
+  L.T_small = std::min(512, std::max(256, pow2_at_least(g.spairs * g.mz / 4)));
+  s.d_sy = make_mdiv(g.sy); s.d_np = make_mdiv(s.np); s.d_nzh = make_mdiv(g.nzh); s.d_mzh = make_mdiv(g.mzh);
+  s.d_nzv = make_mdiv(g.nz / (g.nz % 4 ? 2 : 4));
+  s.d_mz = make_mdiv(g.mz); s.d_mzv = make_mdiv(g.mz / (g.mz % 4 ? 2 : 4));
+  s.d_my = make_mdiv(g.my); s.d_mx = make_mdiv(g.mx); s.d_cpc = make_mdiv(s.cpc);
+  s.d_cpcmx = make_mdiv(s.cpc * g.mx); s.d_cpcxb = make_mdiv(s.cpc * g.xb); s.d_xb = make_mdiv(g.xb);
+  const int last = g.K - (g.K - 1) / s.kg * s.kg;   // harmonics of the last group
+  s.d_kgcpc = make_mdiv(s.kg * s.cpc); s.d_klcpc = make_mdiv(last * s.cpc);
+  s.d_spairs = make_mdiv(g.spairs); s.d_xbmzh = make_mdiv(g.xb * g.mzh); s.d_nxb = make_mdiv(s.nxb);
+}
 
 // A class-kernel element split e is valid when it is one of the compiled splits
 // (1, 2, 3, 4, 6, 8, 9), divides S, and S/e is a power of two <= 64 (the fold
@@ -134,7 +197,10 @@ static mh3d_status derive_tiles(Geo& g, Launch& L, int E_req, int cpw_req, int x
     g.xb = 1;
     for (int xb : {8, 4, 2, 1}) {
       if (g.mx % xb) continue;
-      if ((long)g.K * (g.mx / xb) >= 256 || xb == 1) { g.xb = xb; break; }
+      // (at most 2048 samples per block: larger planes fill a block on their own, and a block
+      // of several would leave CUs idle: 64 x 64 planes of 128 x', K = 8, in blocks of 4
+      // took 24 us)
+      if (xb == 1 || ((long)g.K * (g.mx / xb) >= 256 && xb * g.my * g.mz <= 2048)) { g.xb = xb; break; }
     }
   }
   g.spairs = (g.xb * g.my + 1) / 2;
@@ -149,9 +215,7 @@ static mh3d_status derive_tiles(Geo& g, Launch& L, int E_req, int cpw_req, int x
   g.f_W = make_fastdiv(g.cpw * g.nmem); g.f_xb = make_fastdiv(g.xb); g.f_S = make_fastdiv(g.S);
   g.f_mxS = make_fastdiv(g.mx * g.S); g.f_cpwmx = make_fastdiv(g.cpw * g.mx);
   g.f_cpwxb = make_fastdiv(g.cpw * g.xb); g.f_ny = make_fastdiv(g.ny); g.f_my = make_fastdiv(g.my);
-  // 256 threads per decimated x'-plane of the block (the small-grid kernels loop over
-  // blockDim, so the count only sets how much of the block's work runs side by side)
-  L.T_small = std::min(1024, 256 * g.xb);
+  derive_sep(g, L);
   L.T_merge = g.ps >= 2 ? 512 : 1024;   // the autotuner times both
   L.lds_small = sizeof(float2) * ((size_t)g.my + g.mz + 2 * (size_t)small_lds(g));
   if (L.lds_small > kLdsLimit) return fail(MH3D_ERR_UNSUPPORTED, "small-grid plane does not fit in LDS");
@@ -255,12 +319,9 @@ static const char* kKernelNames[MH3D_NKERNEL] = {"plane_fwd", "class_fwd", "smal
                                                   "plane_adj", "aux", "solve_iter", "vol_update", "class_normal",
                                                   "adj_and_store"};
 
-struct FastOps;
-
 struct mh3d_plan_s {
-  const FastOps* fast = nullptr;   // compile-time-geometry passes of the fused sequences (or none)
+  const FastOps* fast = nullptr;   // compile-time-geometry passes (or none)
   bool fast_on = true;             // whether the fused sequences use them (mh3d_plan_path)
-  bool each_batched = false;       // the single-harmonic descriptors have separate Q buffers
   mh3d_plan_desc desc;
   std::vector<int> harm;
   Geo g;
@@ -271,7 +332,10 @@ struct mh3d_plan_s {
   uint32_t imag_mask;
   uint32_t cmask[3];           // present (component, harmonic) PSF blocks, vector model
   // device memory
-  void* hs = nullptr;          // spectra in class layout
+  void* hs = nullptr;          // user PSFs: spectra in class layout
+  double2* fhat = nullptr;     // analytic PSF: x spectra [K][nx], envelope spectrum [ny][nzh]
+  double2* ehat = nullptr;     // and scales [K] in FP64 (export)
+  double* scale = nullptr;
   float* b = nullptr;          // sensitivity
   float2* uperm = nullptr;     // class-layout yz spectra of one volume (also adjoint V)
   float* sfs = nullptr;        // separable spectra (analytic PSF): x factors [K][nx]
@@ -320,16 +384,25 @@ static mh3d_status dalloc(mh3d_plan_t p, void** ptr, size_t bytes) {
   return MH3D_OK;
 }
 
+// Complex values of the buffer between the plane and the class or column passes: the
+// class-layout spectra of every component (user PSFs); the sy shares and Q, or the K
+// harmonics' own Q of a back-projection, of nx * columns each (analytic PSF).
+static size_t uperm_elems(const Geo& g, bool compact) {
+  if (!compact) return (size_t)g.C * g.nx * g.plane;
+  return (size_t)std::max(g.sy + 1, g.K) * g.nx * g.ncls;
+}
+
 static size_t plan_bytes(const Geo& g, bool compact) {
   size_t s = 0;
-  s += (size_t)g.C * g.K * g.hsz * (compact ? 4 : 8);
+  if (!compact) s += (size_t)g.C * g.K * g.hsz * 8;   // spectra
   s += (size_t)g.C * g.N * 4;                         // b
-  s += (size_t)g.C * g.nx * g.plane * 8;              // uperm
+  s += uperm_elems(g, compact) * 8;                   // uperm
   s += 2 * (size_t)g.K * g.mx * g.ncls * 8;           // G, Gp
   s += 5 * (size_t)g.N * 4;                           // vol
   s += (size_t)(2 * (g.nx + g.ny + g.nz) + g.mx + g.my + g.mz) * 24;
   s += ((size_t)g.K * g.nx + (size_t)g.ny * g.nz) * 8;
-  if (compact) s += (size_t)g.K * g.nx * 4 + (size_t)g.sy * g.my * g.nzh * 8;   // separable factors
+  if (compact)   // separable factors
+    s += (size_t)g.K * g.nx * (4 + 16) + (size_t)g.sy * g.my * g.nzh * 8 + (size_t)g.ny * g.nzh * 16 + (size_t)g.K * 8;
   return s;
 }
 
@@ -382,97 +455,14 @@ struct Timer {
   }
 };
 
-// ---------------------------------------------------------------------------- fast passes
-// Launchers of the compile-time-geometry passes (fast.hpp) of one grid, decimation and
-// tile shape.  All passes of a fused sequence come from one entry (their slot layout is
-// their own).
-struct FastOps {
-  int nx, ny, nz, sx, sy, sz, kmax;
-  int nbp, ncls_blocks, tc;
-  size_t lds_plane, lds_class;
-  void (*plane_fwd)(hipStream_t, const VolDesc*, int src, const float* a);
-  void (*cls)(hipStream_t, const VolDesc*, int mode, int chk);
-  void (*plane_adj)(hipStream_t, const VolDesc*, int out, AdjOut ao);
-  void (*adj_and_store)(hipStream_t, const VolDesc*, AdjOut ao, float* d, int nsmall, int xb);
-  void (*small_inv)(hipStream_t, const VolDesc*, float* d, int nsmall, int xb);
-  // A^T of nv single-harmonic descriptors at once (each with its own qx): out volumes
-  // out + v N for v < nv
-  void (*adjoint_each)(hipStream_t, const VolDesc*, int nv, float* out);
-  // the portraits' small-grid spectra into G' (as k_small_fwd)
-  void (*small_fwd)(hipStream_t, const VolDesc*, const float* r, float2* out, int nsmall, int xb);
-};
-
-template <class G>
-struct FastImpl {
-  static void plane_fwd(hipStream_t s, const VolDesc* vd, int src, const float* a) {
-    const dim3 grid(G::NBP), block(G::TPF);
-    switch (src) {
-      case SRC_PLAIN: k_fast_plane_fwd<G, SRC_PLAIN><<<grid, block, G::LDS_PLANE, s>>>(vd, a); break;
-      case SRC_FISTA_Y: k_fast_plane_fwd<G, SRC_FISTA_Y><<<grid, block, G::LDS_PLANE, s>>>(vd, a); break;
-      default: k_fast_plane_fwd<G, SRC_SCALED><<<grid, block, G::LDS_PLANE, s>>>(vd, a); break;
-    }
-  }
-  static void cls(hipStream_t s, const VolDesc* vd, int mode, int chk) {
-    const dim3 grid(G::NCLS / G::CPC), block(G::TC);
-    switch (mode) {
-      case NRM_RESID: k_fast_col<G, NRM_RESID><<<grid, block, G::LDS_COL, s>>>(vd, chk); break;
-      case NRM_PLAIN: k_fast_col<G, NRM_PLAIN><<<grid, block, G::LDS_COL, s>>>(vd, chk); break;
-      case COL_FWD: k_fast_col<G, COL_FWD><<<grid, block, G::LDS_COL, s>>>(vd, chk); break;
-      case COL_ADJ: k_fast_col<G, COL_ADJ><<<grid, block, G::LDS_COL, s>>>(vd, chk); break;
-      default: k_fast_col<G, NRM_STORE><<<grid, block, G::LDS_COL, s>>>(vd, chk); break;
-    }
-  }
-  static void plane_adj(hipStream_t s, const VolDesc* vd, int out, AdjOut ao) {
-    const dim3 grid(G::NBP), block(G::TP);
-    if (out == OUT_STEP_NORMAL) k_fast_plane_adj<G, OUT_STEP_NORMAL><<<grid, block, G::LDS_PLANE, s>>>(vd, ao);
-    else if (out == OUT_STEP_FISTA) k_fast_plane_adj<G, OUT_STEP_FISTA><<<grid, block, G::LDS_PLANE, s>>>(vd, ao);
-    else k_fast_plane_adj<G, OUT_SCALE_B><<<grid, block, G::LDS_PLANE, s>>>(vd, ao);
-  }
-  static void adj_and_store(hipStream_t s, const VolDesc* vd, AdjOut ao, float* d, int nsmall, int xb) {
-    k_fast_adj_and_store<G><<<dim3(G::NBP + nsmall), dim3(G::TP), std::max(G::small_lds(xb), G::LDS_PLANE), s>>>(
-        vd, ao, d);
-  }
-  static void small_inv(hipStream_t s, const VolDesc* vd, float* d, int nsmall, int xb) {
-    k_fast_small_inv<G><<<dim3(nsmall), dim3(G::TP), G::small_lds(xb), s>>>(vd, d);
-  }
-  static void small_fwd(hipStream_t s, const VolDesc* vd, const float* r, float2* out, int nsmall, int xb) {
-    k_fast_small_fwd<G><<<dim3(nsmall), dim3(G::TP), G::small_lds(xb), s>>>(vd, r, out);
-  }
-  static void adjoint_each(hipStream_t s, const VolDesc* vd, int nv, float* out) {
-    k_fast_col<G, COL_ADJ><<<dim3(G::NCLS / G::CPC, nv), dim3(G::TC), G::LDS_COL, s>>>(vd, 0);
-    AdjOut ao;
-    ao.out = out;
-    ao.yin = nullptr;
-    k_fast_plane_adj<G, OUT_SCALE_B><<<dim3(G::NBP, nv), dim3(G::TP), G::LDS_PLANE, s>>>(vd, ao);
-  }
-  static FastOps ops() {
-    return FastOps{G::NX, G::NY, G::NZ, G::SX, G::SY, G::SZ, G::KMAX, G::NBP, G::NCLS / G::CPC, G::TC,
-                   G::LDS_PLANE, G::LDS_COL, &plane_fwd, &cls, &plane_adj, &adj_and_store, &small_inv,
-                   &adjoint_each, &small_fwd};
-  }
-};
-
-// Grids with compile-time passes: (nx, ny, nz, sx, sy, sz, columns per column-pass block,
-// largest harmonic count).
-static const FastOps kFast[] = {
-    FastImpl<FastGeo<128, 128, 128, 2, 4, 4, 4, 12, 512, 512, 134>>::ops(),   // 128^3, k = 2..12
-    FastImpl<FastGeo<96, 96, 64, 2, 2, 2, 4, 8, 512, 512>>::ops(),            // 96 x 96 x 64, k = 2..8
-    // small grids of the parity tests: every y split (1 to 4), radix 3 along x and y
-    FastImpl<FastGeo<32, 32, 32, 2, 4, 4, 4, 12>>::ops(),
-    FastImpl<FastGeo<16, 24, 16, 2, 2, 2, 4, 8>>::ops(),
-    FastImpl<FastGeo<16, 16, 16, 2, 1, 2, 4, 8>>::ops(),
-    FastImpl<FastGeo<24, 24, 16, 2, 3, 2, 4, 8>>::ops(),
-};
-
-// The entry serving plan p (scalar model, analytic spectra, no padding), or NULL.  Its
-// intermediates (sy shares and one more of nx * columns) live in the class-layout
-// buffer, which holds nx * columns * sy * sz values.
+// The entry serving plan p (scalar model, analytic spectra, no padding), or NULL.
 static const FastOps* find_fast(const Geo& g, bool compact) {
   if (!compact || g.C != 1 || g.padded) return nullptr;
-  if (g.sy + 1 > g.nmem) return nullptr;
-  for (const FastOps& f : kFast)
+  for (int i = 0; i < kFastCount; ++i) {
+    const FastOps& f = kFast[i];
     if (f.nx == g.nx && f.ny == g.ny && f.nz == g.nz && f.sx == g.sx && f.sy == g.sy && f.sz == g.sz && g.K <= f.kmax)
       return &f;
+  }
   return nullptr;
 }
 
@@ -489,43 +479,43 @@ static mh3d_status launch_plane_fwd(mh3d_plan_t p, int src, const float* a) {
   dim3 grid((src == SRC_RAW ? 1 : p->g.C) * p->psa * p->g.nx), block(p->L.T_plane);
   const size_t lds = p->L.lds_plane;
   switch (src) {
-    case SRC_PLAIN: k_plane_fwd<SRC_PLAIN><<<grid, block, lds, p->ls>>>(p->vda, nullptr, a); break;
-    case SRC_RAW: k_plane_fwd<SRC_RAW><<<grid, block, lds, p->ls>>>(p->vda, nullptr, a); break;
-    case SRC_FISTA_Y: k_plane_fwd<SRC_FISTA_Y><<<grid, block, lds, p->ls>>>(p->vda, nullptr, a); break;
-    default: k_plane_fwd<SRC_SCALED><<<grid, block, lds, p->ls>>>(p->vda, nullptr, a); break;
+    case SRC_PLAIN: k_plane_fwd<SRC_PLAIN><<<grid, block, lds, p->ls>>>(p->vda, a); break;
+    case SRC_RAW: k_plane_fwd<SRC_RAW><<<grid, block, lds, p->ls>>>(p->vda, a); break;
+    case SRC_FISTA_Y: k_plane_fwd<SRC_FISTA_Y><<<grid, block, lds, p->ls>>>(p->vda, a); break;
+    default: k_plane_fwd<SRC_SCALED><<<grid, block, lds, p->ls>>>(p->vda, a); break;
   }
   return last_launch("k_plane_fwd");
 }
 
-// HC: 0 compact (analytic) spectra, 1 complex (user) spectra, 2 complex spectra of a
-// vector-model plan (components looped inside the class passes).
-template <int HC, int E>
+template <int E>
 static void class_fwd_t(mh3d_plan_t p, int chk, const VolDesc* vd, int mode) {
-  k_class_fwd<HC == 0 ? 0 : 1, E, HC == 2>
-      <<<dim3(p->g.ncls / p->g.cpw), dim3(p->L.T_class), p->L.lds_class, p->ls>>>(vd, chk, mode);
+  const dim3 grid(p->g.ncls / p->g.cpw), block(p->L.T_class);
+  if (p->g.C > 1) k_class_fwd<E, true><<<grid, block, p->L.lds_class, p->ls>>>(vd, chk, mode);
+  else k_class_fwd<E, false><<<grid, block, p->L.lds_class, p->ls>>>(vd, chk, mode);
 }
-template <int HC, int E>
+template <int E>
 static void class_adj_t(mh3d_plan_t p, int chk, const VolDesc* vd, int) {
-  k_class_adj<HC == 0 ? 0 : 1, E, HC == 2>
-      <<<dim3(p->g.ncls / p->g.cpw), dim3(p->L.T_class), p->L.lds_class, p->ls>>>(vd, chk);
+  const dim3 grid(p->g.ncls / p->g.cpw), block(p->L.T_class);
+  if (p->g.C > 1) k_class_adj<E, true><<<grid, block, p->L.lds_class, p->ls>>>(vd, chk);
+  else k_class_adj<E, false><<<grid, block, p->L.lds_class, p->ls>>>(vd, chk);
 }
 
-#define E_DISPATCH(HCV, FN)                             \
-  switch (p->g.E) {                                     \
-    case 9: FN<HCV, 9>(p, chk, vd, mode); break;        \
-    case 8: FN<HCV, 8>(p, chk, vd, mode); break;        \
-    case 6: FN<HCV, 6>(p, chk, vd, mode); break;        \
-    case 4: FN<HCV, 4>(p, chk, vd, mode); break;        \
-    case 3: FN<HCV, 3>(p, chk, vd, mode); break;        \
-    case 2: FN<HCV, 2>(p, chk, vd, mode); break;        \
-    default: FN<HCV, 1>(p, chk, vd, mode); break;       \
+#define E_DISPATCH(FN)                             \
+  switch (p->g.E) {                                \
+    case 9: FN<9>(p, chk, vd, mode); break;        \
+    case 8: FN<8>(p, chk, vd, mode); break;        \
+    case 6: FN<6>(p, chk, vd, mode); break;        \
+    case 4: FN<4>(p, chk, vd, mode); break;        \
+    case 3: FN<3>(p, chk, vd, mode); break;        \
+    case 2: FN<2>(p, chk, vd, mode); break;        \
+    default: FN<1>(p, chk, vd, mode); break;       \
   }
 
 // mode: FWD_G, FWD_ADJ, FWD_G_AND_ADJ or FWD_RESID (where the decimated spectra go).
 static mh3d_status launch_class_fwd(mh3d_plan_t p, int chk, int mode) {
   Timer t(p, KID_CLASS_FWD);
   const VolDesc* vd = p->vda;
-  if (p->compact) { E_DISPATCH(0, class_fwd_t) } else if (p->g.C > 1) { E_DISPATCH(2, class_fwd_t) } else { E_DISPATCH(1, class_fwd_t) }
+  E_DISPATCH(class_fwd_t)
   return last_launch("k_class_fwd");
 }
 // vd: a single-harmonic descriptor (per-harmonic back-projection) or NULL for the plan's.
@@ -533,44 +523,38 @@ static mh3d_status launch_class_adj(mh3d_plan_t p, int chk, const VolDesc* vd = 
   Timer t(p, KID_CLASS_ADJ);
   if (!vd) vd = p->vda;
   const int mode = 0;
-  if (p->compact) { E_DISPATCH(0, class_adj_t) } else if (p->g.C > 1) { E_DISPATCH(2, class_adj_t) } else { E_DISPATCH(1, class_adj_t) }
+  E_DISPATCH(class_adj_t)
   return last_launch("k_class_adj");
 }
 
-// Scalar plans without boundary padding run the forward and adjoint class passes of the
-// normal operator, the solver's updates and A then A^T as one (k_class_normal).
+// Scalar plans without boundary padding run the forward and adjoint class (or column)
+// passes of the normal operator, the solver's updates and A then A^T as one.
 static bool fused_class(mh3d_plan_t p) { return p->g.C == 1 && !p->g.padded; }
 
-template <int HC, int E>
+template <int E>
 static void class_normal_t(mh3d_plan_t p, int chk, const VolDesc* vd, int mode) {
-  k_class_normal<HC, E><<<dim3(p->g.ncls / p->g.cpw), dim3(p->L.T_class), p->L.lds_class, p->ls>>>(vd, chk, mode);
+  k_class_normal<E><<<dim3(p->g.ncls / p->g.cpw), dim3(p->L.T_class), p->L.lds_class, p->ls>>>(vd, chk, mode);
 }
 // mode: NRM_RESID, NRM_PLAIN or NRM_STORE.
 static mh3d_status launch_class_normal(mh3d_plan_t p, int chk, int mode) {
   Timer t(p, KID_CLASS_NORMAL);
   const VolDesc* vd = p->vda;
-  if (p->compact) { E_DISPATCH(0, class_normal_t) } else { E_DISPATCH(1, class_normal_t) }
+  E_DISPATCH(class_normal_t)
   return last_launch("k_class_normal");
 }
 
 static mh3d_status launch_small_inv(mh3d_plan_t p, int epi, float* d) {
   Timer t(p, KID_SMALL_INV);
-  dim3 grid(p->g.K * (p->g.mx / p->g.xb)), block(p->L.T_small);
-  const size_t lds = p->L.lds_small;
-  switch (epi) {
-    case EPI_STORE: k_small_inv<EPI_STORE><<<grid, block, lds, p->ls>>>(p->vda, nullptr, d); break;
-    case EPI_RESID_BACK: k_small_inv<EPI_RESID_BACK><<<grid, block, lds, p->ls>>>(p->vda, nullptr, d); break;
-    case EPI_STORE_BACK: k_small_inv<EPI_STORE_BACK><<<grid, block, lds, p->ls>>>(p->vda, nullptr, d); break;
-    default: k_small_inv<EPI_BACK><<<grid, block, lds, p->ls>>>(p->vda, nullptr, d); break;
-  }
-  return last_launch("k_small_inv");
+  sep_launch_small_inv(dim3(p->g.K * (p->g.mx / p->g.xb)), dim3(p->L.T_small), p->L.lds_small, p->ls, p->vda, nullptr, d, epi);
+  return last_launch("k_sep_small_inv");
 }
 
 // out: destination of the spectra (NULL: G', the adjoint's input).
 static mh3d_status launch_small_fwd(mh3d_plan_t p, const float* r, float2* out = nullptr) {
   Timer t(p, KID_SMALL_FWD);
-  k_small_fwd<<<dim3(p->g.K * (p->g.mx / p->g.xb)), dim3(p->L.T_small), p->L.lds_small, p->ls>>>(p->vda, r, out);
-  return last_launch("k_small_fwd");
+  sep_launch_small_fwd(dim3(p->g.K * (p->g.mx / p->g.xb)), dim3(p->L.T_small), p->L.lds_small, p->ls, p->vda, r,
+                       out ? out : p->Gp);
+  return last_launch("k_sep_small_fwd");
 }
 static bool use_fast(mh3d_plan_t p);
 // The portraits' small-grid spectra into G' for A^T alone and the back-projections: the
@@ -592,10 +576,10 @@ static mh3d_status launch_plane_adj(mh3d_plan_t p, int out, float* o, const floa
   ao.out = o;
   ao.yin = yin;
   switch (out) {
-    case OUT_SCALE_B: k_plane_adj<OUT_SCALE_B><<<grid, block, lds, p->ls>>>(vd, nullptr, ao); break;
-    case OUT_STEP_NORMAL: k_plane_adj<OUT_STEP_NORMAL><<<grid, block, lds, p->ls>>>(vd, nullptr, ao); break;
-    case OUT_STEP_FISTA: k_plane_adj<OUT_STEP_FISTA><<<grid, block, lds, p->ls>>>(vd, nullptr, ao); break;
-    default: k_plane_adj<OUT_U><<<grid, block, lds, p->ls>>>(vd, nullptr, ao); break;
+    case OUT_SCALE_B: k_plane_adj<OUT_SCALE_B><<<grid, block, lds, p->ls>>>(vd, ao); break;
+    case OUT_STEP_NORMAL: k_plane_adj<OUT_STEP_NORMAL><<<grid, block, lds, p->ls>>>(vd, ao); break;
+    case OUT_STEP_FISTA: k_plane_adj<OUT_STEP_FISTA><<<grid, block, lds, p->ls>>>(vd, ao); break;
+    default: k_plane_adj<OUT_U><<<grid, block, lds, p->ls>>>(vd, ao); break;
   }
   return last_launch("k_plane_adj");
 }
@@ -608,69 +592,89 @@ static mh3d_status launch_adj_and_store(mh3d_plan_t p, float* d, float* x) {
   ao.out = x;
   ao.yin = nullptr;
   const dim3 grid(p->psa * p->g.nx + p->g.K * (p->g.mx / p->g.xb)), block(p->L.T_merge);
-  k_adj_and_store<<<grid, block, std::max(p->L.lds_plane, p->L.lds_small), p->ls>>>(p->vda, ao, d);
+  launch_user_adj_and_store(grid, block, std::max(p->L.lds_plane, p->L.lds_small), p->ls, p->vda, ao, d);
   return last_launch("k_adj_and_store");
 }
 
-// The fused sequences run the compile-time passes of fast.hpp when the plan has them.
+// Analytic plans run the compile-time passes of fast.hpp when there are any for them.
 static bool use_fast(mh3d_plan_t p) {
   // the compile-time small-grid pass takes x'-blocks of 1, 2, 4 or 8 planes
   const int xb = p->g.xb;
   return p->fast && p->fast_on && (xb == 1 || xb == 2 || xb == 4 || xb == 8);
 }
 
-// Scalar plans with one workgroup per x-plane also run the next update's forward plane
-// pass in the launch of the step (k_step_and_fwd).
-static bool step_and_fwd(mh3d_plan_t p) { return p->g.C == 1 && p->psa == 1 && !use_fast(p); }
+// Scalar user-PSF plans with one workgroup per x-plane also run the next update's forward
+// plane pass in the launch of the step (k_step_and_fwd).
+static bool step_and_fwd(mh3d_plan_t p) { return p->g.C == 1 && p->psa == 1; }
 
-// ---- the fused sequences on the compile-time passes
-static mh3d_status fast_plane_fwd(mh3d_plan_t p, int src, const float* a) {
+// ---- passes of analytic plans: the compile-time ones where the plan has them, else the
+// separable ones of run-time geometry
+static mh3d_status sep_plane_fwd(mh3d_plan_t p, int src, const float* a) {
   Timer t(p, KID_PLANE_FWD);
-  p->fast->plane_fwd(p->ls, p->vda, src, a);
-  return last_launch("k_fast_plane_fwd");
+  if (use_fast(p)) p->fast->plane_fwd(p->ls, p->vda, src, a);
+  else sep_launch_plane_fwd(dim3(p->g.nx * p->g.sy), dim3(p->L.T_sep), p->L.lds_sep, p->ls, p->vda, nullptr, a, src);
+  return last_launch("separable plane pass");
 }
-static mh3d_status fast_class(mh3d_plan_t p, int chk, int mode) {
-  Timer t(p, KID_CLASS_NORMAL);
-  p->fast->cls(p->ls, p->vda, mode, chk);
-  return last_launch("k_fast_class");
+// mode: NRM_*, COL_FWD, COL_ADJ or COL_DATA (the last always on the run-time pass).
+static mh3d_status sep_column(mh3d_plan_t p, int chk, int mode) {
+  Timer t(p, mode == COL_FWD ? KID_CLASS_FWD : mode == COL_ADJ ? KID_CLASS_ADJ : mode == COL_DATA ? KID_AUX : KID_CLASS_NORMAL);
+  if (use_fast(p) && mode != COL_DATA) p->fast->cls(p->ls, p->vda, mode, chk);
+  else
+    sep_launch_col(p->L.col_any, mode, dim3(p->L.col_blocks), dim3(p->L.T_col), p->L.lds_col_of(mode), p->ls, p->vda, nullptr, chk);
+  return last_launch("separable column pass");
 }
-static mh3d_status fast_adj_and_store(mh3d_plan_t p, float* d, float* x) {
+static mh3d_status sep_plane_adj_launch(mh3d_plan_t p, int out, AdjOut ao) {
+  Timer t(p, KID_PLANE_ADJ);
+  const dim3 grid(p->g.nx * p->g.sy), block(p->L.T_sep);
+  const size_t lds = p->L.lds_sep;
+  if (use_fast(p)) p->fast->plane_adj(p->ls, p->vda, out, ao);
+  else sep_launch_plane_adj(out, grid, block, lds, p->ls, p->vda, nullptr, ao);
+  return last_launch("separable adjoint plane pass");
+}
+static mh3d_status sep_plane_adj_out(mh3d_plan_t p, float* x) {
+  AdjOut ao;
+  ao.out = x;
+  ao.yin = nullptr;
+  return sep_plane_adj_launch(p, OUT_SCALE_B, ao);
+}
+static mh3d_status sep_adj_and_store(mh3d_plan_t p, float* d, float* x) {
   Timer t(p, KID_ADJ_AND_STORE);
   AdjOut ao;
   ao.out = x;
   ao.yin = nullptr;
-  p->fast->adj_and_store(p->ls, p->vda, ao, d, p->g.K * (p->g.mx / p->g.xb), p->g.xb);
-  return last_launch("k_fast_adj_and_store");
+  const int nsmall = p->g.K * (p->g.mx / p->g.xb);
+  if (use_fast(p)) p->fast->adj_and_store(p->ls, p->vda, ao, d, nsmall, p->g.xb);
+  else
+    sep_launch_adj_and_store(dim3(p->g.nx * p->g.sy + nsmall), dim3(p->L.T_sep), std::max(p->L.lds_sep, p->L.lds_small), p->ls,
+                             p->vda, ao, d, p->g.nx * p->g.sy);
+  return last_launch("separable adjoint and store pass");
 }
-static mh3d_status fast_class_alone(mh3d_plan_t p, int mode) {
-  Timer t(p, mode == COL_FWD ? KID_CLASS_FWD : KID_CLASS_ADJ);
-  p->fast->cls(p->ls, p->vda, mode, 0);
-  return last_launch("k_fast_col");
-}
-static mh3d_status fast_small_inv(mh3d_plan_t p, float* d) {
+static mh3d_status sep_small_inv(mh3d_plan_t p, float* d) {
+  if (!use_fast(p)) return launch_small_inv(p, EPI_STORE, d);
   Timer t(p, KID_SMALL_INV);
   p->fast->small_inv(p->ls, p->vda, d, p->g.K * (p->g.mx / p->g.xb), p->g.xb);
   return last_launch("k_fast_small_inv");
 }
-static mh3d_status fast_plane_adj_out(mh3d_plan_t p, float* x) {
-  Timer t(p, KID_PLANE_ADJ);
-  AdjOut ao;
-  ao.out = x;
-  ao.yin = nullptr;
-  p->fast->plane_adj(p->ls, p->vda, OUT_SCALE_B, ao);
-  return last_launch("k_fast_plane_adj");
+// A^T of the nv single-harmonic descriptors from vd at once, into consecutive volumes
+static mh3d_status sep_adjoint_each(mh3d_plan_t p, const VolDesc* vd, int nv, float* out) {
+  if (use_fast(p)) {
+    p->fast->adjoint_each(p->ls, vd, nv, out);
+  } else {
+    sep_launch_col(p->g.sx > SXR, COL_ADJ, dim3(p->L.col_blocks, nv), dim3(p->L.T_col), p->L.lds_col, p->ls, vd, nullptr, 0);
+    AdjOut ao;
+    ao.out = out;
+    ao.yin = nullptr;
+    sep_launch_plane_adj(OUT_SCALE_B, dim3(p->g.nx * p->g.sy, nv), dim3(p->L.T_sep), p->L.lds_sep, p->ls, vd, nullptr, ao);
+  }
+  return last_launch("per-harmonic adjoint passes");
 }
 // the adjoint plane pass that ends a step (UPD_NORMAL: out, w = yin; UPD_FISTA), then the
 // one-block finish of its FP64 sums
-static mh3d_status fast_adjoint_step(mh3d_plan_t p, int upd, float* o, const float* yin) {
+static mh3d_status sep_adjoint_step(mh3d_plan_t p, int upd, float* o, const float* yin) {
   AdjOut ao;
   ao.out = o;
   ao.yin = yin;
-  {
-    Timer t(p, KID_PLANE_ADJ);
-    p->fast->plane_adj(p->ls, p->vda, upd == UPD_NORMAL ? OUT_STEP_NORMAL : OUT_STEP_FISTA, ao);
-    CHK(last_launch("k_fast_plane_adj"));
-  }
+  CHK(sep_plane_adj_launch(p, upd == UPD_NORMAL ? OUT_STEP_NORMAL : OUT_STEP_FISTA, ao));
   Timer t(p, KID_UPDATE);
   if (upd == UPD_NORMAL) k_vol_finish<UPD_NORMAL><<<1, 256, 0, p->ls>>>(p->vda, nullptr);
   else k_vol_finish<UPD_FISTA><<<1, 256, 0, p->ls>>>(p->vda, nullptr);
@@ -683,7 +687,7 @@ static mh3d_status launch_step_and_fwd(mh3d_plan_t p) {
     AdjOut ao;
     ao.out = nullptr;
     ao.yin = nullptr;
-    k_step_and_fwd<<<dim3(p->g.nx), dim3(p->L.T_plane), p->L.lds_plane, p->ls>>>(p->vda, nullptr, ao);
+    k_step_and_fwd<<<dim3(p->g.nx), dim3(p->L.T_plane), p->L.lds_plane, p->ls>>>(p->vda, ao);
     CHK(last_launch("k_step_and_fwd"));
   }
   Timer t(p, KID_UPDATE);
@@ -710,10 +714,10 @@ static mh3d_status launch_adjoint_step(mh3d_plan_t p, int upd, float* o, const f
   ao.yin = yin;
   const dim3 grid(update_blocks(p->g.N)), block(UPD_THREADS);
   if (upd == UPD_NORMAL) {
-    if (!step_in_plane_pass(p)) k_vol_update<UPD_NORMAL><<<grid, block, 0, p->ls>>>(p->vda, nullptr, ao);
+    if (!step_in_plane_pass(p)) k_vol_update<UPD_NORMAL><<<grid, block, 0, p->ls>>>(p->vda, ao);
     k_vol_finish<UPD_NORMAL><<<1, 256, 0, p->ls>>>(p->vda, nullptr);
   } else {
-    if (!step_in_plane_pass(p)) k_vol_update<UPD_FISTA><<<grid, block, 0, p->ls>>>(p->vda, nullptr, ao);
+    if (!step_in_plane_pass(p)) k_vol_update<UPD_FISTA><<<grid, block, 0, p->ls>>>(p->vda, ao);
     k_vol_finish<UPD_FISTA><<<1, 256, 0, p->ls>>>(p->vda, nullptr);
   }
   return last_launch("k_vol_update / k_vol_finish");
@@ -730,11 +734,18 @@ static mh3d_status state_set(mh3d_plan_t p, const DevState& v) {
   return last_launch("k_state_set");
 }
 
+// Blocks whose FP64 sums a solver step leaves: the adjoint plane pass's (scalar plans) or
+// the update pass's (vector plans).
+static int step_blocks(mh3d_plan_t p) {
+  if (p->compact) return p->g.nx * p->g.sy;
+  return p->g.C == 1 ? p->ps_solve * p->g.nx : update_blocks(p->g.N);
+}
+
 static mh3d_status upload_desc(mh3d_plan_t p) {
   p->vdu[0] = p->vdh;
   p->vdu[1] = p->vdh;
   p->vdu[1].g.ps = p->ps_solve;
-  p->vdu[1].nb_upd = use_fast(p) ? p->fast->nbp : (p->g.C == 1 ? p->ps_solve * p->g.nx : update_blocks(p->g.N));
+  p->vdu[1].nb_upd = step_blocks(p);
   HIPCHK(hipMemcpyAsync(p->vdd, p->vdu, sizeof p->vdu, hipMemcpyHostToDevice, p->stream));
   HIPCHK(hipStreamSynchronize(p->stream));
   return MH3D_OK;
@@ -796,16 +807,18 @@ static mh3d_status build_spectra_analytic(mh3d_plan_t p) {
     if (order[k] % 2 == 0) p->imag_mask |= (1u << k);   // odd profile -> imaginary spectrum
   }
   int* d_order = nullptr;
-  double2 *fhat = nullptr, *tmp = nullptr, *ehat = nullptr;
-  double *fn2 = nullptr, *rows = nullptr, *scale = nullptr;
+  double2* tmp = nullptr;
+  double *fn2 = nullptr, *rows = nullptr;
+  CHK(dalloc(p, (void**)&p->fhat, sizeof(double2) * g.K * g.nx));
+  CHK(dalloc(p, (void**)&p->ehat, sizeof(double2) * g.ny * g.nzh));
+  CHK(dalloc(p, (void**)&p->scale, sizeof(double) * g.K));
+  double2 *fhat = p->fhat, *ehat = p->ehat;
+  double* scale = p->scale;
   size_t keep = p->bytes;
   CHK(dalloc(p, (void**)&d_order, sizeof(int) * g.K));
-  CHK(dalloc(p, (void**)&fhat, sizeof(double2) * g.K * g.nx));
   CHK(dalloc(p, (void**)&tmp, sizeof(double2) * g.ny * g.nz));
-  CHK(dalloc(p, (void**)&ehat, sizeof(double2) * g.ny * g.nzh));
   CHK(dalloc(p, (void**)&fn2, sizeof(double) * g.K));
   CHK(dalloc(p, (void**)&rows, sizeof(double) * g.ny));
-  CHK(dalloc(p, (void**)&scale, sizeof(double) * g.K));
   HIPCHK(hipMemcpyAsync(d_order, order.data(), sizeof(int) * g.K, hipMemcpyHostToDevice, p->stream));
   const int T = 256;
   hipLaunchKernelGGL(k_psf_profile, dim3(g.K), dim3(T), sizeof(double2) * 3 * g.nx, p->stream, g.nx, d_order,
@@ -819,14 +832,12 @@ static mh3d_status build_spectra_analytic(mh3d_plan_t p) {
   CHK(last_launch("k_psf_env_cols"));
   hipLaunchKernelGGL(k_psf_scales, dim3(1), dim3(64), 0, p->stream, g.K, g.ny, g.N, fn2, rows, scale);
   CHK(last_launch("k_psf_scales"));
-  hipLaunchKernelGGL(k_psf_assemble, dim3(2048), dim3(256), 0, p->stream, g, fhat, ehat, scale, p->imag_mask, 1, p->hs);
-  CHK(last_launch("k_psf_assemble"));
   hipLaunchKernelGGL(k_sep_tables, dim3(64), dim3(256), 0, p->stream, g, fhat, ehat, scale, p->imag_mask,
                      p->tw64 + p->off[1], p->sfs, p->set);
   CHK(last_launch("k_sep_tables"));
   HIPCHK(hipStreamSynchronize(p->stream));
-  (void)hipFree(d_order); (void)hipFree(fhat); (void)hipFree(tmp); (void)hipFree(ehat);
-  (void)hipFree(fn2); (void)hipFree(rows); (void)hipFree(scale);
+  (void)hipFree(d_order); (void)hipFree(tmp);
+  (void)hipFree(fn2); (void)hipFree(rows);
   p->bytes = keep;
   return MH3D_OK;
 }
@@ -882,7 +893,7 @@ extern "C" void mh3d_destroy(mh3d_plan_t p) {
   for (auto& e : p->pending) { (void)hipEventDestroy(e.second.first); (void)hipEventDestroy(e.second.second); }
   for (auto e : p->free_events) (void)hipEventDestroy(e);
   void* bufs[] = {p->hs, p->b, p->uperm, p->G, p->Gp, p->vol[0], p->vol[1], p->vol[2], p->vol[3], p->vol[4],
-                  p->tw32, p->tw64, p->prof, p->env, p->partials, p->st, p->vdd, p->vdk, p->hist, p->sfs, p->set};
+                  p->tw32, p->tw64, p->prof, p->env, p->partials, p->st, p->vdd, p->vdk, p->hist, p->sfs, p->set, p->fhat, p->ehat, p->scale};
   for (void* q : bufs)
     if (q) (void)hipFree(q);
   delete p;
@@ -894,7 +905,6 @@ static void fill_desc(mh3d_plan_t p) {
   v.g = p->g;
   v.hs = p->hs;
   v.imag_mask = p->imag_mask;
-  v.compact = p->compact;
   v.b = p->b;
   v.uperm = p->uperm;
   v.G = p->G;
@@ -917,9 +927,7 @@ static void fill_desc(mh3d_plan_t p) {
   v.aw = p->desc.alpha_width;
   v.T_class = p->L.T_class;
   v.u = p->vol[4];
-  // blocks whose FP64 sums a step leaves: the adjoint plane pass's (scalar plans) or the
-  // update pass's (vector plans)
-  v.nb_upd = p->g.C == 1 ? p->g.ps * p->g.nx : update_blocks(p->g.N);
+  v.nb_upd = step_blocks(p);
   v.ncomp = p->g.C;
   v.hs_cstride = (long long)p->g.K * p->g.hsz;
   v.sfs = p->sfs;
@@ -935,20 +943,20 @@ static void fill_desc(mh3d_plan_t p) {
 static mh3d_status upload_harmonic_descs(mh3d_plan_t p) {
   const Geo& g = p->g;
   std::vector<VolDesc> h(g.K, p->vdh);
-  const size_t esz = p->compact ? sizeof(float) : sizeof(float2);
-  // the compile-time passes: harmonic k's x factors, and its own Q buffer when the K of
-  // them fit in the class-layout buffer (the column pass of A^T alone does not read the
-  // shares that otherwise sit there), so the K adjoints run in one launch per pass
+  // the separable passes: harmonic k's x factors, and its own Q buffer (the column pass of
+  // A^T alone does not read the shares that otherwise sit there), so the K adjoints run in
+  // one launch per pass
   const size_t nq = (size_t)g.nx * g.ncls;
-  p->each_batched = p->fast && (size_t)g.K * nq <= (size_t)g.C * g.nx * g.plane;
   for (int k = 0; k < g.K; ++k) {
     h[k].g.K = 1;
-    h[k].hs = (const char*)p->vdh.hs + (size_t)k * g.hsz * esz;
+    if (p->hs) h[k].hs = (const float2*)p->vdh.hs + (size_t)k * g.hsz;
+    h[k].g.sep.kg = 1;
+    h[k].g.sep.d_kgcpc = make_mdiv(g.sep.cpc);
     h[k].Gp = p->vdh.Gp + (size_t)k * g.mx * g.ncls;
     h[k].imag_mask = (p->vdh.imag_mask >> k) & 1u;
     for (int c = 0; c < 3; ++c) h[k].cmask[c] = (p->vdh.cmask[c] >> k) & 1u;
     if (p->sfs) h[k].sfs = p->sfs + (size_t)k * g.nx;
-    if (p->each_batched) h[k].qx = p->uperm + (size_t)k * nq;
+    if (p->compact) h[k].qx = p->uperm + (size_t)k * nq;
   }
   HIPCHK(hipMemcpyAsync(p->vdk, h.data(), sizeof(VolDesc) * g.K, hipMemcpyHostToDevice, p->stream));
   HIPCHK(hipStreamSynchronize(p->stream));
@@ -978,10 +986,9 @@ extern "C" mh3d_status mh3d_plan(const mh3d_plan_desc* desc, mh3d_plan_t* out) {
   memset(p->launches, 0, sizeof p->launches);
   auto bail = [&](mh3d_status s) { mh3d_destroy(p); return s; };
   mh3d_status s;
-  const size_t hbytes = (size_t)g.C * g.K * g.hsz * (p->compact ? sizeof(float) : sizeof(float2));
-  if ((s = dalloc(p, &p->hs, hbytes)) != MH3D_OK) return bail(s);
+  if (!p->compact && (s = dalloc(p, &p->hs, sizeof(float2) * (size_t)g.C * g.K * g.hsz)) != MH3D_OK) return bail(s);
   if ((s = dalloc(p, (void**)&p->b, sizeof(float) * g.C * g.N)) != MH3D_OK) return bail(s);
-  if ((s = dalloc(p, (void**)&p->uperm, sizeof(float2) * (size_t)g.C * g.nx * g.plane)) != MH3D_OK) return bail(s);
+  if ((s = dalloc(p, (void**)&p->uperm, sizeof(float2) * uperm_elems(g, p->compact))) != MH3D_OK) return bail(s);
   if (p->compact) {
     if ((s = dalloc(p, (void**)&p->sfs, sizeof(float) * (size_t)g.K * g.nx)) != MH3D_OK) return bail(s);
     if ((s = dalloc(p, (void**)&p->set, sizeof(float2) * (size_t)g.sy * g.my * g.nzh)) != MH3D_OK) return bail(s);
@@ -992,7 +999,8 @@ extern "C" mh3d_status mh3d_plan(const mh3d_plan_desc* desc, mh3d_plan_t* out) {
     if ((s = dalloc(p, (void**)&p->vol[i], sizeof(float) * g.N)) != MH3D_OK) return bail(s);
   if ((s = dalloc(p, (void**)&p->prof, sizeof(double) * (size_t)g.K * g.nx)) != MH3D_OK) return bail(s);
   if ((s = dalloc(p, (void**)&p->env, sizeof(double) * (size_t)g.ny * g.nz)) != MH3D_OK) return bail(s);
-  if ((s = dalloc(p, (void**)&p->partials, sizeof(double) * 4 * 1024)) != MH3D_OK) return bail(s);
+  const size_t npart = std::max<size_t>(4 * 1024, 3 * (size_t)g.nx * (p->compact ? g.sy : 4));
+  if ((s = dalloc(p, (void**)&p->partials, sizeof(double) * npart)) != MH3D_OK) return bail(s);
   if ((s = dalloc(p, (void**)&p->st, sizeof(DevState))) != MH3D_OK) return bail(s);
   if ((s = dalloc(p, (void**)&p->vdd, 2 * sizeof(VolDesc))) != MH3D_OK) return bail(s);
   p->vda = p->vdd;
@@ -1033,10 +1041,16 @@ static mh3d_status check_plan(mh3d_plan_t p) {
 extern "C" mh3d_status mh3d_forward_adjoint(mh3d_plan_t p, const float* rho, float* d, float* x) {
   CHK(check_plan(p));
   if (!rho || !d || !x) return fail(MH3D_ERR_INVALID, "NULL array");
-  if (use_fast(p)) {
-    CHK(fast_plane_fwd(p, SRC_PLAIN, rho));
-    CHK(fast_class(p, 0, NRM_STORE));   // d's spectra and A^T's class pass
-    return fast_adj_and_store(p, d, x);
+  if (p->compact) {
+    CHK(sep_plane_fwd(p, SRC_PLAIN, rho));
+    if (!p->g.padded) {
+      CHK(sep_column(p, 0, NRM_STORE));   // d's spectra and A^T's column pass
+      return sep_adj_and_store(p, d, x);
+    }
+    CHK(sep_column(p, 0, COL_FWD));
+    CHK(launch_small_inv(p, EPI_STORE_BACK, d));   // stores d and starts A^T on its cropped copy
+    CHK(sep_column(p, 0, COL_ADJ));
+    return sep_plane_adj_out(p, x);
   }
   if (fused_class(p)) {
     {
@@ -1066,10 +1080,10 @@ extern "C" mh3d_status mh3d_forward_adjoint(mh3d_plan_t p, const float* rho, flo
 extern "C" mh3d_status mh3d_forward(mh3d_plan_t p, const float* rho, float* d) {
   CHK(check_plan(p));
   if (!rho || !d) return fail(MH3D_ERR_INVALID, "NULL array");
-  if (use_fast(p)) {
-    CHK(fast_plane_fwd(p, SRC_PLAIN, rho));
-    CHK(fast_class_alone(p, COL_FWD));
-    return fast_small_inv(p, d);
+  if (p->compact) {
+    CHK(sep_plane_fwd(p, SRC_PLAIN, rho));
+    CHK(sep_column(p, 0, COL_FWD));
+    return sep_small_inv(p, d);
   }
   CHK(launch_plane_fwd(p, SRC_PLAIN, rho));
   CHK(launch_class_fwd(p, 0, FWD_G));
@@ -1080,10 +1094,10 @@ extern "C" mh3d_status mh3d_forward(mh3d_plan_t p, const float* rho, float* d) {
 extern "C" mh3d_status mh3d_adjoint(mh3d_plan_t p, const float* d, float* rho) {
   CHK(check_plan(p));
   if (!rho || !d) return fail(MH3D_ERR_INVALID, "NULL array");
-  if (use_fast(p)) {
+  if (p->compact) {
     CHK(launch_small_fwd_adj(p, d));   // the portraits' small-grid spectra, into G'
-    CHK(fast_class_alone(p, COL_ADJ));
-    return fast_plane_adj_out(p, rho);
+    CHK(sep_column(p, 0, COL_ADJ));
+    return sep_plane_adj_out(p, rho);
   }
   CHK(launch_small_fwd(p, d));
   CHK(launch_class_adj(p, 0));
@@ -1095,19 +1109,8 @@ extern "C" mh3d_status mh3d_backproject(mh3d_plan_t p, const float* d, float* c)
   CHK(check_plan(p));
   if (!c || !d) return fail(MH3D_ERR_INVALID, "NULL array");
   CHK(launch_small_fwd_adj(p, d));
-  if (use_fast(p)) {
-    // column and plane passes of A^T with one descriptor per harmonic (all K at once when
-    // their Q buffers fit, else one harmonic after another through the shared one)
-    if (p->each_batched) {
-      p->fast->adjoint_each(p->ls, p->vdk, p->g.K, c);
-      return last_launch("k_fast_col / k_fast_plane_adj (per harmonic)");
-    }
-    for (int k = 0; k < p->g.K; ++k) {
-      p->fast->adjoint_each(p->ls, p->vdk + k, 1, c + (size_t)k * p->g.N);
-      CHK(last_launch("k_fast_col / k_fast_plane_adj (per harmonic)"));
-    }
-    return MH3D_OK;
-  }
+  // column and plane passes of A^T with one descriptor per harmonic, all K at once
+  if (p->compact) return sep_adjoint_each(p, p->vdk, p->g.K, c);
   for (int k = 0; k < p->g.K; ++k) {
     CHK(launch_class_adj(p, 0, p->vdk + k));
     CHK(launch_plane_adj(p, OUT_SCALE_B, c + (size_t)k * p->g.N, nullptr, p->vdk + k));
@@ -1117,10 +1120,16 @@ extern "C" mh3d_status mh3d_backproject(mh3d_plan_t p, const float* d, float* c)
 
 // out = (A^T A + lambda T^T T)(s w): s from the state (1/||w|| in power iteration).
 static mh3d_status apply_normal_scaled(mh3d_plan_t p, const float* w, float* out) {
-  if (use_fast(p)) {
-    CHK(fast_plane_fwd(p, SRC_SCALED, w));
-    CHK(fast_class(p, 1, NRM_PLAIN));
-    return fast_adjoint_step(p, UPD_NORMAL, out, w);
+  if (p->compact) {
+    CHK(sep_plane_fwd(p, SRC_SCALED, w));
+    if (p->g.padded) {
+      CHK(sep_column(p, 1, COL_FWD));
+      CHK(launch_small_inv(p, EPI_BACK, nullptr));   // crop to the field of view
+      CHK(sep_column(p, 1, COL_ADJ));
+    } else {
+      CHK(sep_column(p, 1, NRM_PLAIN));
+    }
+    return sep_adjoint_step(p, UPD_NORMAL, out, w);
   }
   CHK(launch_plane_fwd(p, SRC_SCALED, w));
   if (fused_class(p)) {
@@ -1196,10 +1205,16 @@ extern "C" mh3d_status mh3d_power_iteration(mh3d_plan_t p, int32_t iters, uint64
 // every later update ran in the previous update's last launch).
 static mh3d_status enqueue_update(mh3d_plan_t p, bool first) {
   Timer t(p, KID_SOLVE_ITER);
-  if (use_fast(p)) {
-    CHK(fast_plane_fwd(p, SRC_FISTA_Y, nullptr));
-    CHK(fast_class(p, 1, NRM_RESID));   // against the data's spectra, held in G'
-    return fast_adjoint_step(p, UPD_FISTA, nullptr, nullptr);
+  if (p->compact) {
+    CHK(sep_plane_fwd(p, SRC_FISTA_Y, nullptr));
+    if (p->g.padded) {
+      CHK(sep_column(p, 1, COL_FWD));
+      CHK(launch_small_inv(p, EPI_RESID_BACK, nullptr));   // residual on the field of view
+      CHK(sep_column(p, 1, COL_ADJ));
+    } else {
+      CHK(sep_column(p, 1, NRM_RESID));   // against the data's spectra, held in G'
+    }
+    return sep_adjoint_step(p, UPD_FISTA, nullptr, nullptr);
   }
   if (first || !step_and_fwd(p)) CHK(launch_plane_fwd(p, SRC_FISTA_Y, nullptr));
   if (fused_class(p)) {
@@ -1251,11 +1266,7 @@ static mh3d_status solve_setup(mh3d_plan_t p, const float* d, const float* rho0,
   // held in G for the whole solve (the fused class pass takes it one x' transform
   // further, into G')
   if (!g.padded) CHK(launch_small_fwd(p, d, p->G));
-  if (fused_class(p)) {
-    Timer t(p, KID_AUX);
-    k_class_data<<<dim3(g.ncls / g.cpw), dim3(p->L.T_class), p->L.lds_class, p->ls>>>(p->vda);
-    CHK(last_launch("k_class_data"));
-  }
+  if (fused_class(p)) CHK(sep_column(p, 0, COL_DATA));
   DevState s0;
   memset(&s0, 0, sizeof s0);
   s0.k = k0;
@@ -1414,12 +1425,14 @@ struct mh3d_batch_s {
   std::vector<mh3d_plan_t> plans;
   hipStream_t stream;
   VolDesc* vds = nullptr;            // device descriptors of all volumes
-  std::vector<VolDesc> hvd;          // their host copies (plane passes at one workgroup per plane)
-  // plane, class (padded volumes), small (padded volumes), fused class (the others), per-volume
+  std::vector<VolDesc> hvd;          // their host copies
+  // plane blocks, column blocks (padded volumes), small blocks (padded volumes), column
+  // blocks (the others), per-volume
   int2* tasks[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
   int ntask[5] = {0, 0, 0, 0, 0};
-  int T_class = 0, T_small = 0;
-  size_t lds_plane = 0, lds_class = 0, lds_small = 0;
+  int T_plane = 0, T_col = 0, T_small = 0;
+  bool col_any = false;
+  size_t lds_plane = 0, lds_col = 0, lds_col_resid = 0, lds_col_plain = 0, lds_small = 0;
   hipGraphExec_t gexec = nullptr;
   hipGraph_t graph = nullptr;
   hipStream_t cap_stream = nullptr;
@@ -1472,18 +1485,20 @@ extern "C" mh3d_status mh3d_batch_create(int32_t n, const mh3d_plan_t* plans, mh
   std::vector<int2> t[5];
   for (int v = 0; v < n; ++v) {
     const mh3d_plan_t p = plans[v];
-    // one workgroup per x-plane: the batch already fills the chip with the planes of
-    // many volumes, so splitting planes would only add work
-    for (int i = 0; i < p->g.nx; ++i) t[0].push_back(make_int2(v, i));
-    // volumes without padding run their class passes as one; the small-grid pass of the
+    for (int i = 0; i < p->g.nx * p->g.sy; ++i) t[0].push_back(make_int2(v, i));
+    // volumes without padding run their column passes as one; the small-grid pass of the
     // updates is needed only to crop to a field of view
-    push_xcd_grouped(t[p->g.padded ? 1 : 3], v, p->g.ncls / p->g.cpw);
+    push_xcd_grouped(t[p->g.padded ? 1 : 3], v, p->L.col_blocks);
     if (p->g.padded)
       for (int i = 0; i < p->g.K * (p->g.mx / p->g.xb); ++i) t[2].push_back(make_int2(v, i));
     t[4].push_back(make_int2(v, 0));
-    b->T_class = std::max(b->T_class, p->L.T_class);
-    b->lds_plane = std::max(b->lds_plane, p->L.lds_plane);
-    b->lds_class = std::max(b->lds_class, p->L.lds_class);
+    b->T_plane = std::max(b->T_plane, p->L.T_sep);
+    b->T_col = std::max(b->T_col, p->L.T_col);
+    b->col_any = b->col_any || p->L.col_any;
+    b->lds_plane = std::max(b->lds_plane, p->L.lds_sep);
+    b->lds_col = std::max(b->lds_col, p->L.lds_col);
+    b->lds_col_resid = std::max(b->lds_col_resid, p->L.lds_col_resid);
+    b->lds_col_plain = std::max(b->lds_col_plain, p->L.lds_col_plain);
     b->lds_small = std::max(b->lds_small, p->L.lds_small);
     if (p->g.padded) b->T_small = std::max(b->T_small, p->L.T_small);
   }
@@ -1501,69 +1516,60 @@ extern "C" mh3d_status mh3d_batch_create(int32_t n, const mh3d_plan_t* plans, mh
   return MH3D_OK;
 }
 
-// Device descriptor of volume v: the plan's, with one workgroup per x-plane.
+// Device descriptor of volume v: the plan's.
 static mh3d_status batch_upload(mh3d_batch_t b, int v) {
   b->hvd[v] = b->plans[v]->vdh;
-  b->hvd[v].g.ps = 1;
-  b->hvd[v].nb_upd = b->plans[v]->g.nx;   // the step's sums: one plane-pass block per x-plane
   HIPCHK(hipMemcpyAsync(b->vds + v, &b->hvd[v], sizeof(VolDesc), hipMemcpyHostToDevice, b->stream));
   return MH3D_OK;
 }
 
-// The class passes of every volume: one fused launch for the volumes without padding,
-// then forward class pass, crop (small-grid pass) and adjoint class pass for the padded
+// The column passes of every volume: one fused launch for the volumes without padding,
+// then forward column pass, crop (small-grid pass) and adjoint column pass for the padded
 // ones.  mode: NRM_RESID (updates) or NRM_PLAIN (power iteration).
-static mh3d_status batch_class(mh3d_batch_t b, hipStream_t st, int mode) {
+static mh3d_status batch_column(mh3d_batch_t b, hipStream_t st, int mode) {
   if (b->ntask[3]) {
-    k_class_normal_batch<<<dim3(b->ntask[3]), dim3(b->T_class), b->lds_class, st>>>(b->vds, b->tasks[3], mode);
-    CHK(last_launch("k_class_normal_batch"));
+    sep_launch_col(b->col_any, mode, dim3(b->ntask[3]), dim3(b->T_col), mode == NRM_RESID ? b->lds_col_resid : b->lds_col_plain, st,
+               b->vds, b->tasks[3], 1);
+    CHK(last_launch("k_sep_col (batch)"));
   }
   if (b->ntask[1]) {
-    k_class_fwd_batch<<<dim3(b->ntask[1]), dim3(b->T_class), b->lds_class, st>>>(b->vds, b->tasks[1], FWD_G);
-    CHK(last_launch("k_class_fwd_batch"));
-    if (mode == NRM_RESID)
-      k_small_inv<EPI_RESID_BACK><<<dim3(b->ntask[2]), dim3(b->T_small), b->lds_small, st>>>(b->vds, b->tasks[2], nullptr);
-    else
-      k_small_inv<EPI_BACK><<<dim3(b->ntask[2]), dim3(b->T_small), b->lds_small, st>>>(b->vds, b->tasks[2], nullptr);
-    CHK(last_launch("k_small_inv (batch)"));
-    k_class_adj_batch<<<dim3(b->ntask[1]), dim3(b->T_class), b->lds_class, st>>>(b->vds, b->tasks[1]);
-    CHK(last_launch("k_class_adj_batch"));
+    sep_launch_col(b->col_any, COL_FWD, dim3(b->ntask[1]), dim3(b->T_col), b->lds_col, st, b->vds, b->tasks[1], 1);
+    CHK(last_launch("k_sep_col (batch, forward)"));
+    sep_launch_small_inv(dim3(b->ntask[2]), dim3(b->T_small), b->lds_small, st, b->vds, b->tasks[2], nullptr,
+                         mode == NRM_RESID ? EPI_RESID_BACK : EPI_BACK);
+    CHK(last_launch("k_sep_small_inv (batch)"));
+    sep_launch_col(b->col_any, COL_ADJ, dim3(b->ntask[1]), dim3(b->T_col), b->lds_col, st, b->vds, b->tasks[1], 1);
+    CHK(last_launch("k_sep_col (batch, adjoint)"));
   }
   return MH3D_OK;
 }
 
-// One update of every volume of the batch: three launches over the task tables (three
-// more when some volume is padded: its forward class, small-grid and adjoint class
-// passes).  The batch runs one workgroup per x-plane, so the step's
-// launch also runs the next update's forward plane pass (k_step_and_fwd); the first
-// update of a solve call is preceded by batch_first_plane_pass.
+// One update of every volume of the batch over the task tables: forward plane pass, column
+// passes, adjoint plane pass ending in the step, finish.
 static mh3d_status batch_update(mh3d_batch_t b, hipStream_t st) {
-  CHK(batch_class(b, st, NRM_RESID));
+  sep_launch_plane_fwd(dim3(b->ntask[0]), dim3(b->T_plane), b->lds_plane, st, b->vds, b->tasks[0], nullptr, SRC_FISTA_Y);
+  CHK(last_launch("k_sep_plane_fwd (batch)"));
+  CHK(batch_column(b, st, NRM_RESID));
   AdjOut ao;
   ao.out = nullptr;
   ao.yin = nullptr;
-  k_step_and_fwd<<<dim3(b->ntask[0]), dim3(1024), b->lds_plane, st>>>(b->vds, b->tasks[0], ao);
-  CHK(last_launch("k_step_and_fwd (batch)"));
+  sep_launch_plane_adj(OUT_STEP_FISTA, dim3(b->ntask[0]), dim3(b->T_plane), b->lds_plane, st, b->vds, b->tasks[0], ao);
+  CHK(last_launch("k_sep_plane_adj (batch)"));
   k_vol_finish<UPD_FISTA><<<dim3(b->ntask[4]), dim3(256), 0, st>>>(b->vds, b->tasks[4]);
   CHK(last_launch("k_vol_finish (batch)"));
   return MH3D_OK;
 }
 
-static mh3d_status batch_first_plane_pass(mh3d_batch_t b, hipStream_t st) {
-  k_plane_fwd<SRC_FISTA_Y><<<dim3(b->ntask[0]), dim3(1024), b->lds_plane, st>>>(b->vds, b->tasks[0], nullptr);
-  return last_launch("k_plane_fwd (batch)");
-}
-
 // One power-iteration step of every volume: w_{t+1} = N (s w_t), w_t in rho[k & 1].
 static mh3d_status batch_power_step(mh3d_batch_t b, hipStream_t st) {
-  k_plane_fwd<SRC_SCALED><<<dim3(b->ntask[0]), dim3(1024), b->lds_plane, st>>>(b->vds, b->tasks[0], nullptr);
-  CHK(last_launch("k_plane_fwd (batch power)"));
-  CHK(batch_class(b, st, NRM_PLAIN));
+  sep_launch_plane_fwd(dim3(b->ntask[0]), dim3(b->T_plane), b->lds_plane, st, b->vds, b->tasks[0], nullptr, SRC_SCALED);
+  CHK(last_launch("k_sep_plane_fwd (batch power)"));
+  CHK(batch_column(b, st, NRM_PLAIN));
   AdjOut ao;
   ao.out = nullptr;
   ao.yin = nullptr;
-  k_plane_adj<OUT_STEP_NORMAL><<<dim3(b->ntask[0]), dim3(1024), b->lds_plane, st>>>(b->vds, b->tasks[0], ao);
-  CHK(last_launch("k_plane_adj (batch power)"));
+  sep_launch_plane_adj(OUT_STEP_NORMAL, dim3(b->ntask[0]), dim3(b->T_plane), b->lds_plane, st, b->vds, b->tasks[0], ao);
+  CHK(last_launch("k_sep_plane_adj (batch power)"));
   k_vol_finish<UPD_NORMAL><<<dim3(b->ntask[4]), dim3(256), 0, st>>>(b->vds, b->tasks[4]);
   CHK(last_launch("k_vol_finish (batch power)"));
   return MH3D_OK;
@@ -1654,7 +1660,6 @@ extern "C" mh3d_status mh3d_solve_batch(mh3d_batch_t b, const float* const* d, f
   // per-volume state snapshots after each replay; the graph is replayed until every
   // volume reports done (each volume stops updating at its own r_k <= tol)
   std::vector<DevState> hs(n);
-  CHK(batch_first_plane_pass(b, b->stream));
   int issued = 0;
   while (issued < opts->max_iter) {
     HIPCHK(hipGraphLaunch(b->gexec, b->stream));
@@ -1704,10 +1709,15 @@ extern "C" mh3d_status mh3d_plan_export(mh3d_plan_t p, mh3d_field field, void* d
     case MH3D_FIELD_ENVELOPE: HIPCHK(hipMemcpyAsync(dst, p->env, need, hipMemcpyDeviceToDevice, p->stream)); break;
     case MH3D_FIELD_SENS: HIPCHK(hipMemcpyAsync(dst, p->b, need, hipMemcpyDeviceToDevice, p->stream)); break;
     default:
+      if (p->compact) {
+        hipLaunchKernelGGL(k_spectrum_analytic, dim3(1024), dim3(256), 0, p->stream, g, p->fhat, p->ehat, p->scale,
+                           p->imag_mask, reinterpret_cast<float2*>(dst));
+        CHK(last_launch("k_spectrum_analytic"));
+        break;
+      }
       for (int c = 0; c < g.C; ++c) {
-        const size_t esz = p->compact ? sizeof(float) : sizeof(float2);
         hipLaunchKernelGGL(k_spectrum_export, dim3(1024), dim3(256), 0, p->stream, g,
-                           (const char*)p->hs + (size_t)c * g.K * g.hsz * esz, p->imag_mask, p->compact,
+                           (const float2*)p->hs + (size_t)c * g.K * g.hsz,
                            reinterpret_cast<float2*>(dst) + (size_t)c * g.K * g.nx * g.ny * g.nzh);
         CHK(last_launch("k_spectrum_export"));
       }
@@ -1786,17 +1796,19 @@ extern "C" mh3d_status mh3d_time_pass(mh3d_plan_t p, int32_t pass, int32_t reps,
   HIPCHK(hipMalloc(&dtmp, sizeof(float) * (size_t)p->g.K * p->g.M));
   (void)hipMemsetAsync(p->vol[0], 0, sizeof(float) * p->g.N, p->stream);
   (void)hipMemsetAsync(dtmp, 0, sizeof(float) * (size_t)p->g.K * p->g.M, p->stream);
-  const bool fast = use_fast(p);
   auto launch = [&]() -> mh3d_status {
-    // the compile-time passes where the plan has them
-    if (fast && pass == 0) return fast_plane_fwd(p, SRC_PLAIN, p->vol[0]);
-    if (fast && pass == 1) return fast_class_alone(p, COL_FWD);
-    if (fast && pass == 2) return fast_small_inv(p, dtmp);
-    if (fast && pass == 3) return launch_small_fwd_adj(p, dtmp);
-    if (fast && pass == 4) return fast_class_alone(p, COL_ADJ);
-    if (fast && pass == 5) return fast_plane_adj_out(p, p->vol[1]);
-    if (fast && pass == 6) return fast_class(p, 0, NRM_STORE);
-    if (fast && pass == 7) return fast_adj_and_store(p, dtmp, p->vol[1]);
+    if (p->compact) {
+      switch (pass) {
+        case 0: return sep_plane_fwd(p, SRC_PLAIN, p->vol[0]);
+        case 1: return sep_column(p, 0, COL_FWD);
+        case 2: return sep_small_inv(p, dtmp);
+        case 3: return launch_small_fwd_adj(p, dtmp);
+        case 4: return sep_column(p, 0, COL_ADJ);
+        case 6: return sep_column(p, 0, NRM_STORE);
+        case 7: return sep_adj_and_store(p, dtmp, p->vol[1]);
+        default: return sep_plane_adj_out(p, p->vol[1]);
+      }
+    }
     switch (pass) {
       case 0: return launch_plane_fwd(p, SRC_PLAIN, p->vol[0]);
       case 1: return launch_class_fwd(p, 0, FWD_G);
@@ -1812,7 +1824,7 @@ extern "C" mh3d_status mh3d_time_pass(mh3d_plan_t p, int32_t pass, int32_t reps,
   // the passes' inputs: one full A and A^T first so every intermediate buffer is set
   s = mh3d_forward(p, p->vol[0], dtmp);
   if (s == MH3D_OK) s = mh3d_adjoint(p, dtmp, p->vol[1]);
-  if (s == MH3D_OK && fast) s = mh3d_forward_adjoint(p, p->vol[0], dtmp, p->vol[1]);
+  if (s == MH3D_OK && p->compact) s = mh3d_forward_adjoint(p, p->vol[0], dtmp, p->vol[1]);
   for (int i = 0; i < 3 && s == MH3D_OK; ++i) s = launch();
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (s == MH3D_OK && (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess))
@@ -2049,6 +2061,8 @@ static mh3d_status tune_general(mh3d_plan_t p, const char* cache_path, mh3d_tile
         }
       }
     }
+    // analytic plans run no class passes: of the tiles only xb counts
+    if (p->compact) cands.assign(1, mh3d_tiles{g0.E, g0.cpw, 0, g0.ps});
     mh3d_tiles best{0, 0, 0, 0};
     int best_tm = 0;
     double best_us = 1e30;
@@ -2069,6 +2083,10 @@ static mh3d_status tune_general(mh3d_plan_t p, const char* cache_path, mh3d_tile
     const mh3d_tiles cls = best;
     for (int xb : {1, 2, 4, 8, 16, 32}) {
       if (g0.mx % xb) continue;
+      if (p->compact) {
+        CHK(trial(mh3d_tiles{cls.E, cls.cpw, xb, cls.ps}, 0));
+        continue;
+      }
       for (int ps : {1, 2, 4}) {
         if (ps > g0.nzh || ps > g0.npairs) continue;
         for (int tm : {512, 1024}) CHK(trial(mh3d_tiles{cls.E, cls.cpw, xb, ps}, tm));
@@ -2084,7 +2102,7 @@ static mh3d_status tune_general(mh3d_plan_t p, const char* cache_path, mh3d_tile
     int best_pss = best.ps;
     double best_nus = 1e30;
     for (int ps : {1, 2, 4}) {
-      if (!valid_ps(p->g, ps)) continue;
+      if (p->compact || !valid_ps(p->g, ps)) continue;
       p->ps_solve = ps;
       CHK(upload_desc(p));
       double us = 0;

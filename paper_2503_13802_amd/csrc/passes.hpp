@@ -1,0 +1,56 @@
+// Launchers of the separable passes, defined in translation units of their own (sep.hip,
+// fast.hip): their kernels are most of the library's code, and the units compile side by
+// side.
+#pragma once
+#include "kernels.hpp"
+
+namespace mh3d {
+
+// Column-pass modes beyond NRM_RESID, NRM_PLAIN and NRM_STORE (kernels.hpp): A alone, A^T
+// alone, and COL_DATA, the x' transform of the measured portraits' small-grid spectra (G,
+// as the small-grid pass left them) into G' as [k][column][q'x], the solver's data term.
+enum { COL_FWD = 16, COL_ADJ = 17, COL_DATA = 18 };
+constexpr int SXR = 4;   // x aliases that the column pass keeps in registers
+
+// ---------------------------------------------------------------------------- fast passes
+// Launchers of the compile-time-geometry passes (fast.hpp) of one grid, decimation and
+// tile shape.  All passes of a fused sequence come from one entry (their slot layout is
+// their own).
+struct FastOps {
+  int nx, ny, nz, sx, sy, sz, kmax;
+  int nbp, ncls_blocks, tc;
+  size_t lds_plane, lds_class;
+  void (*plane_fwd)(hipStream_t, const VolDesc*, int src, const float* a);
+  void (*cls)(hipStream_t, const VolDesc*, int mode, int chk);
+  void (*plane_adj)(hipStream_t, const VolDesc*, int out, AdjOut ao);
+  void (*adj_and_store)(hipStream_t, const VolDesc*, AdjOut ao, float* d, int nsmall, int xb);
+  void (*small_inv)(hipStream_t, const VolDesc*, float* d, int nsmall, int xb);
+  // A^T of nv single-harmonic descriptors at once (each with its own qx): out volumes
+  // out + v N for v < nv
+  void (*adjoint_each)(hipStream_t, const VolDesc*, int nv, float* out);
+  // the portraits' small-grid spectra into G' (as k_sep_small_fwd)
+  void (*small_fwd)(hipStream_t, const VolDesc*, const float* r, float2* out, int nsmall, int xb);
+};
+
+// The compiled grids.
+extern const FastOps kFast[];
+extern const int kFastCount;
+
+// ---------------------------------------------------------------------------- run-time geometry
+// tasks: the task table of a batch, or NULL (descriptor blockIdx.y, block blockIdx.x).
+void sep_launch_plane_fwd(dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, const int2* tasks,
+                          const float* a, int src);
+// any: the general form (harmonics in groups, any number of x aliases)
+void sep_launch_col(bool any, int mode, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd,
+                    const int2* tasks, int chk);
+void sep_launch_plane_adj(int out, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, const int2* tasks,
+                          AdjOut ao);
+void sep_launch_adj_and_store(dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, AdjOut ao, float* d,
+                              int nbp);
+void sep_launch_small_inv(dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, const int2* tasks, float* d,
+                          int epi);
+void sep_launch_small_fwd(dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, const float* r, float2* out);
+// the adjoint plane pass of a user-PSF plan beside the small-grid pass
+void launch_user_adj_and_store(dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, AdjOut ao, float* d);
+
+}  // namespace mh3d
