@@ -26,17 +26,25 @@ struct NetLayer {
   long long w_off, b_off;  // offsets in the flat FP32 parameter vector
   uint16_t* Wf = nullptr;  // BF16 forward matrix
   uint16_t* Wt = nullptr;  // BF16 flipped transposed matrix
-  float* gWf = nullptr;    // FP32 gradient of the forward matrix (a slice of the network's gW)
 };
 
 // Activations and gradients of one grid shape.
 struct NetWork {
   int lx, ly, lz;
-  std::vector<uint16_t*> bufs;
+  char* mem = nullptr;                    // every tensor below but xin
   uint16_t* x0 = nullptr;                 // input [N0][4]
   std::vector<uint16_t*> ea, es, pl;      // enc conv a / conv b (skip) outputs, pooled inputs (level l+1)
   std::vector<uint16_t*> cat, da, db;     // decoder concat input, conv a, conv b outputs
-  std::vector<uint16_t*> g1, g2, g3, gs;  // gradient scratch per level (max channel stride) and skip grads
+  std::vector<uint16_t*> gl;              // gradient of every layer's pre-activation output (the head's: gy)
+  std::vector<uint16_t*> gcat, gpl;       // gradients of the concatenations and of the pooled inputs
+  // weight gradients (k_wgrad): layer and task tables, the tasks' sums, in one allocation
+  char* wgmem = nullptr;
+  WgLayer* wgl = nullptr;
+  WgTask* wgt = nullptr;
+  int nwgt = 0, wsum_blocks = 0;
+  WgBlocks wsum_first;
+  size_t wg_lds = 0;
+  float* wgpart = nullptr;
   float* y = nullptr;                     // head output FP32 [N0]
   float* xin = nullptr;                   // warm start: per-harmonic back-projections [C][N0] (lazy)
   uint16_t* gy = nullptr;                 // head output gradient [N0][4]
@@ -59,10 +67,8 @@ struct mh3d_net_s {
   hipStream_t stream;
   std::map<std::tuple<int, int, int>, NetWork> work;
   bool packed = false;
-  float* gW = nullptr;           // every layer's FP32 forward-matrix gradient, one buffer
-  long long gW_len = 0;
-  PackDesc* pack = nullptr;      // device table of the layers for k_pack_all / k_unpack_all
-  int pack_blocks = 0, unpack_blocks = 0;
+  PackDesc* pack = nullptr;      // device table of the layers for k_pack_all
+  int pack_blocks = 0;
 };
 
 namespace {
@@ -92,6 +98,105 @@ mh3d_status net_pack(mh3d_net_t n) {
   return MH3D_OK;
 }
 
+Dims dims_of(const NetWork& w, int l) { return Dims{w.lx - l, w.ly - l, w.lz - l}; }
+
+// Level of layer i in the parameter order.
+int layer_level(int L, int i) { return i < 2 * L ? i / 2 : (i == 4 * L - 2 ? 0 : L - 2 - (i - 2 * L) / 2); }
+
+// The tables of the weight gradients and the tasks' sums, for a workspace whose tensors are allocated.
+mh3d_status net_train_work(mh3d_net_t n, NetWork* w) {
+  const int L = (int)n->widths.size(), nl = (int)n->layers.size();
+  // inputs of the layers, in the parameter order
+  std::vector<const uint16_t*> in(nl);
+  for (int l = 0; l < L; ++l) {
+    in[enc_index(l, 0)] = l ? w->pl[l] : w->x0;
+    in[enc_index(l, 1)] = w->ea[l];
+    if (l < L - 1) {
+      in[dec_index(L, l, 0)] = w->cat[l];
+      in[dec_index(L, l, 1)] = w->da[l];
+    }
+  }
+  in[nl - 1] = w->db[0];
+  std::vector<WgLayer> wl(nl);
+  std::vector<std::pair<long long, WgTask>> tasks;   // (cost, task)
+  std::fill(w->wsum_first.sb0, w->wsum_first.sb0 + 24, INT_MAX);
+  long long off = 0;
+  for (int i = 0; i < nl; ++i) {
+    const NetLayer& ly = n->layers[i];
+    const Dims dm = dims_of(*w, layer_level(L, i));
+    WgLayer& d = wl[i];
+    memset(&d, 0, sizeof d);
+    d.in = in[i];
+    d.gout = w->gl[i];
+    d.dm = dm;
+    d.cs_in = ly.cs_in;
+    d.cs_g = ly.cs_out;
+    d.cout = ly.cout;
+    d.cin = ly.cin;
+    d.ntap = ly.ks == 3 ? 27 : 1;
+    // 4 x 4 x 16 voxels where the grid is that long, else the most the axes give up to 256; z
+    // at least a lane's 8 (beyond a shorter grid the tile holds zeros)
+    d.ltz = std::min(4, std::max(3, dm.lz));
+    d.lty = std::min(dm.ly, 8 - d.ltz - std::min(2, dm.lx));
+    d.ltx = std::min(dm.lx, 8 - d.ltz - d.lty);
+    auto halo = [&] { return ((1 << d.ltx) + 2) * ((1 << d.lty) + 2) * ((1 << d.ltz) + 2); };
+    while (halo() > WG_HALO) --(d.lty > d.ltx ? d.lty : d.ltx);
+    d.ntx = dm.lx - d.ltx;
+    d.nty = dm.ly - d.lty;
+    d.ntz = std::max(0, dm.lz - d.ltz);
+    const int ntiles = 1 << (d.ntx + d.nty + d.ntz);
+    const int nh = halo();
+    d.gw = n->g + ly.w_off;
+    d.gb = n->g + ly.b_off;
+    d.nchunk = (ly.cs_in + WG_CC - 1) / WG_CC;
+    // time of a tile in MFMA steps of a wave, staging about 60; tiles per task: WG_COST of them, so
+    // that the level-0 layers make about three blocks per CU (the LDS of a task allows three) and the
+    // deep layers still split; at most WG_SPLIT slices
+    constexpr int WG_COST = 1000, WG_SPLIT = 512;
+    const int steps = std::max(1, (1 << (d.ltx + d.lty + d.ltz)) / 32);
+    auto cost = [&](int q) {
+      const int groups = wg_groups(d.ntap, wg_chunk(ly.cs_in, q)), wc = wg_waves(groups);
+      return 60 + 3 * ((groups + wc - 1) / wc) * std::max(1, steps * wc / 4);
+    };
+    const int tpb = std::max({1, std::min(ntiles, WG_COST / cost(0)), (ntiles + WG_SPLIT - 1) / WG_SPLIT});
+    d.nsplit = (ntiles + tpb - 1) / tpb;
+    d.sb0 = w->wsum_blocks;
+    if (i) w->wsum_first.sb0[i - 1] = d.sb0;
+    d.snb = (ly.cout * (d.ntap * ly.cin + 1) + ws_vals(d.nsplit) - 1) / ws_vals(d.nsplit);
+    w->wsum_blocks += d.snb;
+    const int nu = (ly.cout + 15) / 16;
+    for (int q = 0; q < d.nchunk; ++q) {
+      const int cc = wg_chunk(ly.cs_in, q);
+      d.base[q] = off;
+      off += (long long)nu * d.nsplit * 16 * wg_cols(d.ntap, cc);
+      w->wg_lds = std::max(w->wg_lds, wgrad_lds(d.ntap, cc, nh));
+      for (int u = 0; u < nu; ++u)
+        for (int sp = 0; sp < d.nsplit; ++sp) {
+          const int t0 = sp * tpb, nt = std::min(tpb, ntiles - t0);
+          tasks.push_back({(long long)nt * cost(q), WgTask{i, q, u, sp, t0, nt}});
+        }
+    }
+    d.bbase = off;
+    off += (long long)nu * d.nsplit * 16;
+  }
+  if (w->wg_lds > kLdsLimit) return fail(MH3D_ERR_UNSUPPORTED, "weight-gradient tile does not fit in LDS");
+  // the longest tasks first
+  std::stable_sort(tasks.begin(), tasks.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+  w->nwgt = (int)tasks.size();
+  // one allocation: the layer table, the task table, the sums; the tables in one copy
+  const size_t lb = (sizeof(WgLayer) * nl + 255) & ~(size_t)255, tb = (sizeof(WgTask) * tasks.size() + 255) & ~(size_t)255;
+  std::vector<char> host(lb + tb);
+  memcpy(host.data(), wl.data(), sizeof(WgLayer) * nl);
+  for (size_t i = 0; i < tasks.size(); ++i) memcpy(host.data() + lb + i * sizeof(WgTask), &tasks[i].second, sizeof(WgTask));
+  CHK(net_alloc((void**)&w->wgmem, lb + tb + sizeof(float) * (size_t)off));
+  w->wgl = (WgLayer*)w->wgmem;
+  w->wgt = (WgTask*)(w->wgmem + lb);
+  w->wgpart = (float*)(w->wgmem + lb + tb);
+  HIPCHK(hipMemcpyAsync(w->wgmem, host.data(), host.size(), hipMemcpyHostToDevice, n->stream));
+  HIPCHK(hipStreamSynchronize(n->stream));
+  return MH3D_OK;
+}
+
 mh3d_status net_work(mh3d_net_t n, int nx, int ny, int nz, NetWork** out) {
   auto key = std::make_tuple(nx, ny, nz);
   auto it = n->work.find(key);
@@ -100,65 +205,79 @@ mh3d_status net_work(mh3d_net_t n, int nx, int ny, int nz, NetWork** out) {
   NetWork w;
   w.lx = ilog2(nx); w.ly = ilog2(ny); w.lz = ilog2(nz);
   auto nvox = [&](int l) { return 1ll << (w.lx + w.ly + w.lz - 3 * l); };
-  auto mk = [&](long long elems, uint16_t** p) -> mh3d_status {
-    void* q = nullptr;
-    CHK(net_alloc(&q, sizeof(uint16_t) * (size_t)elems));
-    (void)hipMemsetAsync(q, 0, sizeof(uint16_t) * (size_t)elems, n->stream);
-    w.bufs.push_back((uint16_t*)q);
-    *p = (uint16_t*)q;
-    return MH3D_OK;
+  // every tensor in one allocation, 256-byte aligned
+  std::vector<std::pair<size_t, void**>> parts;
+  size_t total = 0;
+  auto take = [&](size_t bytes, void** p) {
+    parts.push_back({total, p});
+    total += (bytes + 255) & ~(size_t)255;
   };
-  CHK(mk(nvox(0) * round4(n->in_ch), &w.x0));
+  auto mk = [&](long long elems, uint16_t** p) { take(sizeof(uint16_t) * (size_t)elems, (void**)p); };
+  mk(nvox(0) * round4(n->in_ch), &w.x0);
   w.ea.resize(L); w.es.resize(L); w.pl.resize(L); w.cat.resize(L); w.da.resize(L); w.db.resize(L);
-  w.g1.resize(L); w.g2.resize(L); w.g3.resize(L); w.gs.resize(L);
-  int cmax_all = 4;
+  w.gl.resize(n->layers.size()); w.gcat.resize(L); w.gpl.resize(L);
   for (int l = 0; l < L; ++l) {
     const int cs = round4(n->widths[l]);
     const int cats = l < L - 1 ? round4(n->widths[l] + n->widths[l + 1]) : 4;
-    const int cmax = std::max(std::max(cs, cats), l ? round4(n->widths[l - 1]) : 4);
-    cmax_all = std::max(cmax_all, cmax);
-    CHK(mk(nvox(l) * cs, &w.ea[l]));
-    CHK(mk(nvox(l) * cs, &w.es[l]));
-    if (l) CHK(mk(nvox(l) * round4(n->widths[l - 1]), &w.pl[l]));
+    mk(nvox(l) * cs, &w.ea[l]);
+    mk(nvox(l) * cs, &w.es[l]);
+    if (l) mk(nvox(l) * round4(n->widths[l - 1]), &w.pl[l]);
     if (l < L - 1) {
-      CHK(mk(nvox(l) * cats, &w.cat[l]));
-      CHK(mk(nvox(l) * cs, &w.da[l]));
-      CHK(mk(nvox(l) * cs, &w.db[l]));
+      mk(nvox(l) * cats, &w.cat[l]);
+      mk(nvox(l) * cs, &w.da[l]);
+      mk(nvox(l) * cs, &w.db[l]);
     }
-    CHK(mk(nvox(l) * cmax, &w.g1[l]));
-    CHK(mk(nvox(l) * cmax, &w.g2[l]));
-    CHK(mk(nvox(l) * cmax, &w.g3[l]));
-    CHK(mk(nvox(l) * cs, &w.gs[l]));
   }
-  CHK(mk(nvox(0) * 4, &w.gy));
-  CHK(net_alloc((void**)&w.y, sizeof(float) * (size_t)nvox(0)));
-  // [scale, loss, (unused), (unused), absmax slot]
-  CHK(net_alloc((void**)&w.scale, sizeof(double) * 5));
-  (void)hipMemsetAsync(w.scale, 0, sizeof(double) * 5, n->stream);
+  mk(nvox(0) * 4, &w.gy);
+  // training: every layer's gradient
+  const int nl = (int)n->layers.size();
+  for (int i = 0; i + 1 < nl; ++i) mk(nvox(layer_level(L, i)) * n->layers[i].cs_out, &w.gl[i]);
+  for (int l = 0; l < L; ++l) {
+    if (l < L - 1) mk(nvox(l) * round4(n->widths[l] + n->widths[l + 1]), &w.gcat[l]);
+    if (l) mk(nvox(l) * round4(n->widths[l - 1]), &w.gpl[l]);
+  }
+  take(sizeof(float) * (size_t)nvox(0), (void**)&w.y);
+  take(sizeof(double) * 5, (void**)&w.scale);   // [scale, loss, (unused), (unused), absmax slot]
+  CHK(net_alloc((void**)&w.mem, total));
+  (void)hipMemsetAsync(w.mem, 0, total, n->stream);
+  for (auto& e : parts) *e.second = w.mem + e.first;
+  w.gl[nl - 1] = w.gy;
   w.loss = w.scale + 1;
-  (void)cmax_all;
+  if (mh3d_status st = net_train_work(n, &w)) {
+    (void)hipStreamSynchronize(n->stream);
+    (void)hipFree(w.mem);
+    (void)hipFree(w.wgmem);
+    return st;
+  }
   auto res = n->work.emplace(key, w);
   *out = &res.first->second;
   return MH3D_OK;
 }
 
-Dims dims_of(const NetWork& w, int l) { return Dims{w.lx - l, w.ly - l, w.lz - l}; }
 
 // One convolution out = act(conv(in, W) + bias), BF16 channels-last output with
 // channel stride cs_out (or FP32 single-channel for the head).  3x3x3 layers with at
 // most 32 output channels on grids of at least 4 x 4 x 16 run the LDS-tiled kernel.
 // k_conv_ct for the channel strides it is compiled for (false: none, or kp does not
 // match the compile-time K).
+// At most this many blocks (two per CU) run with the weights loaded up front.
+constexpr int kPreBlocks = 512;
 template <int CS>
 bool conv_ct_try(hipStream_t s, int ntile, bool relu, int blocks, const uint16_t* in, Dims dm, const uint16_t* W,
-                 int kp, const float* bias, int cout, int cs_out, uint16_t* o) {
+                 int kp, const float* bias, int cout, int cs_out, uint16_t* o, const uint16_t* mask, uint16_t* pool) {
   if (kp != 16 * ((27 * CS + 15) / 16) || ntile < 1 || ntile > 2) return false;
-  if (ntile == 1) {
-    if (relu) k_conv_ct<CS, 1, true><<<blocks, 256, conv_ct_lds<CS, 1>(), s>>>(in, dm, W, kp, bias, cout, cs_out, o, nullptr);
-    else k_conv_ct<CS, 1, false><<<blocks, 256, conv_ct_lds<CS, 1>(), s>>>(in, dm, W, kp, bias, cout, cs_out, o, nullptr);
+  // a short reduction in one tile gains nothing (16^3 voxels, 16 -> 16 channels: 5.4 against 5.9 us),
+  // and 48 channels of weights leave a SIMD one wave (9.1 against 11.7 us at 32^3)
+  if (blocks * ntile <= kPreBlocks && CS <= 32 && (CS >= 24 || ntile == 2)) {
+    const dim3 gr(blocks, ntile);
+    if (relu) k_conv_ct<CS, 1, true, 0, true><<<gr, 256, conv_ct_lds<CS, 1>(), s>>>(in, dm, W, kp, bias, cout, cs_out, o, nullptr, mask, pool);
+    else k_conv_ct<CS, 1, false, 0, true><<<gr, 256, conv_ct_lds<CS, 1>(), s>>>(in, dm, W, kp, bias, cout, cs_out, o, nullptr, mask, pool);
+  } else if (ntile == 1) {
+    if (relu) k_conv_ct<CS, 1, true><<<blocks, 256, conv_ct_lds<CS, 1>(), s>>>(in, dm, W, kp, bias, cout, cs_out, o, nullptr, mask, pool);
+    else k_conv_ct<CS, 1, false><<<blocks, 256, conv_ct_lds<CS, 1>(), s>>>(in, dm, W, kp, bias, cout, cs_out, o, nullptr, mask, pool);
   } else {
-    if (relu) k_conv_ct<CS, 2, true><<<blocks, 256, conv_ct_lds<CS, 2>(), s>>>(in, dm, W, kp, bias, cout, cs_out, o, nullptr);
-    else k_conv_ct<CS, 2, false><<<blocks, 256, conv_ct_lds<CS, 2>(), s>>>(in, dm, W, kp, bias, cout, cs_out, o, nullptr);
+    if (relu) k_conv_ct<CS, 2, true><<<blocks, 256, conv_ct_lds<CS, 2>(), s>>>(in, dm, W, kp, bias, cout, cs_out, o, nullptr, mask, pool);
+    else k_conv_ct<CS, 2, false><<<blocks, 256, conv_ct_lds<CS, 2>(), s>>>(in, dm, W, kp, bias, cout, cs_out, o, nullptr, mask, pool);
   }
   return true;
 }
@@ -169,94 +288,118 @@ template <int CS, int C1>
 bool conv_ct_cat_try(hipStream_t s, int ntile, int blocks, const uint16_t* skip, const uint16_t* coarse, Dims dm,
                      const uint16_t* W, int kp, const float* bias, int cout, int cs_out, uint16_t* o) {
   if (kp != 16 * ((27 * CS + 15) / 16) || ntile < 1 || ntile > 2) return false;
-  if (ntile == 1)
-    k_conv_ct<CS, 1, true, C1><<<blocks, 256, conv_ct_lds<CS, 1>(), s>>>(skip, dm, W, kp, bias, cout, cs_out, o, coarse);
+  if (blocks * ntile <= kPreBlocks && CS <= 32 && (CS >= 24 || ntile == 2))
+    k_conv_ct<CS, 1, true, C1, true><<<dim3(blocks, ntile), 256, conv_ct_lds<CS, 1>(), s>>>(skip, dm, W, kp, bias, cout, cs_out, o, coarse, nullptr, nullptr);
+  else if (ntile == 1)
+    k_conv_ct<CS, 1, true, C1><<<blocks, 256, conv_ct_lds<CS, 1>(), s>>>(skip, dm, W, kp, bias, cout, cs_out, o, coarse, nullptr, nullptr);
   else
-    k_conv_ct<CS, 2, true, C1><<<blocks, 256, conv_ct_lds<CS, 2>(), s>>>(skip, dm, W, kp, bias, cout, cs_out, o, coarse);
+    k_conv_ct<CS, 2, true, C1><<<blocks, 256, conv_ct_lds<CS, 2>(), s>>>(skip, dm, W, kp, bias, cout, cs_out, o, coarse, nullptr, nullptr);
   return true;
 }
 
-// k_conv_splitk8 with the output tile count as a compile-time constant.
-template <int NT>
-void splitk8_nt(hipStream_t s, bool relu, int blocks, const uint16_t* in, Dims dm, int cs_in, int ks, const uint16_t* W,
-                int kp, const float* bias, int cout, int cs_out, uint16_t* o) {
-  if (relu) k_conv_splitk8<true, NT><<<blocks, 256, 0, s>>>(in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o);
-  else k_conv_splitk8<false, NT><<<blocks, 256, 0, s>>>(in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o);
+// k_conv_splitk8 with the output tile count as a compile-time constant; groups of 16 voxels.
+template <int NT, int VG = 1>
+void splitk8_nt(hipStream_t s, bool relu, dim3 groups, const uint16_t* in, Dims dm, int cs_in, int ks, const uint16_t* W,
+                int kp, const float* bias, int cout, int cs_out, uint16_t* o, const uint16_t* mask) {
+  const dim3 blocks((groups.x + VG - 1) / VG, groups.y);
+  if (relu) k_conv_splitk8<true, NT, VG><<<blocks, 256, 0, s>>>(in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o, mask);
+  else k_conv_splitk8<false, NT, VG><<<blocks, 256, 0, s>>>(in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o, mask);
 }
 
 void splitk8(hipStream_t s, bool relu, int ntile, int blocks, const uint16_t* in, Dims dm, int cs_in, int ks,
-             const uint16_t* W, int kp, const float* bias, int cout, int cs_out, uint16_t* o) {
+             const uint16_t* W, int kp, const float* bias, int cout, int cs_out, uint16_t* o, const uint16_t* mask) {
+  // few voxels: the output tiles on blocks of their own (each repeats the input gathers;
+  // the sums are the same).  8^3 voxels, 80 channels: 12.5 against
+  // 8.2 us; 16^3: 13.8 against 12.4
+  if (blocks * ntile <= 2048 && ntile > 1 && blocks <= 512) {
+    splitk8_nt<1>(s, relu, dim3(blocks, ntile), in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o, mask);
+    return;
+  }
+  // many voxels: four groups of them per block
+  if (blocks >= 1024 && ntile <= 2) {
+    if (ntile == 1) splitk8_nt<1, 4>(s, relu, dim3(blocks), in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o, mask);
+    else splitk8_nt<2, 4>(s, relu, dim3(blocks), in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o, mask);
+    return;
+  }
   switch (ntile) {
-    case 1: splitk8_nt<1>(s, relu, blocks, in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o); break;
-    case 2: splitk8_nt<2>(s, relu, blocks, in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o); break;
-    case 3: splitk8_nt<3>(s, relu, blocks, in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o); break;
-    case 4: splitk8_nt<4>(s, relu, blocks, in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o); break;
-    case 5: splitk8_nt<5>(s, relu, blocks, in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o); break;
-    case 6: splitk8_nt<6>(s, relu, blocks, in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o); break;
-    case 7: splitk8_nt<7>(s, relu, blocks, in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o); break;
-    default: splitk8_nt<8>(s, relu, blocks, in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o); break;
+    case 1: splitk8_nt<1>(s, relu, dim3(blocks), in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o, mask); break;
+    case 2: splitk8_nt<2>(s, relu, dim3(blocks), in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o, mask); break;
+    case 3: splitk8_nt<3>(s, relu, dim3(blocks), in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o, mask); break;
+    case 4: splitk8_nt<4>(s, relu, dim3(blocks), in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o, mask); break;
+    case 5: splitk8_nt<5>(s, relu, dim3(blocks), in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o, mask); break;
+    case 6: splitk8_nt<6>(s, relu, dim3(blocks), in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o, mask); break;
+    case 7: splitk8_nt<7>(s, relu, dim3(blocks), in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o, mask); break;
+    default: splitk8_nt<8>(s, relu, dim3(blocks), in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o, mask); break;
   }
 }
 
 bool conv_ct(hipStream_t s, int cs_in, int ntile, bool relu, int blocks, const uint16_t* in, Dims dm, const uint16_t* W,
-             int kp, const float* bias, int cout, int cs_out, uint16_t* o) {
+             int kp, const float* bias, int cout, int cs_out, uint16_t* o, const uint16_t* mask, uint16_t* pool) {
   switch (cs_in) {
-    case 4: return conv_ct_try<4>(s, ntile, relu, blocks, in, dm, W, kp, bias, cout, cs_out, o);
-    case 8: return conv_ct_try<8>(s, ntile, relu, blocks, in, dm, W, kp, bias, cout, cs_out, o);
-    case 12: return conv_ct_try<12>(s, ntile, relu, blocks, in, dm, W, kp, bias, cout, cs_out, o);
-    case 16: return conv_ct_try<16>(s, ntile, relu, blocks, in, dm, W, kp, bias, cout, cs_out, o);
-    case 24: return conv_ct_try<24>(s, ntile, relu, blocks, in, dm, W, kp, bias, cout, cs_out, o);
-    case 32: return conv_ct_try<32>(s, ntile, relu, blocks, in, dm, W, kp, bias, cout, cs_out, o);
-    case 48: return conv_ct_try<48>(s, ntile, relu, blocks, in, dm, W, kp, bias, cout, cs_out, o);
+    case 4: return conv_ct_try<4>(s, ntile, relu, blocks, in, dm, W, kp, bias, cout, cs_out, o, mask, pool);
+    case 8: return conv_ct_try<8>(s, ntile, relu, blocks, in, dm, W, kp, bias, cout, cs_out, o, mask, pool);
+    case 12: return conv_ct_try<12>(s, ntile, relu, blocks, in, dm, W, kp, bias, cout, cs_out, o, mask, pool);
+    case 16: return conv_ct_try<16>(s, ntile, relu, blocks, in, dm, W, kp, bias, cout, cs_out, o, mask, pool);
+    case 24: return conv_ct_try<24>(s, ntile, relu, blocks, in, dm, W, kp, bias, cout, cs_out, o, mask, pool);
+    case 32: return conv_ct_try<32>(s, ntile, relu, blocks, in, dm, W, kp, bias, cout, cs_out, o, mask, pool);
+    case 48: return conv_ct_try<48>(s, ntile, relu, blocks, in, dm, W, kp, bias, cout, cs_out, o, mask, pool);
     default: return false;
   }
 }
 
+// BF16 output.  pool (or NULL): where the 2x2x2 averages of the output go; set to NULL if they were
+// formed here.  mask (or NULL): the post-ReLU tensor whose gradient this is (zeroed where it is not > 0).
 mh3d_status launch_conv(mh3d_net_t n, const uint16_t* in, Dims dm, int cs_in, int ks, const uint16_t* W, int kp,
-                        const float* bias, int cout, int cs_out, void* out, bool relu, bool f32) {
+                        const float* bias, int cout, int cs_out, uint16_t* o, bool relu, const uint16_t* mask = nullptr,
+                        uint16_t** pool = nullptr) {
   const long long N = 1ll << (dm.lx + dm.ly + dm.lz);
   const int ntile = (cout + 15) / 16;
   const size_t halo = sizeof(uint16_t) * 648 * (size_t)cs_in;
-  if (!f32 && ks == 3 && ntile <= 2 && dm.lz >= 4 && dm.ly >= 2 && dm.lx >= 2 && halo <= 64 * 1024) {
+  const bool tiles = ks == 3 && dm.lz >= 4 && dm.ly >= 2 && dm.lx >= 2 && halo <= 64 * 1024;
+  if (tiles && ntile <= 2) {
     const int blocks = (int)(N / 256);
-    uint16_t* o = reinterpret_cast<uint16_t*>(out);
-    if (conv_ct(n->stream, cs_in, ntile, relu, blocks, in, dm, W, kp, bias, cout, cs_out, o))
+    if (conv_ct(n->stream, cs_in, ntile, relu, blocks, in, dm, W, kp, bias, cout, cs_out, o, mask, pool ? *pool : nullptr)) {
+      if (pool) *pool = nullptr;
       return last_launch("k_conv_ct");
+    }
     if (relu) {
-      if (ntile == 1) k_conv_tiled<true, 1><<<blocks, 256, halo, n->stream>>>(in, dm, cs_in, W, kp, bias, cout, cs_out, o);
-      else k_conv_tiled<true, 2><<<blocks, 256, halo, n->stream>>>(in, dm, cs_in, W, kp, bias, cout, cs_out, o);
+      if (ntile == 1) k_conv_tiled<true, 1><<<blocks, 256, halo, n->stream>>>(in, dm, cs_in, W, kp, bias, cout, cs_out, o, mask);
+      else k_conv_tiled<true, 2><<<blocks, 256, halo, n->stream>>>(in, dm, cs_in, W, kp, bias, cout, cs_out, o, mask);
     } else {
-      if (ntile == 1) k_conv_tiled<false, 1><<<blocks, 256, halo, n->stream>>>(in, dm, cs_in, W, kp, bias, cout, cs_out, o);
-      else k_conv_tiled<false, 2><<<blocks, 256, halo, n->stream>>>(in, dm, cs_in, W, kp, bias, cout, cs_out, o);
+      if (ntile == 1) k_conv_tiled<false, 1><<<blocks, 256, halo, n->stream>>>(in, dm, cs_in, W, kp, bias, cout, cs_out, o, mask);
+      else k_conv_tiled<false, 2><<<blocks, 256, halo, n->stream>>>(in, dm, cs_in, W, kp, bias, cout, cs_out, o, mask);
     }
     return last_launch("k_conv_tiled");
   }
-  if (!f32 && (kp >> 4) >= 32 && N <= (1ll << 17)) {
+  if ((kp >> 4) >= 32 && N <= (1ll << 17)) {
     // deep reduction on a small grid: split K over the block's waves
     const int blocks = (int)((N + 15) / 16);
-    uint16_t* o = reinterpret_cast<uint16_t*>(out);
     if (cs_in % 8 == 0 && ntile <= 8) {
-      splitk8(n->stream, relu, ntile, blocks, in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o);
+      splitk8(n->stream, relu, ntile, blocks, in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o, mask);
       return last_launch("k_conv_splitk8");
     }
-    if (relu) k_conv_splitk<true><<<blocks, 256, 0, n->stream>>>(in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o);
-    else k_conv_splitk<false><<<blocks, 256, 0, n->stream>>>(in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o);
+    if (relu) k_conv_splitk<true><<<blocks, 256, 0, n->stream>>>(in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o, mask);
+    else k_conv_splitk<false><<<blocks, 256, 0, n->stream>>>(in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o, mask);
     return last_launch("k_conv_splitk");
   }
-  if (f32 && ks == 1 && cout == 1) {   // the head: one output channel
-    k_head1<<<std::min(grid_for(N, 256), 8192), 256, 0, n->stream>>>(in, N, cs_in, cs_in, W, bias,
-                                                                   reinterpret_cast<float*>(out));
-    return last_launch("k_head1");
+  // three output tiles with a shallow reduction (the data gradient of a level-1
+  // concatenation): the tile in LDS, one output tile per block, the sums in k_conv's order.
+  // 32^3 voxels, 16 -> 48 channels: 17.2 us, all
+  // three in one block 21.4
+  if (tiles && ntile == 3) {
+    const dim3 blocks((unsigned)(N / 256), 3);
+    if (relu) k_conv_tiled<true, 1, true><<<blocks, 256, halo, n->stream>>>(in, dm, cs_in, W, kp, bias, cout, cs_out, o, mask);
+    else k_conv_tiled<false, 1, true><<<blocks, 256, halo, n->stream>>>(in, dm, cs_in, W, kp, bias, cout, cs_out, o, mask);
+    return last_launch("k_conv_tiled");
   }
   const int blocks = (int)((N + 63) / 64);
-  if (f32) k_conv<false, true><<<blocks, 256, 0, n->stream>>>(in, dm, cs_in, ks, W, kp, bias, cout, cs_out, out);
-  else if (relu) k_conv<true, false><<<blocks, 256, 0, n->stream>>>(in, dm, cs_in, ks, W, kp, bias, cout, cs_out, out);
-  else k_conv<false, false><<<blocks, 256, 0, n->stream>>>(in, dm, cs_in, ks, W, kp, bias, cout, cs_out, out);
+  if (relu) k_conv<true><<<blocks, 256, 0, n->stream>>>(in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o, mask);
+  else k_conv<false><<<blocks, 256, 0, n->stream>>>(in, dm, cs_in, ks, W, kp, bias, cout, cs_out, o, mask);
   return last_launch("k_conv");
 }
 
-mh3d_status conv_fwd(mh3d_net_t n, const NetLayer& ly, const uint16_t* in, Dims dm, void* out, bool relu, bool f32) {
-  return launch_conv(n, in, dm, ly.cs_in, ly.ks, ly.Wf, ly.kp, n->p + ly.b_off, ly.cout, ly.cs_out, out, relu, f32);
+mh3d_status conv_fwd(mh3d_net_t n, const NetLayer& ly, const uint16_t* in, Dims dm, uint16_t* out, uint16_t** pool = nullptr) {
+  return launch_conv(n, in, dm, ly.cs_in, ly.ks, ly.Wf, ly.kp, n->p + ly.b_off, ly.cout, ly.cs_out, out, true, nullptr, pool);
 }
 
 // The decoder's first convolution with ReLU on the concatenation of skip (c1 channels,
@@ -277,44 +420,12 @@ bool conv_fwd_cat(mh3d_net_t n, const NetLayer& ly, const uint16_t* skip, int c1
   return ok;
 }
 
-// Gradients of one conv layer given the gradient g of its (pre-activation) output:
-// accumulates dW, db and writes the input gradient gin (unless null).
-mh3d_status conv_bwd(mh3d_net_t n, const NetLayer& ly, const uint16_t* in, Dims dm, const uint16_t* g, int cs_g,
-                     uint16_t* gin, float* zero_bias) {
-  const long long N = 1ll << (dm.lx + dm.ly + dm.lz);
-  const int ncot = (ly.cout + 15) / 16, nkc = ly.kp / 16;
-  const size_t wlds = sizeof(uint16_t) * (648 * (size_t)ly.cs_in + 256 * 16 * (size_t)ncot);
-  if (ly.ks == 3 && dm.lz >= 4 && dm.ly >= 2 && dm.lx >= 2 && wlds <= 96 * 1024) {
-    const int ntiles = (int)(N >> 8);
-    const int nbg = (ncot * nkc + 15) / 16;
-    int tpb = (int)((ntiles * (long long)nbg + 767) / 768);
-    tpb = std::max(1, std::min(tpb, 64));
-    const dim3 grid((ntiles + tpb - 1) / tpb, nbg);
-    k_conv_wgrad_tiled<<<grid, 256, wlds, n->stream>>>(in, dm, ly.cs_in, g, cs_g, ly.cout, ly.kp, ly.gWf, tpb);
-    CHK(last_launch("k_conv_wgrad_tiled"));
-  } else {
-    // voxel ranges of 256 per wave (8 MFMA instructions): enough waves in flight on the
-    // small grids and the 1x1x1 head, whose chains are their loads' latency
-    long long chunk = 256;
-    int nsplit = (int)((N + chunk - 1) / chunk);
-    k_conv_wgrad<<<ncot * nkc * nsplit, 64, 0, n->stream>>>(in, dm, ly.cs_in, ly.ks, g, cs_g, ly.cout, ly.kp, ly.gWf,
-                                                            nsplit, chunk);
-    CHK(last_launch("k_conv_wgrad"));
-  }
-  {
-    // cs_g <= 256 channels; blocks: a multiple of cs_g / 4 (each thread keeps one channel group)
-    if (cs_g > 256 || cs_g % 4) return fail(MH3D_ERR_UNSUPPORTED, "gradient channel stride %d (at most 256)", cs_g);
-    const int cq = cs_g / 4;
-    const long long items = N * cq;
-    long long nb = std::max<long long>(1, std::min<long long>(items / (256 * 16), 1024 / cq));
-    k_bias_grad<<<(int)(nb * cq), 256, 0, n->stream>>>(g, N, cs_g, ly.cout, n->g + ly.b_off);
-  }
-  CHK(last_launch("k_bias_grad"));
-  if (gin) {
-    // data gradient = convolution of g with the flipped, transposed weights (no bias)
-    CHK(launch_conv(n, g, dm, cs_g, ly.ks, ly.Wt, ly.kpt, zero_bias, ly.cin, ly.cs_in, gin, false, false));
-  }
-  return MH3D_OK;
+// Input gradient of layer i from its output gradient gl[i]: the convolution with the
+// flipped, transposed weights (no bias), masked by act if given.
+mh3d_status conv_bwd_data(mh3d_net_t n, NetWork* w, int i, Dims dm, uint16_t* gin, const uint16_t* act) {
+  const NetLayer& ly = n->layers[i];
+  const float* zero_bias = n->g + n->nparam;   // the zero tail of the gradient buffer
+  return launch_conv(n, w->gl[i], dm, ly.cs_out, ly.ks, ly.Wt, ly.kpt, zero_bias, ly.cin, ly.cs_in, gin, false, act);
 }
 
 // x (FP32, volume grid `src`, crop window o + dst dims) -> forward through the net;
@@ -325,25 +436,27 @@ mh3d_status net_forward(mh3d_net_t n, NetWork* w, const float* x, Dims src, long
   if (!n->packed) CHK(net_pack(n));
   unsigned* slot = reinterpret_cast<unsigned*>(w->scale + 4);
   if (nsrc % 4) return fail(MH3D_ERR_INVALID, "volume size %lld is not a multiple of 4", nsrc);
-  k_absmax<<<std::min(grid_for(nsrc / 4, 256), 4096), 256, 0, n->stream>>>(x, nsrc, n->in_ch, slot);
+  k_absmax<<<std::min(grid_for(nsrc / 4, 256), 1024), 256, 0, n->stream>>>(x, nsrc, n->in_ch, slot);
   CHK(last_launch("k_absmax"));
-  k_absmax_final<<<1, 64, 0, n->stream>>>(slot, w->scale);
-  CHK(last_launch("k_absmax_final"));
   Dims d0 = dims_of(*w, 0);
-  k_to_bf16_crop<<<grid_for(d0.n()), 256, 0, n->stream>>>(x, n->in_ch, src, ox, oy, oz, d0, w->scale,
+  k_to_bf16_crop<<<grid_for(d0.n()), 256, 0, n->stream>>>(x, n->in_ch, src, ox, oy, oz, d0, slot, w->scale, w->loss,
                                                           round4(n->in_ch), w->x0);
   CHK(last_launch("k_to_bf16_crop"));
   const uint16_t* h = w->x0;
+  uint16_t* pool = nullptr;
   for (int l = 0; l < L; ++l) {
     Dims dl = dims_of(*w, l);
     if (l) {
-      const int cs = round4(n->widths[l - 1]);
-      k_avgpool<<<grid_for(dl.n() * cs), 256, 0, n->stream>>>(h, dims_of(*w, l - 1), cs, w->pl[l], dl);
-      CHK(last_launch("k_avgpool"));
+      if (pool) {   // not formed with the last convolution
+        const int cs = round4(n->widths[l - 1]);
+        k_avgpool<<<grid_for(dl.n() * cs), 256, 0, n->stream>>>(h, dims_of(*w, l - 1), cs, w->pl[l], dl);
+        CHK(last_launch("k_avgpool"));
+      }
       h = w->pl[l];
     }
-    CHK(conv_fwd(n, n->layers[enc_index(l, 0)], h, dl, w->ea[l], true, false));
-    CHK(conv_fwd(n, n->layers[enc_index(l, 1)], w->ea[l], dl, w->es[l], true, false));
+    pool = l + 1 < L ? w->pl[l + 1] : nullptr;
+    CHK(conv_fwd(n, n->layers[enc_index(l, 0)], h, dl, w->ea[l]));
+    CHK(conv_fwd(n, n->layers[enc_index(l, 1)], w->ea[l], dl, w->es[l], pool ? &pool : nullptr));
     h = w->es[l];
   }
   for (int l = L - 2; l >= 0; --l) {
@@ -359,89 +472,58 @@ mh3d_status net_forward(mh3d_net_t n, NetWork* w, const float* x, Dims src, long
       k_upcat<<<grid_for(dl.n() * (cats / 4)), 256, 0, n->stream>>>(w->es[l], round4(c1), c1, h, round4(c2), c2, dl,
                                                               dims_of(*w, l + 1), cats, w->cat[l]);
       CHK(last_launch("k_upcat"));
-      CHK(conv_fwd(n, la, w->cat[l], dl, w->da[l], true, false));
+      CHK(conv_fwd(n, la, w->cat[l], dl, w->da[l]));
     }
-    CHK(conv_fwd(n, n->layers[dec_index(L, l, 1)], w->da[l], dl, w->db[l], true, false));
+    CHK(conv_fwd(n, n->layers[dec_index(L, l, 1)], w->da[l], dl, w->db[l]));
     h = w->db[l];
   }
-  CHK(conv_fwd(n, n->layers.back(), h, d0, w->y, false, true));
-  return MH3D_OK;
+  const NetLayer& hd = n->layers.back();   // the head: one output channel, FP32
+  k_head1<<<std::min(grid_for(d0.n(), 256), 8192), 256, 0, n->stream>>>(h, d0.n(), hd.cs_in, hd.cs_in, hd.Wf, n->p + hd.b_off,
+                                                                      w->y, slot);
+  return last_launch("k_head1");
 }
 
+// Data gradients layer by layer (each stored as the gradient of a pre-activation output: the
+// ReLU's backward is the mask of the kernel that forms it), then every weight gradient.
 mh3d_status net_backward(mh3d_net_t n, NetWork* w) {
   const int L = (int)n->widths.size();
-  float* zb = n->g + n->nparam;   // zero bias of the data-gradient convolutions (tail of the gradient buffer)
-  Dims d0 = dims_of(*w, 0);
-  // head (1x1x1): gradient of the last decoder output
-  const uint16_t* top = L >= 2 ? w->db[0] : w->es[0];
-  uint16_t* g = w->g1[0];
-  CHK(conv_bwd(n, n->layers.back(), top, d0, w->gy, 4, g, zb));
-  // decoder, level 0 upwards: g is the gradient of db[l] (post-ReLU output)
+  const Dims d0 = dims_of(*w, 0);
+  const NetLayer& hd = n->layers.back();
+  k_head_bwd<<<grid_for(d0.n() * (hd.cs_in / 4)), 256, 0, n->stream>>>(w->gy, d0.n(), hd.cs_in, hd.cin, hd.Wf, w->db[0],
+                                                                      w->gl[dec_index(L, 0, 1)]);
+  CHK(last_launch("k_head_bwd"));
+  // decoder, level 0 upwards
   for (int l = 0; l <= L - 2; ++l) {
-    Dims dl = dims_of(*w, l);
-    const int cs = round4(n->widths[l]);
-    const NetLayer& lb = n->layers[dec_index(L, l, 1)];
-    const NetLayer& la = n->layers[dec_index(L, l, 0)];
-    k_relu_bwd<<<grid_for(dl.n() * cs), 256, 0, n->stream>>>(g, w->db[l], dl.n() * cs);
-    CHK(last_launch("k_relu_bwd"));
-    uint16_t* g_da = (g == w->g1[l]) ? w->g2[l] : w->g1[l];
-    CHK(conv_bwd(n, lb, w->da[l], dl, g, cs, g_da, zb));
-    k_relu_bwd<<<grid_for(dl.n() * cs), 256, 0, n->stream>>>(g_da, w->da[l], dl.n() * cs);
-    CHK(last_launch("k_relu_bwd"));
-    const int cats = round4(n->widths[l] + n->widths[l + 1]);
-    uint16_t* g_cat = w->g3[l];
-    CHK(conv_bwd(n, la, w->cat[l], dl, g_da, cs, g_cat, zb));
-    // split: skip part -> gs[l], coarse part -> gradient of the next level's output
-    Dims dc = dims_of(*w, l + 1);
+    const Dims dl = dims_of(*w, l), dc = dims_of(*w, l + 1);
+    const int ia = dec_index(L, l, 0), ib = dec_index(L, l, 1);
+    CHK(conv_bwd_data(n, w, ib, dl, w->gl[ia], w->da[l]));
+    CHK(conv_bwd_data(n, w, ia, dl, w->gcat[l], nullptr));
+    // the coarse half of the concatenation: the output of the next decoder level, or the bottom's
     const int cs2 = round4(n->widths[l + 1]);
-    uint16_t* g_next = w->g1[l + 1];
-    k_upcat_bwd<<<grid_for(dl.n() * cs), 256, 0, n->stream>>>(g_cat, cats, n->widths[l], n->widths[l + 1], dl, dc,
-                                                              w->gs[l], cs, g_next, cs2);
-    CHK(last_launch("k_upcat_bwd"));
-    g = g_next;
+    const bool bottom = l == L - 2;
+    k_up_bwd<<<grid_for(dc.n() * cs2), 256, 0, n->stream>>>(
+        w->gcat[l], round4(n->widths[l] + n->widths[l + 1]), n->widths[l], n->widths[l + 1], dl, dc,
+        bottom ? w->es[l + 1] : w->db[l + 1], w->gl[bottom ? enc_index(l + 1, 1) : dec_index(L, l + 1, 1)], cs2);
+    CHK(last_launch("k_up_bwd"));
   }
-  // encoder, bottom level downwards: g is the gradient of es[l]
+  // encoder, bottom level downwards
   for (int l = L - 1; l >= 0; --l) {
-    Dims dl = dims_of(*w, l);
-    const int cs = round4(n->widths[l]);
-    if (l < L - 1) {
-      // total gradient of the skip tensor: concat part (gs) + pooled part (already in g)
-      // g currently holds the pooled-path gradient accumulated into gs[l]
-      g = w->gs[l];
-    }
-    const NetLayer& lb = n->layers[enc_index(l, 1)];
-    const NetLayer& la = n->layers[enc_index(l, 0)];
-    k_relu_bwd<<<grid_for(dl.n() * cs), 256, 0, n->stream>>>(g, w->es[l], dl.n() * cs);
-    CHK(last_launch("k_relu_bwd"));
-    uint16_t* g_ea = (g == w->g2[l]) ? w->g3[l] : w->g2[l];
-    CHK(conv_bwd(n, lb, w->ea[l], dl, g, cs, g_ea, zb));
-    k_relu_bwd<<<grid_for(dl.n() * cs), 256, 0, n->stream>>>(g_ea, w->ea[l], dl.n() * cs);
-    CHK(last_launch("k_relu_bwd"));
-    const uint16_t* in = l ? w->pl[l] : w->x0;
-    if (l) {
-      uint16_t* g_in = (g_ea == w->g1[l]) ? w->g3[l] : w->g1[l];
-      CHK(conv_bwd(n, la, in, dl, g_ea, cs, g_in, zb));
-      // average-pool backward adds into the skip gradient of level l-1
-      const int csp = round4(n->widths[l - 1]);
-      k_avgpool_bwd_add<<<grid_for(dims_of(*w, l - 1).n() * csp), 256, 0, n->stream>>>(g_in, dl, csp, w->gs[l - 1],
-                                                                                       dims_of(*w, l - 1));
-      CHK(last_launch("k_avgpool_bwd_add"));
-    } else {
-      CHK(conv_bwd(n, la, in, dl, g_ea, cs, nullptr, zb));
-    }
+    const Dims dl = dims_of(*w, l);
+    const int ia = enc_index(l, 0), ib = enc_index(l, 1);
+    CHK(conv_bwd_data(n, w, ib, dl, w->gl[ia], w->ea[l]));
+    if (!l) break;
+    CHK(conv_bwd_data(n, w, ia, dl, w->gpl[l], nullptr));
+    const Dims df = dims_of(*w, l - 1);
+    const int cs = round4(n->widths[l - 1]);
+    k_skip_pool_bwd<<<grid_for(df.n() * (cs / 4)), 256, 0, n->stream>>>(
+        w->gcat[l - 1], round4(n->widths[l - 1] + n->widths[l]), w->gpl[l], dl, cs, n->widths[l - 1], w->es[l - 1],
+        w->gl[enc_index(l - 1, 1)], df);
+    CHK(last_launch("k_skip_pool_bwd"));
   }
-  // padded forward-matrix gradients -> flat layout
-  k_unpack_all<<<n->unpack_blocks, 256, 0, n->stream>>>(n->pack, (int)n->layers.size());
-  CHK(last_launch("k_unpack_all"));
-  return MH3D_OK;
-}
-
-mh3d_status net_zero_grads(mh3d_net_t n) {
-  k_fill_f32<<<grid_for(n->nparam), 256, 0, n->stream>>>(n->g, n->nparam + 128, 0.f);
-  CHK(last_launch("k_fill_f32"));
-  k_fill_f32<<<grid_for(n->gW_len), 256, 0, n->stream>>>(n->gW, n->gW_len, 0.f);
-  CHK(last_launch("k_fill_f32"));
-  return MH3D_OK;
+  k_wgrad<<<w->nwgt, 256, w->wg_lds, n->stream>>>(w->wgl, w->wgt, w->wgpart);
+  CHK(last_launch("k_wgrad"));
+  k_wgrad_sum<<<w->wsum_blocks, 256, 0, n->stream>>>(w->wgl, w->wsum_first, w->wgpart);
+  return last_launch("k_wgrad_sum");
 }
 
 // He-normal initialisation from Philox (Box-Muller), zero biases.
@@ -519,32 +601,22 @@ extern "C" mh3d_status mh3d_net_create(int32_t levels, const int32_t* widths, in
   for (auto& ly : n->layers) {
     if ((st = net_alloc((void**)&ly.Wf, sizeof(uint16_t) * (size_t)ly.rows_f * ly.kp)) != MH3D_OK) return bail(st);
     if ((st = net_alloc((void**)&ly.Wt, sizeof(uint16_t) * (size_t)ly.rows_t * ly.kpt)) != MH3D_OK) return bail(st);
-    n->gW_len += ((long long)ly.rows_f * ly.kp + 63) & ~63ll;   // 256-byte aligned slices
   }
-  if ((st = net_alloc((void**)&n->gW, sizeof(float) * (size_t)n->gW_len)) != MH3D_OK) return bail(st);
   {
-    // the layer table of the one-launch packing kernels (blocks per layer as one
+    // the layer table of the one-launch packing kernel (blocks per layer as one
     // launch per layer would take, at most 1024)
     std::vector<PackDesc> pd(n->layers.size());
-    long long goff = 0;
     for (size_t i = 0; i < n->layers.size(); ++i) {
       NetLayer& ly = n->layers[i];
-      ly.gWf = n->gW + goff;
-      goff += ((long long)ly.rows_f * ly.kp + 63) & ~63ll;
       PackDesc& d = pd[i];
       d.p = n->p + ly.w_off;
-      d.gp = n->g + ly.w_off;
       d.Wf = ly.Wf;
       d.Wt = ly.Wt;
-      d.gWf = ly.gWf;
       d.cin = ly.cin; d.cout = ly.cout; d.ks = ly.ks; d.cs_in = ly.cs_in; d.cs_out = ly.cs_out;
       d.kp = ly.kp; d.kpt = ly.kpt; d.rows_f = ly.rows_f; d.rows_t = ly.rows_t;
       d.pb0 = n->pack_blocks;
       d.pnb = std::min(grid_for((long long)ly.rows_f * ly.kp + (long long)ly.rows_t * ly.kpt), 1024);
       n->pack_blocks += d.pnb;
-      d.ub0 = n->unpack_blocks;
-      d.unb = std::min(grid_for((long long)ly.cout * ly.ks * ly.ks * ly.ks * ly.cin), 1024);
-      n->unpack_blocks += d.unb;
     }
     if ((st = net_alloc((void**)&n->pack, sizeof(PackDesc) * pd.size())) != MH3D_OK) return bail(st);
     if (hipMemcpy(n->pack, pd.data(), sizeof(PackDesc) * pd.size(), hipMemcpyHostToDevice) != hipSuccess)
@@ -559,7 +631,8 @@ extern "C" mh3d_status mh3d_net_create(int32_t levels, const int32_t* widths, in
     k_net_init<<<grid_for(nw), 256, 0, n->stream>>>(n->p, ly.w_off, nw, ly.cin * ly.ks * ly.ks * ly.ks, seed, (uint32_t)i);
   }
   if ((st = last_launch("k_net_init")) != MH3D_OK) return bail(st);
-  if ((st = net_zero_grads(n)) != MH3D_OK) return bail(st);
+  k_fill_f32<<<grid_for(off + 128), 256, 0, n->stream>>>(n->g, off + 128, 0.f);   // and the zero bias in its tail
+  if ((st = last_launch("k_fill_f32")) != MH3D_OK) return bail(st);
   if (hipStreamSynchronize(n->stream) != hipSuccess) return bail(fail(MH3D_ERR_HIP, "network init failed"));
   *out = n;
   return MH3D_OK;
@@ -569,16 +642,15 @@ extern "C" void mh3d_net_destroy(mh3d_net_t n) {
   if (!n) return;
   (void)hipStreamSynchronize(n->stream);
   for (auto& kv : n->work) {
-    for (auto* b : kv.second.bufs) (void)hipFree(b);
-    if (kv.second.y) (void)hipFree(kv.second.y);
-    if (kv.second.scale) (void)hipFree(kv.second.scale);
-    if (kv.second.xin) (void)hipFree(kv.second.xin);
+    void* mem[] = {kv.second.mem, kv.second.wgmem, kv.second.xin};
+    for (void* q : mem)
+      if (q) (void)hipFree(q);
   }
   for (auto& ly : n->layers) {
     if (ly.Wf) (void)hipFree(ly.Wf);
     if (ly.Wt) (void)hipFree(ly.Wt);
   }
-  void* bufs[] = {n->p, n->g, n->m, n->v, n->gW, n->pack};
+  void* bufs[] = {n->p, n->g, n->m, n->v, n->pack};
   for (void* q : bufs)
     if (q) (void)hipFree(q);
   delete n;
@@ -639,11 +711,9 @@ extern "C" mh3d_status mh3d_net_loss_grad(mh3d_net_t n, const float* x, const fl
   NetWork* w;
   CHK(net_work(n, c[0], c[1], c[2], &w));
   Dims src{ilog2(nx), ilog2(ny), ilog2(nz)};
-  CHK(net_zero_grads(n));
   CHK(net_forward(n, w, x, src, (long long)nx * ny * nz, o[0], o[1], o[2]));
   Dims d0 = dims_of(*w, 0);
-  k_fill_f64<<<1, 64, 0, n->stream>>>(w->loss, 1, 0.0);
-  k_mse<<<grid_for(d0.n()), 256, 0, n->stream>>>(w->y, t, src, o[0], o[1], o[2], d0, w->scale, 4, w->gy, w->loss);
+  k_mse<<<std::min(grid_for(d0.n()), 256), 256, 0, n->stream>>>(w->y, t, src, o[0], o[1], o[2], d0, w->scale, w->gy, w->loss);
   CHK(last_launch("k_mse"));
   CHK(net_backward(n, w));
   if (loss) {

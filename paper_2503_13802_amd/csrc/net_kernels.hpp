@@ -42,6 +42,15 @@ constexpr int NT_MAX = 7;   // output-channel tiles per wave (112 channels)
 __device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
+// ReLU backward of a data gradient in the kernel that forms it: mask, the post-ReLU tensor
+// the gradient belongs to (NULL: keep everything), zeroes the gradient where it is not > 0.
+__device__ __forceinline__ bool keep(const uint16_t* mask, long long i) { return !mask || bf2f(mask[i]) > 0.f; }
+template <typename V> __device__ __forceinline__ V masked(V g, V act) {
+#pragma unroll
+  for (int q = 0; q < (int)(sizeof(V) / 2); ++q) g[q] = bf2f((uint16_t)act[q]) > 0.f ? g[q] : (short)0;
+  return g;
+}
+
 struct Dims {
   int lx, ly, lz;          // log2 of the axes
   __host__ __device__ __forceinline__ long long n() const { return 1ll << (lx + ly + lz); }
@@ -66,13 +75,13 @@ __device__ __forceinline__ void tap_offset(int tap, int ks, int& dx, int& dy, in
 }
 
 // Convolution (ks = 3 or 1).  in: [N][cs_in]; W: [cout_tiles*16][kp] BF16; bias FP32
-// [cout]; out: BF16 [N][cs_out] or FP32 [N] (OUTF32, cout == 1).  Padding output
+// [cout]; out: BF16 [N][cs_out].  Padding output
 // channels cout..cs_out-1 are written as zeros.  block = 256 (4 waves, 64 voxels).
-template <bool RELU, bool OUTF32>
+template <bool RELU>
 __global__ __launch_bounds__(256) void k_conv(const uint16_t* __restrict__ in, Dims dm, int cs_in, int ks,
                                               const uint16_t* __restrict__ W, int kp,
                                               const float* __restrict__ bias, int cout, int cs_out,
-                                              void* __restrict__ out) {
+                                              uint16_t* __restrict__ out, const uint16_t* __restrict__ mask) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const long long N = dm.n();
   const long long n0 = ((long long)blockIdx.x * 4 + wave) * 16;
@@ -135,16 +144,12 @@ __global__ __launch_bounds__(256) void k_conv(const uint16_t* __restrict__ in, D
     for (int j = 0; j < 4; ++j) {
       const long long nn = n0 + 4 * g + j;
       if (nn >= N) continue;
-      if constexpr (OUTF32) {
-        if (co == 0) reinterpret_cast<float*>(out)[nn] = acc[t][j] + bv;
-      } else {
-        if (co < cout) {
-          float v = acc[t][j] + bv;
-          if (RELU) v = fmaxf(v, 0.f);
-          reinterpret_cast<uint16_t*>(out)[nn * cs_out + co] = f2bf(v);
-        } else if (co < cs_out) {
-          reinterpret_cast<uint16_t*>(out)[nn * cs_out + co] = 0;
-        }
+      if (co < cout) {
+        float v = acc[t][j] + bv;
+        if (RELU) v = fmaxf(v, 0.f);
+        out[nn * cs_out + co] = keep(mask, nn * cs_out + co) ? f2bf(v) : (uint16_t)0;
+      } else if (co < cs_out) {
+        out[nn * cs_out + co] = 0;
       }
     }
   }
@@ -159,7 +164,7 @@ template <bool RELU>
 __global__ __launch_bounds__(256) void k_conv_splitk(const uint16_t* __restrict__ in, Dims dm, int cs_in, int ks,
                                                      const uint16_t* __restrict__ W, int kp,
                                                      const float* __restrict__ bias, int cout, int cs_out,
-                                                     uint16_t* __restrict__ out) {
+                                                     uint16_t* __restrict__ out, const uint16_t* __restrict__ mask) {
   __shared__ f4v part[3][NT_MAX][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const long long N = dm.n();
@@ -236,7 +241,7 @@ __global__ __launch_bounds__(256) void k_conv_splitk(const uint16_t* __restrict_
       if (co < cout) {
         float o = v[j] + bv;
         if (RELU) o = fmaxf(o, 0.f);
-        out[nn * cs_out + co] = f2bf(o);
+        out[nn * cs_out + co] = keep(mask, nn * cs_out + co) ? f2bf(o) : (uint16_t)0;
       } else if (co < cs_out) {
         out[nn * cs_out + co] = 0;
       }
@@ -277,42 +282,55 @@ __device__ __forceinline__ void stage_halo(uint16_t* __restrict__ tile, const ui
 // k_conv_splitk for input channel strides divisible by 8: MFMA m takes the reduction
 // indices 32 m .. 32 m + 31, lane group g the 8 consecutive channels 32 m + 8 g .. + 7 of
 // one tap (one 16-byte gather of A, one 16-byte load of B per output tile); wave w takes
-// m = w, w + 4, ..., U of them with all their loads issued before their MFMAs.
-template <bool RELU, int NT>
+// m = w, w + 4, ..., U of them with all their loads issued before their MFMAs.  A block takes
+// VG groups of 16 voxels, which share the weight loads: every block reads all of W, and
+// with one group that is most of the traffic from L2 (32^3
+// voxels, 112 -> 32 channels: 49 us with one group, 36 with two, 30 with four).
+// grid.y splits the output tiles (NT per block) where the voxels alone give few blocks.
+template <bool RELU, int NT, int VG>
 __global__ __launch_bounds__(256) void k_conv_splitk8(const uint16_t* __restrict__ in, Dims dm, int cs_in, int ks,
                                                       const uint16_t* __restrict__ W, int kp,
                                                       const float* __restrict__ bias, int cout, int cs_out,
-                                                      uint16_t* __restrict__ out) {
-  constexpr int U = NT <= 2 ? 4 : 2;   // loads in flight per wave: U gathers and U * NT weight slices
-  __shared__ f4v part[3][NT][64];
+                                                      uint16_t* __restrict__ out, const uint16_t* __restrict__ mask) {
+  constexpr int U = NT <= 2 && VG <= 2 ? 4 : 2;   // steps in flight per wave: U * VG gathers and U * NT weight slices
+  __shared__ f4v part[3][VG * NT][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const long long N = dm.n();
-  const long long n0 = (long long)blockIdx.x * 16;
+  const long long n0 = (long long)blockIdx.x * (16 * VG);
   const int r = lane & 15, g = lane >> 4;
-  const long long n = n0 + r;
-  const bool nvalid = n < N;
-  int x = 0, y = 0, z = 0;
-  if (nvalid) dm.decode(n, x, y, z);
-  const int ntap = ks * ks * ks;
-  f4v acc[NT];
+  int x[VG], y[VG], z[VG];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) acc[t] = f4v{0.f, 0.f, 0.f, 0.f};
+  for (int v = 0; v < VG; ++v) {
+    const long long n = n0 + 16 * v + r;
+    x[v] = y[v] = z[v] = 0;
+    if (n < N) dm.decode(n, x[v], y[v], z[v]);
+    else x[v] = -2;                    // every tap outside
+  }
+  const int ntap = ks * ks * ks;
+  const int t0 = blockIdx.y * NT;   // first output tile of the block
+  f4v acc[VG][NT];
+#pragma unroll
+  for (int v = 0; v < VG; ++v)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[v][t] = f4v{0.f, 0.f, 0.f, 0.f};
   // k = 32 m + 8 g for m = wave + 4 i: start, then step 128 reduction indices
   int tap = 0, ci = 32 * wave + 8 * g;
   while (ci >= cs_in) { ci -= cs_in; ++tap; }
   const int nm = (kp + 31) >> 5;
-  const uint16_t* wr = W + (long long)r * kp + 8 * g;
+  const uint16_t* wr = W + (long long)(t0 * 16 + r) * kp + 8 * g;
   for (int m0 = wave; m0 < nm; m0 += 4 * U) {
-    s8v a[U], b[U][NT];
+    s8v a[U][VG], b[U][NT];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int m = m0 + 4 * u;
-      a[u] = s8v{0, 0, 0, 0, 0, 0, 0, 0};
-      if (m < nm && nvalid && tap < ntap) {
-        int dx, dy, dz;
-        tap_offset(tap, ks, dx, dy, dz);
-        const int xx = x + dx, yy = y + dy, zz = z + dz;
-        if (dm.inside(xx, yy, zz)) a[u] = *reinterpret_cast<const s8v*>(in + dm.encode(xx, yy, zz) * cs_in + ci);
+      int dx = 0, dy = 0, dz = 0;
+      const bool live = m < nm && tap < ntap;
+      if (live) tap_offset(tap, ks, dx, dy, dz);
+#pragma unroll
+      for (int v = 0; v < VG; ++v) {
+        a[u][v] = s8v{0, 0, 0, 0, 0, 0, 0, 0};
+        const int xx = x[v] + dx, yy = y[v] + dy, zz = z[v] + dz;
+        if (live && dm.inside(xx, yy, zz)) a[u][v] = *reinterpret_cast<const s8v*>(in + dm.encode(xx, yy, zz) * cs_in + ci);
       }
       const bool kin = m < nm && 32 * m + 8 * g < kp;
 #pragma unroll
@@ -324,36 +342,42 @@ __global__ __launch_bounds__(256) void k_conv_splitk8(const uint16_t* __restrict
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int t = 0; t < NT; ++t)
-          acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, a[u]), __builtin_bit_cast(bf8v, b[u][t]),
-                                                           acc[t], 0, 0, 0);
+      for (int v = 0; v < VG; ++v)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          acc[v][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, a[u][v]),
+                                                              __builtin_bit_cast(bf8v, b[u][t]), acc[v][t], 0, 0, 0);
   }
   if (wave) {
 #pragma unroll
-    for (int t = 0; t < NT; ++t) part[wave - 1][t][lane] = acc[t];
+    for (int v = 0; v < VG; ++v)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) part[wave - 1][v * NT + t][lane] = acc[v][t];
   }
   __syncthreads();
   if (wave) return;
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    f4v v = acc[t];
+  for (int v = 0; v < VG; ++v)
 #pragma unroll
-    for (int w = 0; w < 3; ++w) v += part[w][t][lane];
-    const int co = t * 16 + r;
-    const float bv = co < cout ? bias[co] : 0.f;
+    for (int t = 0; t < NT; ++t) {
+      f4v s = acc[v][t];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const long long nn = n0 + 4 * g + j;
-      if (nn >= N) continue;
-      if (co < cout) {
-        float o = v[j] + bv;
-        if (RELU) o = fmaxf(o, 0.f);
-        out[nn * cs_out + co] = f2bf(o);
-      } else if (co < cs_out) {
-        out[nn * cs_out + co] = 0;
+      for (int w = 0; w < 3; ++w) s += part[w][v * NT + t][lane];
+      const int co = (t0 + t) * 16 + r;
+      const float bv = co < cout ? bias[co] : 0.f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const long long nn = n0 + 16 * v + 4 * g + j;
+        if (nn >= N) continue;
+        if (co < cout) {
+          float o = s[j] + bv;
+          if (RELU) o = fmaxf(o, 0.f);
+          out[nn * cs_out + co] = keep(mask, nn * cs_out + co) ? f2bf(o) : (uint16_t)0;
+        } else if (co < cs_out) {
+          out[nn * cs_out + co] = 0;
+        }
       }
     }
-  }
 }
 
 // 3x3x3 convolution on an LDS-staged tile with the input channel stride CS fixed at
@@ -367,12 +391,20 @@ __global__ __launch_bounds__(256) void k_conv_splitk8(const uint16_t* __restrict
 // (no concatenated copy): channels [0, C1) of voxel n from `in` (stride C1), the other
 // CS - C1 from `in2` (stride CS - C1) at the coarse voxel (x/2, y/2, z/2), the halo
 // tile holding the same values the concatenated tensor would.
-template <int CS, int NT, bool RELU, int C1 = 0>
+// pool (or NULL): also the 2x2x2 average of the BF16 output (k_avgpool's sums), from the staged
+// tile.
+// PRE (NT = 1): for grids of few blocks, where a wave has a SIMD to itself and each weight
+// load's latency shows: every weight fragment is loaded before the halo, and the output
+// tiles go over grid.y.  The sums are the same.  16^3 voxels, 32 -> 32 channels: 13.2 us
+// with one block for both output tiles and four loads in flight, 8.3 us so.
+template <int CS, int NT, bool RELU, int C1 = 0, bool PRE = false>
 __global__ __launch_bounds__(256) void k_conv_ct(const uint16_t* __restrict__ in, Dims dm,
                                                  const uint16_t* __restrict__ W, int kp,
                                                  const float* __restrict__ bias, int cout, int cs_out,
-                                                 uint16_t* __restrict__ out, const uint16_t* __restrict__ in2) {
+                                                 uint16_t* __restrict__ out, const uint16_t* __restrict__ in2,
+                                                 const uint16_t* __restrict__ mask, uint16_t* __restrict__ pool) {
   static_assert(C1 % 4 == 0 && C1 < CS, "the skip channels are whole 4-channel groups");
+  static_assert(!PRE || NT == 1, "one output tile per block");
   constexpr int NKC = (27 * CS + 15) / 16;
   constexpr int RS = 18 * CS;                       // one (x, y) row of the halo
   constexpr int HALO = 648 * CS;
@@ -389,6 +421,25 @@ __global__ __launch_bounds__(256) void k_conv_ct(const uint16_t* __restrict__ in
   const int ty = rest & ((1 << nyt) - 1);
   const int tx = rest >> nyt;
   const int x0 = tx * 4, y0 = ty * 4, z0 = tz * 16;
+  // first channel of the block's output tiles, and how many of the stored channels they hold
+  const int co0 = PRE ? 16 * blockIdx.y : 0, csl = PRE ? (cs_out - co0 < 16 ? cs_out - co0 : 16) : cs_out;
+  if (PRE) W += (long long)co0 * kp;
+  constexpr int KP = 16 * NKC, NM = (KP + 31) / 32;   // W's row length (kp), 32-deep steps
+  // the weights of the steps, PRE only
+  s8v bpre[PRE ? NM : 1];
+  if constexpr (PRE && CS % 8 == 0) {
+#pragma unroll
+    for (int m = 0; m < NM; ++m)
+      bpre[m] = (32 * m + 8 * g < KP) ? *reinterpret_cast<const s8v*>(W + (long long)r * KP + 8 * g + 32 * m)
+                                      : s8v{0, 0, 0, 0, 0, 0, 0, 0};
+  } else if constexpr (PRE) {
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+      const uint16_t* p = W + (long long)r * KP + 4 * g + 32 * m;
+      const s4v lo = *reinterpret_cast<const s4v*>(p), hi = 2 * m + 1 < NKC ? *reinterpret_cast<const s4v*>(p + 16) : s4v{0, 0, 0, 0};
+      bpre[m] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+  }
   // reduction index k = 16 kc + 4 g + j -> (tap, channel) -> halo offset; the padding
   // columns (tap >= 27) meet zero rows of W and read any finite halo entry (offset 0)
   // (CS % 8 == 0: entry m * 4 + g holds k = 32 m + 8 g; else entry kc * 4 + g, k = 16 kc + 4 g)
@@ -444,15 +495,14 @@ __global__ __launch_bounds__(256) void k_conv_ct(const uint16_t* __restrict__ in
     // lane group g takes the 8 consecutive reduction indices 32 m + 8 g .. + 7 of MFMA m:
     // 8 channels of one tap, one 16-byte LDS read of A and one 16-byte load of B (the
     // same index on both operands); W's padding columns (k >= 16 NKC) read as zeros
-    constexpr int KP = 16 * NKC, NM = (KP + 31) / 32;
     const uint16_t* wr8 = W + (long long)r * KP + 8 * g;
-#pragma unroll 4
+#pragma unroll PRE ? NM : 4
     for (int m = 0; m < NM; ++m) {
       const int o = lbase + toff[m * 4 + g];
       s8v b[NT];
 #pragma unroll
       for (int t = 0; t < NT; ++t)
-        b[t] = (32 * m + 8 * g < KP) ? *reinterpret_cast<const s8v*>(wr8 + t * 16 * KP + 32 * m)
+        b[t] = PRE ? bpre[PRE ? m : 0] : (32 * m + 8 * g < KP) ? *reinterpret_cast<const s8v*>(wr8 + t * 16 * KP + 32 * m)
                                      : s8v{0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
       for (int yy = 0; yy < 4; ++yy) {
@@ -471,6 +521,11 @@ __global__ __launch_bounds__(256) void k_conv_ct(const uint16_t* __restrict__ in
     s4v b0[NT], b1[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
+      if constexpr (PRE) {
+        b0[t] = __builtin_shufflevector(bpre[kc / 2], bpre[kc / 2], 0, 1, 2, 3);
+        b1[t] = __builtin_shufflevector(bpre[kc / 2], bpre[kc / 2], 4, 5, 6, 7);
+        continue;
+      }
       b0[t] = *reinterpret_cast<const s4v*>(wr + (long long)t * 16 * kp + kc * 16);
       b1[t] = two ? *reinterpret_cast<const s4v*>(wr + (long long)t * 16 * kp + kc * 16 + 16) : s4v{0, 0, 0, 0};
     }
@@ -482,20 +537,20 @@ __global__ __launch_bounds__(256) void k_conv_ct(const uint16_t* __restrict__ in
       for (int t = 0; t < NT; ++t) acc[yy][t] = mfma2(a0, a1, b0[t], b1[t], acc[yy][t]);
     }
   };
-#pragma unroll 4
+#pragma unroll PRE ? NKC : 4
   for (int kc = 0; kc + 1 < NKC; kc += 2) pair(kc, true);
   if constexpr (NKC & 1) pair(NKC - 1, false);
   }
   __syncthreads();   // every wave is done with the halo: its space stages the output
   // D[row = 4g + j][col = r]: voxel z0 + 4g + j of row (x0 + wave, y0 + yy), channel t*16 + r
-  uint16_t* st = tile + wave * 64 * cs_out;
+  uint16_t* st = tile + wave * 64 * csl;
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     const int co = t * 16 + r;
-    const bool live = co < cout;
-    const float bv = live ? bias[co] : 0.f;
-    if (co < cs_out) {
-      uint16_t* sl = st + 4 * g * cs_out + co;
+    const bool live = co0 + co < cout;
+    const float bv = live ? bias[co0 + co] : 0.f;
+    if (co < csl) {
+      uint16_t* sl = st + 4 * g * csl + co;
 #pragma unroll
       for (int yy = 0; yy < 4; ++yy)
 #pragma unroll
@@ -503,28 +558,54 @@ __global__ __launch_bounds__(256) void k_conv_ct(const uint16_t* __restrict__ in
           float v = acc[yy][t][j] + bv;
           if (RELU) v = fmaxf(v, 0.f);
           const uint16_t h = f2bf(v);
-          sl[(yy * 16 + j) * cs_out] = live ? h : (uint16_t)0;
+          sl[(yy * 16 + j) * csl] = live ? h : (uint16_t)0;
         }
     }
   }
   __syncthreads();
-  // each (x, y) row of 16 voxels is a contiguous run of 16 cs_out channels in memory: the
-  // wave's 4 rows as 16-byte (8-byte) pieces, piece p of row p / per_row
-  const long long row0 = dm.encode(x0 + wave, y0, z0) * cs_out;
+  // each (x, y) row of 16 voxels is a contiguous run of 16 cs_out channels in memory (PRE: of
+  // csl channels per voxel): the wave's 4 rows as 16-byte (8-byte) pieces, piece p of row
+  // p / per_row
+  const long long row0 = dm.encode(x0 + wave, y0, z0) * cs_out + co0;
   const long long ystride = (long long)cs_out << (dm.lz);   // one y step, in elements
+  auto spread = [&](int e) { return PRE ? e / csl * cs_out + e % csl : e; };   // element of a row in memory
   if ((cs_out & 7) == 0) {
-    const int per_row = 2 * cs_out;
+    const int per_row = 2 * csl;
     for (int p = lane; p < 4 * per_row; p += 64) {
       const int yy = p / per_row, q = p - yy * per_row;
-      *reinterpret_cast<uint4*>(out + row0 + yy * ystride + 8 * q) =
-          *reinterpret_cast<const uint4*>(st + yy * 16 * cs_out + 8 * q);
+      const long long o = row0 + yy * ystride + spread(8 * q);
+      s8v v = *reinterpret_cast<const s8v*>(st + yy * 16 * csl + 8 * q);
+      if (mask) v = masked(v, *reinterpret_cast<const s8v*>(mask + o));
+      *reinterpret_cast<s8v*>(out + o) = v;
     }
   } else {
-    const int per_row = 4 * cs_out;
+    const int per_row = 4 * csl;
     for (int p = lane; p < 4 * per_row; p += 64) {
       const int yy = p / per_row, q = p - yy * per_row;
-      *reinterpret_cast<s4v*>(out + row0 + yy * ystride + 4 * q) =
-          *reinterpret_cast<const s4v*>(st + yy * 16 * cs_out + 4 * q);
+      const long long o = row0 + yy * ystride + spread(4 * q);
+      s4v v = *reinterpret_cast<const s4v*>(st + yy * 16 * csl + 4 * q);
+      if (mask) v = masked(v, *reinterpret_cast<const s4v*>(mask + o));
+      *reinterpret_cast<s4v*>(out + o) = v;
+    }
+  }
+  if (pool) {
+    // 2 x 2 x 8 coarse voxels, 4 channels per item
+    const Dims dc{dm.lx - 1, dm.ly - 1, dm.lz - 1};
+    const int cq = csl >> 2;
+    for (int i = threadIdx.x; i < 32 * cq; i += 256) {
+      const int v = i / cq, c = 4 * (i - v * cq), xc = v >> 4, yc = (v >> 3) & 1, zc = v & 7;
+      float a[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const s4v e = *reinterpret_cast<const s4v*>(
+            tile + (((2 * xc + (q >> 2)) * 4 + 2 * yc + ((q >> 1) & 1)) * 16 + 2 * zc + (q & 1)) * csl + c);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) a[k] += bf2f((uint16_t)e[k]);
+      }
+      s4v o;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o[k] = (short)f2bf(0.125f * a[k]);
+      *reinterpret_cast<s4v*>(pool + dc.encode((x0 >> 1) + xc, (y0 >> 1) + yc, (z0 >> 1) + zc) * cs_out + co0 + c) = o;
     }
   }
 }
@@ -545,11 +626,13 @@ constexpr size_t conv_ct_lds() {
 // wave w takes x = x0 + w and four 16-voxel z rows (y = y0 .. y0+3), so each weight
 // fragment feeds 4 x NT MFMAs.  Needs lz >= 4, ly >= 2, lx >= 2 and NT*16 >= cout.
 // grid = (X/4)(Y/4)(Z/16), block = 256, dynamic LDS = 648 cs_in BF16.
-template <bool RELU, int NT>
+// grid.y splits the output tiles (NT per block).  ODD16: an odd last chunk as a 16-deep
+// instruction, as k_conv does, whose layers of three output tiles this form takes.
+template <bool RELU, int NT, bool ODD16 = false>
 __global__ __launch_bounds__(256) void k_conv_tiled(const uint16_t* __restrict__ in, Dims dm, int cs_in,
                                                     const uint16_t* __restrict__ W, int kp,
                                                     const float* __restrict__ bias, int cout, int cs_out,
-                                                    uint16_t* __restrict__ out) {
+                                                    uint16_t* __restrict__ out, const uint16_t* __restrict__ mask) {
   extern __shared__ uint16_t tile[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nzt = dm.lz - 4, nyt = dm.ly - 2;
@@ -560,7 +643,7 @@ __global__ __launch_bounds__(256) void k_conv_tiled(const uint16_t* __restrict__
   const int x0 = tx * 4, y0 = ty * 4, z0 = tz * 16;
   stage_halo(tile, in, dm, cs_in, x0, y0, z0);
   __syncthreads();
-  const int r = lane & 15, g = lane >> 4;
+  const int r = lane & 15, g = lane >> 4, co0 = 16 * NT * blockIdx.y;
   f4v acc[4][NT];
 #pragma unroll
   for (int yy = 0; yy < 4; ++yy)
@@ -585,7 +668,7 @@ __global__ __launch_bounds__(256) void k_conv_tiled(const uint16_t* __restrict__
     return off >= 0 ? *reinterpret_cast<const s4v*>(tile + off + yy * row_stride) : s4v{0, 0, 0, 0};
   };
   const int nkc = kp >> 4;
-  const uint16_t* wr = W + (long long)r * kp + 4 * g;
+  const uint16_t* wr = W + (long long)(co0 + r) * kp + 4 * g;
   // B slices of the chunk pair (kc, kc + 1), loaded one pair ahead; an odd last chunk
   // pairs with zeros (its products add exact zeros)
   s4v nb0[NT], nb1[NT];
@@ -603,6 +686,15 @@ __global__ __launch_bounds__(256) void k_conv_tiled(const uint16_t* __restrict__
     for (int t = 0; t < NT; ++t) { b0[t] = nb0[t]; b1[t] = nb1[t]; }
     if (kc + 2 < nkc) load_b(kc + 2);
     const int off0 = off_next();
+    if (ODD16 && kc + 1 >= nkc) {
+#pragma unroll
+      for (int yy = 0; yy < 4; ++yy) {
+        const s4v a0 = a_at(off0, yy);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[yy][t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a0, b0[t], acc[yy][t], 0, 0, 0);
+      }
+      break;
+    }
     const int off1 = kc + 1 < nkc ? off_next() : -1;
 #pragma unroll
     for (int yy = 0; yy < 4; ++yy) {
@@ -616,7 +708,7 @@ __global__ __launch_bounds__(256) void k_conv_tiled(const uint16_t* __restrict__
   for (int yy = 0; yy < 4; ++yy) {
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      const int co = t * 16 + r;
+      const int co = co0 + t * 16 + r;
       const float bv = co < cout ? bias[co] : 0.f;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -624,7 +716,7 @@ __global__ __launch_bounds__(256) void k_conv_tiled(const uint16_t* __restrict__
         if (co < cout) {
           float v = acc[yy][t][j] + bv;
           if (RELU) v = fmaxf(v, 0.f);
-          out[nn * cs_out + co] = f2bf(v);
+          out[nn * cs_out + co] = keep(mask, nn * cs_out + co) ? f2bf(v) : (uint16_t)0;
         } else if (co < cs_out) {
           out[nn * cs_out + co] = 0;
         }
@@ -633,202 +725,282 @@ __global__ __launch_bounds__(256) void k_conv_tiled(const uint16_t* __restrict__
   }
 }
 
-// Weight gradient of a 3x3x3 layer on LDS-staged tiles:
-//   gW[co][k] += sum_n gout[n][co] in[n + d(tap(k))][ci(k)].
-// A block walks tpb consecutive 4 x 4 x 16 voxel tiles; per tile it stages the input
-// block with its halo (as k_conv_tiled) and the output gradient transposed to
-// [co][voxel] (rows up to 16*ceil(cout/16), the padding rows zero).  Its 16 output
-// blocks of 16 (co) x 16 (k) -- blockIdx.y selects which -- are spread 4 per wave;
-// per 16-voxel row an MFMA takes A[co][v] = gout[v][co], B[v][k] = in-patch[v][k].
-// The FP32 sums stay in registers over the tiles, then one atomic add per value.
-// grid = (ceil(tiles / tpb), ceil(blocks / 16)), block = 256,
-// dynamic LDS = (648 cs_in + 256 * 16 ceil(cout/16)) BF16.
-__global__ __launch_bounds__(256) void k_conv_wgrad_tiled(const uint16_t* __restrict__ in, Dims dm, int cs_in,
-                                                          const uint16_t* __restrict__ gout, int cs_g, int cout,
-                                                          int kp, float* __restrict__ gW, int tpb) {
-  extern __shared__ uint16_t sm[];
-  const int ncot = (cout + 15) >> 4, nkc = kp >> 4, nblk = ncot * nkc;
-  uint16_t* halo = sm;
-  uint16_t* gT = sm + 648 * cs_in;
+// Weight and bias gradients of every layer in one launch:
+//   gW[co][tap][ci] = sum_n gout[n][co] in[n + d(tap)][ci],   gb[co] = sum_n gout[n][co].
+// The reduction runs over voxels, so both MFMA operands need 8 voxels of one channel per
+// lane while the tensors are channels-last: gfx950's transposing LDS read gives lane i of
+// 16 the i-th of the 16 channels that the lanes read 4 at a time over 4 voxels, so an operand
+// comes from the tensors' own layout, with no transposed copy and no gather of 2-byte values.
+// A lane's 8 voxels are consecutive in z, and three reads (12 voxels) hold the operands of
+// the three z taps, each one voxel on from the last.
+//
+// A task is (layer, up to WG_CC input channels, 16 output channels, a run of voxel tiles).  Per
+// tile the block stages the input's halo [voxel][channels] and the gradients [voxel][16].  The
+// columns (x and y tap, channel) go in groups of 16, each with its three z taps, over wc of
+// the 4 waves, the voxels over the other 4 / wc: the sums stay in registers over the tiles.
+// Each task writes its sums to a slice of its own and k_wgrad_sum adds the slices in a fixed
+// order (the result is the same on every run, and no buffer has to be cleared).
+// What bounds it: the LDS reads and the staging's latency.  It replaced a kernel per
+// layer that gathered the operands 2 bytes at a time and added every block's sums with
+// atomics, a kernel per layer for small grids and the head, one per layer for the bias and
+// one to bring the sums into the flat layout: 610 us together for the 15 layers of the
+// (8, 16, 32, 80) network on 64^3 voxels with 11 input channels, 60 us with k_wgrad_sum now.
+constexpr int WG_CC = 32;    // input channels per task
+constexpr int WG_KG = 5;     // column groups per wave: 9 * 32 / 16 over 4 waves
+constexpr int WG_HALO = 648; // halo voxels of a tile at most (4 x 4 x 16)
+
+struct WgLayer {
+  const uint16_t* in;
+  const uint16_t* gout;    // gradient of the layer's pre-activation output
+  Dims dm;
+  int cs_in, cs_g, cout, cin, ntap;
+  int ltx, lty, ltz;       // log2 of the voxel tile (at most 256 voxels, halo <= WG_HALO; z at least 8)
+  int ntx, nty, ntz;       // log2 of the tile counts
+  // flat gradients, and the slices: chunk q (input channels), output tile u, split s at
+  // base[q] + (u * nsplit + s) * 16 * wg_cols(q), the bias sums at bbase + (u * nsplit + s) * 16
+  float* gw;
+  float* gb;
+  int nsplit, nchunk;
+  int sb0, snb;            // blocks of k_wgrad_sum
+  long long base[4], bbase;
+};
+struct WgTask {
+  int layer, q, u, split, tile0, ntiles;
+};
+__host__ __device__ inline int wg_chunk(int cs, int q) { return cs - q * WG_CC < WG_CC ? cs - q * WG_CC : WG_CC; }
+// Column groups of a chunk of cc channels, the columns of its slice (group, z tap, 16), and
+// the waves that share the columns: enough that a wave's groups fit its registers.
+__host__ __device__ inline int wg_groups(int ntap, int cc) { return ((ntap == 1 ? 1 : 9) * cc + 15) / 16; }
+__host__ __device__ inline int wg_cols(int ntap, int cc) { return 48 * wg_groups(ntap, cc); }
+__host__ __device__ inline int wg_waves(int groups) { return groups <= WG_KG ? 1 : groups <= 2 * WG_KG ? 2 : 4; }
+
+typedef __attribute__((address_space(3))) s4v lds_s4v;
+typedef __attribute__((ext_vector_type(2))) unsigned u2v;
+typedef __attribute__((ext_vector_type(4))) unsigned u4v;
+// 4 voxels of a lane's channel
+__device__ __forceinline__ u2v tr_read(const uint16_t* p) {
+  return __builtin_bit_cast(u2v, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v*)p));
+}
+
+__global__ __launch_bounds__(256) void k_wgrad(const WgLayer* __restrict__ layers, const WgTask* __restrict__ tasks,
+                                               float* __restrict__ part) {
+  extern __shared__ __align__(16) uint16_t sm[];
+  const WgTask tk = tasks[blockIdx.x];
+  const WgLayer& ly = layers[tk.layer];
+  const Dims dm = ly.dm;
+  const int cs_in = ly.cs_in, cs_g = ly.cs_g, ntap = ly.ntap;
+  const int cc = wg_chunk(cs_in, tk.q), cq = cc >> 2;
+  const int lty = ly.lty, ltz = ly.ltz, nty = ly.nty, ntz = ly.ntz, ltx = ly.ltx;
+  const int HX = (1 << ltx) + 2, HY = (1 << lty) + 2, HZ = (1 << ltz) + 2, nh = HX * HY * HZ;
+  const int nv = 1 << (ltx + lty + ltz), nvp = nv < 32 ? 32 : nv;
+  const int ng = wg_groups(ntap, cc), wc = wg_waves(ng), wv = 4 / wc;
+  const uint16_t* __restrict__ in = ly.in + tk.q * WG_CC;
+  const uint16_t* __restrict__ gout = ly.gout + 16 * tk.u;
+  const int gmax = cs_g - 16 * tk.u;
+  uint16_t* gt = sm;                 // [nvp][16]
+  uint16_t* halo = sm + 256 * 16;    // [nh][cc], two voxels more are read
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r = lane & 15, g4 = lane >> 4;
-  const int nzt = dm.lz - 4, nyt = dm.ly - 2;
-  const int ntiles = (int)(dm.n() >> 8);
-  // this wave's four blocks and, per lane, the column k = kc*16 + r of each
-  int bco[4], bkc[4], boff[4];
-  bool bval[4], tval[4];
+  const int wcol = wave & (wc - 1), wvox = wave / wc;
+  const int r = lane & 15, g4 = lane >> 4, rq = r & 3, rv = r >> 2;
+  // halo offset of this lane's 4 columns of each of its groups (columns past the last tap
+  // read offset 0 and are not summed)
+  int off[WG_KG];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int b = blockIdx.y * 16 + wave * 4 + i;
-    bval[i] = b < nblk;
-    bco[i] = bval[i] ? b % ncot : 0;
-    bkc[i] = bval[i] ? b / ncot : 0;
-    const int k = bkc[i] * 16 + r;
-    const int tap = k / cs_in, ci = k - tap * cs_in;
-    tval[i] = bval[i] && tap < 27;
-    boff[i] = tval[i] ? (((tap / 9) * 6 + (tap / 3) % 3) * 18 + tap % 3) * cs_in + ci : 0;
+  for (int k = 0; k < WG_KG; ++k) {
+    const int col = (wcol + wc * k) * 16 + 4 * rq, tap = col / cc, ci = col - tap * cc;
+    const int dx = ntap == 1 ? 1 : tap / 3, dy = ntap == 1 ? 1 : tap - 3 * (tap / 3);
+    off[k] = tap < (ntap == 1 ? 1 : 9) ? (dx * HY + dy) * HZ * cc + ci : 0;
   }
-  f4v acc[4];
+  f4v acc[WG_KG][3], accb = f4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int i = 0; i < 4; ++i) acc[i] = f4v{0.f, 0.f, 0.f, 0.f};
-  // padding rows of the transposed gradient stay zero for every tile
-  for (int q = threadIdx.x; q < (ncot * 16 - cs_g) * 256; q += 256) gT[cs_g * 256 + q] = 0;
-  const int cqg = cs_g >> 2;
-  for (int it = 0; it < tpb; ++it) {
-    const int tile = blockIdx.x * tpb + it;
-    if (tile >= ntiles) break;
-    const int tz = tile & ((1 << nzt) - 1), rest = tile >> nzt;
-    const int ty = rest & ((1 << nyt) - 1), tx = rest >> nyt;
-    const int x0 = tx * 4, y0 = ty * 4, z0 = tz * 16;
-    __syncthreads();      // the previous tile's reads are done
-    stage_halo(halo, in, dm, cs_in, x0, y0, z0);
-    {
-      // the tile's output gradients, transposed to [channel][voxel]: thread = voxel v,
-      // its cqg loads issued (in batches of 8) before the LDS writes
-      const int v = threadIdx.x;
-      const long long nn = dm.encode(x0 + (v >> 6), y0 + ((v >> 4) & 3), z0 + (v & 15));
-      for (int c0 = 0; c0 < cqg; c0 += 8) {
-        s4v val[8];
+  for (int k = 0; k < WG_KG; ++k)
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (c0 + u < cqg) val[u] = *reinterpret_cast<const s4v*>(gout + nn * cs_g + 4 * (c0 + u));
+    for (int t = 0; t < 3; ++t) acc[k][t] = f4v{0.f, 0.f, 0.f, 0.f};
+  const bool bias = tk.q == 0 && wcol == wc - 1;   // the wave with the fewest columns
+  s8v ones;
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (c0 + u < cqg) {
+  for (int j = 0; j < 8; ++j) ones[j] = (short)0x3f80;
+  constexpr int HI = (WG_HALO + 255) / 256;
+  for (int it = 0; it < tk.ntiles; ++it) {
+    const int tile = tk.tile0 + it;
+    const int x0 = (tile >> (nty + ntz)) << ltx, y0 = ((tile >> ntz) & ((1 << nty) - 1)) << lty,
+              z0 = (tile & ((1 << ntz) - 1)) << ltz;
+    // every load of the tile before the first store
+    s4v val[HI][WG_CC / 4], vg[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) gT[(4 * (c0 + u) + j) * 256 + v] = (uint16_t)val[u][j];
-          }
+    for (int i = 0; i < HI; ++i) {
+      const int h0 = threadIdx.x + 256 * i;
+      const int hx = h0 / (HY * HZ), hr = h0 - hx * (HY * HZ), hy = hr / HZ, hz = hr - hy * HZ;
+      const int gx = x0 + hx - 1, gy = y0 + hy - 1, gz = z0 + hz - 1;
+      const bool in_grid = h0 < nh && dm.inside(gx, gy, gz);
+      const uint16_t* src = in + dm.encode(in_grid ? gx : 0, in_grid ? gy : 0, in_grid ? gz : 0) * cs_in;
+#pragma unroll
+      for (int u = 0; u < WG_CC / 4; ++u) {
+        val[i][u] = s4v{0, 0, 0, 0};
+        if (u < cq && in_grid) val[i][u] = *reinterpret_cast<const s4v*>(src + 4 * u);
       }
+    }
+    {
+      const int v = threadIdx.x;
+      const int vx = x0 + (v >> (lty + ltz)), vy = y0 + ((v >> ltz) & ((1 << lty) - 1)), vz = z0 + (v & ((1 << ltz) - 1));
+      const bool in_grid = v < nv && vz < (1 << dm.lz);
+      const uint16_t* src = gout + dm.encode(in_grid ? vx : 0, in_grid ? vy : 0, in_grid ? vz : 0) * cs_g;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        vg[u] = s4v{0, 0, 0, 0};
+        if (in_grid && 4 * u < gmax) vg[u] = *reinterpret_cast<const s4v*>(src + 4 * u);
+      }
+    }
+    __syncthreads();      // the previous tile's reads are done
+#pragma unroll
+    for (int i = 0; i < HI; ++i) {
+      const int h0 = threadIdx.x + 256 * i;
+      if (h0 < nh) {
+#pragma unroll
+        for (int u = 0; u < WG_CC / 4; ++u)
+          if (u < cq) *reinterpret_cast<s4v*>(halo + h0 * cc + 4 * u) = val[i][u];
+      }
+    }
+    if ((int)threadIdx.x < nvp) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) *reinterpret_cast<s4v*>(gt + threadIdx.x * 16 + 4 * u) = vg[u];
     }
     __syncthreads();
-#pragma unroll 1
-    for (int vc = 0; vc < 16; vc += 2) {   // 16-voxel rows vc and vc + 1 in one instruction
-      // voxels v = vc*16 + 4*g4 + j: row (xl, yl) = (vc / 4, vc % 4), z = 4*g4 + j
-      const int rowoff0 = ((vc >> 2) * 6 + (vc & 3)) * 18 * cs_in + 4 * g4 * cs_in;
-      const int rowoff1 = (((vc + 1) >> 2) * 6 + ((vc + 1) & 3)) * 18 * cs_in + 4 * g4 * cs_in;
+    for (int vb = 32 * wvox; vb < nvp; vb += 32 * wv) {
+      // this lane's 8 voxels along z; past the tile's last voxel the gradients are zero and
+      // the input any finite entry
+      const int v8 = vb + 8 * g4, vi = v8 & (nv - 1);
+      const uint16_t* h = halo + (((vi >> (lty + ltz)) * HY + ((vi >> ltz) & ((1 << lty) - 1))) * HZ + (vi & ((1 << ltz) - 1)) + rv) * cc;
+      const u2v al = tr_read(gt + (v8 + rv) * 16 + 4 * rq), ah = tr_read(gt + (v8 + 4 + rv) * 16 + 4 * rq);
+      const bf8v a = __builtin_bit_cast(bf8v, u4v{al[0], al[1], ah[0], ah[1]});
+      if (bias) accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf8v, ones), accb, 0, 0, 0);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (!bval[i]) continue;
-        const uint16_t* ar = gT + (bco[i] * 16 + r) * 256 + vc * 16 + 4 * g4;
-        const s4v a0 = *reinterpret_cast<const s4v*>(ar);
-        const s4v a1 = *reinterpret_cast<const s4v*>(ar + 16);
-        s4v b0 = s4v{0, 0, 0, 0}, b1 = s4v{0, 0, 0, 0};
-        if (tval[i]) {
+      for (int k = 0; k < WG_KG; ++k) {
+        if (wcol + wc * k < ng) {
+          const u2v w0 = tr_read(h + off[k]), w1 = tr_read(h + off[k] + 4 * cc), w2 = tr_read(h + off[k] + 8 * cc);
+          const u4v b0 = {w0[0], w0[1], w1[0], w1[1]}, b2 = {w0[1], w1[0], w1[1], w2[0]};
+          u4v b1;
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            b0[j] = (short)halo[boff[i] + rowoff0 + j * cs_in];
-            b1[j] = (short)halo[boff[i] + rowoff1 + j * cs_in];
-          }
-        }
-        acc[i] = mfma2(a0, a1, b0, b1, acc[i]);
-      }
-    }
-  }
-  // D[row = 4*g4 + j][col = r] -> (co = bco*16 + 4*g4 + j, k = bkc*16 + r)
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if (!bval[i]) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int co = bco[i] * 16 + 4 * g4 + j;
-      if (co < cout && acc[i][j] != 0.f) atomicAdd(&gW[(long long)co * kp + bkc[i] * 16 + r], acc[i][j]);
-    }
-  }
-}
-
-// Weight gradient  gW[co][k] += sum_n gout[n][co] in[n + d(tap(k))][ci(k)]
-// (FP32 atomics).  grid = co_tiles * k_tiles * nsplit blocks of one wave; each
-// wave reduces over its voxel range in chunks of 16 (4 voxels per lane group).
-__global__ __launch_bounds__(64) void k_conv_wgrad(const uint16_t* __restrict__ in, Dims dm, int cs_in, int ks,
-                                                   const uint16_t* __restrict__ gout, int cs_g, int cout, int kp,
-                                                   float* __restrict__ gW, int nsplit, long long chunk) {
-  const int lane = threadIdx.x & 63;
-  const int r = lane & 15, g = lane >> 4;
-  const int ncot = (cout + 15) >> 4;
-  const int tile = blockIdx.x / nsplit, split = blockIdx.x - (blockIdx.x / nsplit) * nsplit;
-  const int tc = tile % ncot, kc = tile / ncot;
-  const long long N = dm.n();
-  const long long v0 = (long long)split * chunk;
-  const long long v1 = v0 + chunk < N ? v0 + chunk : N;
-  const int co = tc * 16 + r;
-  const int k = kc * 16 + r;
-  const int tap = k / cs_in, ci = k - (k / cs_in) * cs_in;
-  const bool kvalid = tap < ks * ks * ks;
-  int dx = 0, dy = 0, dz = 0;
-  if (kvalid) tap_offset(tap, ks, dx, dy, dz);
-  f4v acc = f4v{0.f, 0.f, 0.f, 0.f};
-  // the 4 voxels of this lane group in the 16-voxel chunk at nb (zero past v1)
-  auto slices = [&](long long nb, s4v& a, s4v& b) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const long long n = nb + 4 * g + j;
-      uint16_t av = 0, bv = 0;
-      if (n < v1) {
-        if (co < cout) av = gout[n * cs_g + co];
-        if (kvalid) {
-          int x, y, z;
-          dm.decode(n, x, y, z);
-          const int xx = x + dx, yy = y + dy, zz = z + dz;
-          if (dm.inside(xx, yy, zz)) bv = in[dm.encode(xx, yy, zz) * cs_in + ci];
+          for (int i = 0; i < 4; ++i) b1[i] = __builtin_amdgcn_alignbit(b2[i], b0[i], 16);
+          acc[k][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf8v, b0), acc[k][0], 0, 0, 0);
+          acc[k][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf8v, b1), acc[k][1], 0, 0, 0);
+          acc[k][2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf8v, b2), acc[k][2], 0, 0, 0);
         }
       }
-      a[j] = (short)av;
-      b[j] = (short)bv;
     }
-  };
-  // two chunks per instruction (the second may be empty); the loads of U instructions are
-  // issued before their MFMAs, which run in the same order as one at a time
-  constexpr int U = 4;
-  for (long long nb = v0; nb < v1; nb += 32 * U) {
-    s4v a0[U], b0[U], a1[U], b1[U];
+  }
+  // the waves that share columns, added into the first in order
+  f4v* red = reinterpret_cast<f4v*>(sm) + wcol * (3 * WG_KG + 1) * 64 + lane;
+  for (int s = 1; s < wv; ++s) {
+    __syncthreads();
+    if (wvox == s) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      slices(nb + 32 * u, a0[u], b0[u]);
-      slices(nb + 32 * u + 16, a1[u], b1[u]);
+      for (int k = 0; k < WG_KG; ++k)
+#pragma unroll
+        for (int t = 0; t < 3; ++t) red[(3 * k + t) * 64] = acc[k][t];
+      red[3 * WG_KG * 64] = accb;
     }
+    __syncthreads();
+    if (!wvox) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) acc = mfma2(a0[u], a1[u], b0[u], b1[u], acc);
-  }
-  // D[row = co 4g+j][col = k r]
+      for (int k = 0; k < WG_KG; ++k)
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int cor = tc * 16 + 4 * g + j;
-    if (cor < cout && k < kp && acc[j] != 0.f) atomicAdd(&gW[(long long)cor * kp + k], acc[j]);
+        for (int t = 0; t < 3; ++t) acc[k][t] += red[(3 * k + t) * 64];
+      accb += red[3 * WG_KG * 64];
+    }
   }
+  if (wvox) return;
+  // D[row = 4 g4 + j][col = r]: output channel 4 g4 + j, column r of the group and z tap
+  const int ncol = 48 * ng;
+  const long long slice = tk.u * ly.nsplit + tk.split;
+  float* __restrict__ dst = part + ly.base[tk.q] + slice * (16 * ncol);
+#pragma unroll
+  for (int k = 0; k < WG_KG; ++k) {
+    if (wcol + wc * k < ng) {
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) dst[(4 * g4 + j) * ncol + 48 * (wcol + wc * k) + 16 * t + r] = acc[k][t][j];
+    }
+  }
+  if (bias && r == 0) *reinterpret_cast<f4v*>(part + ly.bbase + slice * 16 + 4 * g4) = accb;
 }
 
-// Bias gradient gb[co] += sum_n g[n][co] (cs_g <= 256), 256 threads per block.
-__global__ void k_bias_grad(const uint16_t* __restrict__ gout, long long N, int cs_g, int cout, float* __restrict__ gb) {
-  // items (voxel, group of 4 channels) in memory order, 8-byte loads; the grid's thread
-  // count is a multiple of cs_g / 4, so each thread always meets the same channel group
-  __shared__ float bins[256];
-  const int cq = cs_g >> 2;
-  const long long nitem = N * cq;
-  const long long stride = (long long)gridDim.x * blockDim.x;
-  const long long i0 = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  for (int c = threadIdx.x; c < cs_g; c += blockDim.x) bins[c] = 0.f;
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (long long i = i0; i < nitem; i += stride) {
-    const s4v v = *reinterpret_cast<const s4v*>(gout + 4 * i);
-    acc.x += bf2f((uint16_t)v[0]); acc.y += bf2f((uint16_t)v[1]);
-    acc.z += bf2f((uint16_t)v[2]); acc.w += bf2f((uint16_t)v[3]);
+// LDS bytes of k_wgrad for cc channels and nh halo voxels.
+inline size_t wgrad_lds(int ntap, int cc, int nh) {
+  const int wc = wg_waves(wg_groups(ntap, cc));
+  const size_t stage = sizeof(uint16_t) * (256 * 16 + (size_t)(nh + 2) * cc), red = wc < 4 ? sizeof(f4v) * 64 * (3 * WG_KG + 1) * wc : 0;
+  return stage > red ? stage : red;
+}
+
+// The slices of k_wgrad added up into the flat gradient, every layer in one launch (blocks
+// [sb0, sb0 + snb) serve layer l).  Latency bounds it: the level-0 layers have few values of
+// many slices, which one thread per value with four loads in flight added in 26 us for 15
+// layers of up to 256 slices.  So a value of WS_MANY slices or more has 16 threads, each
+// with eight loads in flight, whose sums are added in order: 9.9 us.
+constexpr int WS_MANY = 32;
+__host__ __device__ inline int ws_vals(int nsplit) { return nsplit >= WS_MANY ? 16 : 256; }   // values per block
+struct WgBlocks {
+  int sb0[24];   // first block of layers 1, 2, ... (23 layers at most), INT_MAX beyond the last
+};
+__global__ __launch_bounds__(256) void k_wgrad_sum(const WgLayer* __restrict__ layers, WgBlocks first, const float* __restrict__ part) {
+  __shared__ float sums[256];
+  int l = 0;
+#pragma unroll
+  for (int k = 0; k < 24; ++k) l += (int)blockIdx.x >= first.sb0[k];
+  const WgLayer& ly = layers[l];
+  const int nw = ly.cout * ly.ntap * ly.cin, n = nw + ly.cout, ns = ly.nsplit;
+  const int vals = ws_vals(ns), ngrp = 256 / vals, grp = threadIdx.x / vals, v0 = threadIdx.x & (vals - 1);
+  const int i = (blockIdx.x - ly.sb0) * vals + v0;
+  float acc = 0.f;
+  if (i < n) {
+    const float* src;
+    long long step;
+    if (i < nw) {
+      const int rest = i / ly.cin, ci = i - rest * ly.cin, co = rest / ly.ntap, tap = rest - co * ly.ntap;
+      const int q = ci / WG_CC, cc = wg_chunk(ly.cs_in, q), ncol = wg_cols(ly.ntap, cc);
+      const int xy = ly.ntap == 1 ? 0 : tap / 3, dz = ly.ntap == 1 ? 1 : tap - 3 * xy, col = xy * cc + ci - q * WG_CC;
+      step = 16 * ncol;
+      src = part + ly.base[q] + (long long)(co >> 4) * ns * step + (co & 15) * ncol + (3 * (col >> 4) + dz) * 16 + (col & 15);
+    } else {
+      const int co = i - nw;
+      step = 16;
+      src = part + ly.bbase + (long long)(co >> 4) * ns * step + (co & 15);
+    }
+    constexpr int U = 8;
+    for (int s0 = grp; s0 < ns; s0 += ngrp * U) {
+      float v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = s0 + ngrp * u < ns ? src[(s0 + ngrp * u) * step] : 0.f;
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc += v[u];
+    }
   }
-  __syncthreads();
-  const int c4 = (int)(i0 % cq);
-  atomicAdd(&bins[4 * c4 + 0], acc.x);
-  atomicAdd(&bins[4 * c4 + 1], acc.y);
-  atomicAdd(&bins[4 * c4 + 2], acc.z);
-  atomicAdd(&bins[4 * c4 + 3], acc.w);
-  __syncthreads();
-  for (int c = threadIdx.x; c < cout; c += blockDim.x) atomicAdd(&gb[c], bins[c]);
+  if (ngrp > 1) {
+    sums[threadIdx.x] = acc;
+    __syncthreads();
+    if (!grp)
+      for (int k = 1; k < 16; ++k) acc += sums[k * 16 + v0];
+  }
+  if (grp || i >= n) return;
+  if (i < nw) ly.gw[i] = acc;
+  else ly.gb[i - nw] = acc;
 }
 
 // FP32 channel-major volumes [C][src] / scale -> BF16 channels-last [N][cs] (crop
-// window (o, dst) of the source; channels C..cs-1 zero).
+// window (o, dst) of the source; channels C..cs-1 zero).  The scale comes from k_absmax's
+// slot; it is stored for the kernels after the network, and the loss is cleared.
 __global__ void k_to_bf16_crop(const float* __restrict__ x, int C, Dims src, int ox, int oy, int oz, Dims dst,
-                               const double* __restrict__ scale, int cs, uint16_t* __restrict__ out) {
+                               const unsigned* __restrict__ slot, double* __restrict__ scale, double* __restrict__ loss, int cs,
+                               uint16_t* __restrict__ out) {
   const long long N = dst.n(), ns = src.n();
-  const float inv = (float)(1.0 / *scale);
+  const float top = __uint_as_float(*slot);
+  const double sc = top > 0.f ? (double)top : 1.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *scale = sc;
+    *loss = 0.0;
+  }
+  const float inv = (float)(1.0 / sc);
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < N; i += (long long)gridDim.x * blockDim.x) {
     int x0, y0, z0;
     dst.decode(i, x0, y0, z0);
@@ -856,16 +1028,29 @@ __global__ void k_avgpool(const uint16_t* __restrict__ in, Dims di, int cs, uint
   }
 }
 
-// gin[child] = gout[parent]/8 added to gin (average-pool backward).
-__global__ void k_avgpool_bwd_add(const uint16_t* __restrict__ gout, Dims dout, int cs, uint16_t* __restrict__ gin, Dims di) {
-  const long long N = di.n() * cs;
+// Gradient of an encoder output that feeds both the skip connection and the pool: the
+// concatenation's gradient (its first cs channels, stride cs_cat) plus an eighth of the
+// pooled voxel's, zeroed where the output act is not > 0.  Items of 4 channels.
+__global__ void k_skip_pool_bwd(const uint16_t* __restrict__ gcat, int cs_cat, const uint16_t* __restrict__ gpool, Dims dp,
+                                int cs, int c1, const uint16_t* __restrict__ act, uint16_t* __restrict__ out, Dims di) {
+  const int cq = cs >> 2;
+  const long long N = di.n() * cq;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < N; i += (long long)gridDim.x * blockDim.x) {
-    const long long n = i / cs;
-    const int c = (int)(i - n * cs);
+    const long long n = i / cq;
+    const int c = 4 * (int)(i - n * cq);
     int x, y, z;
     di.decode(n, x, y, z);
-    const float v = bf2f(gout[dout.encode(x >> 1, y >> 1, z >> 1) * cs + c]);
-    gin[i] = f2bf(bf2f(gin[i]) + 0.125f * v);
+    const s4v gp = *reinterpret_cast<const s4v*>(gpool + dp.encode(x >> 1, y >> 1, z >> 1) * cs + c);
+    const s4v av = *reinterpret_cast<const s4v*>(act + n * cs + c);
+    // the skip channels of the concatenation end at c1, its padding is not part of them
+    const s4v gc = *reinterpret_cast<const s4v*>(gcat + n * cs_cat + c);
+    s4v v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float skip = c + q < c1 ? bf2f((uint16_t)gc[q]) : 0.f;
+      v[q] = (short)f2bf(skip + 0.125f * bf2f((uint16_t)gp[q]));
+    }
+    *reinterpret_cast<s4v*>(out + n * cs + c) = masked(v, av);
   }
 }
 
@@ -900,15 +1085,10 @@ __global__ void k_upcat(const uint16_t* __restrict__ skip, int cs1, int c1, cons
   }
 }
 
-// Backward of k_upcat: gskip[n][c] = g[n][c] (c < c1); gcoarse[m][c] = sum of its 8 children.
-__global__ void k_upcat_bwd(const uint16_t* __restrict__ g, int cs, int c1, int c2, Dims df, Dims dc,
-                            uint16_t* __restrict__ gskip, int cs1, uint16_t* __restrict__ gcoarse, int cs2) {
-  const long long Nf = df.n() * cs1;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < Nf; i += (long long)gridDim.x * blockDim.x) {
-    const long long n = i / cs1;
-    const int c = (int)(i - n * cs1);
-    gskip[i] = c < c1 ? g[n * cs + c] : (uint16_t)0;
-  }
+// Gradient of the coarse tensor of a concatenation: the sum over its 8 children of the
+// channels c1 .. c1 + c2 - 1, zeroed where act (the coarse tensor) is not > 0.
+__global__ void k_up_bwd(const uint16_t* __restrict__ g, int cs, int c1, int c2, Dims df, Dims dc,
+                         const uint16_t* __restrict__ act, uint16_t* __restrict__ gcoarse, int cs2) {
   const long long Nc = dc.n() * cs2;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < Nc; i += (long long)gridDim.x * blockDim.x) {
     const long long m = i / cs2;
@@ -917,22 +1097,36 @@ __global__ void k_upcat_bwd(const uint16_t* __restrict__ g, int cs, int c1, int 
     if (c < c2) {
       int x, y, z;
       dc.decode(m, x, y, z);
-      for (int q = 0; q < 8; ++q) s += bf2f(g[df.encode(2 * x + (q >> 2), 2 * y + ((q >> 1) & 1), 2 * z + (q & 1)) * cs + c1 + c]);
+      uint16_t v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = g[df.encode(2 * x + (q >> 2), 2 * y + ((q >> 1) & 1), 2 * z + (q & 1)) * cs + c1 + c];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) s += bf2f(v[q]);
     }
-    gcoarse[i] = f2bf(s);
+    gcoarse[i] = bf2f(act[i]) > 0.f ? f2bf(s) : (uint16_t)0;
   }
 }
 
-// g *= (act > 0)  (ReLU backward, act = the layer's post-ReLU output).
-__global__ void k_relu_bwd(uint16_t* __restrict__ g, const uint16_t* __restrict__ act, long long n) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
-    if (!(bf2f(act[i]) > 0.f)) g[i] = 0;
+// Data gradient of the 1x1x1 head (one output channel, W the first row of its packed matrix):
+// g[n][c] = gy[n] W[c], zeroed where act is not > 0.  gy is channel 0 of stride 4.
+__global__ void k_head_bwd(const uint16_t* __restrict__ gy, long long N, int cs, int c, const uint16_t* __restrict__ W,
+                           const uint16_t* __restrict__ act, uint16_t* __restrict__ g) {
+  const int cq = cs >> 2;
+  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < N * cq; i += (long long)gridDim.x * blockDim.x) {
+    const long long n = i / cq;
+    const int c4 = 4 * (int)(i - n * cq);
+    const float gv = bf2f(gy[4 * n]);
+    s4v v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = (short)(c4 + q < c ? f2bf(gv * bf2f(W[c4 + q]) + 0.f) : (uint16_t)0);
+    *reinterpret_cast<s4v*>(g + 4 * i) = masked(v, *reinterpret_cast<const s4v*>(act + 4 * i));
+  }
 }
 
-// MSE on a crop: loss += sum (y - t/s)^2 / n (FP64 atomics); gy = 2 (y - t/s) / n as BF16 [N][cs].
+// MSE on a crop: loss += sum (y - t/s)^2 / n (FP64 atomics); gy = 2 (y - t/s) / n as BF16 [N][4] (channel 0).
 __global__ void k_mse(const float* __restrict__ y, const float* __restrict__ t, Dims src, int ox, int oy, int oz,
-                      Dims dm, const double* __restrict__ scale, int cs, uint16_t* __restrict__ gy, double* __restrict__ loss) {
-  __shared__ double part[256];
+                      Dims dm, const double* __restrict__ scale, uint16_t* __restrict__ gy, double* __restrict__ loss) {
+  __shared__ double part[4];   // 256 threads
   const long long N = dm.n();
   const float inv = (float)(1.0 / *scale);
   double acc = 0.0;
@@ -941,48 +1135,50 @@ __global__ void k_mse(const float* __restrict__ y, const float* __restrict__ t, 
     dm.decode(i, x, yy, z);
     const float e = y[i] - t[src.encode(x + ox, yy + oy, z + oz)] * inv;
     acc += (double)e * (double)e;
-    gy[i * cs] = f2bf(2.f * e / (float)N);
-    for (int c = 1; c < cs; ++c) gy[i * cs + c] = 0;
+    *reinterpret_cast<s4v*>(gy + 4 * i) = s4v{(short)f2bf(2.f * e / (float)N), 0, 0, 0};
   }
-  part[threadIdx.x] = acc;
+  for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int q = 0; q < (int)blockDim.x; ++q) s += part[q];
-    atomicAdd(loss, s / (double)N);
-  }
+  if (threadIdx.x == 0) atomicAdd(loss, (part[0] + part[1] + part[2] + part[3]) / (double)N);
 }
 
 // max_i |sum_c x[c][i]| over C channel-major volumes of n voxels: per-block maxima
 // folded into *slot with an integer atomic max (the bit patterns of non-negative
-// floats order like their values), then k_absmax_final writes it as FP64 to *out
-// (1 if the maximum is 0) and clears the slot for the next call.
-// Items of 4 consecutive voxels (n is a multiple of 4), channels summed in order.
+// floats order like their values).  k_to_bf16_crop turns the slot into the scale (1 if the
+// maximum is 0) and k_head1, the last kernel of the forward pass, clears it for the next call.
+// Items of 4 consecutive voxels (n is a multiple of 4), channels summed in order.  128^3, 11
+// channels: 35.2 us with the channels loaded one after another (2.6 TB/s) and an atomic from each of 2048 blocks,
+// 23 us (4.0 TB/s) with six in flight and 1024 blocks.
 __global__ void k_absmax(const float* __restrict__ x, long long n, int C, unsigned* __restrict__ slot) {
-  __shared__ float part[256];
+  __shared__ float part[4];   // 256 threads
   float m = 0.f;
   const long long n4 = n >> 2;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n4; i += (long long)gridDim.x * blockDim.x) {
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int c = 0; c < C; ++c) {
-      const float4 a = reinterpret_cast<const float4*>(x + c * n)[i];
-      v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w;
+    constexpr int U = 6;   // channels in flight
+    for (int c0 = 0; c0 < C; c0 += U) {
+      float4 a[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (c0 + u < C) a[u] = reinterpret_cast<const float4*>(x + (c0 + u) * n)[i];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (c0 + u < C) { v.x += a[u].x; v.y += a[u].y; v.z += a[u].z; v.w += a[u].w; }
     }
     m = fmaxf(fmaxf(m, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w)));
   }
-  part[threadIdx.x] = m;
+  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) part[threadIdx.x] = fmaxf(part[threadIdx.x], part[threadIdx.x + o]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) atomicMax(slot, __float_as_uint(part[0]));
+  if (threadIdx.x == 0) atomicMax(slot, __float_as_uint(fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]))));
 }
 // 1x1x1 convolution to one FP32 output channel (the head): y[n] = b + sum_c W[c] in[n][c],
 // W the first row of the packed BF16 forward matrix, FP32 sums.
 __global__ void k_head1(const uint16_t* __restrict__ in, long long N, int cs_in, int cin, const uint16_t* __restrict__ W,
-                        const float* __restrict__ bias, float* __restrict__ y) {
+                        const float* __restrict__ bias, float* __restrict__ y, unsigned* __restrict__ slot) {
   const float b = bias[0];
+  if (blockIdx.x == 0 && threadIdx.x == 0) *slot = 0u;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < N; i += (long long)gridDim.x * blockDim.x) {
     float acc = 0.f;
     for (int c4 = 0; c4 < cs_in; c4 += 4) {
@@ -992,14 +1188,6 @@ __global__ void k_head1(const uint16_t* __restrict__ in, long long N, int cs_in,
         if (c4 + q < cin) acc += bf2f((uint16_t)v[q]) * bf2f(W[c4 + q]);
     }
     y[i] = acc + b;
-  }
-}
-
-__global__ void k_absmax_final(unsigned* __restrict__ slot, double* __restrict__ out) {
-  if (threadIdx.x == 0) {
-    const float t = __uint_as_float(*slot);
-    *out = t > 0.f ? (double)t : 1.0;
-    *slot = 0u;
   }
 }
 
@@ -1014,13 +1202,10 @@ __global__ void k_scale_relu(const float* __restrict__ y, long long n, const dou
 // that serve it (every layer in one launch: blocks [b0, b0 + nb) take layer l).
 struct PackDesc {
   const float* p;          // the layer's weights in the flat FP32 parameters
-  float* gp;               // the layer's weight gradient in the flat FP32 gradient
   uint16_t* Wf;
   uint16_t* Wt;
-  const float* gWf;
   int cin, cout, ks, cs_in, cs_out, kp, kpt, rows_f, rows_t;
   int pb0, pnb;            // blocks of k_pack_all
-  int ub0, unb;            // blocks of k_unpack_all
 };
 
 // Master FP32 layer parameters (flat layout W[co][tap][cin], bias) -> BF16 GEMM
@@ -1052,22 +1237,6 @@ __global__ void k_pack_all(const PackDesc* __restrict__ ds, int nl) {
   }
 }
 
-// Gradient of each padded forward GEMM matrix back to the flat layout, all layers in one launch.
-__global__ void k_unpack_all(const PackDesc* __restrict__ ds, int nl) {
-  int l = 0;
-  while (l + 1 < nl && (int)blockIdx.x >= ds[l + 1].ub0) ++l;
-  const PackDesc& d = ds[l];
-  const int ntap = d.ks * d.ks * d.ks;
-  const long long n = (long long)d.cout * ntap * d.cin;
-  for (long long i = (blockIdx.x - d.ub0) * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)d.unb * blockDim.x) {
-    const int ci = (int)(i % d.cin);
-    const long long rest = i / d.cin;
-    const int tap = (int)(rest % ntap), co = (int)(rest / ntap);
-    d.gp[i] = d.gWf[(long long)co * d.kp + tap * d.cs_in + ci];
-  }
-}
-
 // Adam (Kingma & Ba 2015) on FP32 master parameters.
 __global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m, float* __restrict__ v,
                        long long n, float lr, float b1, float b2, float eps, float c1, float c2) {
@@ -1082,9 +1251,6 @@ __global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float
 }
 
 __global__ void k_fill_f32(float* __restrict__ p, long long n, float v) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) p[i] = v;
-}
-__global__ void k_fill_f64(double* __restrict__ p, long long n, double v) {
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) p[i] = v;
 }
 
