@@ -6,7 +6,8 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libmh3d.so")
-SOURCES = [os.path.join(PKG, "csrc", f) for f in ("mh3d.hip", "sep.hip", "fast.hip")]
+SOURCES = [os.path.join(PKG, "csrc", f) for f in ("mh3d.hip", "sep.hip", "fast.hip", "user.hip", "user_class1.hip",
+                                                       "user_class2.hip", "user_class4.hip", "user_class3689.hip")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [

@@ -437,7 +437,7 @@ static __global__ __launch_bounds__(G::TC) void k_fast_col(const VolDesc* __rest
 
 // ============================================================================ solver step
 // The end of a solver step on the block's voxels (rows y = sy*y1 + y0 of plane x), with
-// u = b . v from the packed rows Z in LDS: the same arithmetic as StepCtx (kernels.hpp),
+// u = b . v from the packed rows Z in LDS: the same arithmetic as sep_step (sep.hpp),
 //   UPD_NORMAL  out = u + lam R(s w);  FP64 <s w, out>, ||out||^2
 //   UPD_FISTA   g = u + lam R(y^k); rho^{k+1} = max(y^k - tau g, 0);
 //               y^{k+1} = rho^{k+1} + k/(k+3) (rho^{k+1} - rho^k); FP64 ||rho^{k+1} - y^k||^2,
@@ -571,7 +571,7 @@ __device__ __forceinline__ void fast_step(const VolDesc& vd, const AdjOut& ao, c
 // Block (x, y0): the residue's half spectrum Q(x, q'y, qz mod mz) conj(Et(y0, q'y, qz)),
 // inverse length-my DFT along y1, C2R along z, then per voxel of rows y = sy*y1 + y0:
 //   OUT_SCALE_B      ao.out = b . v
-//   OUT_STEP_NORMAL  / OUT_STEP_FISTA: the solver step with u = b . v (StepCtx), FP64
+//   OUT_STEP_NORMAL  / OUT_STEP_FISTA: the solver step with u = b . v (sep_step), FP64
 //                    block partials in vd.partials[lb] for k_vol_finish (nb_upd = NBP).
 template <class G, int OUT>
 __device__ __forceinline__ void fast_plane_adj_body(const VolDesc& vd, int lb, const AdjOut& ao) {

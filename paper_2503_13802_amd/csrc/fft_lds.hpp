@@ -274,6 +274,7 @@ typedef float gvec4 __attribute__((ext_vector_type(4)));
 #define MH3D_GLOBAL __attribute__((address_space(1)))
 template <typename T>
 __device__ __forceinline__ T ldg(const T* p) { return *p; }
+__device__ __forceinline__ int ldg(const int* p) { return *(const MH3D_GLOBAL int*)p; }
 __device__ __forceinline__ float ldg(const float* p) { return *(const MH3D_GLOBAL float*)p; }
 __device__ __forceinline__ float2 ldg(const float2* p) {
   const gvec2 v = *(const MH3D_GLOBAL gvec2*)p;

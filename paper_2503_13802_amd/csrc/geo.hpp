@@ -70,6 +70,18 @@ struct SepGeo {
       d_xbmzh, d_nxb;
 };
 
+// Launch shapes and divisors of the user-PSF passes (user.hpp).
+struct UserGeo {
+  int pl;                  // one LDS buffer of a component's plane (complex values)
+  int pcb;                 // components per round of the adjoint plane pass (1 or C)
+  int cb;                  // components at once in the class passes: all C, or 0 for rounds of one
+  int fls;                 // LDS line stride of the folded spectra
+  // of the plane passes: npairs, alone and times pcb; the two column counts of a workgroup; pcb (nz/2 + 1); the two
+  // counts of row pairs of a workgroup, times pcb and alone.  Of the class passes: cpw nmem, that
+  // times the components at once, K cpw, cpw mx and cpw xb.
+  MDiv d_np, d_cnp, d_qlo, d_qhi, d_ycols, d_jlo, d_jhi, d_j1lo, d_j1hi, d_w, d_cbw, d_kc, d_cm, d_cxb;
+};
+
 struct Geo {
   int nx, ny, nz, nzh;     // grid, nzh = nz/2 + 1
   int mx, my, mz, mzh;     // decimated grid, mzh = mz/2 + 1
@@ -95,6 +107,7 @@ struct Geo {
   long long Mf;            // mxf*myf*mzf (= M without padding)
   long long hsz;           // spectrum elements per harmonic = ncls*mx*S = plane*nx
   SepGeo sep;
+  UserGeo usr;
   FastDiv f_nz, f_nzh, f_nmem, f_mzh, f_sz, f_mz, f_W, f_xb, f_S, f_mxS, f_cpwmx, f_cpwxb, f_ny, f_my;
 };
 

@@ -43,17 +43,6 @@ __device__ __forceinline__ int class_index_of(const Geo& g, int qy, int qz, bool
   return c * g.nmem + m;
 }
 
-// Source position (qy, qz <= nz/2) in a half plane of the class-layout element e,
-// and whether the element is the conjugate of that position.
-__device__ __forceinline__ int halfplane_of_member(const Geo& g, int e, bool& cj) {
-  const int c = e / g.nmem, m = e % g.nmem;
-  const int qy = (c / g.mzh) + (m / g.sz) * g.my;
-  const int qz = (c % g.mzh) + (m % g.sz) * g.mz;
-  if (2 * qz <= g.nz) { cj = false; return qy * g.nzh + qz; }
-  cj = true;
-  return ((g.ny - qy) % g.ny) * g.nzh + (g.nz - qz);
-}
-
 // LDS line strides: transforms run on contiguous lines padded to an odd length so
 // that the transposing passes between them hit distinct banks.
 __host__ __device__ inline int pad_odd(int n) { return (n & 1) ? n : n + 1; }
@@ -167,10 +156,11 @@ struct VolDesc {
   int reg_kind;
   float lam;
   int T_class;             // threads of the class passes doing element work
-  float* u;                // A^T A part of the current step (k_plane_adj<OUT_U> -> k_vol_update)
+  float* u;                // A^T A part of the current step, summed over the components so far
+  const int* cidx;         // user PSFs: the class layout's positions in a half plane (user.hpp)
   float alpha;             // boundary prior weight (eq. finalR), 0 = off
   int aw;                  // its shell depth in voxels
-  int nb_upd;              // blocks of k_vol_update for this volume
+  int nb_upd;              // blocks whose sums a solver step leaves
   // Vector model (components i of the PSF vector and of the sensitivity): component
   // i's spectra at hs + i * hs_cstride elements, its sensitivity at b + i * N and its
   // class-layout spectra at uperm + i * hsz.  ncomp = 1 is the scalar model.
@@ -205,158 +195,6 @@ __device__ __forceinline__ const VolDesc& vol_of(const VolDesc* __restrict__ vds
 // ============================================================================ pass 1: x-plane R2C
 enum { SRC_PLAIN = 0, SRC_RAW = 1, SRC_FISTA_Y = 2, SRC_SCALED = 3 };
 
-// Value fed to the forward FFT at flat voxel i.
-template <int SRC>
-__device__ __forceinline__ float plane_source(long long i, const float* __restrict__ a,
-                                              const float* __restrict__ a2,
-                                              const float* __restrict__ b, float coef) {
-  if constexpr (SRC == SRC_PLAIN) return b[i] * a[i];
-  else if constexpr (SRC == SRC_RAW) return a[i];
-  else if constexpr (SRC == SRC_FISTA_Y) return b[i] * a[i];   // a = y^k, skipped once done
-  else return b[i] * (coef * a[i]);                             // SRC_SCALED
-}
-
-// Row <-> column addressing of the R2C/C2R helpers.  Row r of the real data maps
-// to the half-spectrum column layout X[col(r, q)]: col(r, q) = colbase(r) + q * qstride.
-struct RowCols {
-  int qstride;        // stride between consecutive q of one row
-  int per_blk;        // rows per block (my for the small kernels, nrows otherwise)
-  FastDiv f_blk;      // divides by per_blk
-  int blk_stride;     // offset between blocks (mzh*lsmy for the small kernels)
-  __device__ __forceinline__ int base(int r) const {
-    const int b = (int)f_blk.div((uint32_t)r);
-    return b * blk_stride + (r - b * per_blk);
-  }
-};
-
-// R2C along z of nrows real rows held as packed pairs Z[j][lsz] in *a (row 2j in
-// .x, row 2j+1 in .y): FFT each pair, then split into the half spectra written to
-// X[rc.base(row) + q * rc.qstride], q in [0, nz/2].  Returns the buffer holding X.
-__device__ float2* r2c_rows(float2* a, float2* b, const float2* twz, int nrows, int nz, int nzh,
-                            int npairs, const RowCols& rc, const FastDiv& f_nzh) {
-  const int lsz = pad_odd(nz);
-  float2* Z = fft_lines<-1>(a, b, twz, nz, npairs, lsz);
-  float2* X = (Z == a) ? b : a;
-  const int items = npairs * nzh;
-  for (int it = threadIdx.x; it < items; it += blockDim.x) {
-    const int j = (int)f_nzh.div((uint32_t)it), q = it - j * nzh;
-    const float2 zq = Z[j * lsz + q];
-    const float2 zm = Z[j * lsz + (q == 0 ? 0 : nz - q)];
-    // A = (Z(q) + conj Z(-q))/2 ; B = (Z(q) - conj Z(-q))/(2i)
-    X[rc.base(2 * j) + q * rc.qstride] = make_float2(0.5f * (zq.x + zm.x), 0.5f * (zq.y - zm.y));
-    if (2 * j + 1 < nrows)
-      X[rc.base(2 * j + 1) + q * rc.qstride] = make_float2(0.5f * (zq.y + zm.y), -0.5f * (zq.x - zm.x));
-  }
-  __syncthreads();
-  return X;
-}
-
-// C2R along z of the row pairs [j0, j1): half spectra X[rc.base(row) + q * rc.qstride] in *a
-// -> packed pairs Z[j - j0][lsz] (Z = A + iB with the Hermitian extension), inverse FFT.  The
-// imaginary parts of the q = 0 and q = nz/2 bins are dropped (they vanish for a Hermitian
-// input).  Returns the buffer holding the packed real rows.
-__device__ float2* c2r_rows_range(float2* a, float2* b, const float2* twz, int nrows, int nz, int j0, int j1,
-                                  const RowCols& rc, const FastDiv& f_nz) {
-  const int lsz = pad_odd(nz);
-  const int items = (j1 - j0) * nz;
-  for (int it = threadIdx.x; it < items; it += blockDim.x) {
-    const int jl = (int)f_nz.div((uint32_t)it), q = it - jl * nz;
-    const int j = j0 + jl;
-    const bool up = 2 * q > nz;
-    const int qq = up ? nz - q : q;
-    float2 x = a[rc.base(2 * j) + qq * rc.qstride];
-    float2 y = (2 * j + 1 < nrows) ? a[rc.base(2 * j + 1) + qq * rc.qstride] : make_float2(0.f, 0.f);
-    if (qq == 0 || 2 * qq == nz) { x.y = 0.f; y.y = 0.f; }
-    if (up) { x.y = -x.y; y.y = -y.y; }
-    b[jl * lsz + q] = make_float2(x.x - y.y, x.y + y.x);      // x + i y
-  }
-  return fft_lines<+1>(b, a, twz, nz, j1 - j0, lsz);
-}
-
-__device__ __forceinline__ RowCols plane_rowcols(const Geo& g) {
-  RowCols rc;
-  rc.qstride = g.lsy;
-  rc.per_blk = g.ny;
-  rc.f_blk = g.f_ny;
-  rc.blk_stride = 0;
-  return rc;
-}
-
-// Forward pass 1.  ps blocks per x-plane and component (vector model).  SRC_FISTA_Y
-// reads y^k of the volume (a ignored) and is skipped once the volume's solve is done.
-// LDS: tables (nz + ny) + two buffers of plane_lds complex.
-template <int SRC>
-__device__ __forceinline__ void plane_fwd_body(const VolDesc& vd, int lb, const float* __restrict__ a) {
-  const Geo& g = vd.g;
-  extern __shared__ float2 lds[];
-  const int pl = plane_lds(g);
-  float2* twz = lds;
-  float2* twy = twz + g.nz;
-  float2* P0 = twy + g.ny;
-  float2* P1 = P0 + pl;
-  // vector model: component comp of the plane is a workgroup of its own (components
-  // outermost; a raw source has one)
-  const int per_comp = g.ps * g.nx;
-  const int comp = (SRC == SRC_RAW) ? 0 : lb / per_comp;
-  lb -= comp * per_comp;
-  // ps workgroups per plane: all of them transform every row along z, workgroup h
-  // then takes the y-transforms of the columns qz in [q0, q1)
-  const int h = lb / g.nx;
-  const int x = plane_of_block(lb - h * g.nx, g.nx);
-  const int q0 = h * g.nzh / g.ps, q1 = (h + 1) * g.nzh / g.ps;
-  load_table(twz, vd.tw + vd.off[2], g.nz);
-  load_table(twy, vd.tw + vd.off[1], g.ny);
-  float c = 1.f;
-  if constexpr (SRC == SRC_SCALED) c = (float)vd.st->scale;
-  const long long pbase = (long long)x * g.ny * g.nz;
-  const int nyz = g.ny * g.nz;
-  const int lsz = pad_odd(g.nz);
-  float* Zf = reinterpret_cast<float*>(P0);
-  const float* __restrict__ b = vd.b + (long long)comp * g.N;
-  batched<8, float>(nyz, [&](int p) { return plane_source<SRC>(pbase + p, a, nullptr, b, c); },
-                    [&](int p, float v) {
-                      const int y = (int)g.f_nz.div((uint32_t)p), z = p - y * g.nz;
-                      Zf[2 * ((y >> 1) * lsz + z) + (y & 1)] = v;
-                    });
-  if (g.ny & 1) {
-    for (int z = threadIdx.x; z < g.nz; z += blockDim.x) Zf[2 * ((g.ny >> 1) * lsz + z) + 1] = 0.f;
-  }
-  const RowCols rc = plane_rowcols(g);
-  float2* X = r2c_rows(P0, P1, twz, g.ny, g.nz, g.nzh, g.npairs, rc, g.f_nzh);   // X[qz][lsy]
-  // column qz of the result at Y[(qz - q0) * lsy]
-  float2* Y = fft_lines<-1>(X + q0 * g.lsy, (X == P0 ? P1 : P0) + q0 * g.lsy, twy, g.ny, q1 - q0, g.lsy);
-  float2* dst = vd.uperm + (long long)comp * g.hsz + (long long)x * g.plane;
-  for (int e = threadIdx.x; e < g.plane; e += blockDim.x) {
-    const int cc = (int)g.f_nmem.div((uint32_t)e), m = e - cc * g.nmem;
-    const int cy = (int)g.f_mzh.div((uint32_t)cc), cz = cc - cy * g.mzh;
-    const int jy = (int)g.f_sz.div((uint32_t)m), jz = m - jy * g.sz;
-    const int qy = cy + jy * g.my, qz = cz + jz * g.mz;
-    const bool direct = 2 * qz <= g.nz;
-    const int col = direct ? qz : g.nz - qz;
-    if (col < q0 || col >= q1) continue;
-    float2 v;
-    if (direct) {
-      v = Y[(col - q0) * g.lsy + qy];
-    } else {
-      v = Y[(col - q0) * g.lsy + (qy == 0 ? 0 : g.ny - qy)];
-      v.y = -v.y;
-    }
-    dst[e] = v;
-  }
-}
-template <int SRC>
-static __global__ __launch_bounds__(1024) void k_plane_fwd(const VolDesc* __restrict__ vds, const float* __restrict__ a) {
-  const VolDesc& vd = vds[0];
-  if constexpr (SRC == SRC_FISTA_Y || SRC == SRC_SCALED) {
-    if (vd.st->done) return;
-  }
-  if constexpr (SRC == SRC_FISTA_Y) a = vd.y[vd.st->k & 1];
-  if constexpr (SRC == SRC_SCALED) {
-    if (!a) a = vd.rho[vd.st->k & 1];
-  }
-  plane_fwd_body<SRC>(vd, blockIdx.x, a);
-}
-
 // ============================================================================ pass 2: classes
 // E consecutive spectrum elements.
 template <int E>
@@ -367,12 +205,12 @@ struct HLoad {
     if constexpr (E % 2 == 0) {
 #pragma unroll
       for (int i = 0; i < E; i += 2) {
-        const float4 t = *reinterpret_cast<const float4*>(p + i);
+        const float4 t = ldg(reinterpret_cast<const float4*>(p + i));
         v[i] = make_float2(t.x, t.y); v[i + 1] = make_float2(t.z, t.w);
       }
     } else {
 #pragma unroll
-      for (int i = 0; i < E; ++i) v[i] = p[i];
+      for (int i = 0; i < E; ++i) v[i] = ldg(p + i);
     }
   }
 };
@@ -391,528 +229,26 @@ struct HLoad {
 // With padding the crop to the field of view sits between them and the pass stays.
 enum { FWD_G = 0, FWD_ADJ = 1, FWD_G_AND_ADJ = 2, FWD_RESID = 3 };
 
-// LDS layout of the class kernels: tables (nx + mx), U0/U1 (W lines of lsx, the
-// x-transforms of the W = cpw*nmem member columns), F0/F1 (K*cpw lines of mx).
-__host__ __device__ inline size_t class_lds_elems(const Geo& g) {
+// LDS of the class passes with cb components per round and line stride fls of the folded
+// spectra: tables (nx + mx), two buffers of cb * cpw * nmem x lines, two of K * cpw x' lines.
+__host__ __device__ inline size_t class_lds_elems(const Geo& g, int cb, int fls) {
   const size_t W = (size_t)g.cpw * g.nmem;
-  return (size_t)g.nx + g.mx + 2 * W * g.lsx + 2 * (size_t)g.K * g.cpw * g.mx;
+  return (size_t)g.nx + g.mx + 2 * cb * W * g.lsx + 2 * (size_t)g.K * g.cpw * fls;
 }
 
-// Harmonics of spectra prefetched ahead in the class kernels.
-constexpr int HPF = 4;
-
-// Position of class-layout element p of a (k, x'-block, class, x'-in-block) store,
-// p over K*cpw*mx, as offsets into F ((k*cpw + c)*mx + x') and G.
-__device__ __forceinline__ void class_g_index(const Geo& g, int p, int c0, int& fo, long long& go) {
-  const int k = (int)g.f_cpwmx.div((uint32_t)p), r = p - k * g.cpw * g.mx;
-  const int xbi = (int)g.f_cpwxb.div((uint32_t)r), r2 = r - xbi * g.cpw * g.xb;
-  const int c = (int)g.f_xb.div((uint32_t)r2), xi = r2 - c * g.xb;
-  const int nxb = g.mx / g.xb;
-  fo = (k * g.cpw + c) * g.mx + xbi * g.xb + xi;
-  go = (((long long)k * nxb + xbi) * g.ncls + c0 + c) * g.xb + xi;
-}
-
-// Forward pass 2 of one block (cpw classes).
-// VEC: vector model, vd.ncomp components (else one, and the loop folds away).
-// mode (FWD_*) selects where the decimated spectra go.
-template <int E, bool VEC = false>
-__device__ __forceinline__ void class_fwd_body(const VolDesc& vd, int lb, int mode) {
-  const Geo& g = vd.g;
-  extern __shared__ float2 lds[];
-  const int W = g.cpw * g.nmem;
-  float2* twx = lds;
-  float2* twm = twx + g.nx;
-  float2* U0 = twm + g.mx;
-  float2* U1 = U0 + W * g.lsx;
-  float2* F0 = U1 + W * g.lsx;
-  float2* F1 = F0 + g.K * g.cpw * g.mx;
-  const int c0 = lb * g.cpw;
-  const bool act = (int)threadIdx.x < vd.T_class;
-  // this thread's E spectrum elements: all share class cl and folded frequency qxp
-  const int e0 = act ? (int)threadIdx.x * E : 0;
-  const int per_cls = g.mx * g.S;
-  const int cl = (int)g.f_mxS.div((uint32_t)e0);
-  const int rem = e0 - cl * per_cls;
-  const int qxp = (int)g.f_S.div((uint32_t)rem);
-  const int within = rem - qxp * g.S;
-  const void* hs = vd.hs;
-  const int LG = g.S / E;
-  // vector model: the products of every component accumulate in F0 before the one
-  // inverse transform (the sum over i commutes with it)
-  const int ncomp = VEC ? vd.ncomp : 1;
-  uint32_t before = 0;   // harmonics some earlier component has written to F0
-  for (int comp = 0; comp < ncomp; ++comp) {
-  if (comp) __syncthreads();   // the previous component's U is still being read
-  const uint32_t pm = VEC ? vd.cmask[comp] : ~0u;
-  const long long hoff0 = (long long)c0 * per_cls + e0 + comp * vd.hs_cstride;
-  // spectra do not depend on the data: start streaming them first
-  HLoad<E> hb[HPF];
-#pragma unroll
-  for (int i = 0; i < HPF; ++i)
-    if (act && i < g.K && ((pm >> i) & 1u)) hb[i].load(hs, (long long)i * g.hsz + hoff0);
-  if (comp == 0) {
-    load_table(twx, vd.tw + vd.off[0], g.nx);
-    load_table(twm, vd.tw + vd.off[3], g.mx);
-  }
-  const float2* __restrict__ uperm = vd.uperm + (long long)comp * g.hsz;
-  batched<8, float2>(g.nx * W,
-                     [&](int p) {
-                       const int xx = (int)g.f_W.div((uint32_t)p), e = p - xx * W;
-                       return uperm[(long long)xx * g.plane + (long long)c0 * g.nmem + e];
-                     },
-                     [&](int p, float2 v) {
-                       const int xx = (int)g.f_W.div((uint32_t)p), e = p - xx * W;
-                       U0[e * g.lsx + xx] = v;
-                     });
-  const float2* U = fft_lines<-1>(U0, U1, twx, g.nx, W, g.lsx);
-  float2 ur[E];
-#pragma unroll
-  for (int i = 0; i < E; ++i) {
-    const int w = within + i;
-    const int jx = (int)g.f_nmem.div((uint32_t)w), m = w - jx * g.nmem;
-    ur[i] = act ? U[(cl * g.nmem + m) * g.lsx + qxp + jx * g.mx] : make_float2(0.f, 0.f);
-  }
-  for (int k0 = 0; k0 < g.K; k0 += HPF) {
-#pragma unroll
-    for (int i = 0; i < HPF; ++i) {
-      const int k = k0 + i;
-      if (k < g.K) {
-        // pk is the same for the whole block (it depends on k and the component only)
-        const bool pk = ((pm >> k) & 1u) != 0;
-        float2 acc = make_float2(0.f, 0.f);
-        if (act) {
-          if (pk) {
-#pragma unroll
-            for (int t = 0; t < E; ++t) acc = cadd(acc, cmul(hb[i].v[t], ur[t]));
-          }
-          if (k + HPF < g.K && ((pm >> (k + HPF)) & 1u)) hb[i].load(hs, (long long)(k + HPF) * g.hsz + hoff0);
-        }
-        if (pk) {
-          for (int o = LG >> 1; o >= 1; o >>= 1) {
-            acc.x += __shfl_xor(acc.x, o, 64);
-            acc.y += __shfl_xor(acc.y, o, 64);
-          }
-          if (act && (threadIdx.x & (LG - 1)) == 0) {
-            float2& f = F0[(k * g.cpw + cl) * g.mx + qxp];
-            f = ((before >> k) & 1u) ? cadd(f, acc) : acc;
-          }
-        }
-      }
-    }
-  }
-  before |= pm;
-  }
-  const float2* F = fft_lines<+1>(F0, F1, twm, g.mx, g.K * g.cpw, g.mx);
-  float2* __restrict__ G = vd.G;
-  float2* __restrict__ Gp = vd.Gp;
-  // the small-grid transforms are unnormalised: their round trip scales by my mz
-  const float syz = (float)(g.my * g.mz);
-  for (int p = threadIdx.x; p < g.K * g.cpw * g.mx; p += blockDim.x) {
-    int fo;
-    long long go;
-    class_g_index(g, p, c0, fo, go);
-    const float2 f = F[fo];
-    if (mode == FWD_G || mode == FWD_G_AND_ADJ) G[go] = f;
-    if (mode == FWD_ADJ || mode == FWD_G_AND_ADJ) Gp[go] = make_float2(syz * f.x, syz * f.y);
-    if (mode == FWD_RESID) {
-      const float2 dh = G[go];
-      Gp[go] = make_float2(syz * f.x - dh.x, syz * f.y - dh.y);
-    }
-  }
-}
-
-// Adjoint pass 2 of one block.
-template <int E, bool VEC = false>
-__device__ __forceinline__ void class_adj_body(const VolDesc& vd, int lb) {
-  const Geo& g = vd.g;
-  extern __shared__ float2 lds[];
-  const int W = g.cpw * g.nmem;
-  float2* twx = lds;
-  float2* twm = twx + g.nx;
-  float2* U0 = twm + g.mx;
-  float2* U1 = U0 + W * g.lsx;
-  float2* F0 = U1 + W * g.lsx;
-  float2* F1 = F0 + g.K * g.cpw * g.mx;
-  const int c0 = lb * g.cpw;
-  const bool act = (int)threadIdx.x < vd.T_class;
-  const int e0 = act ? (int)threadIdx.x * E : 0;
-  const int per_cls = g.mx * g.S;
-  const int cl = (int)g.f_mxS.div((uint32_t)e0);
-  const int rem = e0 - cl * per_cls;
-  const int qxp = (int)g.f_S.div((uint32_t)rem);
-  const int within = rem - qxp * g.S;
-  const void* hs = vd.hs;
-  HLoad<E> hb[HPF];
-  const uint32_t pm0 = VEC ? vd.cmask[0] : ~0u;
-#pragma unroll
-  for (int i = 0; i < HPF; ++i)
-    if (act && i < g.K && ((pm0 >> i) & 1u)) hb[i].load(hs, (long long)i * g.hsz + (long long)c0 * per_cls + e0);
-  load_table(twx, vd.tw + vd.off[0], g.nx);
-  load_table(twm, vd.tw + vd.off[3], g.mx);
-  const float2* __restrict__ Gp = vd.Gp;
-  batched<8, float2>(g.K * g.cpw * g.mx,
-                     [&](int p) {
-                       int fo;
-                       long long go;
-                       class_g_index(g, p, c0, fo, go);
-                       return Gp[go];
-                     },
-                     [&](int p, float2 v) {
-                       int fo;
-                       long long go;
-                       class_g_index(g, p, c0, fo, go);
-                       F0[fo] = v;
-                     });
-  const float2* F = fft_lines<-1>(F0, F1, twm, g.mx, g.K * g.cpw, g.mx);
-  // vector model: H_{k,i}^T of every component i from the one transform of the data
-  const int ncomp = VEC ? vd.ncomp : 1;
-  for (int comp = 0; comp < ncomp; ++comp) {
-  const long long hoff0 = (long long)c0 * per_cls + e0 + comp * vd.hs_cstride;
-  const uint32_t pm = VEC ? vd.cmask[comp] : ~0u;
-  if (comp) {
-    __syncthreads();   // the previous component's store still reads U0/U1
-#pragma unroll
-    for (int i = 0; i < HPF; ++i)
-      if (act && i < g.K && ((pm >> i) & 1u)) hb[i].load(hs, (long long)i * g.hsz + hoff0);
-  }
-  float2 acc[E];
-#pragma unroll
-  for (int t = 0; t < E; ++t) acc[t] = make_float2(0.f, 0.f);
-  for (int k0 = 0; k0 < g.K; k0 += HPF) {
-#pragma unroll
-    for (int i = 0; i < HPF; ++i) {
-      const int k = k0 + i;
-      if (act && k < g.K) {
-        if ((pm >> k) & 1u) {
-          float2 R = F[(k * g.cpw + cl) * g.mx + qxp];
-#pragma unroll
-          for (int t = 0; t < E; ++t) acc[t] = cadd(acc[t], cmulcj(hb[i].v[t], R));
-        }
-        if (k + HPF < g.K && ((pm >> (k + HPF)) & 1u)) hb[i].load(hs, (long long)(k + HPF) * g.hsz + hoff0);
-      }
-    }
-  }
-  // every element of the group is written exactly once
-  if (act) {
-#pragma unroll
-    for (int t = 0; t < E; ++t) {
-      const int w = within + t;
-      const int jx = (int)g.f_nmem.div((uint32_t)w), m = w - jx * g.nmem;
-      U0[(cl * g.nmem + m) * g.lsx + qxp + jx * g.mx] = acc[t];
-    }
-  }
-  const float2* V = fft_lines<+1>(U0, U1, twx, g.nx, W, g.lsx);
-  float2* __restrict__ vperm = vd.uperm + (long long)comp * g.hsz;
-  for (int p = threadIdx.x; p < g.nx * W; p += blockDim.x) {
-    const int xx = (int)g.f_W.div((uint32_t)p), e = p - xx * W;
-    vperm[(long long)xx * g.plane + (long long)c0 * g.nmem + e] = V[e * g.lsx + xx];
-  }
-  }
-}
-
-// Forward and adjoint class passes in one (scalar model, no boundary padding), for the
-// solver's updates, the normal operator and A then A^T.  The folded spectra Fhat_k of
-// the block's classes (class_fwd_body's F0, before its inverse x' transform) stay in
-// LDS, and the adjoint starts from them: the inverse x' transform, the small-grid
-// inverse and forward transforms and the forward x' transform between the two passes
-// compose to multiplication by M = mx my mz (up to rounding), so the adjoint's decimated
-// spectra are
-//   NRM_RESID  R_k = M Fhat_k - Dt_k, Dt = the x' transform of the measured portraits'
-//              small-grid spectra (COL_DATA of sep.hpp, in G' as [k][class][qx'])
-//   NRM_PLAIN  R_k = M Fhat_k                       (normal operator)
-//   NRM_STORE  R_k = M Fhat_k, and G = the inverse x' transform of Fhat (the small-grid
-//              pass turns it into the portraits)
-// Each spectrum Hhat_k is read from HBM once: with K at most the prefetch ring's depth the
-// ring still holds all of them for the adjoint, else the adjoint's second read is of the
-// block's own recently read spectra (L2).
+// Destinations of the fused class (or column) pass: see user.hpp and sep.hpp.
 enum { NRM_RESID = 0, NRM_PLAIN = 1, NRM_STORE = 2 };
-
-template <int E>
-__device__ __forceinline__ void class_normal_body(const VolDesc& vd, int lb, int mode) {
-  const Geo& g = vd.g;
-  extern __shared__ float2 lds[];
-  const int W = g.cpw * g.nmem;
-  float2* twx = lds;
-  float2* twm = twx + g.nx;
-  float2* U0 = twm + g.mx;
-  float2* U1 = U0 + W * g.lsx;
-  float2* F0 = U1 + W * g.lsx;
-  float2* F1 = F0 + g.K * g.cpw * g.mx;
-  const int c0 = lb * g.cpw;
-  const bool act = (int)threadIdx.x < vd.T_class;
-  const int e0 = act ? (int)threadIdx.x * E : 0;
-  const int per_cls = g.mx * g.S;
-  const int cl = (int)g.f_mxS.div((uint32_t)e0);
-  const int rem = e0 - cl * per_cls;
-  const int qxp = (int)g.f_S.div((uint32_t)rem);
-  const int within = rem - qxp * g.S;
-  const long long hoff0 = (long long)c0 * per_cls + e0;
-  const void* hs = vd.hs;
-  const int LG = g.S / E;
-  const int KCM = g.K * g.cpw * g.mx;
-  HLoad<E> hb[HPF];
-#pragma unroll
-  for (int i = 0; i < HPF; ++i)
-    if (act && i < g.K) hb[i].load(hs, (long long)i * g.hsz + hoff0);
-  // the data term of the block's classes (F1[(k cpw + c) mx + qx'])
-  if (mode == NRM_RESID) {
-    const float2* __restrict__ Dt = vd.Gp;
-    batched<8, float2>(KCM,
-                       [&](int p) {
-                         const int k = (int)g.f_cpwmx.div((uint32_t)p), r = p - k * g.cpw * g.mx;
-                         const int c = r / g.mx, q = r - c * g.mx;
-                         return Dt[((long long)k * g.ncls + c0 + c) * g.mx + q];
-                       },
-                       [&](int p, float2 v) { F1[p] = v; });
-  }
-  load_table(twx, vd.tw + vd.off[0], g.nx);
-  load_table(twm, vd.tw + vd.off[3], g.mx);
-  const float2* __restrict__ uperm = vd.uperm;
-  batched<8, float2>(g.nx * W,
-                     [&](int p) {
-                       const int xx = (int)g.f_W.div((uint32_t)p), e = p - xx * W;
-                       return uperm[(long long)xx * g.plane + (long long)c0 * g.nmem + e];
-                     },
-                     [&](int p, float2 v) {
-                       const int xx = (int)g.f_W.div((uint32_t)p), e = p - xx * W;
-                       U0[e * g.lsx + xx] = v;
-                     });
-  const float2* U = fft_lines<-1>(U0, U1, twx, g.nx, W, g.lsx);
-  float2 ur[E];
-#pragma unroll
-  for (int i = 0; i < E; ++i) {
-    const int w = within + i;
-    const int jx = (int)g.f_nmem.div((uint32_t)w), m = w - jx * g.nmem;
-    ur[i] = act ? U[(cl * g.nmem + m) * g.lsx + qxp + jx * g.mx] : make_float2(0.f, 0.f);
-  }
-  // forward: Fhat_k(cl, qx') = sum over the S alias members of Hhat_k U
-  for (int k0 = 0; k0 < g.K; k0 += HPF) {
-#pragma unroll
-    for (int i = 0; i < HPF; ++i) {
-      const int k = k0 + i;
-      if (k < g.K) {
-        float2 acc = make_float2(0.f, 0.f);
-        if (act) {
-#pragma unroll
-          for (int t = 0; t < E; ++t) acc = cadd(acc, cmul(hb[i].v[t], ur[t]));
-          if (k + HPF < g.K) hb[i].load(hs, (long long)(k + HPF) * g.hsz + hoff0);
-        }
-        for (int o = LG >> 1; o >= 1; o >>= 1) {
-          acc.x += __shfl_xor(acc.x, o, 64);
-          acc.y += __shfl_xor(acc.y, o, 64);
-        }
-        if (act && (threadIdx.x & (LG - 1)) == 0) F0[(k * g.cpw + cl) * g.mx + qxp] = acc;
-      }
-    }
-  }
-  __syncthreads();   // Fhat complete; U0/U1 free for the adjoint
-  // adjoint: sum_k conj(Hhat_k) R_k for each alias member, then the inverse x transform.
-  // With K <= HPF the ring still holds every harmonic's spectra.
-  if (g.K > HPF) {
-#pragma unroll
-    for (int i = 0; i < HPF; ++i)
-      if (act) hb[i].load(hs, (long long)i * g.hsz + hoff0);
-  }
-  const float Mf = (float)g.M;
-  float2 acc[E];
-#pragma unroll
-  for (int t = 0; t < E; ++t) acc[t] = make_float2(0.f, 0.f);
-  for (int k0 = 0; k0 < g.K; k0 += HPF) {
-#pragma unroll
-    for (int i = 0; i < HPF; ++i) {
-      const int k = k0 + i;
-      if (act && k < g.K) {
-        const int fi = (k * g.cpw + cl) * g.mx + qxp;
-        const float2 f = F0[fi];
-        float2 R = make_float2(Mf * f.x, Mf * f.y);
-        if (mode == NRM_RESID) R = csub(R, F1[fi]);
-#pragma unroll
-        for (int t = 0; t < E; ++t) acc[t] = cadd(acc[t], cmulcj(hb[i].v[t], R));
-        if (k + HPF < g.K) hb[i].load(hs, (long long)(k + HPF) * g.hsz + hoff0);
-      }
-    }
-  }
-  if (act) {
-#pragma unroll
-    for (int t = 0; t < E; ++t) {
-      const int w = within + t;
-      const int jx = (int)g.f_nmem.div((uint32_t)w), m = w - jx * g.nmem;
-      U0[(cl * g.nmem + m) * g.lsx + qxp + jx * g.mx] = acc[t];
-    }
-  }
-  const float2* V = fft_lines<+1>(U0, U1, twx, g.nx, W, g.lsx);
-  float2* __restrict__ vperm = vd.uperm;
-  for (int p = threadIdx.x; p < g.nx * W; p += blockDim.x) {
-    const int xx = (int)g.f_W.div((uint32_t)p), e = p - xx * W;
-    vperm[(long long)xx * g.plane + (long long)c0 * g.nmem + e] = V[e * g.lsx + xx];
-  }
-  if (mode == NRM_STORE) {
-    // the portraits' small-grid spectra, as class_fwd_body writes them (F0 still holds
-    // Fhat: the adjoint only read it)
-    const float2* F = fft_lines<+1>(F0, F1, twm, g.mx, g.K * g.cpw, g.mx);
-    float2* __restrict__ G = vd.G;
-    for (int p = threadIdx.x; p < KCM; p += blockDim.x) {
-      int fo;
-      long long go;
-      class_g_index(g, p, c0, fo, go);
-      G[go] = F[fo];
-    }
-  }
-}
-
-// Single-volume class passes, grid = ncls/cpw blocks of T_class threads.
-// check_done skips the launch once the volume's solve is done.
-// XCD-aware: consecutive class blocks run on one XCD, so the short runs of G, G' and
-// the class-layout spectra that neighbouring blocks share are fetched into one L2.
-template <int E, bool VEC>
-static __global__ __launch_bounds__(1024) void k_class_fwd(const VolDesc* __restrict__ vds, int check_done, int mode) {
-  const VolDesc& vd = vds[0];
-  const int lb = blockIdx.x;
-  if (check_done && vd.st->done) return;
-  class_fwd_body<E, VEC>(vd, plane_of_block(lb, gridDim.x), mode);
-}
-template <int E>
-static __global__ __launch_bounds__(1024) void k_class_normal(const VolDesc* __restrict__ vds, int check_done, int mode) {
-  const VolDesc& vd = vds[0];
-  const int lb = blockIdx.x;
-  if (check_done && vd.st->done) return;
-  class_normal_body<E>(vd, plane_of_block(lb, gridDim.x), mode);
-}
-template <int E, bool VEC>
-static __global__ __launch_bounds__(1024) void k_class_adj(const VolDesc* __restrict__ vds, int check_done) {
-  const VolDesc& vd = vds[0];
-  const int lb = blockIdx.x;
-  if (check_done && vd.st->done) return;
-  class_adj_body<E, VEC>(vd, plane_of_block(lb, gridDim.x));
-}
 
 // ============================================================================ pass 3: small grid
 enum { EPI_STORE = 0, EPI_RESID = 1, EPI_RESID_BACK = 2, EPI_BACK = 3, EPI_STORE_BACK = 4 };
 
 // ============================================================================ pass 1 adjoint
-enum { OUT_SCALE_B = 0, OUT_U = 1, OUT_STEP_NORMAL = 2, OUT_STEP_FISTA = 3 };
+enum { OUT_SCALE_B = 0, OUT_STEP_NORMAL = 2, OUT_STEP_FISTA = 3 };
 enum { UPD_NORMAL = 1, UPD_FISTA = 2 };
 
 struct AdjOut {
   float* out;              // OUT_SCALE_B / UPD_NORMAL: result (UPD_NORMAL: NULL -> rho[(k+1) & 1])
   const float* yin;        // UPD_NORMAL: w_{t-1} (v = scale * w_{t-1}); NULL -> rho[k & 1]
-};
-
-// The 13 values of one voxel's regulariser stencil and the values its update reads.
-struct StencilVals {
-  float c, zm2, zm1, zp1, zp2, ym2, ym1, yp1, yp2, xm2, xm1, xp1, xp2, u, rk;
-  bool shell;              // on the boundary prior's shell
-};
-
-// The voxel-wise end of a solver step, after the adjoint left u = b . v (the A^T A part):
-//   UPD_NORMAL  out = u + lam T^T T (s w_prev); FP64 <s w_prev, out>, ||out||^2
-//               (power iteration: lmax, next scale 1/||out||)
-//   UPD_FISTA   g = u + lam T^T T y^k; rho^{k+1} = max(y^k - tau g, 0);
-//               y^{k+1} = rho^{k+1} + k/(k+3) (rho^{k+1} - rho^k);
-//               FP64 ||rho^{k+1} - y^k||^2, ||rho^{k+1}||^2, count of non-finite g
-// T^T T is the periodic 13-point stencil sum_a (v[+2] - 4v[+1] + 6v - 4v[-1] + v[-2])
-// of stacked second differences (reg_kind 1: T = I); neighbours are read from global
-// memory (cache resident).  Used by k_vol_update and by the adjoint plane pass that
-// finishes the step itself (OUT_STEP_*).
-template <int UPD>
-struct StepCtx {
-  const Geo& g;
-  const float* __restrict__ yv;
-  const float* __restrict__ rk;
-  float* __restrict__ out;       // UPD_NORMAL
-  float* __restrict__ rho_next;  // UPD_FISTA
-  float* __restrict__ y_next;
-  float s, lam, alpha, tau, beta1;
-  bool stencil;
-  int aw;
-  long long pl;
-  __device__ StepCtx(const VolDesc& vd, const AdjOut& ao) : g(vd.g) {
-    const int kk = vd.st->k;
-    yv = (UPD == UPD_NORMAL) ? (ao.yin ? ao.yin : vd.rho[kk & 1]) : vd.y[kk & 1];
-    rk = vd.rho[kk & 1];
-    out = (UPD == UPD_NORMAL) ? (ao.out ? ao.out : vd.rho[(kk + 1) & 1]) : nullptr;
-    rho_next = vd.rho[(kk + 1) & 1];
-    y_next = vd.y[(kk + 1) & 1];
-    s = (UPD == UPD_NORMAL) ? (float)vd.st->scale : 1.f;
-    lam = vd.lam;
-    alpha = vd.alpha;
-    tau = (float)vd.st->tau;
-    beta1 = (float)((double)kk / (kk + 3.0));      // (k+1-1)/(k+1+2)
-    stencil = vd.reg_kind == 0;
-    aw = vd.aw;
-    pl = (long long)g.ny * g.nz;
-  }
-  __device__ __forceinline__ StencilVals load(long long i, float u) const {
-    StencilVals v;
-    v.c = yv[i];
-    v.u = u;
-    v.rk = (UPD == UPD_FISTA) ? rk[i] : 0.f;
-    v.shell = false;
-    if (stencil || alpha > 0.f) {
-      const uint32_t r = g.f_nz.div((uint32_t)i);
-      const int z = (int)((uint32_t)i - r * (uint32_t)g.nz);
-      const int y = (int)g.f_ny.mod(r), x = (int)g.f_ny.div(r);
-      // a 2D grid's projection axis (ny = 1) has no faces
-      v.shell = x < aw || x >= g.nx - aw || (g.ny > 1 && (y < aw || y >= g.ny - aw)) || z < aw || z >= g.nz - aw;
-      if (!stencil) return v;
-      const long long row = i - z;
-      // periodic neighbours (every axis is >= 4 long, so one wrap suffices, except the
-      // projection axis of a 2D grid: length 1, every neighbour is the voxel itself and
-      // its second differences vanish)
-      auto wz = [&](int d) { int q = z + d; q += q < 0 ? g.nz : 0; q -= q >= g.nz ? g.nz : 0; return yv[row + q]; };
-      auto wy = [&](int d) {
-        if (g.ny == 1) return v.c;
-        int q = y + d; q += q < 0 ? g.ny : 0; q -= q >= g.ny ? g.ny : 0;
-        return yv[i + (long long)(q - y) * g.nz];
-      };
-      auto wx = [&](int d) {
-        int q = x + d; q += q < 0 ? g.nx : 0; q -= q >= g.nx ? g.nx : 0;
-        return yv[i + (long long)(q - x) * pl];
-      };
-      v.zm2 = wz(-2); v.zm1 = wz(-1); v.zp1 = wz(1); v.zp2 = wz(2);
-      v.ym2 = wy(-2); v.ym1 = wy(-1); v.yp1 = wy(1); v.yp2 = wy(2);
-      v.xm2 = wx(-2); v.xm1 = wx(-1); v.xp1 = wx(1); v.xp2 = wx(2);
-    }
-    return v;
-  }
-  // T^T T (s y) + alpha P_alpha^T P_alpha (s y).  No contraction into fused
-  // multiply-adds here or in apply: the two kernels that inline these functions then
-  // round every operation alike and finish a step bitwise identically.
-  __device__ __forceinline__ float reg(const StencilVals& v) const {
-#pragma clang fp contract(off)
-    float t;
-    if (!stencil) {
-      t = s * v.c;
-    } else {
-      t = 18.f * (s * v.c);
-      t += s * (v.zp2 + v.zm2) - 4.f * s * (v.zp1 + v.zm1);
-      t += s * (v.yp2 + v.ym2) - 4.f * s * (v.yp1 + v.ym1);
-      t += s * (v.xp2 + v.xm2) - 4.f * s * (v.xp1 + v.xm1);
-    }
-    if (alpha > 0.f && v.shell) t += alpha * (s * v.c);
-    return t;
-  }
-  static constexpr int NV = UPD == UPD_NORMAL ? 2 : 3;
-  // the update of voxel i and its terms of the FP64 sums
-  __device__ __forceinline__ void apply(long long i, const StencilVals& v, double* acc) const {
-#pragma clang fp contract(off)
-    if constexpr (UPD == UPD_NORMAL) {
-      const float o = v.u + lam * reg(v);
-      out[i] = o;
-      acc[0] += (double)(s * v.c) * (double)o;
-      acc[1] += (double)o * (double)o;
-    } else {
-      const float yk = v.c;
-      const float gr = v.u + lam * reg(v);
-      const float rn = fmaxf(yk - tau * gr, 0.f);
-      rho_next[i] = rn;
-      y_next[i] = rn + beta1 * (rn - v.rk);
-      const double dd = (double)rn - (double)yk;
-      acc[0] += dd * dd;
-      acc[1] += (double)rn * (double)rn;
-      if (!isfinite(gr) || !isfinite(yk)) acc[2] += 1.0;   // max(NaN, 0) would hide it
-    }
-  }
 };
 
 // The block's FP64 sums into vd.partials[NV * lb ...] (k_vol_finish reduces them).
@@ -961,174 +297,7 @@ __device__ __forceinline__ bool grid_reduce_last(double* v, double* partials, De
   return threadIdx.x == 0;
 }
 
-// Adjoint pass 1: gather the class layout into a half plane, inverse y FFT, C2R
-// along z, times the sensitivity:
-//   OUT_SCALE_B      ao.out = b . v                          (A^T)
-//   OUT_U            vd.u = b . v  (the A^T A part of a solver step; skipped once the
-//                    volume's solve is done; k_vol_update finishes the step)
-//   OUT_STEP_NORMAL  the step itself on the block's voxels with u = b . v (StepCtx),
-//   OUT_STEP_FISTA   its FP64 sums in vd.partials[lb] for k_vol_finish (scalar model:
-//                    one component)
-// grid = ps * nx blocks (ps per x-plane); lb = the block's index among them.
-template <int OUT>
-__device__ __forceinline__ void plane_adj_body(const VolDesc& vd, int lb, const AdjOut& ao) {
-  const Geo& g = vd.g;
-  constexpr bool kStep = (OUT == OUT_STEP_NORMAL || OUT == OUT_STEP_FISTA);
-  if constexpr (OUT == OUT_U || kStep) {
-    if (vd.st->done) return;
-  }
-  extern __shared__ float2 lds[];
-  const int pl = plane_lds(g);
-  float2* twz = lds;
-  float2* twy = twz + g.nz;
-  float2* P0 = twy + g.ny;
-  float2* P1 = P0 + pl;
-  load_table(twz, vd.tw + vd.off[2], g.nz);
-  load_table(twy, vd.tw + vd.off[1], g.ny);
-  // ps workgroups per plane: all of them transform every column along y, workgroup h
-  // then takes the z-transforms of the row pairs [j0, j1)
-  const int h = lb / g.nx;
-  const int x = plane_of_block(lb - h * g.nx, g.nx);
-  const int j0 = h * g.npairs / g.ps, j1 = (h + 1) * g.npairs / g.ps;
-  // vector model: out = sum_i b_i . v_i, the components added in order by the thread
-  // that owns the voxel (a plane workgroup fills its CU, so components in workgroups of
-  // their own would only queue behind each other)
-  for (int comp = 0; comp < vd.ncomp; ++comp) {
-  if (comp) __syncthreads();   // the previous component's store still reads the LDS planes
-  const float2* src = vd.uperm + (long long)comp * g.hsz + (long long)x * g.plane;
-  batched<8, float2>(g.plane, [&](int e) { return src[e]; }, [&](int e, float2 v) { P1[e] = v; });
-  __syncthreads();
-  for (int p = threadIdx.x; p < g.ny * g.nzh; p += blockDim.x) {
-    const int qz = (int)g.f_ny.div((uint32_t)p), qy = p - qz * g.ny;
-    bool cj;
-    const int e = class_index_of(g, qy, qz, cj);
-    const float2 v = P1[e];
-    P0[qz * g.lsy + qy] = cj ? make_float2(v.x, -v.y) : v;
-  }
-  float2* X = fft_lines<+1>(P0, P1, twy, g.ny, g.nzh, g.lsy);
-  float2* Z = c2r_rows_range(X, X == P0 ? P1 : P0, twz, g.ny, g.nz, j0, j1, plane_rowcols(g), g.f_nz);
-  const int lsz = pad_odd(g.nz);
-  const float* Xf = reinterpret_cast<const float*>(Z);
-  // rows [2 j0, min(2 j1, ny)) of the plane; row y is in line (y >> 1) - j0
-  const int y0 = 2 * j0, y1 = 2 * j1 < g.ny ? 2 * j1 : g.ny;
-  auto vidx = [&](int p) {
-    const int y = (int)g.f_nz.div((uint32_t)p), z = p - y * g.nz;
-    return 2 * (((y >> 1) - j0) * lsz + z) + (y & 1);
-  };
-  const float* __restrict__ b = vd.b + (long long)comp * g.N;
-  const long long pbase = (long long)x * g.ny * g.nz + (long long)y0 * g.nz;
-  if constexpr (kStep) {
-    // u = b . v of the block's voxels stays in registers: the step reads it there
-    constexpr int UPD = OUT == OUT_STEP_NORMAL ? UPD_NORMAL : UPD_FISTA;
-    constexpr int NV = StepCtx<UPD>::NV;
-    __shared__ double red[64];
-    const StepCtx<UPD> ctx(vd, ao);
-    double acc[NV];
-#pragma unroll
-    for (int j = 0; j < NV; ++j) acc[j] = 0.0;
-    const int n = (y1 - y0) * g.nz;
-    // voxels whose loads are in flight together (half a 96 x 64 plane over 1024 threads
-    // is one round; 3 measured 1.7 % faster per update than 2 at 96 x 96 x 64)
-    constexpr int U = 3;
-    for (int p = threadIdx.x; p < n; p += U * (int)blockDim.x) {
-      StencilVals v[U];
-#pragma unroll
-      for (int q = 0; q < U; ++q) {
-        const int pq = p + q * (int)blockDim.x;
-        // a rounded product, as the stored u that k_vol_update reads (no contraction
-        // into the step's sums), so both ways of finishing a step agree bitwise
-        if (pq < n) v[q] = ctx.load(pbase + pq, __fmul_rn(b[pbase + pq], Xf[vidx(pq + y0 * g.nz)]));
-      }
-#pragma unroll
-      for (int q = 0; q < U; ++q) {
-        const int pq = p + q * (int)blockDim.x;
-        if (pq < n) ctx.apply(pbase + pq, v[q], acc);
-      }
-    }
-    store_step_partials<NV>(vd, acc, red, lb);
-    return;
-  }
-  float* __restrict__ out = (OUT == OUT_U) ? vd.u : ao.out;
-  if (comp == 0) {
-    batched<8, float>((y1 - y0) * g.nz, [&](int p) { return b[pbase + p]; },
-                      [&](int p, float bv) { out[pbase + p] = bv * Xf[vidx(p + y0 * g.nz)]; });
-  } else {
-    batched<8, float>((y1 - y0) * g.nz, [&](int p) { return b[pbase + p]; },
-                      [&](int p, float bv) { out[pbase + p] += bv * Xf[vidx(p + y0 * g.nz)]; });
-  }
-  }
-}
-template <int OUT>
-static __global__ __launch_bounds__(1024) void k_plane_adj(const VolDesc* __restrict__ vds, AdjOut ao) {
-  plane_adj_body<OUT>(vds[0], blockIdx.x, ao);
-}
-
-// A solver update's adjoint plane pass and step (OUT_STEP_FISTA), then, in the same
-// workgroup, the next update's forward plane pass on the y^{k+1} the step just wrote
-// (u = b . y^{k+1}, as k_plane_fwd<SRC_FISTA_Y> forms it): a plane's forward pass needs
-// only that plane's y, so with one workgroup per x-plane (ps = 1) no other block is
-// awaited, and the next update starts at its class pass.  If this step ends the solve,
-// the extra forward pass is unused.  grid = nx blocks (ps must be 1).
-static __global__ __launch_bounds__(1024) void k_step_and_fwd(const VolDesc* __restrict__ vds, AdjOut ao) {
-  const VolDesc& vd = vds[0];
-  const int lb = blockIdx.x;
-  if (vd.st->done) return;
-  const float* ynext = vd.y[(vd.st->k + 1) & 1];
-  plane_adj_body<OUT_STEP_FISTA>(vd, lb, ao);
-  __syncthreads();   // the block's stores of y^{k+1} are visible to it; the LDS is free
-  plane_fwd_body<SRC_PLAIN>(vd, lb, ynext);
-}
-
-// Blocks of the volume-wide update pass, each a contiguous run of whole UPD_THREADS-voxel
-// tiles: about 2048 voxels per block, at most 256 blocks per volume (their FP64
-// partials are summed by k_vol_finish).  512 threads let two blocks share a CU, which
-// matters when a batch launches thousands of them.
-constexpr int UPD_THREADS = 512;
-__host__ __device__ inline int update_blocks(long long n) {
-  long long b = (n + 2047) / 2048;
-  return (int)(b < 1 ? 1 : (b > 256 ? 256 : b));
-}
-
-// Finishes a solver step after k_plane_adj<OUT_U> left u = b . v (see StepCtx).  Each
-// block leaves its FP64 sums in vd.partials; k_vol_finish reduces them and updates the
-// state.  grid = vd.nb_upd blocks of UPD_THREADS threads per volume.
-template <int UPD>
-static __global__ __launch_bounds__(UPD_THREADS) void k_vol_update(const VolDesc* __restrict__ vds, AdjOut ao) {
-  const VolDesc& vd = vds[0];
-  const int lb = blockIdx.x;
-  const Geo& g = vd.g;
-  if (vd.st->done) return;
-  __shared__ double red[64];
-  const StepCtx<UPD> ctx(vd, ao);
-  const float* __restrict__ u = vd.u;
-  const long long N = g.N;
-  const int nb = vd.nb_upd;
-  constexpr int T = UPD_THREADS;
-  const long long chunk = ((N + nb - 1) / nb + T - 1) / T * T;
-  // XCD-aware: blocks of one XCD take consecutive chunks (the planes k_plane_adj
-  // wrote on that XCD, and their x-neighbours)
-  const long long i0 = (long long)plane_of_block(lb, nb) * chunk;
-  const long long i1 = i0 + chunk < N ? i0 + chunk : N;
-  constexpr int U = 4;
-  constexpr int NV = StepCtx<UPD>::NV;
-  double acc[NV];
-#pragma unroll
-  for (int j = 0; j < NV; ++j) acc[j] = 0.0;
-  for (long long i = i0 + threadIdx.x; i < i1; i += U * T) {
-    StencilVals v[U];
-#pragma unroll
-    for (int q = 0; q < U; ++q)
-      if (i + q * T < i1) v[q] = ctx.load(i + q * T, u[i + q * T]);
-#pragma unroll
-    for (int q = 0; q < U; ++q) {
-      if (i + q * T >= i1) break;
-      ctx.apply(i + q * T, v[q], acc);
-    }
-  }
-  store_step_partials<NV>(vd, acc, red, lb);
-}
-
-// Sums the block partials of k_vol_update in a fixed order (thread t takes blocks
+// Sums the block partials of a solver step in a fixed order (thread t takes blocks
 // t, t + 256, ..., then the fixed-order block reduction) and advances the state.
 // One block per volume; the kernel boundary orders it after every partial store.
 template <int UPD>

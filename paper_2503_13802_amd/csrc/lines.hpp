@@ -83,8 +83,17 @@ template <int R, int SGN, typename C> __device__ __forceinline__ void dft_any(C*
   else dft<R, SGN>(v);
 }
 
-// Radix of stage s for the lengths of the switch below.
-__host__ __device__ constexpr int line_radix(int n, int s) {
+// Radix of stage s for the lengths of the switch below.  few: of the class passes,
+// whose workgroups have a few lines each.  A radix-16 stage is then one partly filled wave, and a wave
+// alone takes about 5000 cycles for the two of a length-256 line against 2600 for three
+// stages of radix 8 and 4 over four times the lanes (class pass of 256 x 256 images: 15.6 against
+// 14.0 us).
+__host__ __device__ constexpr int line_radix(int n, int s, bool few) {
+  if (few) {
+    constexpr int plan[][4] = {{96, 8, 4, 3}, {128, 8, 4, 4}, {144, 6, 6, 4}, {256, 8, 8, 4}};
+    for (auto& p : plan)
+      if (p[0] == n) return s < 3 ? p[1 + s] : 0;
+  }
   constexpr int plan[][4] = {
       {2, 2, 0, 0},   {3, 3, 0, 0},   {4, 4, 0, 0},   {6, 6, 0, 0},   {8, 8, 0, 0},   {9, 9, 0, 0},
       {12, 4, 3, 0},  {16, 4, 4, 0},  {18, 6, 3, 0},  {24, 8, 3, 0},  {27, 9, 3, 0},  {32, 8, 4, 0},
@@ -128,15 +137,15 @@ __device__ __forceinline__ void line_stage(Load ld, float2* __restrict__ out, co
   }
 }
 
-template <int N, int S, int NS, int SGN>
+template <int N, int S, int NS, int SGN, bool FEW>
 __device__ __forceinline__ float2* line_stages(float2* a, float2* b, const float2* tw, const Lines& L) {
-  constexpr int R = S < 3 ? line_radix(N, S) : 0;
+  constexpr int R = S < 3 ? line_radix(N, S, FEW) : 0;
   if constexpr (R == 0) {
     return a;
   } else {
     line_stage<N, R, NS, SGN>([&](int l, int p) { return a[__mul24(l, L.ls) + p]; }, b, tw, L);
     __syncthreads();
-    return line_stages<N, S + 1, NS * R, SGN>(b, a, tw, L);
+    return line_stages<N, S + 1, NS * R, SGN, FEW>(b, a, tw, L);
   }
 }
 
@@ -145,15 +154,15 @@ __device__ __forceinline__ float2* line_stages(float2* a, float2* b, const float
 // ping-pong between *a and *b.  Returns the buffer holding the result.  No leading
 // barrier; ends with one.  Lengths that the switch does not know are copied to *a and
 // take the run-time engine.
-template <int SGN, class Load>
+template <int SGN, bool FEW = false, class Load>
 __device__ __forceinline__ float2* line_fft_ld(Load ld, float2* a, float2* b, const float2* tw, int n, const Lines& L) {
   switch (n) {
 #define MH3D_LN(NN)                                                                       \
   case NN: {                                                                              \
-    constexpr int R = line_radix(NN, 0);                                                  \
+    constexpr int R = line_radix(NN, 0, FEW);                                                \
     line_stage<NN, R, 1, SGN>(ld, a, tw, L);                                              \
     __syncthreads();                                                                      \
-    return line_stages<NN, 1, R, SGN>(a, b, tw, L);                                       \
+    return line_stages<NN, 1, R, SGN, FEW>(a, b, tw, L);                                  \
   }
     MH3D_LN(4) MH3D_LN(6) MH3D_LN(8) MH3D_LN(9) MH3D_LN(12) MH3D_LN(16) MH3D_LN(18) MH3D_LN(24) MH3D_LN(27)
     MH3D_LN(32) MH3D_LN(36) MH3D_LN(48) MH3D_LN(54) MH3D_LN(64) MH3D_LN(72) MH3D_LN(96) MH3D_LN(108) MH3D_LN(128)
@@ -171,10 +180,10 @@ __device__ __forceinline__ float2* line_fft_ld(Load ld, float2* a, float2* b, co
 }
 
 // The same for lines in *a: the stages ping-pong between *b and *a, starting from *a.
-template <int SGN>
+template <int SGN, bool FEW = false>
 __device__ __forceinline__ float2* line_fft(float2* a, float2* b, const float2* tw, int n, const Lines& L) {
   const int ls = L.ls;
-  return line_fft_ld<SGN>([=](int l, int p) { return a[__mul24(l, ls) + p]; }, b, a, tw, n, L);
+  return line_fft_ld<SGN, FEW>([=](int l, int p) { return a[__mul24(l, ls) + p]; }, b, a, tw, n, L);
 }
 
 }  // namespace mh3d

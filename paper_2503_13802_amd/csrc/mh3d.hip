@@ -61,11 +61,15 @@ static bool is_23_smooth(int n) {
 static const size_t kLdsLimit = 160 * 1024;
 
 struct Launch {
-  int T_plane, T_class, T_small;
+  int T_class, T_small;
   // threads per block of k_adj_and_store (512 or 1024; both bodies loop over blockDim):
   // with 512 two blocks share a CU, so more small-grid blocks run beside the plane blocks
   int T_merge;
-  size_t lds_plane, lds_class, lds_small;
+  size_t lds_class, lds_small;
+  // the passes of user-PSF plans (user.hpp): threads and LDS of the forward and adjoint plane
+  // passes and of the class passes
+  int T_uf, T_ua, T_uc;
+  size_t lds_uf, lds_ua;
   // the separable passes of analytic plans (sep.hpp)
   int T_sep, T_col, col_blocks;
   bool col_any;            // column passes of the general form (more than one group or 4 x aliases)
@@ -131,6 +135,47 @@ static void derive_sep(Geo& g, Launch& L) {
   s.d_spairs = make_mdiv(g.spairs); s.d_xbmzh = make_mdiv(g.xb * g.mzh); s.d_nxb = make_mdiv(s.nxb);
 }
 
+// The column and row-pair counts of the ps workgroups of a plane.
+static void user_split(Geo& g) {
+  UserGeo& u = g.usr;
+  const int q = g.nzh / g.ps, j = g.npairs / g.ps;
+  u.d_qlo = make_mdiv(q); u.d_qhi = make_mdiv(q + 1);
+  u.d_j1lo = make_mdiv(j); u.d_j1hi = make_mdiv(j + 1);
+  u.d_jlo = make_mdiv(u.pcb * j); u.d_jhi = make_mdiv(u.pcb * (j + 1));
+}
+
+// Launch shapes of the user-PSF passes.
+static void derive_user(Geo& g, Launch& L) {
+  UserGeo& u = g.usr;
+  const int lsz = pad_odd(g.nz);
+  u.pl = std::max(g.npairs * lsz, g.nzh * g.lsy);
+  auto plane_bytes = [&](int c) { return sizeof(float2) * ((size_t)g.ny + g.nz + 2 * (size_t)c * u.pl); };
+  // all components of a plane together where they fit (96 x 64 planes of 3 components take one
+  // CU, which a workgroup per plane half leaves to itself anyway)
+  u.pcb = g.C > 1 && plane_bytes(g.C) + 1024 <= kLdsLimit ? g.C : 1;
+  L.lds_uf = plane_bytes(1);
+  L.lds_ua = plane_bytes(u.pcb);
+  // four points per thread, as the separable plane passes
+  const int want = pow2_at_least(g.npairs * g.nz / 4);
+  L.T_uf = std::min(512, std::max(128, want));
+  L.T_ua = std::min(1024, std::max(128, pow2_at_least(u.pcb * g.npairs * g.nz / 4)));
+  u.d_np = make_mdiv(g.npairs);
+  u.d_cnp = make_mdiv(u.pcb * g.npairs);
+  u.d_ycols = make_mdiv(u.pcb * g.nzh);
+  user_split(g);
+  // class passes: within the 64 KiB that the tile shapes are chosen for, an odd stride of the
+  // folded spectra and all components at once
+  const size_t cap = 64 * 1024;
+  u.fls = class_lds_elems(g, 1, pad_odd(g.mx)) * sizeof(float2) <= cap ? pad_odd(g.mx) : g.mx;
+  u.cb = (g.C == 1 || user_all_at_once(g.E)) && class_lds_elems(g, g.C, u.fls) * sizeof(float2) <= cap ? g.C : 0;
+  const int cb = std::max(u.cb, 1);
+  L.lds_class = class_lds_elems(g, cb, u.fls) * sizeof(float2);
+  const int W = g.cpw * g.nmem, lines = cb * W * g.nx / 4;
+  L.T_uc = std::max((L.T_class + 63) / 64 * 64, std::min(256, (lines + 63) / 64 * 64));
+  u.d_w = make_mdiv(W); u.d_cbw = make_mdiv(cb * W); u.d_kc = make_mdiv(g.K * g.cpw);
+  u.d_cm = make_mdiv(g.cpw * g.mx); u.d_cxb = make_mdiv(g.cpw * g.xb);
+}
+
 // A class-kernel element split e is valid when it is one of the compiled splits
 // (1, 2, 3, 4, 6, 8, 9), divides S, and S/e is a power of two <= 64 (the fold
 // reduction then stays inside aligned lane groups).
@@ -168,7 +213,7 @@ static mh3d_status derive_tiles(Geo& g, Launch& L, int E_req, int cpw_req, int x
     const long T = (long)cpw_req * g.mx * g.S / g.E;
     Geo t = g;
     t.cpw = cpw_req;
-    if (T > 1024 || class_lds_elems(t) * sizeof(float2) > 64 * 1024)
+    if (T > 1024 || class_lds_elems(t, 1, t.mx) * sizeof(float2) > 64 * 1024)
       return fail(MH3D_ERR_INVALID, "cpw = %d gives %ld threads / too much LDS", cpw_req, T);
     g.cpw = cpw_req;
   } else {
@@ -179,7 +224,7 @@ static mh3d_status derive_tiles(Geo& g, Launch& L, int E_req, int cpw_req, int x
       if (T > 1024) break;
       Geo t = g;
       t.cpw = c;
-      if (class_lds_elems(t) * sizeof(float2) > 64 * 1024) break;
+      if (class_lds_elems(t, 1, t.mx) * sizeof(float2) > 64 * 1024) break;
       best_cpw = c;
       if (T >= 128 && T % 64 == 0) break;
     }
@@ -187,7 +232,6 @@ static mh3d_status derive_tiles(Geo& g, Launch& L, int E_req, int cpw_req, int x
     g.cpw = best_cpw;
   }
   L.T_class = g.cpw * g.mx * g.S / g.E;
-  L.lds_class = class_lds_elems(g) * sizeof(float2);
 
   // ---- small kernel: x' planes per workgroup (aim for >= 256 workgroups)
   if (xb_req > 0) {
@@ -216,6 +260,7 @@ static mh3d_status derive_tiles(Geo& g, Launch& L, int E_req, int cpw_req, int x
   g.f_mxS = make_fastdiv(g.mx * g.S); g.f_cpwmx = make_fastdiv(g.cpw * g.mx);
   g.f_cpwxb = make_fastdiv(g.cpw * g.xb); g.f_ny = make_fastdiv(g.ny); g.f_my = make_fastdiv(g.my);
   derive_sep(g, L);
+  derive_user(g, L);
   L.T_merge = g.ps >= 2 ? 512 : 1024;   // the autotuner times both
   L.lds_small = sizeof(float2) * ((size_t)g.my + g.mz + 2 * (size_t)small_lds(g));
   if (L.lds_small > kLdsLimit) return fail(MH3D_ERR_UNSUPPORTED, "small-grid plane does not fit in LDS");
@@ -304,11 +349,8 @@ static mh3d_status build_geo(const mh3d_plan_desc* d, Geo& g, Launch& L, const m
 
   CHK(derive_tiles(g, L, tiles ? tiles->E : 0, tiles ? tiles->cpw : 0, tiles ? tiles->xb : 0, tiles ? tiles->ps : 0));
 
-  // ---- plane kernels
-  L.T_plane = 1024;
-  L.lds_plane = sizeof(float2) * ((size_t)g.ny + g.nz + 2 * (size_t)plane_lds(g));
-  // (+512 bytes: the block reduction of the step that the adjoint plane pass can run)
-  if (L.lds_plane + 512 > kLdsLimit) return fail(MH3D_ERR_UNSUPPORTED, "x-plane of %dx%d does not fit in LDS", g.ny, g.nz);
+  // ---- plane kernels (+512 bytes: the block reduction of the step that the adjoint pass runs)
+  if (sizeof(float2) * ((size_t)g.ny + g.nz + 2 * (size_t)plane_lds(g)) + 512 > kLdsLimit) return fail(MH3D_ERR_UNSUPPORTED, "x-plane of %dx%d does not fit in LDS", g.ny, g.nz);
   return MH3D_OK;
 }
 
@@ -348,6 +390,7 @@ struct mh3d_plan_s {
   int off[6];                  // table offsets for nx, ny, nz, mx, my, mz
   double* prof = nullptr;      // [K][nx]
   double* env = nullptr;       // [ny][nz]
+  int* cidx = nullptr;         // user PSFs: the class layout's positions in a half plane
   double* partials = nullptr;
   double* hist = nullptr;      // solver history (device), capacity hist_cap
   int hist_cap = 0;
@@ -394,7 +437,7 @@ static size_t uperm_elems(const Geo& g, bool compact) {
 
 static size_t plan_bytes(const Geo& g, bool compact) {
   size_t s = 0;
-  if (!compact) s += (size_t)g.C * g.K * g.hsz * 8;   // spectra
+  if (!compact) s += (size_t)g.C * g.K * g.hsz * 8 + (size_t)g.plane * 4;   // spectra, layout table
   s += (size_t)g.C * g.N * 4;                         // b
   s += uperm_elems(g, compact) * 8;                   // uperm
   s += 2 * (size_t)g.K * g.mx * g.ncls * 8;           // G, Gp
@@ -476,71 +519,37 @@ static mh3d_status last_launch(const char* what) {
 static mh3d_status launch_plane_fwd(mh3d_plan_t p, int src, const float* a) {
   Timer t(p, KID_PLANE_FWD);
   // vector model: one group of ps * nx blocks per component (a raw source has one)
-  dim3 grid((src == SRC_RAW ? 1 : p->g.C) * p->psa * p->g.nx), block(p->L.T_plane);
-  const size_t lds = p->L.lds_plane;
-  switch (src) {
-    case SRC_PLAIN: k_plane_fwd<SRC_PLAIN><<<grid, block, lds, p->ls>>>(p->vda, a); break;
-    case SRC_RAW: k_plane_fwd<SRC_RAW><<<grid, block, lds, p->ls>>>(p->vda, a); break;
-    case SRC_FISTA_Y: k_plane_fwd<SRC_FISTA_Y><<<grid, block, lds, p->ls>>>(p->vda, a); break;
-    default: k_plane_fwd<SRC_SCALED><<<grid, block, lds, p->ls>>>(p->vda, a); break;
-  }
-  return last_launch("k_plane_fwd");
+  const dim3 grid((src == SRC_RAW ? 1 : p->g.C) * p->psa * p->g.nx);
+  user_launch_plane_fwd(grid, dim3(p->L.T_uf), p->L.lds_uf, p->ls, p->vda, a, src);
+  return last_launch("k_user_plane_fwd");
 }
 
-template <int E>
-static void class_fwd_t(mh3d_plan_t p, int chk, const VolDesc* vd, int mode) {
-  const dim3 grid(p->g.ncls / p->g.cpw), block(p->L.T_class);
-  if (p->g.C > 1) k_class_fwd<E, true><<<grid, block, p->L.lds_class, p->ls>>>(vd, chk, mode);
-  else k_class_fwd<E, false><<<grid, block, p->L.lds_class, p->ls>>>(vd, chk, mode);
+static void launch_class(mh3d_plan_t p, int dir, int chk, int mode, const VolDesc* vd) {
+  user_launch_class(p->g.E, p->g.usr.cb, dir, dim3(p->g.ncls / p->g.cpw), dim3(p->L.T_uc), p->L.lds_class, p->ls, vd, chk, mode);
 }
-template <int E>
-static void class_adj_t(mh3d_plan_t p, int chk, const VolDesc* vd, int) {
-  const dim3 grid(p->g.ncls / p->g.cpw), block(p->L.T_class);
-  if (p->g.C > 1) k_class_adj<E, true><<<grid, block, p->L.lds_class, p->ls>>>(vd, chk);
-  else k_class_adj<E, false><<<grid, block, p->L.lds_class, p->ls>>>(vd, chk);
-}
-
-#define E_DISPATCH(FN)                             \
-  switch (p->g.E) {                                \
-    case 9: FN<9>(p, chk, vd, mode); break;        \
-    case 8: FN<8>(p, chk, vd, mode); break;        \
-    case 6: FN<6>(p, chk, vd, mode); break;        \
-    case 4: FN<4>(p, chk, vd, mode); break;        \
-    case 3: FN<3>(p, chk, vd, mode); break;        \
-    case 2: FN<2>(p, chk, vd, mode); break;        \
-    default: FN<1>(p, chk, vd, mode); break;       \
-  }
 
 // mode: FWD_G, FWD_ADJ, FWD_G_AND_ADJ or FWD_RESID (where the decimated spectra go).
 static mh3d_status launch_class_fwd(mh3d_plan_t p, int chk, int mode) {
   Timer t(p, KID_CLASS_FWD);
-  const VolDesc* vd = p->vda;
-  E_DISPATCH(class_fwd_t)
-  return last_launch("k_class_fwd");
+  launch_class(p, CLS_FWD, chk, mode, p->vda);
+  return last_launch("k_user_class (forward)");
 }
 // vd: a single-harmonic descriptor (per-harmonic back-projection) or NULL for the plan's.
 static mh3d_status launch_class_adj(mh3d_plan_t p, int chk, const VolDesc* vd = nullptr) {
   Timer t(p, KID_CLASS_ADJ);
-  if (!vd) vd = p->vda;
-  const int mode = 0;
-  E_DISPATCH(class_adj_t)
-  return last_launch("k_class_adj");
+  launch_class(p, CLS_ADJ, chk, 0, vd ? vd : p->vda);
+  return last_launch("k_user_class (adjoint)");
 }
 
-// Scalar plans without boundary padding run the forward and adjoint class (or column)
-// passes of the normal operator, the solver's updates and A then A^T as one.
-static bool fused_class(mh3d_plan_t p) { return p->g.C == 1 && !p->g.padded; }
+// Plans without boundary padding run the forward and adjoint class (or column) passes of the
+// normal operator, the solver's updates and A then A^T as one.
+static bool fused_class(mh3d_plan_t p) { return !p->g.padded; }
 
-template <int E>
-static void class_normal_t(mh3d_plan_t p, int chk, const VolDesc* vd, int mode) {
-  k_class_normal<E><<<dim3(p->g.ncls / p->g.cpw), dim3(p->L.T_class), p->L.lds_class, p->ls>>>(vd, chk, mode);
-}
 // mode: NRM_RESID, NRM_PLAIN or NRM_STORE.
 static mh3d_status launch_class_normal(mh3d_plan_t p, int chk, int mode) {
   Timer t(p, KID_CLASS_NORMAL);
-  const VolDesc* vd = p->vda;
-  E_DISPATCH(class_normal_t)
-  return last_launch("k_class_normal");
+  launch_class(p, CLS_NORMAL, chk, mode, p->vda);
+  return last_launch("k_user_class");
 }
 
 static mh3d_status launch_small_inv(mh3d_plan_t p, int epi, float* d) {
@@ -569,19 +578,11 @@ static mh3d_status launch_small_fwd_adj(mh3d_plan_t p, const float* r) {
 static mh3d_status launch_plane_adj(mh3d_plan_t p, int out, float* o, const float* yin,
                                     const VolDesc* vd = nullptr) {
   Timer t(p, KID_PLANE_ADJ);
-  if (!vd) vd = p->vda;
-  dim3 grid(p->psa * p->g.nx), block(p->L.T_plane);
-  const size_t lds = p->L.lds_plane;
   AdjOut ao;
   ao.out = o;
   ao.yin = yin;
-  switch (out) {
-    case OUT_SCALE_B: k_plane_adj<OUT_SCALE_B><<<grid, block, lds, p->ls>>>(vd, ao); break;
-    case OUT_STEP_NORMAL: k_plane_adj<OUT_STEP_NORMAL><<<grid, block, lds, p->ls>>>(vd, ao); break;
-    case OUT_STEP_FISTA: k_plane_adj<OUT_STEP_FISTA><<<grid, block, lds, p->ls>>>(vd, ao); break;
-    default: k_plane_adj<OUT_U><<<grid, block, lds, p->ls>>>(vd, ao); break;
-  }
-  return last_launch("k_plane_adj");
+  user_launch_plane_adj(p->g.usr.pcb < p->g.C, out, dim3(p->psa * p->g.nx), dim3(p->L.T_ua), p->L.lds_ua, p->ls, vd ? vd : p->vda, ao);
+  return last_launch("k_user_plane_adj");
 }
 
 // After the fused class pass of A then A^T: the adjoint plane pass (x = A^T d) and the
@@ -592,8 +593,8 @@ static mh3d_status launch_adj_and_store(mh3d_plan_t p, float* d, float* x) {
   ao.out = x;
   ao.yin = nullptr;
   const dim3 grid(p->psa * p->g.nx + p->g.K * (p->g.mx / p->g.xb)), block(p->L.T_merge);
-  launch_user_adj_and_store(grid, block, std::max(p->L.lds_plane, p->L.lds_small), p->ls, p->vda, ao, d);
-  return last_launch("k_adj_and_store");
+  user_launch_adj_and_store(p->g.usr.pcb < p->g.C, grid, block, std::max(p->L.lds_ua, p->L.lds_small), p->ls, p->vda, ao, d);
+  return last_launch("k_user_adj_and_store");
 }
 
 // Analytic plans run the compile-time passes of fast.hpp when there are any for them.
@@ -603,9 +604,9 @@ static bool use_fast(mh3d_plan_t p) {
   return p->fast && p->fast_on && (xb == 1 || xb == 2 || xb == 4 || xb == 8);
 }
 
-// Scalar user-PSF plans with one workgroup per x-plane also run the next update's forward
-// plane pass in the launch of the step (k_step_and_fwd).
-static bool step_and_fwd(mh3d_plan_t p) { return p->g.C == 1 && p->psa == 1; }
+// User-PSF plans with one workgroup per x-plane also run the next update's forward plane pass
+// in the launch of the step (k_user_step_and_fwd).
+static bool step_and_fwd(mh3d_plan_t p) { return p->psa == 1; }
 
 // ---- passes of analytic plans: the compile-time ones where the plan has them, else the
 // separable ones of run-time geometry
@@ -687,40 +688,23 @@ static mh3d_status launch_step_and_fwd(mh3d_plan_t p) {
     AdjOut ao;
     ao.out = nullptr;
     ao.yin = nullptr;
-    k_step_and_fwd<<<dim3(p->g.nx), dim3(p->L.T_plane), p->L.lds_plane, p->ls>>>(p->vda, ao);
-    CHK(last_launch("k_step_and_fwd"));
+    user_launch_step_and_fwd(p->g.usr.pcb < p->g.C, dim3(p->g.nx), dim3(p->L.T_ua), std::max(p->L.lds_uf, p->L.lds_ua), p->ls, p->vda, ao);
+    CHK(last_launch("k_user_step_and_fwd"));
   }
   Timer t(p, KID_UPDATE);
   k_vol_finish<UPD_FISTA><<<1, 256, 0, p->ls>>>(p->vda, nullptr);
   return last_launch("k_vol_finish");
 }
 
-// Scalar plans finish a solver step inside the adjoint plane pass (its u = b . v stays
-// in registers); vector plans, whose plane pass sums the components, run the update
-// pass after it.  The block count of the step's FP64 sums is the descriptor's nb_upd.
-static bool step_in_plane_pass(mh3d_plan_t p) { return p->g.C == 1; }
-
-// The adjoint plane pass and the rest of a solver step: out = (A^T A + lambda T^T T)(s w)
-// (UPD_NORMAL, w = yin) or one accelerated projected gradient update (UPD_FISTA).
+// The adjoint plane pass, which ends the solver step on its voxels (u = b . v stays in
+// registers): out = (A^T A + lambda T^T T)(s w) (UPD_NORMAL, w = yin) or one accelerated
+// projected gradient update (UPD_FISTA); then the one-block finish of its FP64 sums.
 static mh3d_status launch_adjoint_step(mh3d_plan_t p, int upd, float* o, const float* yin) {
-  if (step_in_plane_pass(p)) {
-    CHK(launch_plane_adj(p, upd == UPD_NORMAL ? OUT_STEP_NORMAL : OUT_STEP_FISTA, o, yin));
-  } else {
-    CHK(launch_plane_adj(p, OUT_U, nullptr, nullptr));
-  }
+  CHK(launch_plane_adj(p, upd == UPD_NORMAL ? OUT_STEP_NORMAL : OUT_STEP_FISTA, o, yin));
   Timer t(p, KID_UPDATE);
-  AdjOut ao;
-  ao.out = o;
-  ao.yin = yin;
-  const dim3 grid(update_blocks(p->g.N)), block(UPD_THREADS);
-  if (upd == UPD_NORMAL) {
-    if (!step_in_plane_pass(p)) k_vol_update<UPD_NORMAL><<<grid, block, 0, p->ls>>>(p->vda, ao);
-    k_vol_finish<UPD_NORMAL><<<1, 256, 0, p->ls>>>(p->vda, nullptr);
-  } else {
-    if (!step_in_plane_pass(p)) k_vol_update<UPD_FISTA><<<grid, block, 0, p->ls>>>(p->vda, ao);
-    k_vol_finish<UPD_FISTA><<<1, 256, 0, p->ls>>>(p->vda, nullptr);
-  }
-  return last_launch("k_vol_update / k_vol_finish");
+  if (upd == UPD_NORMAL) k_vol_finish<UPD_NORMAL><<<1, 256, 0, p->ls>>>(p->vda, nullptr);
+  else k_vol_finish<UPD_FISTA><<<1, 256, 0, p->ls>>>(p->vda, nullptr);
+  return last_launch("k_vol_finish");
 }
 
 // ---------------------------------------------------------------------------- state
@@ -734,17 +718,14 @@ static mh3d_status state_set(mh3d_plan_t p, const DevState& v) {
   return last_launch("k_state_set");
 }
 
-// Blocks whose FP64 sums a solver step leaves: the adjoint plane pass's (scalar plans) or
-// the update pass's (vector plans).
-static int step_blocks(mh3d_plan_t p) {
-  if (p->compact) return p->g.nx * p->g.sy;
-  return p->g.C == 1 ? p->ps_solve * p->g.nx : update_blocks(p->g.N);
-}
+// Blocks whose FP64 sums a solver step leaves: the adjoint plane pass's.
+static int step_blocks(mh3d_plan_t p) { return p->g.nx * (p->compact ? p->g.sy : p->ps_solve); }
 
 static mh3d_status upload_desc(mh3d_plan_t p) {
   p->vdu[0] = p->vdh;
   p->vdu[1] = p->vdh;
   p->vdu[1].g.ps = p->ps_solve;
+  user_split(p->vdu[1].g);
   p->vdu[1].nb_upd = step_blocks(p);
   HIPCHK(hipMemcpyAsync(p->vdd, p->vdu, sizeof p->vdu, hipMemcpyHostToDevice, p->stream));
   HIPCHK(hipStreamSynchronize(p->stream));
@@ -873,6 +854,26 @@ static mh3d_status component_masks(mh3d_plan_t p) {
   return MH3D_OK;
 }
 
+// The class layout's positions in a half plane (see user.hpp).  A position with qz mod mz
+// beyond mz/2 is held by its Hermitian partner's element.
+static mh3d_status build_layout_table(mh3d_plan_t p) {
+  const Geo& g = p->g;
+  std::vector<int> t(g.plane);
+  for (int e = 0; e < g.plane; ++e) {
+    const int c = e / g.nmem, m = e % g.nmem;
+    const int qy = c / g.mzh + m / g.sz * g.my, qz = c % g.mzh + m % g.sz * g.mz;
+    const bool conj = 2 * qz > g.nz;
+    const int col = conj ? g.nz - qz : qz, row = conj ? (g.ny - qy) % g.ny : qy;
+    const bool from_partner = 2 * (col % g.mz) > g.mz;
+    // of the elements that hold a position: the direct one, or the partner's
+    t[e] = row | col << 16 | (conj ? CIDX_CONJ : 0) | (conj == from_partner ? CIDX_OWNER : 0);
+  }
+  CHK(dalloc(p, (void**)&p->cidx, sizeof(int) * t.size()));
+  HIPCHK(hipMemcpyAsync(p->cidx, t.data(), sizeof(int) * t.size(), hipMemcpyHostToDevice, p->stream));
+  HIPCHK(hipStreamSynchronize(p->stream));
+  return MH3D_OK;
+}
+
 static mh3d_status build_spectra_user(mh3d_plan_t p) {
   const Geo& g = p->g;
   p->imag_mask = 0;
@@ -892,7 +893,7 @@ extern "C" void mh3d_destroy(mh3d_plan_t p) {
   if (p->stream) (void)hipStreamSynchronize(p->stream);
   for (auto& e : p->pending) { (void)hipEventDestroy(e.second.first); (void)hipEventDestroy(e.second.second); }
   for (auto e : p->free_events) (void)hipEventDestroy(e);
-  void* bufs[] = {p->hs, p->b, p->uperm, p->G, p->Gp, p->vol[0], p->vol[1], p->vol[2], p->vol[3], p->vol[4],
+  void* bufs[] = {p->hs, p->cidx, p->b, p->uperm, p->G, p->Gp, p->vol[0], p->vol[1], p->vol[2], p->vol[3], p->vol[4],
                   p->tw32, p->tw64, p->prof, p->env, p->partials, p->st, p->vdd, p->vdk, p->hist, p->sfs, p->set, p->fhat, p->ehat, p->scale};
   for (void* q : bufs)
     if (q) (void)hipFree(q);
@@ -927,6 +928,7 @@ static void fill_desc(mh3d_plan_t p) {
   v.aw = p->desc.alpha_width;
   v.T_class = p->L.T_class;
   v.u = p->vol[4];
+  v.cidx = p->cidx;
   v.nb_upd = step_blocks(p);
   v.ncomp = p->g.C;
   v.hs_cstride = (long long)p->g.K * p->g.hsz;
@@ -952,6 +954,7 @@ static mh3d_status upload_harmonic_descs(mh3d_plan_t p) {
     if (p->hs) h[k].hs = (const float2*)p->vdh.hs + (size_t)k * g.hsz;
     h[k].g.sep.kg = 1;
     h[k].g.sep.d_kgcpc = make_mdiv(g.sep.cpc);
+    h[k].g.usr.d_kc = make_mdiv(g.cpw);
     h[k].Gp = p->vdh.Gp + (size_t)k * g.mx * g.ncls;
     h[k].imag_mask = (p->vdh.imag_mask >> k) & 1u;
     for (int c = 0; c < 3; ++c) h[k].cmask[c] = (p->vdh.cmask[c] >> k) & 1u;
@@ -1007,6 +1010,7 @@ extern "C" mh3d_status mh3d_plan(const mh3d_plan_desc* desc, mh3d_plan_t* out) {
   p->psa = p->ps_solve = g.ps;
   if ((s = dalloc(p, (void**)&p->vdk, sizeof(VolDesc) * g.K)) != MH3D_OK) return bail(s);
   if ((s = build_tables(p)) != MH3D_OK) return bail(s);
+  if (!p->compact && (s = build_layout_table(p)) != MH3D_OK) return bail(s);
   fill_desc(p);
   if ((s = upload_desc(p)) != MH3D_OK) return bail(s);
   if (desc->sens) {
@@ -1201,7 +1205,7 @@ extern "C" mh3d_status mh3d_power_iteration(mh3d_plan_t p, int32_t iters, uint64
 // ============================================================================ solver
 // One accelerated projected gradient update of the plan's volume; buffers and the
 // step come from the device state, so the same launches serve every iteration.
-// first: the first update of a solve call (with k_step_and_fwd the forward plane pass of
+// first: the first update of a solve call (with k_user_step_and_fwd the forward plane pass of
 // every later update ran in the previous update's last launch).
 static mh3d_status enqueue_update(mh3d_plan_t p, bool first) {
   Timer t(p, KID_SOLVE_ITER);
@@ -1789,7 +1793,7 @@ extern "C" mh3d_status mh3d_mhad(mh3d_plan_t p, const float* d, double lambda, c
 extern "C" mh3d_status mh3d_time_pass(mh3d_plan_t p, int32_t pass, int32_t reps, double* us) {
   CHK(check_plan(p));
   if (pass < 0 || pass > 7 || reps < 1 || !us) return fail(MH3D_ERR_INVALID, "bad pass timing arguments");
-  if (pass >= 6 && !fused_class(p))
+  if (pass >= 6 && (p->g.C > 1 || !fused_class(p)))
     return fail(MH3D_ERR_UNSUPPORTED, "the plan runs no fused class pass (vector model or boundary padding)");
   if (p->prof_on) return fail(MH3D_ERR_INVALID, "disable mh3d_profile before timing passes");
   float* dtmp = nullptr;

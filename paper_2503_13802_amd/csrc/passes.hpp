@@ -1,5 +1,5 @@
 // Launchers of the separable passes, defined in translation units of their own (sep.hip,
-// fast.hip): their kernels are most of the library's code, and the units compile side by
+// fast.hip, user.hip): their kernels are most of the library's code, and the units compile side by
 // side.
 #pragma once
 #include "kernels.hpp"
@@ -50,7 +50,26 @@ void sep_launch_adj_and_store(dim3 grid, dim3 block, size_t lds, hipStream_t s, 
 void sep_launch_small_inv(dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, const int2* tasks, float* d,
                           int epi);
 void sep_launch_small_fwd(dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, const float* r, float2* out);
-// the adjoint plane pass of a user-PSF plan beside the small-grid pass
-void launch_user_adj_and_store(dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, AdjOut ao, float* d);
+
+// ---------------------------------------------------------------------------- user PSFs
+// Packed class-layout table: row in bits 0-15, column (qz <= nz/2) in bits 16-23
+constexpr int CIDX_CONJ = 1 << 30;      // the element is the conjugate of that position
+constexpr int CIDX_OWNER = 1 << 29;     // the position is read back from this element
+enum { CLS_FWD = 0, CLS_ADJ = 1, CLS_NORMAL = 2 };   // see user_class.hpp
+// splits for which the class passes are compiled with all components of a vector plan at once
+constexpr bool user_all_at_once(int e) { return e == 1 || e == 2 || e == 4; }
+void user_launch_plane_fwd(dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, const float* a, int src);
+// rounds: a workgroup's LDS does not hold every component
+void user_launch_plane_adj(bool rounds, int out, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, AdjOut ao);
+void user_launch_step_and_fwd(bool rounds, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, AdjOut ao);
+void user_launch_adj_and_store(bool rounds, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, AdjOut ao,
+                               float* d);
+void user_launch_class1(int cb, int dir, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, int chk, int mode);
+void user_launch_class2(int cb, int dir, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, int chk, int mode);
+void user_launch_class4(int cb, int dir, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, int chk, int mode);
+void user_launch_class3689(int E, int cb, int dir, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, int chk,
+                           int mode);
+void user_launch_class(int E, int cb, int dir, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, int chk,
+                       int mode);
 
 }  // namespace mh3d

@@ -42,8 +42,4 @@ void sep_launch_small_fwd(dim3 grid, dim3 block, size_t lds, hipStream_t s, cons
   k_sep_small_fwd<<<grid, block, lds, s>>>(vd, r, out);
 }
 
-void launch_user_adj_and_store(dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, AdjOut ao, float* d) {
-  k_adj_and_store<<<grid, block, lds, s>>>(vd, ao, d);
-}
-
 }  // namespace mh3d

@@ -615,8 +615,16 @@ struct SepRows {
   const float* bs;         // the plane's sensitivity
 };
 
+// User PSFs: nc components in the block, whose packed rows lie zs apart and whose
+// sensitivities bstride, added to the plane part (or NULL) of earlier components.
+struct UserRows {
+  int nc, zs;
+  long long bstride;
+  const float* part;
+};
+
 // The end of a solver step on the block's voxels (rows y = sy*y1 + y0 of plane x), with
-// u = b . v from the packed rows Z in LDS: the arithmetic of StepCtx (kernels.hpp) on V
+// u = b . v from the packed rows Z in LDS: on V
 // consecutive voxels along z.  FP64 block partials go to vd.partials[lb].
 struct SepStep {
   const float *yv, *rk;    // y^k or w_{t-1}; rho^k
@@ -655,9 +663,11 @@ __device__ __forceinline__ SepStep sep_step_of(const VolDesc& vd, const AdjOut& 
   return c;
 }
 
-template <int UPD, int V>
+// USER: user PSFs (u summed over the components; 2D grids, whose projection axis of length 1
+// has no faces and no second differences: every neighbour along it is the voxel itself).
+template <int UPD, int V, bool USER = false>
 __device__ __forceinline__ void sep_step(const VolDesc& vd, const SepStep& cx, const SepRows& w, const float2* __restrict__ Z,
-                                         int x, int lb, double* red) {
+                                         int x, int lb, double* red, const UserRows& us = UserRows{}) {
   constexpr int NV = UPD == UPD_NORMAL ? 2 : 3;
   const int T = w.T, y0 = w.y0;
   const float s = cx.s, lam = cx.lam, alpha = cx.alpha, tau = cx.tau, beta1 = cx.beta1;
@@ -672,6 +682,8 @@ __device__ __forceinline__ void sep_step(const VolDesc& vd, const SepStep& cx, c
 #pragma unroll
   for (int j = 0; j < NV; ++j) acc[j] = 0.0;
   auto wrap = [](int q, int n) { return q < 0 ? q + n : (q >= n ? q - n : q); };
+  const bool flat = USER && ny == 1;
+  auto wrap_y = [&](int q) { return flat ? 0 : wrap(q, ny); };
   const int oxm2 = (wrap(x - 2, nx) - x) * PL, oxm1 = (wrap(x - 1, nx) - x) * PL;
   const int oxp1 = (wrap(x + 1, nx) - x) * PL, oxp2 = (wrap(x + 2, nx) - x) * PL;
   const int nv = nz / V, items = w.my * nv;
@@ -682,6 +694,7 @@ __device__ __forceinline__ void sep_step(const VolDesc& vd, const SepStep& cx, c
   for (int f0 = threadIdx.x; f0 < items; f0 += U * T) {
     float c[U][V], ym2[U][V], ym1[U][V], yp1[U][V], yp2[U][V], xm2[U][V], xm1[U][V], xp1[U][V], xp2[U][V], rv[U][V], bv[U][V];
     float zl2[U], zl1[U], zr1[U], zr2[U];
+    float bx[U][2][V], pv[U][V];   // USER: the other components' sensitivities, the sum so far
 #pragma unroll
     for (int q = 0; q < U; ++q) {
       const int f = f0 + q * T;
@@ -690,6 +703,12 @@ __device__ __forceinline__ void sep_step(const VolDesc& vd, const SepStep& cx, c
       const int y = w.sy * y1 + y0, row = pb + y * nz, i0 = row + z0;
       ldv<V>(yv + i0, c[q]);
       ldv<V>(w.bs + y * nz + z0, bv[q]);
+      if constexpr (USER) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          if (i + 1 < us.nc) ldv<V>(w.bs + (i + 1) * us.bstride + y * nz + z0, bx[q][i]);
+        if (us.part) ldv<V>(us.part + y * nz + z0, pv[q]);
+      }
       if (UPD == UPD_FISTA) ldv<V>(rk + i0, rv[q]);
       if (stencil) {
         zl2[q] = ldg(yv + row + wrap(z0 - 2, nz));
@@ -697,10 +716,10 @@ __device__ __forceinline__ void sep_step(const VolDesc& vd, const SepStep& cx, c
         zr1[q] = ldg(yv + row + wrap(z0 + V, nz));
         zr2[q] = ldg(yv + row + wrap(z0 + V + 1, nz));
         const int pz = pb + z0;
-        ldv<V>(yv + pz + wrap(y - 2, ny) * nz, ym2[q]);
-        ldv<V>(yv + pz + wrap(y - 1, ny) * nz, ym1[q]);
-        ldv<V>(yv + pz + wrap(y + 1, ny) * nz, yp1[q]);
-        ldv<V>(yv + pz + wrap(y + 2, ny) * nz, yp2[q]);
+        ldv<V>(yv + pz + wrap_y(y - 2) * nz, ym2[q]);
+        ldv<V>(yv + pz + wrap_y(y - 1) * nz, ym1[q]);
+        ldv<V>(yv + pz + wrap_y(y + 1) * nz, yp1[q]);
+        ldv<V>(yv + pz + wrap_y(y + 2) * nz, yp2[q]);
         ldv<V>(yv + i0 + oxm2, xm2[q]);
         ldv<V>(yv + i0 + oxm1, xm1[q]);
         ldv<V>(yv + i0 + oxp1, xp1[q]);
@@ -724,7 +743,16 @@ __device__ __forceinline__ void sep_step(const VolDesc& vd, const SepStep& cx, c
 #pragma clang fp contract(off)
         const int z = z0 + e;
         const float vz = (y1 & 1) ? zr[e].y : zr[e].x;
-        const float u = __fmul_rn(bv[q][e], vz);
+        float u = __fmul_rn(bv[q][e], vz);
+        if constexpr (USER) {
+          if (us.part) u += pv[q][e];
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            if (i + 1 < us.nc) {
+              const float2 zi = zr[(i + 1) * us.zs + e];
+              u += bx[q][i][e] * ((y1 & 1) ? zi.y : zi.x);
+            }
+        }
         float t;
         if (!stencil) {
           t = s * c[q][e];
@@ -735,7 +763,7 @@ __device__ __forceinline__ void sep_step(const VolDesc& vd, const SepStep& cx, c
           t += s * (xp2[q][e] + xm2[q][e]) - 4.f * s * (xp1[q][e] + xm1[q][e]);
         }
         if (alpha > 0.f) {
-          const bool shell = x < aw || x >= nx - aw || y < aw || y >= ny - aw || z < aw || z >= nz - aw;
+          const bool shell = x < aw || x >= nx - aw || (!flat && (y < aw || y >= ny - aw)) || z < aw || z >= nz - aw;
           if (shell) t += alpha * (s * c[q][e]);
         }
         const float gr = u + lam * t;
@@ -767,8 +795,9 @@ __device__ __forceinline__ void sep_step(const VolDesc& vd, const SepStep& cx, c
 
 // ============================================================================ plane pass (adjoint)
 // out = b . v on the block's rows, from the packed rows Z (out: the plane).
-template <int V>
-__device__ __forceinline__ void sep_store_rows(const SepRows& w, const float2* __restrict__ Z, float* __restrict__ out) {
+template <int V, bool USER = false>
+__device__ __forceinline__ void sep_store_rows(const SepRows& w, const float2* __restrict__ Z, float* __restrict__ out,
+                                               const UserRows& us = UserRows{}) {
   const int nv = w.nz / V, items = w.my * nv;
   constexpr int U = 4;
   for (int i0 = threadIdx.x; i0 < items; i0 += U * w.T) {
@@ -788,6 +817,24 @@ __device__ __forceinline__ void sep_store_rows(const SepRows& w, const float2* _
         float o[V];
 #pragma unroll
         for (int q = 0; q < V; ++q) o[q] = bv[u][q] * ((y1 & 1) ? zr[q].y : zr[q].x);
+        if constexpr (USER) {
+          const int at = (w.sy * y1 + w.y0) * w.nz + V * c;
+          if (us.part) {
+            float pv[V];
+            ldv<V>(us.part + at, pv);
+#pragma unroll
+            for (int q = 0; q < V; ++q) o[q] += pv[q];
+          }
+          for (int i = 1; i < us.nc; ++i) {
+            float bx[V];
+            ldv<V>(w.bs + i * us.bstride + at, bx);
+#pragma unroll
+            for (int q = 0; q < V; ++q) {
+              const float2 zi = zr[i * us.zs + q];
+              o[q] += bx[q] * ((y1 & 1) ? zi.y : zi.x);
+            }
+          }
+        }
         stv<V>(out + (w.sy * y1 + w.y0) * w.nz + V * c, o);
       }
     }
@@ -1115,18 +1162,6 @@ static __global__ __launch_bounds__(512, 6) void k_sep_small_inv(const VolDesc* 
   const VolDesc& vd = vds[v];
   pin(T);
   sep_small_inv_body(vd, lb, d, epi, T);
-}
-
-// A then A^T of scalar user-PSF plans after the fused class pass: both halves read only what
-// that pass wrote, so blocks [0, ps nx) run the adjoint plane pass (ao.out = b . v) while
-// the others run the small-grid inverse pass that writes the portraits d.  The plane
-// blocks come first (their XCD-aware plane order assumes block ids 0 .. ps nx - 1).  Both
-// bodies loop over blockDim (512 or 1024).
-static __global__ __launch_bounds__(1024) void k_adj_and_store(const VolDesc* __restrict__ vds, AdjOut ao, float* __restrict__ d) {
-  const VolDesc& vd = vds[0];
-  const int nplane = vd.g.ps * vd.g.nx;
-  if ((int)blockIdx.x < nplane) plane_adj_body<OUT_SCALE_B>(vd, blockIdx.x, ao);
-  else sep_small_inv_body(vd, blockIdx.x - nplane, d, EPI_STORE, blockDim.x);
 }
 
 // A then A^T after the column pass (NRM_STORE): blocks [0, nbp = sy nx) run the adjoint plane

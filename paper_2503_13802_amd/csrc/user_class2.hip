@@ -1,0 +1,10 @@
+// The class passes with 2 spectrum elements per thread.
+#include "user_class.hpp"
+
+namespace mh3d {
+
+void user_launch_class2(int cb, int dir, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, int chk, int mode) {
+  class_cb<2>(cb, dir, grid, block, lds, s, vd, chk, mode);
+}
+
+}  // namespace mh3d
