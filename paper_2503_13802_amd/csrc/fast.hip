@@ -10,19 +10,20 @@ struct FastImpl {
   static void plane_fwd(hipStream_t s, const VolDesc* vd, int src, const float* a) {
     const dim3 grid(G::NBP), block(G::TPF);
     switch (src) {
-      case SRC_PLAIN: k_fast_plane_fwd<G, SRC_PLAIN><<<grid, block, G::LDS_PLANE, s>>>(vd, a); break;
-      case SRC_FISTA_Y: k_fast_plane_fwd<G, SRC_FISTA_Y><<<grid, block, G::LDS_PLANE, s>>>(vd, a); break;
-      default: k_fast_plane_fwd<G, SRC_SCALED><<<grid, block, G::LDS_PLANE, s>>>(vd, a); break;
+      case SRC_PLAIN: k_fast_plane_fwd<G, SRC_PLAIN><<<grid, block, G::LDS_PLANE, s>>>(vd, a, 0); break;
+      case SRC_FISTA_Y: k_fast_plane_fwd<G, SRC_FISTA_Y><<<grid, block, G::LDS_PLANE, s>>>(vd, a, 0); break;
+      case SRC_FISTA_NEXT: k_fast_plane_fwd<G, SRC_FISTA_Y><<<grid, block, G::LDS_PLANE, s>>>(vd, a, 1); break;
+      default: k_fast_plane_fwd<G, SRC_SCALED><<<grid, block, G::LDS_PLANE, s>>>(vd, a, 0); break;
     }
   }
-  static void cls(hipStream_t s, const VolDesc* vd, int mode, int chk) {
-    const dim3 grid(G::NCLS / G::CPC), block(G::TC);
+  static void cls(hipStream_t s, const VolDesc* vd, int mode, int chk, int fin) {
+    const dim3 grid(G::NCLS / G::CPC + fin), block(G::TC);
     switch (mode) {
-      case NRM_RESID: k_fast_col<G, NRM_RESID><<<grid, block, G::LDS_COL, s>>>(vd, chk); break;
-      case NRM_PLAIN: k_fast_col<G, NRM_PLAIN><<<grid, block, G::LDS_COL, s>>>(vd, chk); break;
-      case COL_FWD: k_fast_col<G, COL_FWD><<<grid, block, G::LDS_COL, s>>>(vd, chk); break;
-      case COL_ADJ: k_fast_col<G, COL_ADJ><<<grid, block, G::LDS_COL, s>>>(vd, chk); break;
-      default: k_fast_col<G, NRM_STORE><<<grid, block, G::LDS_COL, s>>>(vd, chk); break;
+      case NRM_RESID: k_fast_col<G, NRM_RESID><<<grid, block, G::LDS_COL, s>>>(vd, chk, fin); break;
+      case NRM_PLAIN: k_fast_col<G, NRM_PLAIN><<<grid, block, G::LDS_COL, s>>>(vd, chk, fin); break;
+      case COL_FWD: k_fast_col<G, COL_FWD><<<grid, block, G::LDS_COL, s>>>(vd, chk, fin); break;
+      case COL_ADJ: k_fast_col<G, COL_ADJ><<<grid, block, G::LDS_COL, s>>>(vd, chk, fin); break;
+      default: k_fast_col<G, NRM_STORE><<<grid, block, G::LDS_COL, s>>>(vd, chk, fin); break;
     }
   }
   static void plane_adj(hipStream_t s, const VolDesc* vd, int out, AdjOut ao) {
@@ -42,7 +43,7 @@ struct FastImpl {
     k_fast_small_fwd<G><<<dim3(nsmall), dim3(G::TP), G::small_lds(xb), s>>>(vd, r, out);
   }
   static void adjoint_each(hipStream_t s, const VolDesc* vd, int nv, float* out) {
-    k_fast_col<G, COL_ADJ><<<dim3(G::NCLS / G::CPC, nv), dim3(G::TC), G::LDS_COL, s>>>(vd, 0);
+    k_fast_col<G, COL_ADJ><<<dim3(G::NCLS / G::CPC, nv), dim3(G::TC), G::LDS_COL, s>>>(vd, 0, 0);
     AdjOut ao;
     ao.out = out;
     ao.yin = nullptr;

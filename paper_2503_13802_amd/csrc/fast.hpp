@@ -165,12 +165,12 @@ __device__ __forceinline__ void fast_plane_of(int b, int& x, int& y0) {
 // R2C along z, length-my DFT along y1, then the share C(y0; x, q'y, q'z) of the folded
 // plane into cp[y0][x][column].
 template <class G, int SRC>
-static __global__ __launch_bounds__(G::TPF) void k_fast_plane_fwd(const VolDesc* __restrict__ vds, const float* __restrict__ a) {
+static __global__ __launch_bounds__(G::TPF) void k_fast_plane_fwd(const VolDesc* __restrict__ vds, const float* __restrict__ a, int ahead) {
   const VolDesc& vd = vds[0];
   if constexpr (SRC == SRC_FISTA_Y || SRC == SRC_SCALED) {
     if (vd.st->done) return;
   }
-  if constexpr (SRC == SRC_FISTA_Y) a = vd.y[vd.st->k & 1];
+  if constexpr (SRC == SRC_FISTA_Y) a = vd.y[(vd.st->k + ahead) & 1];
   if constexpr (SRC == SRC_SCALED) {
     if (!a) a = vd.rho[vd.st->k & 1];
   }
@@ -304,8 +304,13 @@ __device__ __forceinline__ int fast_col_block(int b) {
 //
 // grid.y > 1 runs one descriptor per y-block (the back-projections of single harmonics).
 template <class G, int MODE>
-static __global__ __launch_bounds__(G::TC) void k_fast_col(const VolDesc* __restrict__ vds, int check_done) {
+static __global__ __launch_bounds__(G::TC) void k_fast_col(const VolDesc* __restrict__ vds, int check_done, int fin) {
   const VolDesc& vd = vds[blockIdx.y];
+  if (fin && (int)blockIdx.x == G::NCLS / G::CPC) {   // one block more: the previous update's finish
+    extern __shared__ float2 lds[];
+    vol_finish<UPD_FISTA>(vd, G::TC, reinterpret_cast<double*>(lds));
+    return;
+  }
   if (check_done && vd.st->done) return;
   constexpr int NX = G::NX, MX = G::MX, SX = G::SX, CPC = G::CPC, KMAX = G::KMAX, LSX = G::LSX;
   constexpr bool kFwd = MODE != COL_ADJ, kAdj = MODE != COL_FWD;

@@ -524,14 +524,16 @@ static mh3d_status launch_plane_fwd(mh3d_plan_t p, int src, const float* a) {
   return last_launch("k_user_plane_fwd");
 }
 
-static void launch_class(mh3d_plan_t p, int dir, int chk, int mode, const VolDesc* vd) {
-  user_launch_class(p->g.E, p->g.usr.cb, dir, dim3(p->g.ncls / p->g.cpw), dim3(p->L.T_uc), p->L.lds_class, p->ls, vd, chk, mode);
+// fin (here and in the column passes): with the finish of the previous update
+static void launch_class(mh3d_plan_t p, int dir, int chk, int mode, const VolDesc* vd, int fin = 0) {
+  user_launch_class(p->g.E, p->g.usr.cb, dir, dim3(p->g.ncls / p->g.cpw + fin), dim3(p->L.T_uc), p->L.lds_class, p->ls, vd, chk,
+                    mode, fin);
 }
 
 // mode: FWD_G, FWD_ADJ, FWD_G_AND_ADJ or FWD_RESID (where the decimated spectra go).
-static mh3d_status launch_class_fwd(mh3d_plan_t p, int chk, int mode) {
+static mh3d_status launch_class_fwd(mh3d_plan_t p, int chk, int mode, int fin = 0) {
   Timer t(p, KID_CLASS_FWD);
-  launch_class(p, CLS_FWD, chk, mode, p->vda);
+  launch_class(p, CLS_FWD, chk, mode, p->vda, fin);
   return last_launch("k_user_class (forward)");
 }
 // vd: a single-harmonic descriptor (per-harmonic back-projection) or NULL for the plan's.
@@ -546,9 +548,9 @@ static mh3d_status launch_class_adj(mh3d_plan_t p, int chk, const VolDesc* vd = 
 static bool fused_class(mh3d_plan_t p) { return !p->g.padded; }
 
 // mode: NRM_RESID, NRM_PLAIN or NRM_STORE.
-static mh3d_status launch_class_normal(mh3d_plan_t p, int chk, int mode) {
+static mh3d_status launch_class_normal(mh3d_plan_t p, int chk, int mode, int fin = 0) {
   Timer t(p, KID_CLASS_NORMAL);
-  launch_class(p, CLS_NORMAL, chk, mode, p->vda);
+  launch_class(p, CLS_NORMAL, chk, mode, p->vda, fin);
   return last_launch("k_user_class");
 }
 
@@ -617,11 +619,12 @@ static mh3d_status sep_plane_fwd(mh3d_plan_t p, int src, const float* a) {
   return last_launch("separable plane pass");
 }
 // mode: NRM_*, COL_FWD, COL_ADJ or COL_DATA (the last always on the run-time pass).
-static mh3d_status sep_column(mh3d_plan_t p, int chk, int mode) {
+static mh3d_status sep_column(mh3d_plan_t p, int chk, int mode, int fin = 0) {
   Timer t(p, mode == COL_FWD ? KID_CLASS_FWD : mode == COL_ADJ ? KID_CLASS_ADJ : mode == COL_DATA ? KID_AUX : KID_CLASS_NORMAL);
-  if (use_fast(p) && mode != COL_DATA) p->fast->cls(p->ls, p->vda, mode, chk);
+  if (use_fast(p) && mode != COL_DATA) p->fast->cls(p->ls, p->vda, mode, chk, fin);
   else
-    sep_launch_col(p->L.col_any, mode, dim3(p->L.col_blocks), dim3(p->L.T_col), p->L.lds_col_of(mode), p->ls, p->vda, nullptr, chk);
+    sep_launch_col(p->L.col_any, mode, dim3(p->L.col_blocks + fin), dim3(p->L.T_col), p->L.lds_col_of(mode), p->ls, p->vda,
+                   nullptr, chk, fin);
   return last_launch("separable column pass");
 }
 static mh3d_status sep_plane_adj_launch(mh3d_plan_t p, int out, AdjOut ao) {
@@ -669,42 +672,38 @@ static mh3d_status sep_adjoint_each(mh3d_plan_t p, const VolDesc* vd, int nv, fl
   }
   return last_launch("per-harmonic adjoint passes");
 }
-// the adjoint plane pass that ends a step (UPD_NORMAL: out, w = yin; UPD_FISTA), then the
-// one-block finish of its FP64 sums
+// The finish of a solver step's FP64 sums as a launch of its own
+static mh3d_status launch_finish(mh3d_plan_t p, int upd) {
+  Timer t(p, KID_UPDATE);
+  if (upd == UPD_NORMAL) k_vol_finish<UPD_NORMAL><<<1, 256, 0, p->ls>>>(p->vda, nullptr);
+  else k_vol_finish<UPD_FISTA><<<1, 256, 0, p->ls>>>(p->vda, nullptr);
+  return last_launch("k_vol_finish");
+}
+// the adjoint plane pass that ends a step (UPD_NORMAL: out, w = yin, and its finish; UPD_FISTA)
 static mh3d_status sep_adjoint_step(mh3d_plan_t p, int upd, float* o, const float* yin) {
   AdjOut ao;
   ao.out = o;
   ao.yin = yin;
   CHK(sep_plane_adj_launch(p, upd == UPD_NORMAL ? OUT_STEP_NORMAL : OUT_STEP_FISTA, ao));
-  Timer t(p, KID_UPDATE);
-  if (upd == UPD_NORMAL) k_vol_finish<UPD_NORMAL><<<1, 256, 0, p->ls>>>(p->vda, nullptr);
-  else k_vol_finish<UPD_FISTA><<<1, 256, 0, p->ls>>>(p->vda, nullptr);
-  return last_launch("k_vol_finish");
+  return upd == UPD_NORMAL ? launch_finish(p, upd) : MH3D_OK;
 }
 
 static mh3d_status launch_step_and_fwd(mh3d_plan_t p) {
-  {
-    Timer t(p, KID_PLANE_ADJ);
-    AdjOut ao;
-    ao.out = nullptr;
-    ao.yin = nullptr;
-    user_launch_step_and_fwd(p->g.usr.pcb < p->g.C, dim3(p->g.nx), dim3(p->L.T_ua), std::max(p->L.lds_uf, p->L.lds_ua), p->ls, p->vda, ao);
-    CHK(last_launch("k_user_step_and_fwd"));
-  }
-  Timer t(p, KID_UPDATE);
-  k_vol_finish<UPD_FISTA><<<1, 256, 0, p->ls>>>(p->vda, nullptr);
-  return last_launch("k_vol_finish");
+  Timer t(p, KID_PLANE_ADJ);
+  AdjOut ao;
+  ao.out = nullptr;
+  ao.yin = nullptr;
+  user_launch_step_and_fwd(p->g.usr.pcb < p->g.C, dim3(p->g.nx), dim3(p->L.T_ua), std::max(p->L.lds_uf, p->L.lds_ua), p->ls, p->vda,
+                           ao);
+  return last_launch("k_user_step_and_fwd");
 }
 
 // The adjoint plane pass, which ends the solver step on its voxels (u = b . v stays in
-// registers): out = (A^T A + lambda T^T T)(s w) (UPD_NORMAL, w = yin) or one accelerated
-// projected gradient update (UPD_FISTA); then the one-block finish of its FP64 sums.
+// registers): out = (A^T A + lambda T^T T)(s w) and its finish (UPD_NORMAL, w = yin) or one
+// accelerated projected gradient update (UPD_FISTA).
 static mh3d_status launch_adjoint_step(mh3d_plan_t p, int upd, float* o, const float* yin) {
   CHK(launch_plane_adj(p, upd == UPD_NORMAL ? OUT_STEP_NORMAL : OUT_STEP_FISTA, o, yin));
-  Timer t(p, KID_UPDATE);
-  if (upd == UPD_NORMAL) k_vol_finish<UPD_NORMAL><<<1, 256, 0, p->ls>>>(p->vda, nullptr);
-  else k_vol_finish<UPD_FISTA><<<1, 256, 0, p->ls>>>(p->vda, nullptr);
-  return last_launch("k_vol_finish");
+  return upd == UPD_NORMAL ? launch_finish(p, upd) : MH3D_OK;
 }
 
 // ---------------------------------------------------------------------------- state
@@ -1203,38 +1202,39 @@ extern "C" mh3d_status mh3d_power_iteration(mh3d_plan_t p, int32_t iters, uint64
 }
 
 // ============================================================================ solver
-// One accelerated projected gradient update of the plan's volume; buffers and the
-// step come from the device state, so the same launches serve every iteration.
+// One accelerated projected gradient update of the plan's volume, up to its finish; buffers and
+// the step come from the device state, so the same launches serve every iteration.
 // first: the first update of a solve call (with k_user_step_and_fwd the forward plane pass of
-// every later update ran in the previous update's last launch).
-static mh3d_status enqueue_update(mh3d_plan_t p, bool first) {
+// every later update ran in the previous update's last launch).  pending: the previous update's
+// finish is still to run, here with the column or class pass.
+static mh3d_status enqueue_update(mh3d_plan_t p, bool first, bool pending) {
   Timer t(p, KID_SOLVE_ITER);
+  const int src = pending ? SRC_FISTA_NEXT : SRC_FISTA_Y, fin = pending ? 1 : 0;
   if (p->compact) {
-    CHK(sep_plane_fwd(p, SRC_FISTA_Y, nullptr));
+    CHK(sep_plane_fwd(p, src, nullptr));
     if (p->g.padded) {
-      CHK(sep_column(p, 1, COL_FWD));
+      CHK(sep_column(p, 1, COL_FWD, fin));
       CHK(launch_small_inv(p, EPI_RESID_BACK, nullptr));   // residual on the field of view
       CHK(sep_column(p, 1, COL_ADJ));
     } else {
-      CHK(sep_column(p, 1, NRM_RESID));   // against the data's spectra, held in G'
+      CHK(sep_column(p, 1, NRM_RESID, fin));   // against the data's spectra, held in G'
     }
     return sep_adjoint_step(p, UPD_FISTA, nullptr, nullptr);
   }
-  if (first || !step_and_fwd(p)) CHK(launch_plane_fwd(p, SRC_FISTA_Y, nullptr));
+  if (first || !step_and_fwd(p)) CHK(launch_plane_fwd(p, src, nullptr));
   if (fused_class(p)) {
-    CHK(launch_class_normal(p, 1, NRM_RESID));   // against the data's spectra, held in G'
+    CHK(launch_class_normal(p, 1, NRM_RESID, fin));   // against the data's spectra, held in G'
   } else {
     if (p->g.padded) {
-      CHK(launch_class_fwd(p, 1, FWD_G));
+      CHK(launch_class_fwd(p, 1, FWD_G, fin));
       CHK(launch_small_inv(p, EPI_RESID_BACK, nullptr));   // residual on the field of view
     } else {
-      CHK(launch_class_fwd(p, 1, FWD_RESID));   // residual spectrum against the data's, held in G
+      CHK(launch_class_fwd(p, 1, FWD_RESID, fin));   // residual spectrum against the data's, held in G
     }
     CHK(launch_class_adj(p, 1));
   }
   if (step_and_fwd(p)) return launch_step_and_fwd(p);
-  CHK(launch_adjoint_step(p, UPD_FISTA, nullptr, nullptr));
-  return MH3D_OK;
+  return launch_adjoint_step(p, UPD_FISTA, nullptr, nullptr);
 }
 
 static mh3d_status ensure_hist(mh3d_plan_t p, int n) {
@@ -1347,7 +1347,8 @@ static mh3d_status run_updates(mh3d_plan_t p, const mh3d_solve_opts* opts, DevSt
   int issued = 0;
   while (issued < opts->max_iter) {
     const int n = std::min(chunk, opts->max_iter - issued);
-    for (int i = 0; i < n; ++i) CHK(enqueue_update(p, issued + i == 0));
+    for (int i = 0; i < n; ++i) CHK(enqueue_update(p, issued + i == 0, i > 0));
+    CHK(launch_finish(p, UPD_FISTA));
     issued += n;
     CHK(read_state(p, h));
     if (h.done) break;
@@ -1434,6 +1435,7 @@ struct mh3d_batch_s {
   // blocks (the others), per-volume
   int2* tasks[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
   int ntask[5] = {0, 0, 0, 0, 0};
+  int nfin[5] = {0, 0, 0, 0, 0};   // finishes after the tasks of a table
   int T_plane = 0, T_col = 0, T_small = 0;
   bool col_any = false;
   size_t lds_plane = 0, lds_col = 0, lds_col_resid = 0, lds_col_plain = 0, lds_small = 0;
@@ -1486,7 +1488,7 @@ extern "C" mh3d_status mh3d_batch_create(int32_t n, const mh3d_plan_t* plans, mh
   b->plans.assign(plans, plans + n);
   for (auto* p : b->plans) p->batch_refs++;
   b->stream = plans[0]->stream;
-  std::vector<int2> t[5];
+  std::vector<int2> t[5], fin[5];   // fin: the finishes that ride with a column pass, after its tasks
   for (int v = 0; v < n; ++v) {
     const mh3d_plan_t p = plans[v];
     for (int i = 0; i < p->g.nx * p->g.sy; ++i) t[0].push_back(make_int2(v, i));
@@ -1496,6 +1498,7 @@ extern "C" mh3d_status mh3d_batch_create(int32_t n, const mh3d_plan_t* plans, mh
     if (p->g.padded)
       for (int i = 0; i < p->g.K * (p->g.mx / p->g.xb); ++i) t[2].push_back(make_int2(v, i));
     t[4].push_back(make_int2(v, 0));
+    fin[p->g.padded ? 1 : 3].push_back(make_int2(v, -1));
     b->T_plane = std::max(b->T_plane, p->L.T_sep);
     b->T_col = std::max(b->T_col, p->L.T_col);
     b->col_any = b->col_any || p->L.col_any;
@@ -1512,6 +1515,8 @@ extern "C" mh3d_status mh3d_batch_create(int32_t n, const mh3d_plan_t* plans, mh
   for (int i = 0; i < 5; ++i) {
     b->ntask[i] = (int)t[i].size();
     if (t[i].empty()) continue;   // e.g. no padded volume
+    b->nfin[i] = (int)fin[i].size();
+    t[i].insert(t[i].end(), fin[i].begin(), fin[i].end());
     if (hipMalloc(&b->tasks[i], sizeof(int2) * t[i].size()) != hipSuccess) return bail(fail(MH3D_ERR_OOM, "batch tasks"));
     if (hipMemcpy(b->tasks[i], t[i].data(), sizeof(int2) * t[i].size(), hipMemcpyHostToDevice) != hipSuccess)
       return bail(fail(MH3D_ERR_HIP, "upload of batch tasks failed"));
@@ -1530,14 +1535,16 @@ static mh3d_status batch_upload(mh3d_batch_t b, int v) {
 // The column passes of every volume: one fused launch for the volumes without padding,
 // then forward column pass, crop (small-grid pass) and adjoint column pass for the padded
 // ones.  mode: NRM_RESID (updates) or NRM_PLAIN (power iteration).
-static mh3d_status batch_column(mh3d_batch_t b, hipStream_t st, int mode) {
+// fin: with the finish of the previous update.
+static mh3d_status batch_column(mh3d_batch_t b, hipStream_t st, int mode, bool fin) {
   if (b->ntask[3]) {
-    sep_launch_col(b->col_any, mode, dim3(b->ntask[3]), dim3(b->T_col), mode == NRM_RESID ? b->lds_col_resid : b->lds_col_plain, st,
-               b->vds, b->tasks[3], 1);
+    sep_launch_col(b->col_any, mode, dim3(b->ntask[3] + (fin ? b->nfin[3] : 0)), dim3(b->T_col),
+                   mode == NRM_RESID ? b->lds_col_resid : b->lds_col_plain, st, b->vds, b->tasks[3], 1, fin);
     CHK(last_launch("k_sep_col (batch)"));
   }
   if (b->ntask[1]) {
-    sep_launch_col(b->col_any, COL_FWD, dim3(b->ntask[1]), dim3(b->T_col), b->lds_col, st, b->vds, b->tasks[1], 1);
+    sep_launch_col(b->col_any, COL_FWD, dim3(b->ntask[1] + (fin ? b->nfin[1] : 0)), dim3(b->T_col), b->lds_col, st, b->vds,
+                   b->tasks[1], 1, fin);
     CHK(last_launch("k_sep_col (batch, forward)"));
     sep_launch_small_inv(dim3(b->ntask[2]), dim3(b->T_small), b->lds_small, st, b->vds, b->tasks[2], nullptr,
                          mode == NRM_RESID ? EPI_RESID_BACK : EPI_BACK);
@@ -1549,26 +1556,28 @@ static mh3d_status batch_column(mh3d_batch_t b, hipStream_t st, int mode) {
 }
 
 // One update of every volume of the batch over the task tables: forward plane pass, column
-// passes, adjoint plane pass ending in the step, finish.
-static mh3d_status batch_update(mh3d_batch_t b, hipStream_t st) {
-  sep_launch_plane_fwd(dim3(b->ntask[0]), dim3(b->T_plane), b->lds_plane, st, b->vds, b->tasks[0], nullptr, SRC_FISTA_Y);
+// passes (pending: with the previous update's finish), adjoint plane pass ending in the step;
+// last: and its finish.
+static mh3d_status batch_update(mh3d_batch_t b, hipStream_t st, bool pending, bool last) {
+  sep_launch_plane_fwd(dim3(b->ntask[0]), dim3(b->T_plane), b->lds_plane, st, b->vds, b->tasks[0], nullptr,
+                       pending ? SRC_FISTA_NEXT : SRC_FISTA_Y);
   CHK(last_launch("k_sep_plane_fwd (batch)"));
-  CHK(batch_column(b, st, NRM_RESID));
+  CHK(batch_column(b, st, NRM_RESID, pending));
   AdjOut ao;
   ao.out = nullptr;
   ao.yin = nullptr;
   sep_launch_plane_adj(OUT_STEP_FISTA, dim3(b->ntask[0]), dim3(b->T_plane), b->lds_plane, st, b->vds, b->tasks[0], ao);
   CHK(last_launch("k_sep_plane_adj (batch)"));
+  if (!last) return MH3D_OK;
   k_vol_finish<UPD_FISTA><<<dim3(b->ntask[4]), dim3(256), 0, st>>>(b->vds, b->tasks[4]);
-  CHK(last_launch("k_vol_finish (batch)"));
-  return MH3D_OK;
+  return last_launch("k_vol_finish (batch)");
 }
 
 // One power-iteration step of every volume: w_{t+1} = N (s w_t), w_t in rho[k & 1].
 static mh3d_status batch_power_step(mh3d_batch_t b, hipStream_t st) {
   sep_launch_plane_fwd(dim3(b->ntask[0]), dim3(b->T_plane), b->lds_plane, st, b->vds, b->tasks[0], nullptr, SRC_SCALED);
   CHK(last_launch("k_sep_plane_fwd (batch power)"));
-  CHK(batch_column(b, st, NRM_PLAIN));
+  CHK(batch_column(b, st, NRM_PLAIN, false));
   AdjOut ao;
   ao.out = nullptr;
   ao.yin = nullptr;
@@ -1652,7 +1661,7 @@ extern "C" mh3d_status mh3d_solve_batch(mh3d_batch_t b, const float* const* d, f
     if (!b->cap_stream) HIPCHK(hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking));
     HIPCHK(hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal));
     mh3d_status s = MH3D_OK;
-    for (int i = 0; i < chunk && s == MH3D_OK; ++i) s = batch_update(b, b->cap_stream);
+    for (int i = 0; i < chunk && s == MH3D_OK; ++i) s = batch_update(b, b->cap_stream, i > 0, i + 1 == chunk);
     hipGraph_t gr = nullptr;
     hipError_t e = hipStreamEndCapture(b->cap_stream, &gr);
     if (s != MH3D_OK) { if (gr) (void)hipGraphDestroy(gr); return s; }

@@ -21,7 +21,7 @@ struct FastOps {
   int nbp, ncls_blocks, tc;
   size_t lds_plane, lds_class;
   void (*plane_fwd)(hipStream_t, const VolDesc*, int src, const float* a);
-  void (*cls)(hipStream_t, const VolDesc*, int mode, int chk);
+  void (*cls)(hipStream_t, const VolDesc*, int mode, int chk, int fin);
   void (*plane_adj)(hipStream_t, const VolDesc*, int out, AdjOut ao);
   void (*adj_and_store)(hipStream_t, const VolDesc*, AdjOut ao, float* d, int nsmall, int xb);
   void (*small_inv)(hipStream_t, const VolDesc*, float* d, int nsmall, int xb);
@@ -40,9 +40,10 @@ extern const int kFastCount;
 // tasks: the task table of a batch, or NULL (descriptor blockIdx.y, block blockIdx.x).
 void sep_launch_plane_fwd(dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, const int2* tasks,
                           const float* a, int src);
-// any: the general form (harmonics in groups, any number of x aliases)
+// fin: with the finish of the previous update (one block more; in a batch the table's tasks of
+// local block -1).  any: the general form (harmonics in groups, any number of x aliases)
 void sep_launch_col(bool any, int mode, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd,
-                    const int2* tasks, int chk);
+                    const int2* tasks, int chk, int fin = 0);
 void sep_launch_plane_adj(int out, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, const int2* tasks,
                           AdjOut ao);
 void sep_launch_adj_and_store(dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, AdjOut ao, float* d,
@@ -64,12 +65,12 @@ void user_launch_plane_adj(bool rounds, int out, dim3 grid, dim3 block, size_t l
 void user_launch_step_and_fwd(bool rounds, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, AdjOut ao);
 void user_launch_adj_and_store(bool rounds, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, AdjOut ao,
                                float* d);
-void user_launch_class1(int cb, int dir, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, int chk, int mode);
-void user_launch_class2(int cb, int dir, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, int chk, int mode);
-void user_launch_class4(int cb, int dir, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, int chk, int mode);
+void user_launch_class1(int cb, int dir, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, int chk, int mode, int fin);
+void user_launch_class2(int cb, int dir, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, int chk, int mode, int fin);
+void user_launch_class4(int cb, int dir, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, int chk, int mode, int fin);
 void user_launch_class3689(int E, int cb, int dir, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, int chk,
-                           int mode);
+                           int mode, int fin);
 void user_launch_class(int E, int cb, int dir, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, int chk,
-                       int mode);
+                       int mode, int fin);
 
 }  // namespace mh3d

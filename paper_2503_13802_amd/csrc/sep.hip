@@ -9,15 +9,15 @@ void sep_launch_plane_fwd(dim3 grid, dim3 block, size_t lds, hipStream_t s, cons
 }
 
 void sep_launch_col(bool any, int mode, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd,
-                    const int2* tasks, int chk) {
-  if (any) k_sep_col<-1><<<grid, block, lds, s>>>(vd, tasks, mode, chk);
+                    const int2* tasks, int chk, int fin) {
+  if (any) k_sep_col<-1><<<grid, block, lds, s>>>(vd, tasks, mode, chk, fin);
   else switch (mode) {
-    case NRM_RESID: k_sep_col<NRM_RESID><<<grid, block, lds, s>>>(vd, tasks, mode, chk); break;
-    case NRM_PLAIN: k_sep_col<NRM_PLAIN><<<grid, block, lds, s>>>(vd, tasks, mode, chk); break;
-    case NRM_STORE: k_sep_col<NRM_STORE><<<grid, block, lds, s>>>(vd, tasks, mode, chk); break;
-    case COL_FWD: k_sep_col<COL_FWD><<<grid, block, lds, s>>>(vd, tasks, mode, chk); break;
-    case COL_ADJ: k_sep_col<COL_ADJ><<<grid, block, lds, s>>>(vd, tasks, mode, chk); break;
-    default: k_sep_col<COL_DATA><<<grid, block, lds, s>>>(vd, tasks, mode, chk); break;
+    case NRM_RESID: k_sep_col<NRM_RESID><<<grid, block, lds, s>>>(vd, tasks, mode, chk, fin); break;
+    case NRM_PLAIN: k_sep_col<NRM_PLAIN><<<grid, block, lds, s>>>(vd, tasks, mode, chk, fin); break;
+    case NRM_STORE: k_sep_col<NRM_STORE><<<grid, block, lds, s>>>(vd, tasks, mode, chk, fin); break;
+    case COL_FWD: k_sep_col<COL_FWD><<<grid, block, lds, s>>>(vd, tasks, mode, chk, fin); break;
+    case COL_ADJ: k_sep_col<COL_ADJ><<<grid, block, lds, s>>>(vd, tasks, mode, chk, fin); break;
+    default: k_sep_col<COL_DATA><<<grid, block, lds, s>>>(vd, tasks, mode, chk, fin); break;
   }
 }
 

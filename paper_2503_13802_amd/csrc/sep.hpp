@@ -267,7 +267,7 @@ __device__ __forceinline__ void sep_plane_fwd_body(const VolDesc& vd, int lb, co
     column(c, [&](int qyp, int qzp, auto& add) { from(qyp, qzp, 0, add); });
 }
 
-// src: SRC_PLAIN, SRC_FISTA_Y (reads y^k of the volume, a ignored) or SRC_SCALED (a = NULL:
+// src: SRC_PLAIN, SRC_FISTA_Y / SRC_FISTA_NEXT (y^k, y^{k+1} of the volume, a ignored) or SRC_SCALED (a = NULL:
 // rho[k & 1]); the solver's sources are skipped once the volume's solve is done.
 static __global__ __launch_bounds__(512, 6) void k_sep_plane_fwd(const VolDesc* __restrict__ vds, const int2* __restrict__ tasks,
                                                        const float* __restrict__ a, int src) {
@@ -275,12 +275,13 @@ static __global__ __launch_bounds__(512, 6) void k_sep_plane_fwd(const VolDesc* 
   sep_task(tasks, v, lb);
   const VolDesc& vd = vds[v];
   if (src != SRC_PLAIN) {
-    const float *v0 = src == SRC_FISTA_Y ? vd.y[0] : vd.rho[0], *v1 = src == SRC_FISTA_Y ? vd.y[1] : vd.rho[1];
+    const bool fista = src != SRC_SCALED;
+    const float *v0 = fista ? vd.y[0] : vd.rho[0], *v1 = fista ? vd.y[1] : vd.rho[1];
     const DevState* st = vd.st;
     pin(v0, v1, st, T);
-    const int done = st->done, k = st->k;
+    const int done = st->done, k = st->k + (src == SRC_FISTA_NEXT);
     if (done) return;
-    if (src == SRC_FISTA_Y || !a) a = (k & 1) ? v1 : v0;
+    if (fista || !a) a = (k & 1) ? v1 : v0;
   }
   sep_plane_fwd_body(vd, lb, a, src, T);
 }
@@ -594,14 +595,20 @@ __device__ __forceinline__ int sep_col_block(int b, int nb) {
   return b < 8 * per ? (b & 7) * per + (b >> 3) : b;
 }
 
-// grid.y > 1 runs one descriptor per y-block (the back-projections of single harmonics).
+// grid.y > 1 runs one descriptor per y-block (the back-projections of single harmonics).  fin: the
+// last block (in a batch the tasks of local block -1) finishes the previous update.
 template <int MODE>
 static __global__ __launch_bounds__(512, MODE < 0 ? 4 : 6) void k_sep_col(const VolDesc* __restrict__ vds, const int2* __restrict__ tasks, int mode,
-                                                    int check_done) {
+                                                    int check_done, int fin) {
   int lb, v, T = blockDim.x;
   sep_task(tasks, v, lb);
   const VolDesc& vd = vds[v];
-  if (!tasks) lb = sep_col_block(lb, gridDim.x);
+  if (fin && (tasks ? lb < 0 : lb == (int)gridDim.x - 1)) {
+    extern __shared__ float2 lds[];
+    vol_finish<UPD_FISTA>(vd, T, reinterpret_cast<double*>(lds));
+    return;
+  }
+  if (!tasks) lb = sep_col_block(lb, gridDim.x - fin);
   if (check_done && vd.st->done) return;
   pin(T);
   sep_col_body<MODE>(vd, lb, mode, T);

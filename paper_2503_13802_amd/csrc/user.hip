@@ -32,12 +32,12 @@ void user_launch_adj_and_store(bool rounds, dim3 grid, dim3 block, size_t lds, h
 
 // the class passes compile in units of their own
 void user_launch_class(int E, int cb, int dir, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, int chk,
-                       int mode) {
+                       int mode, int fin) {
   switch (E) {
-    case 1: user_launch_class1(cb, dir, grid, block, lds, s, vd, chk, mode); break;
-    case 2: user_launch_class2(cb, dir, grid, block, lds, s, vd, chk, mode); break;
-    case 4: user_launch_class4(cb, dir, grid, block, lds, s, vd, chk, mode); break;
-    default: user_launch_class3689(E, cb, dir, grid, block, lds, s, vd, chk, mode); break;
+    case 1: user_launch_class1(cb, dir, grid, block, lds, s, vd, chk, mode, fin); break;
+    case 2: user_launch_class2(cb, dir, grid, block, lds, s, vd, chk, mode, fin); break;
+    case 4: user_launch_class4(cb, dir, grid, block, lds, s, vd, chk, mode, fin); break;
+    default: user_launch_class3689(E, cb, dir, grid, block, lds, s, vd, chk, mode, fin); break;
   }
 }
 

@@ -144,20 +144,21 @@ __device__ __forceinline__ void user_plane_fwd_body(const VolDesc& vd, int x, in
   }
 }
 
-// grid = components x ps x nx (a raw source has one component).  SRC_FISTA_Y reads y^k of the
-// volume (a ignored); the solver's sources are skipped once the volume's solve is done.
+// grid = components x ps x nx (a raw source has one component).  SRC_FISTA_Y and
+// SRC_FISTA_NEXT read y^k and y^{k+1} of the volume (a ignored); the solver's sources are skipped once the volume's solve is done.
 template <bool RAW>
 static __global__ __launch_bounds__(512, 4) void k_user_plane_fwd(const VolDesc* __restrict__ vds, const float* __restrict__ a,
                                                                   int src) {
   const VolDesc& vd = vds[0];
   int nx = vd.g.nx, per = vd.g.ps * nx, T = blockDim.x;
-  const float *v0 = src == SRC_FISTA_Y ? vd.y[0] : vd.rho[0], *v1 = src == SRC_FISTA_Y ? vd.y[1] : vd.rho[1];
+  const bool fista = src == SRC_FISTA_Y || src == SRC_FISTA_NEXT;
+  const float *v0 = fista ? vd.y[0] : vd.rho[0], *v1 = fista ? vd.y[1] : vd.rho[1];
   const DevState* st = vd.st;
   pin(nx, per, T, v0, v1, st);
-  if (src == SRC_FISTA_Y || src == SRC_SCALED) {
-    const int done = st->done, k = st->k;
+  if (fista || src == SRC_SCALED) {
+    const int done = st->done, k = st->k + (src == SRC_FISTA_NEXT);
     if (done) return;
-    if (src == SRC_FISTA_Y || !a) a = (k & 1) ? v1 : v0;
+    if (fista || !a) a = (k & 1) ? v1 : v0;
   }
   const int comp = blockIdx.x / per, r = blockIdx.x - comp * per, h = r / nx;
   user_plane_fwd_body<RAW>(vd, plane_of_block(r - h * nx, nx), h, comp, 1, a, src == SRC_SCALED, T);

@@ -293,33 +293,38 @@ __device__ __forceinline__ void user_class_body(const VolDesc& vd, int lb, int m
   }
 }
 
-// grid = ncls / cpw blocks.  check_done skips the launch once the volume's solve is done.
+// grid = ncls / cpw blocks, fin: and one that finishes the previous update.  check_done skips the launch once the volume's solve is done.
 // XCD-aware: consecutive class blocks run on one XCD, so the short runs of G, G' and the
 // class-layout spectra that neighbouring blocks share are fetched into one L2.
 template <int E, int CB, int DIR>
-static __global__ __launch_bounds__(1024) void k_user_class(const VolDesc* __restrict__ vds, int check_done, int mode) {
+static __global__ __launch_bounds__(1024) void k_user_class(const VolDesc* __restrict__ vds, int check_done, int mode, int fin) {
   const VolDesc& vd = vds[0];
   int T = blockDim.x;
+  if (fin && blockIdx.x == gridDim.x - 1) {
+    extern __shared__ float2 lds[];
+    vol_finish<UPD_FISTA>(vd, T, reinterpret_cast<double*>(lds));
+    return;
+  }
   if (check_done && vd.st->done) return;
   pin(T);
-  user_class_body<E, CB, DIR>(vd, plane_of_block(blockIdx.x, gridDim.x), mode, T);
+  user_class_body<E, CB, DIR>(vd, plane_of_block(blockIdx.x, gridDim.x - fin), mode, T);
 }
 
 // The launchers of one split E (all its component counts and directions).
 template <int E, int CB>
-static void class_dir(int dir, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, int chk, int mode) {
-  if (dir == CLS_FWD) k_user_class<E, CB, CLS_FWD><<<grid, block, lds, s>>>(vd, chk, mode);
-  else if (dir == CLS_ADJ) k_user_class<E, CB, CLS_ADJ><<<grid, block, lds, s>>>(vd, chk, mode);
-  else k_user_class<E, CB, CLS_NORMAL><<<grid, block, lds, s>>>(vd, chk, mode);
+static void class_dir(int dir, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, int chk, int mode, int fin) {
+  if (dir == CLS_FWD) k_user_class<E, CB, CLS_FWD><<<grid, block, lds, s>>>(vd, chk, mode, fin);
+  else if (dir == CLS_ADJ) k_user_class<E, CB, CLS_ADJ><<<grid, block, lds, s>>>(vd, chk, mode, fin);
+  else k_user_class<E, CB, CLS_NORMAL><<<grid, block, lds, s>>>(vd, chk, mode, fin);
 }
 template <int E>
-static void class_cb(int cb, int dir, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, int chk, int mode) {
+static void class_cb(int cb, int dir, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, int chk, int mode, int fin) {
   if constexpr (user_all_at_once(E)) {
-    if (cb == 2) return class_dir<E, 2>(dir, grid, block, lds, s, vd, chk, mode);
-    if (cb == 3) return class_dir<E, 3>(dir, grid, block, lds, s, vd, chk, mode);
+    if (cb == 2) return class_dir<E, 2>(dir, grid, block, lds, s, vd, chk, mode, fin);
+    if (cb == 3) return class_dir<E, 3>(dir, grid, block, lds, s, vd, chk, mode, fin);
   }
-  if (cb) class_dir<E, 1>(dir, grid, block, lds, s, vd, chk, mode);
-  else class_dir<E, 0>(dir, grid, block, lds, s, vd, chk, mode);
+  if (cb) class_dir<E, 1>(dir, grid, block, lds, s, vd, chk, mode, fin);
+  else class_dir<E, 0>(dir, grid, block, lds, s, vd, chk, mode, fin);
 }
 
 }  // namespace mh3d
