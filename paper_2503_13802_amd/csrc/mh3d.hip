@@ -118,13 +118,15 @@ static void derive_sep(Geo& g, Launch& L) {
   L.lds_col_plain = g.sx <= 4 ? fixed : L.lds_col;
   L.T_col = std::max(128, (s.cpc * g.mx + 63) / 64 * 64);
   L.col_blocks = (g.ncls + s.cpc - 1) / s.cpc;
-  // plane and small-grid blocks: four points per thread (two threads per radix-8 butterfly:
-  // the loads, the splits and the stores are shared by more threads than the stages need)
-  L.T_sep = std::min(512, std::max(128, pow2_at_least(s.np * g.nz / 4)));
+  // plane blocks: two points per thread, small-grid blocks: one (four threads and more per radix-8
+  // butterfly: the loads, the splits, the crop and the solver step are shared by more threads
+  // than the stages need).  25 padded updates at 64^3 with four points per thread 1212 us,
+  // so 1138; A and A^T at 72 x 108 x 48 36.3, 35.7
+  L.T_sep = std::min(512, std::max(128, pow2_at_least(s.np * g.nz / 2)));
   L.lds_sep = sizeof(float2) * ((size_t)g.nz + g.my + 2 * (size_t)s.pbuf);
   s.lsmz = pad_odd(g.mz);
   s.nxb = g.mx / g.xb;
-  L.T_small = std::min(512, std::max(256, pow2_at_least(g.spairs * g.mz / 4)));
+  L.T_small = std::min(512, std::max(256, pow2_at_least(g.spairs * g.mz)));
   s.d_sy = make_mdiv(g.sy); s.d_np = make_mdiv(s.np); s.d_nzh = make_mdiv(g.nzh); s.d_mzh = make_mdiv(g.mzh);
   s.d_nzv = make_mdiv(g.nz / (g.nz % 4 ? 2 : 4));
   s.d_mz = make_mdiv(g.mz); s.d_mzv = make_mdiv(g.mz / (g.mz % 4 ? 2 : 4));

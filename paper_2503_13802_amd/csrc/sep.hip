@@ -23,9 +23,10 @@ void sep_launch_col(bool any, int mode, dim3 grid, dim3 block, size_t lds, hipSt
 
 void sep_launch_plane_adj(int out, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, const int2* tasks,
                           AdjOut ao) {
-  if (out == OUT_STEP_NORMAL) k_sep_plane_adj<OUT_STEP_NORMAL><<<grid, block, lds, s>>>(vd, tasks, ao);
-  else if (out == OUT_STEP_FISTA) k_sep_plane_adj<OUT_STEP_FISTA><<<grid, block, lds, s>>>(vd, tasks, ao);
-  else k_sep_plane_adj<OUT_SCALE_B><<<grid, block, lds, s>>>(vd, tasks, ao);
+  if (out == OUT_STEP_NORMAL) k_sep_plane_adj<OUT_STEP_NORMAL, 6><<<grid, block, lds, s>>>(vd, tasks, ao);
+  else if (out == OUT_STEP_FISTA && grid.x > 512) k_sep_plane_adj<OUT_STEP_FISTA, 6><<<grid, block, lds, s>>>(vd, tasks, ao);
+  else if (out == OUT_STEP_FISTA) k_sep_plane_adj<OUT_STEP_FISTA, 5><<<grid, block, lds, s>>>(vd, tasks, ao);
+  else k_sep_plane_adj<OUT_SCALE_B, 6><<<grid, block, lds, s>>>(vd, tasks, ao);
 }
 
 void sep_launch_adj_and_store(dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, AdjOut ao, float* d,

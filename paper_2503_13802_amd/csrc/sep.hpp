@@ -940,8 +940,12 @@ __device__ __forceinline__ void sep_plane_adj_body(const VolDesc& vd, int lb, co
 }
 
 // grid.y > 1 (OUT_SCALE_B only): descriptor y and output volume y of consecutive volumes.
-template <int OUT>
-static __global__ __launch_bounds__(512, 5) void k_sep_plane_adj(const VolDesc* __restrict__ vds, const int2* __restrict__ tasks,
+// W waves per SIMD: a solver step takes 85 registers, which leaves a CU two 512-thread blocks.
+// With more blocks than that fills (512), the form held to 80 registers (five of them
+// spilled) runs three: 672 blocks of a batch of four 26.5 us with two, 22.1 with three; 128
+// blocks at 64^3, padded, 10.5 and 11.1.
+template <int OUT, int W>
+static __global__ __launch_bounds__(512, W) void k_sep_plane_adj(const VolDesc* __restrict__ vds, const int2* __restrict__ tasks,
                                                        AdjOut ao) {
   int lb, v, T = blockDim.x;
   sep_task(tasks, v, lb);
