@@ -264,7 +264,7 @@ mh3d_status mh3d_autotune(mh3d_plan_t plan, const char* cache_path, mh3d_tiles* 
  * (volume, block) pairs, a chunk of updates is captured once as a hipGraph and
  * replayed, and each volume stops at its own r_k <= rel_tol (its blocks exit at
  * once afterwards).  Results equal mh3d_solve on each plan with the same options
- * (bitwise on the general passes; a plan whose own solves run the compile-time passes
+ * (bitwise on the run-time separable passes; a plan whose own solves run the compile-time ones
  * agrees to FP32 rounding).
  * A plan may belong to one batch at a time and must not be used concurrently. */
 typedef struct mh3d_batch_s* mh3d_batch_t;

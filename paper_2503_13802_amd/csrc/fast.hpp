@@ -306,10 +306,12 @@ __device__ __forceinline__ int fast_col_block(int b) {
 template <class G, int MODE>
 static __global__ __launch_bounds__(G::TC) void k_fast_col(const VolDesc* __restrict__ vds, int check_done, int fin) {
   const VolDesc& vd = vds[blockIdx.y];
-  if (fin && (int)blockIdx.x == G::NCLS / G::CPC) {   // one block more: the previous update's finish
-    extern __shared__ float2 lds[];
-    vol_finish<UPD_FISTA>(vd, G::TC, reinterpret_cast<double*>(lds));
-    return;
+  if constexpr (MODE == NRM_RESID) {   // the solver's: one block more, the previous update's finish
+    if (fin && (int)blockIdx.x == G::NCLS / G::CPC) {
+      extern __shared__ float2 lds[];
+      vol_finish<UPD_FISTA>(vd, G::TC, reinterpret_cast<double*>(lds));
+      return;
+    }
   }
   if (check_done && vd.st->done) return;
   constexpr int NX = G::NX, MX = G::MX, SX = G::SX, CPC = G::CPC, KMAX = G::KMAX, LSX = G::LSX;
@@ -769,7 +771,7 @@ static __global__ __launch_bounds__(G::TP) void k_fast_small_inv(const VolDesc* 
 
 // ============================================================================ small-grid forward
 // Block (k, x'-block of XB planes): the small-grid spectra of the portraits r of those
-// planes (A^T alone and the back-projections start here), written as k_small_fwd writes
+// planes (A^T alone and the back-projections start here), written as k_sep_small_fwd writes
 // them, G'[k][x'-block][column][x'-in-block]: rows packed in pairs, R2C along z' (the
 // pairs split into their half spectra by the first stage of the y' transform), the
 // length-my transform along y'.

@@ -2041,7 +2041,7 @@ static bool apply_cached(mh3d_plan_t p, const char* cache_path, const std::strin
   return true;
 }
 
-// Tiles of the general passes: the cache's entry, else timed (class tiles, then the
+// Tiles of the run-time passes: the cache's entry, else timed (class tiles, then the
 // small-grid tiles, the plane split and the merged launch's threads, then the solver's
 // split) and stored.
 static mh3d_status tune_general(mh3d_plan_t p, const char* cache_path, mh3d_tiles* tiles, double* us_out) {
@@ -2155,10 +2155,10 @@ static mh3d_status set_fast_on(mh3d_plan_t p, bool on) {
 }
 
 // Plans on the compile-time passes take only xb from the tiles in their operator calls
-// and solves, but a batch runs such a plan's volume on the general passes.  So the
-// general tiles come first (timed with the compile-time passes switched off, stored under
-// the general key), then xb alone on the compile-time A + A^T; the "|compiled" entry is
-// the general tiles with that xb (a batch's general small-grid pass runs that xb too).
+// and solves, but a batch runs such a plan's volume on the run-time passes.  So their
+// tiles come first (timed with the compile-time passes switched off, stored under
+// the plain key), then xb alone on the compile-time A + A^T; the "|compiled" entry is
+// those tiles with that xb (a batch's small-grid pass runs that xb too).
 extern "C" mh3d_status mh3d_autotune(mh3d_plan_t p, const char* cache_path, mh3d_tiles* tiles, double* us_out) {
   CHK(check_plan(p));
   if (p->batch_refs) return fail(MH3D_ERR_INVALID, "the plan belongs to a batch; tune it before creating the batch");
