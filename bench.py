@@ -66,7 +66,7 @@ def shape_terms(w):
 
 
 def fast_kernel_bytes(w):
-    """Algorithmic bytes per launch of the compile-time (separable) passes of A then A^T:
+    """Algorithmic bytes per launch of the separable passes (analytic PSFs) of A then A^T:
       plane_fwd      rho, b (8N) + the folded shares written (8 sy nx ncls) + the y-residue
                      table (8 sy my (nz/2+1))
       class_normal   (the column pass) shares read (8 sy nx ncls) + Q written (8 nx ncls)
@@ -85,7 +85,7 @@ def fast_kernel_bytes(w):
 
 
 def general_kernel_bytes(w, compact=True, ncomp=1):
-    """Algorithmic bytes per launch of the general passes (kernels.hpp): spectra of
+    """Algorithmic bytes per launch of the user-PSF passes (user.hpp): spectra of
     beta_H = 4 (compact) or 8 bytes per element in the class layout."""
     t = shape_terms(w)
     bh = 4 if compact else 8
@@ -361,10 +361,10 @@ def operator_leg(w, steps, warmup, tile_cache, oracle_check=True, repeats=1):
     sec_sep = time_steps(separate, steps, warmup, repeats)
     with Quiet():
         pass_us = plan.time_passes(reps=200)
-    byte_map = fast_kernel_bytes(w) if separable else general_kernel_bytes(w)
+    byte_map = fast_kernel_bytes(w)
     kern, kbytes, ks = roofline(pass_us, byte_map, ["plane_fwd", "class_normal", "adj_and_store"])
     achieved = kbytes / ks / 1e9
-    op_b = operator_bytes(w, separable)
+    op_b = operator_bytes(w)
     out = {"rate": 1.0 / sec, "ms_per_step": 1e3 * sec, "separate_rate": 1.0 / sec_sep,
            "roofline": {"bound": "hbm", "kernel": kern, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                         "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
@@ -375,7 +375,7 @@ def operator_leg(w, steps, warmup, tile_cache, oracle_check=True, repeats=1):
            "kernel_bytes_per_launch": byte_map,
            "operator_bytes_per_application": op_b,
            "operator_GBps": round(2 * op_b / sec / 1e9, 1),
-           "path": "compile-time separable passes" if separable else "general passes",
+           "path": "compile-time separable passes" if separable else "run-time separable passes",
            "plan_s": round(plan_s, 3), "tiles": tuning}
     if oracle_check:
         from oracle import model as om
