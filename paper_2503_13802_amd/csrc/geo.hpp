@@ -37,15 +37,30 @@ inline FastDiv make_fastdiv(uint32_t d) {
   return f;
 }
 
-// n / d for 0 <= n < 2^16 with n * d < 2^24, by one 24-bit high multiply (full rate, where
+// n / d for 0 <= n < 2^16 with n * d <= 2^24, by one 24-bit high multiply (full rate, where
 // a 32-bit one takes four times as long): with m = ceil(2^24 / d) and e = m d - 2^24 < d
-// the quotient (n 2^8)(m) / 2^32 is exact while n e < 2^24.
+// the quotient (n 2^8)(m) / 2^32 is exact while n e < 2^24.  The passes stay within that: their axes,
+// columns and blocks are few, and transforms with compiled stages have at least 4 points of the
+// 10240 that an LDS buffer holds, so at most 2048 lines of fewer than 4096 butterflies
+// (tests/test_divisors.py goes through all of them).  Lines of two or three points, or one, can
+// be more: the run-time transforms, which take those, deal by div_any.
 struct MDiv {
   uint32_t m, d;
   __host__ __device__ __forceinline__ int div(int n) const {
     const uint32_t a = ((uint32_t)n << 8) & 0xffffffu, b = m & 0xffffffu;
     const int q = (int)(uint32_t)(((uint64_t)a * b) >> 32);
     return d == 1 ? n : q;
+  }
+  // n / d and the remainder for any 0 <= n, d < 2^16: n m / 2^24 exceeds n / d by n e / (d 2^24) < 2^-8, so the
+  // quotient above is at most one too large.
+  __host__ __device__ __forceinline__ int div_any(int n, int& rem) const {
+    int q = div(n);
+    rem = n - q * (int)d;
+    if (rem < 0) {
+      --q;
+      rem += (int)d;
+    }
+    return q;
   }
 };
 

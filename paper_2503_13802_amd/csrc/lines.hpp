@@ -171,7 +171,8 @@ __device__ __forceinline__ float2* line_fft_ld(Load ld, float2* a, float2* b, co
     default: {
       const int total = L.nl * n;
       for (int i = threadIdx.x; i < total; i += L.T) {
-        const int p = L.md.div(i), l = i - p * L.nl;
+        int l;
+        const int p = L.md.div_any(i, l);
         a[l * L.ls + p] = ld(l, p);
       }
       return fft_lds<SGN>(a, b, tw, n, L.nl, LineMap{L.nl, 0, L.ls, 1}, true);
