@@ -168,7 +168,9 @@ template <class G, int SRC>
 static __global__ __launch_bounds__(G::TPF) void k_fast_plane_fwd(const VolDesc* __restrict__ vds, const float* __restrict__ a, int ahead) {
   const VolDesc& vd = vds[0];
   if constexpr (SRC == SRC_FISTA_Y || SRC == SRC_SCALED) {
-    if (vd.st->done) return;
+    const int done = vd.st->done;
+    if (ahead) keep_done(vd.st, done, blockIdx.x == 0);
+    if (done) return;
   }
   if constexpr (SRC == SRC_FISTA_Y) a = vd.y[(vd.st->k + ahead) & 1];
   if constexpr (SRC == SRC_SCALED) {
@@ -313,7 +315,7 @@ static __global__ __launch_bounds__(G::TC) void k_fast_col(const VolDesc* __rest
       return;
     }
   }
-  if (check_done && vd.st->done) return;
+  if (check_done && solve_over(vd, fin)) return;
   constexpr int NX = G::NX, MX = G::MX, SX = G::SX, CPC = G::CPC, KMAX = G::KMAX, LSX = G::LSX;
   constexpr bool kFwd = MODE != COL_ADJ, kAdj = MODE != COL_FWD;
   constexpr bool kStoreG = MODE == NRM_STORE || MODE == COL_FWD;

@@ -277,9 +277,10 @@ static __global__ __launch_bounds__(512, 6) void k_sep_plane_fwd(const VolDesc* 
   if (src != SRC_PLAIN) {
     const bool fista = src != SRC_SCALED;
     const float *v0 = fista ? vd.y[0] : vd.rho[0], *v1 = fista ? vd.y[1] : vd.rho[1];
-    const DevState* st = vd.st;
+    DevState* st = vd.st;
     pin(v0, v1, st, T);
     const int done = st->done, k = st->k + (src == SRC_FISTA_NEXT);
+    if (src == SRC_FISTA_NEXT) keep_done(st, done, lb == 0);
     if (done) return;
     if (fista || !a) a = (k & 1) ? v1 : v0;
   }
@@ -609,7 +610,7 @@ static __global__ __launch_bounds__(512, MODE < 0 ? 4 : 6) void k_sep_col(const 
     return;
   }
   if (!tasks) lb = sep_col_block(lb, gridDim.x - fin);
-  if (check_done && vd.st->done) return;
+  if (check_done && solve_over(vd, fin)) return;
   pin(T);
   sep_col_body<MODE>(vd, lb, mode, T);
 }

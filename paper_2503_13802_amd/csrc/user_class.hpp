@@ -305,7 +305,7 @@ static __global__ __launch_bounds__(1024) void k_user_class(const VolDesc* __res
     vol_finish<UPD_FISTA>(vd, T, reinterpret_cast<double*>(lds));
     return;
   }
-  if (check_done && vd.st->done) return;
+  if (check_done && solve_over(vd, fin)) return;
   pin(T);
   user_class_body<E, CB, DIR>(vd, plane_of_block(blockIdx.x, gridDim.x - fin), mode, T);
 }
