@@ -49,6 +49,7 @@ struct NetWork {
   float* xin = nullptr;                   // warm start: per-harmonic back-projections [C][N0] (lazy)
   uint16_t* gy = nullptr;                 // head output gradient [N0][4]
   double* scale = nullptr;                // max |x| of the current input
+  bool slot_set = false;                  // k_absmax's slot may hold a maximum (see net_forward)
   double* loss = nullptr;
 };
 
@@ -436,6 +437,13 @@ mh3d_status net_forward(mh3d_net_t n, NetWork* w, const float* x, Dims src, long
   if (!n->packed) CHK(net_pack(n));
   unsigned* slot = reinterpret_cast<unsigned*>(w->scale + 4);
   if (nsrc % 4) return fail(MH3D_ERR_INVALID, "volume size %lld is not a multiple of 4", nsrc);
+  // k_head1, the last kernel, clears the slot for the next pass; one that returned an error before
+  // it may have left its maximum there
+  if (w->slot_set) {
+    k_fill_f32<<<1, 64, 0, n->stream>>>(reinterpret_cast<float*>(slot), 1, 0.f);
+    CHK(last_launch("k_fill_f32"));
+  }
+  w->slot_set = true;
   k_absmax<<<std::min(grid_for(nsrc / 4, 256), 1024), 256, 0, n->stream>>>(x, nsrc, n->in_ch, slot);
   CHK(last_launch("k_absmax"));
   Dims d0 = dims_of(*w, 0);
@@ -480,7 +488,9 @@ mh3d_status net_forward(mh3d_net_t n, NetWork* w, const float* x, Dims src, long
   const NetLayer& hd = n->layers.back();   // the head: one output channel, FP32
   k_head1<<<std::min(grid_for(d0.n(), 256), 8192), 256, 0, n->stream>>>(h, d0.n(), hd.cs_in, hd.cs_in, hd.Wf, n->p + hd.b_off,
                                                                       w->y, slot);
-  return last_launch("k_head1");
+  CHK(last_launch("k_head1"));
+  w->slot_set = false;
+  return MH3D_OK;
 }
 
 // Data gradients layer by layer (each stored as the gradient of a pre-activation output: the
