@@ -42,8 +42,8 @@ inline FastDiv make_fastdiv(uint32_t d) {
 // the quotient (n 2^8)(m) / 2^32 is exact while n e < 2^24.  The passes stay within that: their axes,
 // columns and blocks are few, and transforms with compiled stages have at least 4 points of the
 // 10240 that an LDS buffer holds, so at most 2048 lines of fewer than 4096 butterflies
-// (tests/test_divisors.py goes through all of them).  Lines of two or three points, or one, can
-// be more: the run-time transforms, which take those, deal by div_any.
+// (tests/test_divisors.py goes through all of them).  The small grid's y' lines of one to three
+// points can be more: the run-time transforms, which take those, deal by div_any.
 struct MDiv {
   uint32_t m, d;
   __host__ __device__ __forceinline__ int div(int n) const {

@@ -153,8 +153,9 @@ __device__ __forceinline__ float2* line_stages(float2* a, float2* b, const float
 // memory that the first stage is the last to read): the first stage writes *a, the rest
 // ping-pong between *a and *b.  Returns the buffer holding the result.  No leading
 // barrier; ends with one.  Lengths that the switch does not know are copied to *a and
-// take the run-time engine.
-template <int SGN, bool FEW = false, class Load>
+// take the run-time engine.  MANY: where thousands of lines of one to three points can come
+// together (the small grid's y' lines), beyond the range of MDiv::div.
+template <int SGN, bool FEW = false, bool MANY = false, class Load>
 __device__ __forceinline__ float2* line_fft_ld(Load ld, float2* a, float2* b, const float2* tw, int n, const Lines& L) {
   switch (n) {
 #define MH3D_LN(NN)                                                                       \
@@ -171,8 +172,8 @@ __device__ __forceinline__ float2* line_fft_ld(Load ld, float2* a, float2* b, co
     default: {
       const int total = L.nl * n;
       for (int i = threadIdx.x; i < total; i += L.T) {
-        int l;
-        const int p = L.md.div_any(i, l);
+        int p = L.md.div(i), l = i - p * L.nl;
+        if constexpr (MANY) p = L.md.div_any(i, l);
         a[l * L.ls + p] = ld(l, p);
       }
       return fft_lds<SGN>(a, b, tw, n, L.nl, LineMap{L.nl, 0, L.ls, 1}, true);
@@ -181,10 +182,10 @@ __device__ __forceinline__ float2* line_fft_ld(Load ld, float2* a, float2* b, co
 }
 
 // The same for lines in *a: the stages ping-pong between *b and *a, starting from *a.
-template <int SGN, bool FEW = false>
+template <int SGN, bool FEW = false, bool MANY = false>
 __device__ __forceinline__ float2* line_fft(float2* a, float2* b, const float2* tw, int n, const Lines& L) {
   const int ls = L.ls;
-  return line_fft_ld<SGN, FEW>([=](int l, int p) { return a[__mul24(l, ls) + p]; }, b, a, tw, n, L);
+  return line_fft_ld<SGN, FEW, MANY>([=](int l, int p) { return a[__mul24(l, ls) + p]; }, b, a, tw, n, L);
 }
 
 }  // namespace mh3d

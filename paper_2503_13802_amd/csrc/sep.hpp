@@ -1011,7 +1011,7 @@ __device__ __forceinline__ void sep_small_r2c(const SmallGeo& s, float2* a, floa
     return (r & 1) ? make_float2(0.5f * (zq.y + zm.y), -0.5f * (zq.x - zm.x))
                    : make_float2(0.5f * (zq.x + zm.x), 0.5f * (zq.y - zm.y));
   };
-  const float2* Y = line_fft_ld<-1>(split, X, Z, twy, my, ly);
+  const float2* Y = line_fft_ld<-1, false, true>(split, X, Z, twy, my, ly);
   float2* __restrict__ dst = out + ((long long)k * s.nxb + xbi) * s.ncls * s.xb;
   const int n = s.ncls * s.xb;
   for (int p = threadIdx.x; p < n; p += s.T) {
@@ -1118,7 +1118,7 @@ __device__ __forceinline__ void sep_small_inv_body(const VolDesc& vd, int lb, fl
   tz.commit(twz, mz, T);
   __syncthreads();
   const Lines lz{s.spairs, lsmz, T, s.d_spairs}, ly{xb * mzh, lsmy, T, s.d_xbmzh};
-  float2* X = line_fft<+1>(P0, P1, twy, my, ly);
+  float2* X = line_fft<+1, false, true>(P0, P1, twy, my, ly);
   float2* Zb = X == P0 ? P1 : P0;
   const int rows = xb * my;
   const MDiv d_my = s.d_my;

@@ -2,9 +2,9 @@
 the CPU: the header and the transforms' radix table are compiled for the host.
 
 div is exact while n d <= 2^24; every quotient that a pass forms with it is listed below with the
-largest divisor and dividend that an accepted plan or tile gives.  The run-time transforms deal
-their elements by div_any, which has to be exact for everything an LDS buffer holds: axes of
-one to three points give thousands of lines (a decimated grid of 3 x 192 in blocks of 32 x').
+largest divisor and dividend that an accepted plan or tile gives.  The small grid's y' lines of one
+to three points are dealt by div_any, which has to be exact for everything an LDS buffer
+holds: there can be thousands of them (a decimated grid of 3 x 192 in blocks of 32 x').
 """
 import os
 import subprocess
@@ -35,9 +35,13 @@ static void exact_any(const char* what, long d, long n) {   // [0, n) by div_any
   }
 }
 // the dealing of nl lines of n points: butterflies of compiled stages, elements otherwise
-static void lines(const char* what, int n, long nl) {
+static void lines(const char* what, int n, long nl, bool many = false) {
   const int r0 = line_radix(n, 0, false);
-  if (n < 4 || !r0) { exact_any(what, nl, nl * n); return; }
+  if (n < 4 || !r0) {
+    if (many) exact_any(what, nl, nl * n);
+    else exact(what, nl, nl * n);
+    return;
+  }
   for (bool few : {false, true})
     for (int s = 0; s < 3; ++s)
       if (const int r = line_radix(n, s, few)) exact(what, nl, nl * (n / r));
@@ -64,7 +68,7 @@ int main() {
         bool ok = true;
         for (long i = 0; i < xb * mzh * my; ++i) ok = ok && v.div((int)i) == i / (xb * mzh);
         beyond += !ok;
-        lines("y' lines", my, xb * mzh);
+        lines("y' lines", my, xb * mzh, true);
         lines("z' lines", mz, sp);
         const int mv = mz / (mz % 4 ? 2 : 4);
         exact("mz", mz, xb * my * mz);
