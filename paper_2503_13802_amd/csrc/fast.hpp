@@ -168,9 +168,10 @@ template <class G, int SRC>
 static __global__ __launch_bounds__(G::TPF) void k_fast_plane_fwd(const VolDesc* __restrict__ vds, const float* __restrict__ a, int ahead) {
   const VolDesc& vd = vds[0];
   if constexpr (SRC == SRC_FISTA_Y || SRC == SRC_SCALED) {
-    const int done = vd.st->done;
-    if (ahead) keep_done(vd.st, done, blockIdx.x == 0);
-    if (done) return;
+    if (vd.st->done) {
+      set_skip(vd.st, blockIdx.x == 0);
+      return;
+    }
   }
   if constexpr (SRC == SRC_FISTA_Y) a = vd.y[(vd.st->k + ahead) & 1];
   if constexpr (SRC == SRC_SCALED) {

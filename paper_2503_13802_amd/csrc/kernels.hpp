@@ -126,7 +126,7 @@ struct DevState {
   int counter;      // arrivals for the last-block reduction
   double tau, lam, tol;
   int kmax;         // last iteration index allowed (k0 + max_iter - 1)
-  int skip;         // `done` before the finish that runs beside a column or class pass
+  int skip;         // `done` as the launch before a pass with a finish beside it saw it
   double rel_step;  // last r_k
   double scale;     // power iteration: 1/||w_{t-1}||
   double lmax;      // power iteration: latest Rayleigh quotient
@@ -304,9 +304,9 @@ __device__ __forceinline__ bool grid_reduce_last(double* v, double* partials, De
 // boundary orders it after every partial store.
 //
 // An update's finish runs as one more block of the next update's column or class pass, which
-// reads nothing it writes: the pass stops at `skip`, the value of `done` that the launch before
-// it read (solve_over), so the update after the last one fills scratch buffers and the step after
-// it, which reads `done`, ends.  The forward plane pass before it takes y^{k+1} (SRC_FISTA_NEXT).  As a launch of its own, which
+// reads nothing it writes: the pass stops at `skip`, which the launch before it sets if the solve
+// was done then (solve_over).  The pass of the update after the last fills scratch buffers, and
+// the step after it, which reads `done`, ends.  The forward plane pass before it takes y^{k+1} (SRC_FISTA_NEXT).  As a launch of its own, which
 // it still is before the host reads the state, it took 3.6 to 4.9 us: 30 updates at 128^3 1176 us
 // with it, 1054 without; 25 padded ones at 64^3 1301, 1212; 16 of a batch of four 1164, 1106; 30 of
 // a 128 x 256 image 1073, 971.
@@ -314,9 +314,11 @@ __device__ __forceinline__ bool solve_over(const VolDesc& vd, int fin) {
   const DevState* st = vd.st;
   return *(fin ? &st->skip : &st->done) != 0;
 }
-// In the launch before a pass with a finish beside it: its first block keeps `done` for that pass.
-__device__ __forceinline__ void keep_done(DevState* st, int done, bool first) {
-  if (first && threadIdx.x == 0) st->skip = done;
+// The first block of a launch before such a pass, if it finds the solve done.  (Never in a launch that
+// has work to do: a block that first stored `done` waited for that store, 1 us of an update of
+// a batch.)
+__device__ __forceinline__ void set_skip(DevState* st, bool first) {
+  if (first && threadIdx.x == 0) st->skip = 1;
 }
 template <int UPD>
 __device__ __forceinline__ void vol_finish(const VolDesc& vd, int T, double* sh) {

@@ -280,8 +280,10 @@ static __global__ __launch_bounds__(512, 6) void k_sep_plane_fwd(const VolDesc* 
     DevState* st = vd.st;
     pin(v0, v1, st, T);
     const int done = st->done, k = st->k + (src == SRC_FISTA_NEXT);
-    if (src == SRC_FISTA_NEXT) keep_done(st, done, lb == 0);
-    if (done) return;
+    if (done) {
+      set_skip(st, lb == 0);
+      return;
+    }
     if (fista || !a) a = (k & 1) ? v1 : v0;
   }
   sep_plane_fwd_body(vd, lb, a, src, T);

@@ -157,8 +157,10 @@ static __global__ __launch_bounds__(512, 4) void k_user_plane_fwd(const VolDesc*
   pin(nx, per, T, v0, v1, st);
   if (fista || src == SRC_SCALED) {
     const int done = st->done, k = st->k + (src == SRC_FISTA_NEXT);
-    if (src == SRC_FISTA_NEXT) keep_done(st, done, blockIdx.x == 0);
-    if (done) return;
+    if (done) {
+      set_skip(st, blockIdx.x == 0);
+      return;
+    }
     if (fista || !a) a = (k & 1) ? v1 : v0;
   }
   const int comp = blockIdx.x / per, r = blockIdx.x - comp * per, h = r / nx;
@@ -309,9 +311,10 @@ static __global__ __launch_bounds__(1024) void k_user_step_and_fwd(const VolDesc
   const VolDesc& vd = vds[0];
   int T = blockDim.x;
   pin(T);
-  const int done = vd.st->done;
-  keep_done(vd.st, done, blockIdx.x == 0);   // (the next update's forward pass is this launch)
-  if (done) return;
+  if (vd.st->done) {
+    set_skip(vd.st, blockIdx.x == 0);   // (the next update's forward pass is in this launch)
+    return;
+  }
   const float* ynext = vd.y[(vd.st->k + 1) & 1];
   user_plane_adj_body<OUT_STEP_FISTA, ROUNDS>(vd, blockIdx.x, ao, T);
   __syncthreads();   // the block's stores of y^{k+1} are visible to it; the LDS is free
