@@ -1,4 +1,6 @@
 // Launchers of the separable passes of run-time geometry.
+#include <algorithm>
+
 #include "sep.hpp"
 
 namespace mh3d {
@@ -21,12 +23,24 @@ void sep_launch_col(bool any, int mode, dim3 grid, dim3 block, size_t lds, hipSt
   }
 }
 
+// Blocks that the 256 CUs hold at once: by registers `waves` waves on each of a CU's 4 SIMDs, by LDS
+// 160 KiB per CU (512 bytes of a block's are static).
+static unsigned step_blocks_at_once(dim3 block, size_t lds, int waves) {
+  const unsigned by_regs = 4 * waves / ((block.x + 63) / 64), by_lds = (unsigned)(160 * 1024 / (lds + 512));
+  return 256 * std::max(1u, std::min(by_regs, by_lds));
+}
+
 void sep_launch_plane_adj(int out, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, const int2* tasks,
                           AdjOut ao) {
   if (out == OUT_STEP_NORMAL) k_sep_plane_adj<OUT_STEP_NORMAL, 6><<<grid, block, lds, s>>>(vd, tasks, ao);
-  else if (out == OUT_STEP_FISTA && grid.x > 512) k_sep_plane_adj<OUT_STEP_FISTA, 6><<<grid, block, lds, s>>>(vd, tasks, ao);
-  else if (out == OUT_STEP_FISTA) k_sep_plane_adj<OUT_STEP_FISTA, 5><<<grid, block, lds, s>>>(vd, tasks, ao);
-  else k_sep_plane_adj<OUT_SCALE_B, 6><<<grid, block, lds, s>>>(vd, tasks, ao);
+  else if (out == OUT_STEP_FISTA) {
+    // the form of 80 registers where it takes fewer rounds of the chip (see k_sep_plane_adj)
+    const unsigned n5 = step_blocks_at_once(block, lds, 5), n6 = step_blocks_at_once(block, lds, 6);
+    if ((grid.x + n6 - 1) / n6 < (grid.x + n5 - 1) / n5)
+      k_sep_plane_adj<OUT_STEP_FISTA, 6><<<grid, block, lds, s>>>(vd, tasks, ao);
+    else
+      k_sep_plane_adj<OUT_STEP_FISTA, 5><<<grid, block, lds, s>>>(vd, tasks, ao);
+  } else k_sep_plane_adj<OUT_SCALE_B, 6><<<grid, block, lds, s>>>(vd, tasks, ao);
 }
 
 void sep_launch_adj_and_store(dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, AdjOut ao, float* d,

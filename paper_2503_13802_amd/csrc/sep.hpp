@@ -943,10 +943,13 @@ __device__ __forceinline__ void sep_plane_adj_body(const VolDesc& vd, int lb, co
 }
 
 // grid.y > 1 (OUT_SCALE_B only): descriptor y and output volume y of consecutive volumes.
-// W waves per SIMD: a solver step takes 85 registers, which leaves a CU two 512-thread blocks.
-// With more blocks than that fills (512), the form held to 80 registers (five of them
-// spilled) runs three: 672 blocks of a batch of four 26.5 us with two, 22.1 with three; 128
-// blocks at 64^3, padded, 10.5 and 11.1.
+// W waves per SIMD: a solver step takes 85 registers, five waves per SIMD: two blocks of 512 threads,
+// five of 256 or ten of 128 on a CU.  The form held to 80 (five of them spilled) lets three, six
+// or twelve run and is the slower one otherwise, so it runs where it saves a round of blocks on
+// the chip.  Microseconds per update with 85 and with 80 registers: 512 threads, 512 blocks (four
+// volumes of 64^3) 33.8 and 36.7, 640 (five) 45.9 and 42.5, 1024 (eight) 59.8 and 61.1, 1536 (twelve) 80.5
+// and 77.6; 256 threads, 1024 blocks (256 x 64 x 64) 30.7 and 32.9, 1536 (48 of 32^3) 117.7 and 115.8,
+// 2048 149.2 and 153.5; 128 threads, 2560 blocks (40 of 32^3) 86.8 and 89.3, 3072 103.8 and 102.3.
 template <int OUT, int W>
 static __global__ __launch_bounds__(512, W) void k_sep_plane_adj(const VolDesc* __restrict__ vds, const int2* __restrict__ tasks,
                                                        AdjOut ao) {
