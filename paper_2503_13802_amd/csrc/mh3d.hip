@@ -116,7 +116,8 @@ static void derive_sep(Geo& g, Launch& L) {
   L.col_any = s.kg < g.K || g.sx > SXR;
   L.lds_col_resid = g.sx <= 4 ? fixed + s.kg * per : L.lds_col;
   L.lds_col_plain = g.sx <= 4 ? fixed : L.lds_col;
-  L.T_col = std::max(128, (s.cpc * g.mx + 63) / 64 * 64);
+  // a thread per (column, q'x), and with many x aliases one per four points of the x lines
+  L.T_col = std::max(128, (std::max(s.cpc * g.mx, std::min(512, s.cpc * g.nx / 4)) + 63) / 64 * 64);
   L.col_blocks = (g.ncls + s.cpc - 1) / s.cpc;
   // plane blocks: two points per thread, small-grid blocks: one (four threads and more per radix-8
   // butterfly: the loads, the splits, the crop and the solver step are shared by more threads

@@ -10,17 +10,23 @@ void sep_launch_plane_fwd(dim3 grid, dim3 block, size_t lds, hipStream_t s, cons
   k_sep_plane_fwd<<<grid, block, lds, s>>>(vd, tasks, a, src);
 }
 
+template <bool ANY>
+static void launch_col(int mode, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, const int2* tasks, int chk,
+                       int fin) {
+  switch (mode) {
+    case NRM_RESID: k_sep_col<NRM_RESID, ANY><<<grid, block, lds, s>>>(vd, tasks, chk, fin); break;
+    case NRM_PLAIN: k_sep_col<NRM_PLAIN, ANY><<<grid, block, lds, s>>>(vd, tasks, chk, fin); break;
+    case NRM_STORE: k_sep_col<NRM_STORE, ANY><<<grid, block, lds, s>>>(vd, tasks, chk, fin); break;
+    case COL_FWD: k_sep_col<COL_FWD, ANY><<<grid, block, lds, s>>>(vd, tasks, chk, fin); break;
+    case COL_ADJ: k_sep_col<COL_ADJ, ANY><<<grid, block, lds, s>>>(vd, tasks, chk, fin); break;
+    default: k_sep_col<COL_DATA, ANY><<<grid, block, lds, s>>>(vd, tasks, chk, fin); break;
+  }
+}
+
 void sep_launch_col(bool any, int mode, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd,
                     const int2* tasks, int chk, int fin) {
-  if (any) k_sep_col<-1><<<grid, block, lds, s>>>(vd, tasks, mode, chk, fin);
-  else switch (mode) {
-    case NRM_RESID: k_sep_col<NRM_RESID><<<grid, block, lds, s>>>(vd, tasks, mode, chk, fin); break;
-    case NRM_PLAIN: k_sep_col<NRM_PLAIN><<<grid, block, lds, s>>>(vd, tasks, mode, chk, fin); break;
-    case NRM_STORE: k_sep_col<NRM_STORE><<<grid, block, lds, s>>>(vd, tasks, mode, chk, fin); break;
-    case COL_FWD: k_sep_col<COL_FWD><<<grid, block, lds, s>>>(vd, tasks, mode, chk, fin); break;
-    case COL_ADJ: k_sep_col<COL_ADJ><<<grid, block, lds, s>>>(vd, tasks, mode, chk, fin); break;
-    default: k_sep_col<COL_DATA><<<grid, block, lds, s>>>(vd, tasks, mode, chk, fin); break;
-  }
+  if (any) launch_col<true>(mode, grid, block, lds, s, vd, tasks, chk, fin);
+  else launch_col<false>(mode, grid, block, lds, s, vd, tasks, chk, fin);
 }
 
 // Blocks that the 256 CUs hold at once: by registers `waves` waves on each of a CU's 4 SIMDs, by LDS

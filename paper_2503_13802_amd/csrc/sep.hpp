@@ -332,42 +332,72 @@ __device__ __forceinline__ void sep_products(int mode, int k0, int kn, const flo
   }
 }
 
-// The same for any sx: the aliases stay in LDS (W: the x transform, Q: the sums so far).
-// F keeps every harmonic's folded value, which the adjoint half reads back.
-__device__ __forceinline__ void sep_products_any(int mode, int k0, int kn, int sx, const float* fk, int nx, int mx,
-                                                 uint32_t imag, float Mf, const float2* W, float2* Q, float2* F,
-                                                 const float2* D, int fst) {
-  if (mode != COL_ADJ) {
-    for (int i = 0; i < kn; ++i) {
-      float2 a = make_float2(0.f, 0.f);
-      for (int jx = 0; jx < sx; ++jx) fma_acc(a, fk[i * nx + jx * mx], W[jx * mx]);
-      F[i * fst] = ((imag >> (k0 + i)) & 1u) ? make_float2(-a.y, a.x) : a;
-    }
+// The same for any sx: the aliases stay in LDS (W: the x transform, Q: the sums so far) and go
+// through the registers four at a time, `parts` threads sharing a (column, q'x): harmonics part,
+// part + parts, ... of the folded values F (between the runs of aliases F holds the sum so
+// far), then, after a barrier, runs part, part + parts, ... of the adjoint's sums.  One thread that
+// read every alias of every harmonic from LDS in turn was a chain of K sx reads.  Column pass
+// of A, of A^T, of both in one, before and after (with a kernel per mode and up to four times the threads):
+// 64 x 32 x 32, s = (16,1,1), K = 8: 12.7, 6.9; 16.3, 6.8; 28.4, 11.5 us; 256 x 16 x 16, s = (8,1,1),
+// K = 20: 21.9, 12.2; 25.0, 12.8; 40.6, 20.3.
+template <int N>
+__device__ __forceinline__ void sep_fold_run(int j0, bool last, int k0, int kn, int part, int parts, const float* fk, int nx,
+                                             int mx, uint32_t imag, const float2* W, float2* F, int fst) {
+  float2 w[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) w[j] = W[(j0 + j) * mx];
+  fk += j0 * mx;
+#pragma unroll 2
+  for (int i = part; i < kn; i += parts) {
+    float2 a = j0 ? F[i * fst] : make_float2(0.f, 0.f);
+#pragma unroll
+    for (int j = 0; j < N; ++j) fma_acc(a, fk[i * nx + j * mx], w[j]);
+    F[i * fst] = last && ((imag >> (k0 + i)) & 1u) ? make_float2(-a.y, a.x) : a;
   }
-  if (mode == COL_FWD) return;
-  for (int jx = 0; jx < sx; ++jx) {
-    float2 q = Q[jx * mx];
-    for (int i = 0; i < kn; ++i) {
-      float2 R = F[i * fst];
-      if (mode != COL_ADJ) R = col_resid(mode, Mf, R, mode == NRM_RESID ? D[i * fst] : R);
-      if ((imag >> (k0 + i)) & 1u) R = make_float2(R.y, -R.x);
-      fma_acc(q, fk[i * nx + jx * mx], R);
-    }
-    Q[jx * mx] = q;
+}
+template <int N>
+__device__ __forceinline__ void sep_spread_run(int mode, int j0, int k0, int kn, const float* fk, int nx, int mx, uint32_t imag,
+                                               float Mf, float2* Q, const float2* F, const float2* D, int fst) {
+  float2 q[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) q[j] = Q[(j0 + j) * mx];
+  fk += j0 * mx;
+#pragma unroll 2
+  for (int i = 0; i < kn; ++i) {
+    float2 R = F[i * fst];
+    if (mode != COL_ADJ) R = col_resid(mode, Mf, R, mode == NRM_RESID ? D[i * fst] : R);
+    if ((imag >> (k0 + i)) & 1u) R = make_float2(R.y, -R.x);
+#pragma unroll
+    for (int j = 0; j < N; ++j) fma_acc(q[j], fk[i * nx + j * mx], R);
   }
+#pragma unroll
+  for (int j = 0; j < N; ++j) Q[(j0 + j) * mx] = q[j];
+}
+__device__ __forceinline__ void sep_fold_any(int k0, int kn, int sx, int part, int parts, const float* fk, int nx, int mx,
+                                             uint32_t imag, const float2* W, float2* F, int fst) {
+  const int s4 = sx & ~3;   // runs of four, then the other one to three
+  for (int j0 = 0; j0 < s4; j0 += 4) sep_fold_run<4>(j0, j0 + 4 == sx, k0, kn, part, parts, fk, nx, mx, imag, W, F, fst);
+  if (sx & 2) sep_fold_run<2>(s4, s4 + 2 == sx, k0, kn, part, parts, fk, nx, mx, imag, W, F, fst);
+  if (sx & 1) sep_fold_run<1>(sx - 1, true, k0, kn, part, parts, fk, nx, mx, imag, W, F, fst);
+}
+__device__ __forceinline__ void sep_spread_any(int mode, int k0, int kn, int sx, int part, int parts, const float* fk, int nx,
+                                               int mx, uint32_t imag, float Mf, float2* Q, const float2* F, const float2* D,
+                                               int fst) {
+  int r = part;   // runs of four, the last of one to three
+  for (; 4 * r + 4 <= sx; r += parts) sep_spread_run<4>(mode, 4 * r, k0, kn, fk, nx, mx, imag, Mf, Q, F, D, fst);
+  if (4 * r >= sx) return;
+  if (sx & 2) sep_spread_run<2>(mode, 4 * r, k0, kn, fk, nx, mx, imag, Mf, Q, F, D, fst);
+  if (sx & 1) sep_spread_run<1>(mode, sx - 1, k0, kn, fk, nx, mx, imag, Mf, Q, F, D, fst);
 }
 
 // Block: cpc columns, one thread per (column, q'x) owning the x aliases q'x + mx jx.
-// MODE >= 0: that mode, every harmonic's folded spectrum in LDS at once (kg = K) and at most
-// 4 x aliases.  MODE < 0: any mode (mode_rt), harmonics in groups of kg, any sx; its index
-// values for every mode at once do not fit the scalar registers (10.0 us against 6 at 32^3),
-// so it serves only the plans that need it (sep_col_any).
-template <int MODE>
-__device__ __forceinline__ void sep_col_body(const VolDesc& vd, int lb, int mode_rt, int T) {
-  constexpr bool kAny = MODE < 0;
-  const int mode = kAny ? mode_rt : MODE;
-  const bool fwd = mode != COL_ADJ && mode != COL_DATA, adj = mode != COL_FWD && mode != COL_DATA;
-  const bool store_g = mode == NRM_STORE || mode == COL_FWD, load_g = mode == COL_ADJ || mode == COL_DATA;
+// Plain form: every harmonic's folded spectrum in LDS at once (kg = K) and at most 4 x aliases.
+// kAny: harmonics in groups of kg, any sx, for the plans that need it (Launch::col_any).
+template <int MODE, bool kAny>
+__device__ __forceinline__ void sep_col_body(const VolDesc& vd, int lb, int T) {
+  constexpr int mode = MODE;
+  constexpr bool fwd = mode != COL_ADJ && mode != COL_DATA, adj = mode != COL_FWD && mode != COL_DATA;
+  constexpr bool store_g = mode == NRM_STORE || mode == COL_FWD, load_g = mode == COL_ADJ || mode == COL_DATA;
   int nx = vd.g.nx, mx = vd.g.mx, sx = vd.g.sx, sy = vd.g.sy, K = vd.g.K, ncls = vd.g.ncls, xb = vd.g.xb, M = (int)vd.g.M;
   int cpc = vd.g.sep.cpc, lsx = vd.g.sep.lsx, lsm = vd.g.sep.lsm, nxb = vd.g.sep.nxb;
   int kg = kAny ? vd.g.sep.kg : K;
@@ -394,8 +424,14 @@ __device__ __forceinline__ void sep_col_body(const VolDesc& vd, int lb, int mode
   float2* F1 = reinterpret_cast<float2*>(fs + ((K * nx + 1) & ~1));
   float2* F0 = F1 + kg * cpc * lsm;     // (only where the mode stores or reads them: Launch::lds_col_of)
   const int t = threadIdx.x;
-  const int cl = d_mx.div(t), qxp = t - __mul24(cl, mx);
-  const bool act = cl < nc;
+  int tc = t, part = 0, parts = 1;   // kAny: the block's threads are `parts` for each (column, q'x)
+  if constexpr (kAny) {
+    part = vd.g.sep.d_cpcmx.div(t);
+    parts = vd.g.sep.d_cpcmx.div(T);
+    tc = t - part * cpc * mx;
+  }
+  const int cl = d_mx.div(tc), qxp = tc - __mul24(cl, mx);
+  const bool act = cl < nc && part == 0;
   const int own = __mul24(cl, lsm) + qxp;   // this thread's entry of a harmonic in F0 / F1
   const int fst = cpc * lsm;                // one harmonic
   auto load_data = [&](int k0, int kn) {   // this thread's data terms into F1 (no barrier: its own entries)
@@ -544,12 +580,20 @@ __device__ __forceinline__ void sep_col_body(const VolDesc& vd, int lb, int mode
         case 2: sep_products<2>(mode, k0, kn, fk, nx, mx, imag, Mf, w, q, Fo, Do, fst); break;
         case 3: sep_products<3>(mode, k0, kn, fk, nx, mx, imag, Mf, w, q, Fo, Do, fst); break;
         case 4: sep_products<4>(mode, k0, kn, fk, nx, mx, imag, Mf, w, q, Fo, Do, fst); break;
-        default:
-          if constexpr (kAny) sep_products_any(mode, k0, kn, sx, fk, nx, mx, imag, Mf, U + ux, Qb + ux, Fo, Do, fst);
+      }
+    }
+    if constexpr (kAny) {
+      if (sx > SXR) {
+        const bool live = cl < nc && part < parts;
+        const float* fk = fs + k0 * nx + qxp;
+        if (fwd && live) sep_fold_any(k0, kn, sx, part, parts, fk, nx, mx, imag, U + ux, F + own, fst);
+        if (fwd && adj) __syncthreads();
+        if (adj && live)
+          sep_spread_any(mode, k0, kn, sx, part, parts, fk, nx, mx, imag, Mf, Qb + ux, F + own, F1 + own, fst);
       }
     }
     if (store_g) {
-      if (!act && cl < cpc)   // columns past the last one of the grid: finite values for the transform
+      if (!act && part == 0 && cl < cpc)   // columns past the last one of the grid: finite values for the transform
         for (int i = 0; i < kn; ++i) F0[own + i * fst] = make_float2(0.f, 0.f);
       __syncthreads();
       const float2* R = line_fft<+1>(F0, F1, twm, mx, lm);
@@ -571,7 +615,7 @@ __device__ __forceinline__ void sep_col_body(const VolDesc& vd, int lb, int mode
     group(0, K, Lines{K * cpc, lsm, T, d_kgcpc});
   }
   if (adj) {
-    if (cl < cpc) {
+    if (cl < cpc && part == 0) {
       if (!kAny || sx <= SXR) {
 #pragma unroll
         for (int jx = 0; jx < SXR; ++jx)
@@ -600,9 +644,9 @@ __device__ __forceinline__ int sep_col_block(int b, int nb) {
 
 // grid.y > 1 runs one descriptor per y-block (the back-projections of single harmonics).  fin: the
 // last block (in a batch the tasks of local block -1) finishes the previous update.
-template <int MODE>
-static __global__ __launch_bounds__(512, MODE < 0 ? 4 : 6) void k_sep_col(const VolDesc* __restrict__ vds, const int2* __restrict__ tasks, int mode,
-                                                    int check_done, int fin) {
+template <int MODE, bool ANY>
+static __global__ __launch_bounds__(512, ANY ? 4 : 6) void k_sep_col(const VolDesc* __restrict__ vds, const int2* __restrict__ tasks,
+                                                                     int check_done, int fin) {
   int lb, v, T = blockDim.x;
   sep_task(tasks, v, lb);
   const VolDesc& vd = vds[v];
@@ -614,7 +658,7 @@ static __global__ __launch_bounds__(512, MODE < 0 ? 4 : 6) void k_sep_col(const 
   if (!tasks) lb = sep_col_block(lb, gridDim.x - fin);
   if (check_done && solve_over(vd, fin)) return;
   pin(T);
-  sep_col_body<MODE>(vd, lb, mode, T);
+  sep_col_body<MODE, ANY>(vd, lb, T);
 }
 
 // ============================================================================ solver step

@@ -116,6 +116,7 @@ int main() {
     for (int nx : len)
       if (nx % mx == 0) { lines("x lines", nx, cpc); exact("columns", cpc, cpc * nx); }
     exact("threads", mx, 1024);
+    exact("threads per frequency", cpc * mx, 1025);
     for (int xb : len)
       if (mx % xb == 0) exact("x'-blocks", mx / xb, 32 * (mx / xb));
   }
