@@ -72,7 +72,7 @@ struct Launch {
   size_t lds_uf, lds_ua;
   // the separable passes of analytic plans (sep.hpp)
   int T_sep, T_col, col_blocks;
-  bool col_any;            // column passes of the general form (more than one group or 4 x aliases)
+  bool col_any;            // column passes of the general form (more than one group, 4 x aliases or 16 y residues)
   size_t lds_sep, lds_col, lds_col_resid, lds_col_plain;
   size_t lds_col_of(int mode) const {
     return mode == NRM_RESID ? lds_col_resid : mode == NRM_PLAIN ? lds_col_plain : lds_col;
@@ -113,7 +113,9 @@ static void derive_sep(Geo& g, Launch& L) {
   L.lds_col = fixed + 2 * s.kg * per;
   // without G to store (and the x aliases in registers) a pass needs no F0, and F1 only for
   // the data terms: more blocks per CU in the solver
-  L.col_any = s.kg < g.K || g.sx > SXR;
+  // (the general form's registers cost a column pass about 0.7 us, its shares of many y residues
+  // save A 1.2 us at 32 and 2.6 at 64 of them)
+  L.col_any = s.kg < g.K || g.sx > SXR || g.sy > 16;
   L.lds_col_resid = g.sx <= 4 ? fixed + s.kg * per : L.lds_col;
   L.lds_col_plain = g.sx <= 4 ? fixed : L.lds_col;
   // a thread per (column, q'x), and with many x aliases one per four points of the x lines

@@ -41,7 +41,8 @@ extern const int kFastCount;
 void sep_launch_plane_fwd(dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, const int2* tasks,
                           const float* a, int src);
 // fin: with the finish of the previous update (one block more; in a batch the table's tasks of
-// local block -1).  any: the general form (harmonics in groups, any number of x aliases)
+// local block -1).  any: the general form (harmonics in groups, any number of x aliases and y
+// residues)
 void sep_launch_col(bool any, int mode, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd,
                     const int2* tasks, int chk, int fin = 0);
 void sep_launch_plane_adj(int out, dim3 grid, dim3 block, size_t lds, hipStream_t s, const VolDesc* vd, const int2* tasks,

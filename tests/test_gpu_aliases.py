@@ -1,6 +1,6 @@
-"""The general column pass (more than four x aliases): its aliases go through the registers in runs of
+"""The general column pass (more than four x aliases, more than sixteen y residues): its aliases go through the registers in runs of
 four, two and one, and the threads of a block share the products of a frequency where there are
-more of them.  Every remainder, one to several threads per frequency with and without
+more of them; the residues' shares are added eight at a time.  Every remainder, one to several threads per frequency with and without
 idle ones, harmonics in one and several groups, with and without padding, against the FP64
 oracle; volumes of such plans in one batch equal their own solves."""
 import numpy as np
@@ -26,6 +26,9 @@ CASES = [
     ((256, 4, 8), (8, 1, 1), tuple(range(2, 22)), (0, 0, 0)),        # 20 harmonics in two groups
     ((144, 8, 8), (9, 2, 2), (2, 3, 4), (18, 2, 2)),                 # padded: forward and adjoint alone
     ((72, 12, 8), (6, 3, 1), (2, 4), (6, 3, 1)),
+    ((8, 72, 4), (2, 18, 1), (2, 3), (0, 0, 0)),                     # 18 residues: 4 + 8 + 6
+    ((8, 128, 4), (2, 64, 1), (2, 3, 4), (0, 0, 0)),
+    ((16, 96, 8), (8, 32, 2), (2, 3), (0, 0, 0)),                    # both
 ]
 
 
