@@ -356,9 +356,8 @@ mh3d_status mh3d_profile_read(mh3d_plan_t plan, mh3d_profile_data* out);
  * 3 small_fwd, 4 class_adj, 5 plane_adj, 6 class_normal: the forward and adjoint class
  * passes in one, 7 adj_and_store: the adjoint plane pass and the small-grid inverse pass
  * in one launch, both as mh3d_forward_adjoint runs them; 6 and 7 give
- * MH3D_ERR_UNSUPPORTED for plans of the vector model or with boundary padding, which
- * keep the passes apart) over reps
- * back-to-back launches between two HIP events on the plan's stream, after one A and
+ * MH3D_ERR_UNSUPPORTED for plans with boundary padding, which keep the passes apart) over
+ * reps back-to-back launches between two HIP events on the plan's stream, after one A and
  * A^T to set its inputs.  Overwrites the plan's solver volumes; profiling must be off;
  * synchronous. */
 mh3d_status mh3d_time_pass(mh3d_plan_t plan, int32_t pass, int32_t reps, double* us);

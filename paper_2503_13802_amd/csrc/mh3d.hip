@@ -1807,8 +1807,8 @@ extern "C" mh3d_status mh3d_mhad(mh3d_plan_t p, const float* d, double lambda, c
 extern "C" mh3d_status mh3d_time_pass(mh3d_plan_t p, int32_t pass, int32_t reps, double* us) {
   CHK(check_plan(p));
   if (pass < 0 || pass > 7 || reps < 1 || !us) return fail(MH3D_ERR_INVALID, "bad pass timing arguments");
-  if (pass >= 6 && (p->g.C > 1 || !fused_class(p)))
-    return fail(MH3D_ERR_UNSUPPORTED, "the plan runs no fused class pass (vector model or boundary padding)");
+  if (pass >= 6 && !fused_class(p))
+    return fail(MH3D_ERR_UNSUPPORTED, "the plan runs no fused class pass (boundary padding)");
   if (p->prof_on) return fail(MH3D_ERR_INVALID, "disable mh3d_profile before timing passes");
   float* dtmp = nullptr;
   HIPCHK(hipMalloc(&dtmp, sizeof(float) * (size_t)p->g.K * p->g.M));

@@ -342,7 +342,7 @@ class Plan:
     def time_passes(self, reps=200):
         """time_pass of every pass the plan runs: class_normal (the fused class pass) and
         adj_and_store (adjoint plane pass and small-grid inverse in one launch) only for
-        scalar plans without boundary padding, which run them."""
+        plans without boundary padding, which run them."""
         out = {}
         for name in self.PASSES:
             try:
