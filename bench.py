@@ -84,11 +84,11 @@ def fast_kernel_bytes(w):
             "adj_and_store": q + tab + 8 * t["N"] + g + 4 * t["K"] * t["M"]}
 
 
-def general_kernel_bytes(w, compact=True, ncomp=1):
-    """Algorithmic bytes per launch of the user-PSF passes (user.hpp): spectra of
-    beta_H = 4 (compact) or 8 bytes per element in the class layout."""
+def general_kernel_bytes(w, ncomp=1):
+    """Algorithmic bytes per launch of the user-PSF passes (user.hpp): complex spectra in
+    the class layout."""
     t = shape_terms(w)
-    bh = 4 if compact else 8
+    bh = 8
     C = ncomp
     return {"plane_fwd": 4 * C * t["N"] + 4 * t["N"] + 8 * C * t["Nc"],
             "class_normal": bh * C * t["K"] * t["Nc"] + 16 * C * t["Nc"] + 8 * t["K"] * t["Mc"],
@@ -461,7 +461,7 @@ def vector_leg(w, steps, warmup, tile_cache=None):
         x = torch.empty(w.shape, device=dev)
         sec = time_steps(lambda: plan.forward_adjoint(src, d_out=y, x_out=x), steps, warmup, repeats=3)
         pass_us = plan.time_passes(reps=100)
-        bmap = general_kernel_bytes(w, compact=False, ncomp=C)
+        bmap = general_kernel_bytes(w, ncomp=C)
         if "class_normal" in pass_us:
             ck, cb, cs = "class_normal", bmap["class_normal"], pass_us["class_normal"]
         else:

@@ -123,7 +123,7 @@ struct Geo {
   long long hsz;           // spectrum elements per harmonic = ncls*mx*S = plane*nx
   SepGeo sep;
   UserGeo usr;
-  FastDiv f_nz, f_nzh, f_nmem, f_mzh, f_sz, f_mz, f_W, f_xb, f_S, f_mxS, f_cpwmx, f_cpwxb, f_ny, f_my;
+  FastDiv f_nmem, f_my, f_mz, f_W, f_S, f_mxS;
 };
 
 }  // namespace mh3d

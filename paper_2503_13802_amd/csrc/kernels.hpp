@@ -216,20 +216,6 @@ struct HLoad {
   }
 };
 
-// Destination of the forward class pass's decimated spectra F_k (the small-grid spectra
-// of the portraits, before their inverse transform):
-//   FWD_G          G = F  (the small-grid pass turns them into portraits)
-//   FWD_ADJ        G' = my mz F (the adjoint takes them as they are: normal operator)
-//   FWD_G_AND_ADJ  both (A then A^T: the portraits are written and A^T starts at once)
-//   FWD_RESID      G' = my mz F - G, G holding the (unnormalised) small-grid spectra of
-//                  the measured portraits (the solver's residual)
-// Without boundary padding the small-grid inverse and forward transforms between the
-// forward and the adjoint are, up to their scale my mz and to rounding, an identity on
-// these spectra (they only make the two self-conjugate columns of each spectrum
-// Hermitian, which F already is in exact arithmetic), so the adjoint can start from F.
-// With padding the crop to the field of view sits between them and the pass stays.
-enum { FWD_G = 0, FWD_ADJ = 1, FWD_G_AND_ADJ = 2, FWD_RESID = 3 };
-
 // LDS of the class passes with cb components per round and line stride fls of the folded
 // spectra: tables (nx + mx), two buffers of cb * cpw * nmem x lines, two of K * cpw x' lines.
 __host__ __device__ inline size_t class_lds_elems(const Geo& g, int cb, int fls) {
@@ -241,7 +227,7 @@ __host__ __device__ inline size_t class_lds_elems(const Geo& g, int cb, int fls)
 enum { NRM_RESID = 0, NRM_PLAIN = 1, NRM_STORE = 2 };
 
 // ============================================================================ pass 3: small grid
-enum { EPI_STORE = 0, EPI_RESID = 1, EPI_RESID_BACK = 2, EPI_BACK = 3, EPI_STORE_BACK = 4 };
+enum { EPI_STORE = 0, EPI_RESID_BACK = 1, EPI_BACK = 2, EPI_STORE_BACK = 3 };
 
 // ============================================================================ pass 1 adjoint
 enum { OUT_SCALE_B = 0, OUT_STEP_NORMAL = 2, OUT_STEP_FISTA = 3 };

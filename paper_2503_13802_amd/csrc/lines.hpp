@@ -95,7 +95,7 @@ __host__ __device__ constexpr int line_radix(int n, int s, bool few) {
       if (p[0] == n) return s < 3 ? p[1 + s] : 0;
   }
   constexpr int plan[][4] = {
-      {2, 2, 0, 0},   {3, 3, 0, 0},   {4, 4, 0, 0},   {6, 6, 0, 0},   {8, 8, 0, 0},   {9, 9, 0, 0},
+      {4, 4, 0, 0},   {6, 6, 0, 0},   {8, 8, 0, 0},   {9, 9, 0, 0},
       {12, 4, 3, 0},  {16, 4, 4, 0},  {18, 6, 3, 0},  {24, 8, 3, 0},  {27, 9, 3, 0},  {32, 8, 4, 0},
       {36, 6, 6, 0},  {48, 8, 6, 0},  {54, 9, 6, 0},  {64, 8, 8, 0},  {72, 9, 8, 0},  {96, 12, 8, 0},
       {108, 6, 6, 3}, {128, 16, 8, 0}, {144, 12, 12, 0}, {192, 8, 6, 4}, {256, 16, 16, 0}};

@@ -259,11 +259,8 @@ static mh3d_status derive_tiles(Geo& g, Launch& L, int E_req, int cpw_req, int x
     return fail(MH3D_ERR_INVALID, "ps = %d: the plane passes take 1 to 4 workgroups per plane (at most "
                 "min(nz/2+1, (ny+1)/2))", ps_req);
   g.ps = ps_req > 0 ? ps_req : std::min(2, std::min(g.nzh, g.npairs));
-  g.f_nz = make_fastdiv(g.nz); g.f_nzh = make_fastdiv(g.nzh); g.f_nmem = make_fastdiv(g.nmem);
-  g.f_mzh = make_fastdiv(g.mzh); g.f_sz = make_fastdiv(g.sz); g.f_mz = make_fastdiv(g.mz);
-  g.f_W = make_fastdiv(g.cpw * g.nmem); g.f_xb = make_fastdiv(g.xb); g.f_S = make_fastdiv(g.S);
-  g.f_mxS = make_fastdiv(g.mx * g.S); g.f_cpwmx = make_fastdiv(g.cpw * g.mx);
-  g.f_cpwxb = make_fastdiv(g.cpw * g.xb); g.f_ny = make_fastdiv(g.ny); g.f_my = make_fastdiv(g.my);
+  g.f_nmem = make_fastdiv(g.nmem); g.f_my = make_fastdiv(g.my); g.f_mz = make_fastdiv(g.mz);
+  g.f_W = make_fastdiv(g.cpw * g.nmem); g.f_S = make_fastdiv(g.S); g.f_mxS = make_fastdiv(g.mx * g.S);
   derive_sep(g, L);
   derive_user(g, L);
   L.T_merge = g.ps >= 2 ? 512 : 1024;   // the autotuner times both
@@ -535,10 +532,9 @@ static void launch_class(mh3d_plan_t p, int dir, int chk, int mode, const VolDes
                     mode, fin);
 }
 
-// mode: FWD_G, FWD_ADJ, FWD_G_AND_ADJ or FWD_RESID (where the decimated spectra go).
-static mh3d_status launch_class_fwd(mh3d_plan_t p, int chk, int mode, int fin = 0) {
+static mh3d_status launch_class_fwd(mh3d_plan_t p, int chk, int fin = 0) {
   Timer t(p, KID_CLASS_FWD);
-  launch_class(p, CLS_FWD, chk, mode, p->vda, fin);
+  launch_class(p, CLS_FWD, chk, 0, p->vda, fin);
   return last_launch("k_user_class (forward)");
 }
 // vd: a single-harmonic descriptor (per-harmonic back-projection) or NULL for the plan's.
@@ -1072,15 +1068,9 @@ extern "C" mh3d_status mh3d_forward_adjoint(mh3d_plan_t p, const float* rho, flo
     return launch_adj_and_store(p, d, x);
   }
   CHK(launch_plane_fwd(p, SRC_PLAIN, rho));
-  if (p->g.padded) {
-    CHK(launch_class_fwd(p, 0, FWD_G));
-    CHK(launch_small_inv(p, EPI_STORE_BACK, d));   // stores d and starts A^T on its cropped copy
-    CHK(launch_class_adj(p, 0));
-  } else {
-    CHK(launch_class_fwd(p, 0, FWD_G_AND_ADJ));    // A^T starts from d's spectra
-    CHK(launch_small_inv(p, EPI_STORE, d));
-    CHK(launch_class_adj(p, 0));
-  }
+  CHK(launch_class_fwd(p, 0));
+  CHK(launch_small_inv(p, EPI_STORE_BACK, d));   // stores d and starts A^T on its cropped copy
+  CHK(launch_class_adj(p, 0));
   CHK(launch_plane_adj(p, OUT_SCALE_B, x, nullptr));
   return MH3D_OK;
 }
@@ -1094,7 +1084,7 @@ extern "C" mh3d_status mh3d_forward(mh3d_plan_t p, const float* rho, float* d) {
     return sep_small_inv(p, d);
   }
   CHK(launch_plane_fwd(p, SRC_PLAIN, rho));
-  CHK(launch_class_fwd(p, 0, FWD_G));
+  CHK(launch_class_fwd(p, 0));
   CHK(launch_small_inv(p, EPI_STORE, d));
   return MH3D_OK;
 }
@@ -1143,12 +1133,8 @@ static mh3d_status apply_normal_scaled(mh3d_plan_t p, const float* w, float* out
   if (fused_class(p)) {
     CHK(launch_class_normal(p, 1, NRM_PLAIN));
   } else {
-    if (p->g.padded) {
-      CHK(launch_class_fwd(p, 1, FWD_G));
-      CHK(launch_small_inv(p, EPI_BACK, nullptr));   // crop to the field of view
-    } else {
-      CHK(launch_class_fwd(p, 1, FWD_ADJ));
-    }
+    CHK(launch_class_fwd(p, 1));
+    CHK(launch_small_inv(p, EPI_BACK, nullptr));   // crop to the field of view
     CHK(launch_class_adj(p, 1));
   }
   CHK(launch_adjoint_step(p, UPD_NORMAL, out, w));
@@ -1230,12 +1216,8 @@ static mh3d_status enqueue_update(mh3d_plan_t p, bool first, bool pending) {
   if (fused_class(p)) {
     CHK(launch_class_normal(p, 1, NRM_RESID, fin));   // against the data's spectra, held in G'
   } else {
-    if (p->g.padded) {
-      CHK(launch_class_fwd(p, 1, FWD_G, fin));
-      CHK(launch_small_inv(p, EPI_RESID_BACK, nullptr));   // residual on the field of view
-    } else {
-      CHK(launch_class_fwd(p, 1, FWD_RESID, fin));   // residual spectrum against the data's, held in G
-    }
+    CHK(launch_class_fwd(p, 1, fin));
+    CHK(launch_small_inv(p, EPI_RESID_BACK, nullptr));   // residual on the field of view
     CHK(launch_class_adj(p, 1));
   }
   if (step_and_fwd(p)) return launch_step_and_fwd(p);
@@ -1829,7 +1811,7 @@ extern "C" mh3d_status mh3d_time_pass(mh3d_plan_t p, int32_t pass, int32_t reps,
     }
     switch (pass) {
       case 0: return launch_plane_fwd(p, SRC_PLAIN, p->vol[0]);
-      case 1: return launch_class_fwd(p, 0, FWD_G);
+      case 1: return launch_class_fwd(p, 0);
       case 2: return launch_small_inv(p, EPI_STORE, dtmp);
       case 3: return launch_small_fwd(p, dtmp);
       case 4: return launch_class_adj(p, 0);

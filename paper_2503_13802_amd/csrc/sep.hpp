@@ -1043,7 +1043,7 @@ struct SmallFov {
 
 // The block-uniform values of the small-grid passes.
 struct SmallGeo {
-  int K, my, mz, mzh, xb, nxb, ncls, spairs, lsmy, lsmz, padded, M, T;
+  int my, mz, mzh, xb, nxb, ncls, spairs, lsmy, lsmz, padded, M, T;
   MDiv d_spairs, d_xbmzh, d_mzh, d_xb, d_mz, d_mzv, d_my, d_nxb;
   const float2* tw;
   int offy, offz;

@@ -17,7 +17,8 @@ __device__ __forceinline__ void user_g_index(const Geo& g, int fls, int p, int c
 
 // One block: cpw classes, of which a thread owns E consecutive alias members of one folded
 // frequency (the members of S / E neighbouring lanes sum to it).  DIR:
-//   CLS_FWD     the folded spectra, transformed along x' into G and / or G' (mode FWD_*)
+//   CLS_FWD     the folded spectra, transformed along x' into G (the small-grid pass turns them
+//               into portraits)
 //   CLS_ADJ     G' transformed along x', times conj(Hhat), back along x
 //   CLS_NORMAL  both (no boundary padding), for the solver's updates, the normal operator
 //               and A then A^T.  The folded spectra Fhat_k stay in LDS and the adjoint starts
@@ -217,18 +218,10 @@ __device__ __forceinline__ void user_class_body(const VolDesc& vd, int lb, int m
   }
   if constexpr (DIR == CLS_FWD) {
     const float2* R = line_fft<+1, true>(F0, F1, twm, mx, lms);
-    // the small-grid transforms are unnormalised: their round trip scales by my mz
-    const float syz = (float)(g.my * g.mz);
     for (int p = threadIdx.x; p < KCM; p += T) {
       int fo, go;
       user_g_index(g, fls, p, c0, fo, go);
-      const float2 f = R[fo];
-      if (mode == FWD_G || mode == FWD_G_AND_ADJ) stg(G + go, f);
-      if (mode == FWD_ADJ || mode == FWD_G_AND_ADJ) stg(Gp + go, make_float2(syz * f.x, syz * f.y));
-      if (mode == FWD_RESID) {
-        const float2 dh = ldg(G + go);
-        stg(Gp + go, make_float2(syz * f.x - dh.x, syz * f.y - dh.y));
-      }
+      stg(G + go, R[fo]);
     }
     return;
   }
