@@ -704,7 +704,7 @@ static __global__ __launch_bounds__(G::TP) void k_fast_plane_adj(const VolDesc* 
 // Block (k, x'-block of XB planes): the portraits d_k of those planes from their decimated
 // spectra G[k][x'-block][column][x'-in-block] (the column pass's output): inverse
 // length-my transform along y', C2R along z' (row pairs packed), store.  The same
-// transforms as small_inv_body<EPI_STORE> (kernels.hpp) on compile-time sizes.
+// transforms as sep_small_inv_body with EPI_STORE (sep.hpp) on compile-time sizes.
 template <class G, int XB>
 __device__ __forceinline__ void fast_small_inv_body(const VolDesc& vd, int lb, float* __restrict__ d) {
   constexpr int MY = G::MY, MZ = G::MZ, MZH = G::MZH, LSMY = G::LSMY, LSMZ = G::LSMZ;

@@ -292,10 +292,10 @@ __device__ __forceinline__ bool grid_reduce_last(double* v, double* partials, De
 // An update's finish runs as one more block of the next update's column or class pass, which
 // reads nothing it writes: the pass stops at `skip`, which the launch before it sets if the solve
 // was done then (solve_over).  The pass of the update after the last fills scratch buffers, and
-// the step after it, which reads `done`, ends.  The forward plane pass before it takes y^{k+1} (SRC_FISTA_NEXT).  As a launch of its own, which
-// it still is before the host reads the state, it took 3.6 to 4.9 us: 30 updates at 128^3 1176 us
-// with it, 1054 without; 25 padded ones at 64^3 1301, 1212; 16 of a batch of four 1164, 1106; 30 of
-// a 128 x 256 image 1073, 971.
+// the step after it, which reads `done`, ends.  The forward plane pass before it takes y^{k+1}
+// (SRC_FISTA_NEXT).  As a launch of its own, which it still is before the host reads the state, it
+// took 3.6 to 4.9 us: 30 updates at 128^3 1176 us with it, 1054 without; 25 padded ones at 64^3
+// 1301, 1212; 16 of a batch of four 1164, 1106; 30 of a 128 x 256 image 1073, 971.
 __device__ __forceinline__ bool solve_over(const VolDesc& vd, int fin) {
   const DevState* st = vd.st;
   return *(fin ? &st->skip : &st->done) != 0;
@@ -595,8 +595,10 @@ static __global__ void k_sep_tables(Geo g, const double2* __restrict__ fhat, con
 }
 
 // fft(h_k) of the analytic PSF, [k][nx][ny][nzh] complex, from its factors: F_k(qx) Ehat(qy,
-// qz) scale_k N, rounded to FP32 as the separable tables round it (its real part for odd
-// orders, its imaginary part for even ones; tests and tools).
+// qz) scale_k N in FP64, rounded to FP32 once (its real part for odd orders, its imaginary
+// part for even ones; tests and tools).  It shows the factors that the passes' tables are made
+// of, not the tables: sfs and set each round their own sums, and what the passes multiply with
+// is checked by the operator's parity with the oracle.
 static __global__ void k_spectrum_analytic(Geo g, const double2* __restrict__ fhat, const double2* __restrict__ ehat,
                                     const double* __restrict__ scale, uint32_t imag_mask, float2* __restrict__ out) {
   const long long per_k = (long long)g.nx * g.ny * g.nzh, total = (long long)g.K * per_k;

@@ -4,9 +4,10 @@
 // compile-time constant chosen by a block-uniform switch, and the line count and stride
 // run-time values.
 //
-// Radices are chosen for few stages (every length up to 256 that the switch knows takes
-// at most two, but for 108, 162, 192 and 216): a stage costs an LDS round trip and a
-// barrier, and with the few lines of one workgroup that chain is most of a pass.
+// Radices are chosen for few stages (every length that the switch knows takes at most two, but
+// for 108 and 192, and for 96, 128, 144 and 256 in the class passes, see line_radix): a stage costs
+// an LDS round trip and a barrier, and with the few lines of one workgroup that chain is most
+// of a pass.  Other lengths (2, 3, 81, 162, 216, 243) take the run-time engine of fft_lds.hpp.
 #pragma once
 #include "fft_lds.hpp"
 #include "geo.hpp"

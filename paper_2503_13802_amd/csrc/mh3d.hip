@@ -92,9 +92,12 @@ static void derive_sep(Geo& g, Launch& L) {
   s.lsz = pad_odd(g.nz);
   s.lsy = pad_odd(g.my);
   s.pbuf = std::max(s.np * s.lsz, g.nzh * s.lsy);
-  // columns per block: 4 (32-byte runs of the shares, of Q and of G), more while a block
-  // would have less than a wave of (column, q'x) threads, fewer beyond 256 (the largest
-  // blocks leave too few per CU to overlap their chains)
+  // columns per block: 4 (32-byte runs of the shares, of Q and, times xb, of G), more while a
+  // block would have less than a wave of (column, q'x) threads, 2 beyond 256 of those: the
+  // largest blocks leave too few per CU to overlap their chains, which costs more than 16-byte
+  // runs do.  256 x 128 x 128, K = 8, s = (2,2,2): column passes of A and of A^T 19.3 and 16.8 us with
+  // two columns, 23.9 and 21.2 with four; 192 x 96 x 96: 9.0 and 8.2, 9.2 and 8.6; smaller grids
+  // within 0.6 us either way
   s.cpc = 4;
   while (s.cpc * g.mx < 64 && s.cpc < 16) s.cpc *= 2;
   while (s.cpc * g.mx > 256 && s.cpc > 2) s.cpc /= 2;
@@ -119,12 +122,13 @@ static void derive_sep(Geo& g, Launch& L) {
   L.lds_col_resid = g.sx <= 4 ? fixed + s.kg * per : L.lds_col;
   L.lds_col_plain = g.sx <= 4 ? fixed : L.lds_col;
   // a thread per (column, q'x), and with many x aliases one per four points of the x lines
+  // (256 x 32 x 32, s = (8,2,2), K = 12: column pass of A 13.9 us with 128 threads, 11.0 with 256)
   L.T_col = std::max(128, (std::max(s.cpc * g.mx, std::min(512, s.cpc * g.nx / 4)) + 63) / 64 * 64);
   L.col_blocks = (g.ncls + s.cpc - 1) / s.cpc;
   // plane blocks: two points per thread, small-grid blocks: one (four threads and more per radix-8
   // butterfly: the loads, the splits, the crop and the solver step are shared by more threads
   // than the stages need).  25 padded updates at 64^3 with four points per thread 1212 us,
-  // so 1138; A and A^T at 72 x 108 x 48 36.3, 35.7
+  // so 1150; A and A^T at 72 x 108 x 48 36.3, 35.5
   L.T_sep = std::min(512, std::max(128, pow2_at_least(s.np * g.nz / 2)));
   L.lds_sep = sizeof(float2) * ((size_t)g.nz + g.my + 2 * (size_t)s.pbuf);
   s.lsmz = pad_odd(g.mz);

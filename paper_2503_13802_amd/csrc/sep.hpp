@@ -21,10 +21,10 @@
 // its SIMD issues one dependent instruction per 8 cycles), beyond that memory: at 256 x 128
 // x 128, K = 8, s = (2,2,2) the plane passes move 42 and 38 MB in 15.3 and 18.5 us.
 // Measured against the passes they replaced (microseconds per call, before and after):
-// A then A^T at 32^3, K = 2: 20.9, 17.1; A and A^T as two calls at 72 x 108 x 48, K = 5, s =
-// (2,3,2): 68.4, 36.2 and at 256 x 128 x 128: 243.9, 113.5; 25 padded updates at 64^3, K =
-// 6: 1503, 1301; 16 updates of a batch of 48^3, 64^3, 96 x 96 x 64 and 128 x 128 x 96:
-// 2630, 1164.
+// A then A^T at 32^3, K = 2: 20.9, 17.0; A and A^T as two calls at 72 x 108 x 48, K = 5, s =
+// (2,3,2): 68.4, 35.5 and at 256 x 128 x 128: 243.9, 114; 25 padded updates at 64^3, K =
+// 6: 1503, 1150; 16 updates of a batch of 48^3, 64^3, 96 x 96 x 64 and 128 x 128 x 96:
+// 2630, 1040 (both solves with the finish riding along, see vol_finish).
 #pragma once
 #include "kernels.hpp"
 #include "lines.hpp"

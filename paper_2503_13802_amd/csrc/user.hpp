@@ -16,9 +16,9 @@
 // Measured against the passes these replaced, microseconds per call: A and A^T as two calls at
 // 96 x 96 x 64, K = 7, three components 126.2, 77.6 (forward plane pass 32.1, 13.0; adjoint 31.7,
 // 12.8; class passes 25.6 and 22.0, 18.1 and 18.0); 30 updates of a 128 x 256 image of 7
-// harmonics from two scans 1817, 1073 (step and next forward pass 23.8, 12.3 in one launch; class
-// passes 29.2 as two launches, 14.8 as one); a scalar 256 x 256 image 20.7, 20.2 (A) and 20.4,
-// 18.0 (A^T).
+// harmonics from two scans 1817, 965 (step and next forward pass 23.8, 12.3 in one launch; class
+// passes 29.2 as two launches, 14.8 as one; the finish riding along, see vol_finish); a scalar
+// 256 x 256 image 20.7, 20.2 (A) and 20.4, 18.0 (A^T).
 #pragma once
 #include "sep.hpp"
 
